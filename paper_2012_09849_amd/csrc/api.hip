@@ -89,6 +89,7 @@ void carve(Ctx &c, Carver &cv)
     cv.take(w.act1, mb * g.P1 * 32 * ts); cv.take(w.act2, mb * g.P2 * 64 * ts); cv.take(w.a3, mb * g.F * ts);
     cv.take(w.fc_part, (size_t)c.fc_groups * mb * 512 * 4);
     cv.take(w.clip, 2 * 4);
+    cv.take(w.adv_part, (1 + 2 * NRM_BLOCKS) * 8);
     cv.take(w.norm_part, (size_t)((g.P + NORM_CHUNK - 1) / NORM_CHUNK) * 4);
     if (ml > 0) {
         cv.take(w.wd2, 32 * 1024 * ts); cv.take(w.wd3, 64 * 576 * ts); cv.take(w.wfcd, (size_t)512 * g.F * ts);

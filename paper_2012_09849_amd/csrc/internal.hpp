@@ -10,6 +10,7 @@
 namespace hts {
 
 constexpr int NORM_CHUNK = 8192;   // elements per workgroup in the gradient-norm pass (fixes the reduction shape)
+constexpr int NRM_BLOCKS = 256;    // workgroups of the advantage normalisation's sums
 constexpr int N_TERMS = 5;         // per-sample loss terms: policy, value, entropy, clipped flag, kl
 constexpr int FC_GROUP_K = 512;    // the FC layer's reduction is cut into groups of this many inputs (8 segments of 64)
 
@@ -32,6 +33,7 @@ struct Workspace {
     float *fc_part;           // [fc_groups][B][512] partial sums of the FC layer, one per group of FC_GROUP_K inputs
     // backward
     float *dz, *dh, *terms, *grads, *part, *norm_part, *clip;   // clip[0] = scale, clip[1] = ||g||
+    double *adv_part;         // [1 + 2 NRM_BLOCKS] sums of the advantage normalisation
     float *heads_part;        // [HEADS_MAXZ][A+1][513] partials of the heads weight gradient (large minibatches)
     void *dy3, *dy2, *dy1;    // T
     size_t part_elems;

@@ -760,41 +760,142 @@ hipError_t launch_gae(Ctx *c, hipStream_t s, const float *r, const float *v, con
 }
 
 // ------------------------------------------------------------------------------------------------------------
-// advantage normalisation: one workgroup, double-precision fixed-shape sums
+// advantage normalisation: double-precision sums of fixed shape.  Up to NRM_ONE entries one workgroup holds the array in
+// registers (one launch); beyond that up to NRM_BLOCKS workgroups each reduce a share and a second launch combines
+// their sums and rescales.  Kernel times by rocprofv3: 512x16 entries 6.2 us as three strided passes of one workgroup over
+// memory, 4.8 us from registers (launch, one memory round trip, two reductions across 16 wavefronts); 128x4096 entries
+// 281 us with one workgroup (2 MB through one compute unit three times), 3.3 + 3.9 us (two launches; 6 MB moved).
 // ------------------------------------------------------------------------------------------------------------
-__device__ __forceinline__ double block_sum_1024(double x, double *red)
+constexpr int NRM_ONE_THREADS = 1024, NRM_ONE_VECS = 4;                       // 4-entry vectors per thread, one workgroup
+constexpr int NRM_ONE = NRM_ONE_THREADS * NRM_ONE_VECS * 4;
+constexpr int NRM_THREADS = 256;
+
+// sum over a workgroup of NT threads, returned to every thread; red: NT / 64 doubles that nobody else writes
+template <int NT> __device__ __forceinline__ double block_sum_f64(double x, double *red)
 {
-    const int t = threadIdx.x;
-    red[t] = x;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
     __syncthreads();
-    for (int w = 512; w >= 1; w >>= 1) {
-        if (t < w) red[t] += red[t + w];
-        __syncthreads();
-    }
-    const double s = red[0];
-    __syncthreads();
+    double s = 0.0;
+#pragma unroll
+    for (int i = 0; i < NT / 64; ++i) s += red[i];
     return s;
 }
-
-__global__ __launch_bounds__(1024) void normalize_kernel(float *__restrict__ adv, long long n)
+// entries 4 v .. 4 v + 3, zeros behind entry n - 1; VEC: adv is 16-byte aligned
+template <bool VEC> __device__ __forceinline__ f32x4 load_entries(const float *adv, long long v, long long n)
 {
-    __shared__ double red[1024];
+    if (VEC && 4 * v + 4 <= n) return *reinterpret_cast<const f32x4 *>(adv + 4 * v);
+    f32x4 x = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) if (4 * v + e < n) x[e] = adv[4 * v + e];
+    return x;
+}
+template <bool VEC> __device__ __forceinline__ void store_entries(float *adv, long long v, long long n, const f32x4 &x)
+{
+    if (VEC && 4 * v + 4 <= n) { *reinterpret_cast<f32x4 *>(adv + 4 * v) = x; return; }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) if (4 * v + e < n) adv[4 * v + e] = x[e];
+}
+
+template <bool VEC> __global__ __launch_bounds__(NRM_ONE_THREADS) void normalize_one_kernel(float *__restrict__ adv, int n)
+{
+    __shared__ double red[2][NRM_ONE_THREADS / 64];
     const int t = threadIdx.x;
-    double s = 0.0;
-    for (long long i = t; i < n; i += 1024) s += (double)adv[i];
-    const double mean = block_sum_1024(s, red) / (double)n;
-    double q = 0.0;
-    for (long long i = t; i < n; i += 1024) { const double dlt = (double)adv[i] - mean; q += dlt * dlt; }
-    const double var = block_sum_1024(q, red) / (double)(n > 1 ? n - 1 : 1);
+    f32x4 x[NRM_ONE_VECS];
+#pragma unroll
+    for (int i = 0; i < NRM_ONE_VECS; ++i) x[i] = load_entries<VEC>(adv, t + i * NRM_ONE_THREADS, n);
+    double s = 0.0, q = 0.0;
+#pragma unroll
+    for (int i = 0; i < NRM_ONE_VECS; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s += (double)x[i][e];
+    const double mean = block_sum_f64<NRM_ONE_THREADS>(s, red[0]) / (double)n;
+#pragma unroll
+    for (int i = 0; i < NRM_ONE_VECS; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const double d = 4 * (t + i * NRM_ONE_THREADS) + e < n ? (double)x[i][e] - mean : 0.0;
+            q += d * d;
+        }
+    const double var = block_sum_f64<NRM_ONE_THREADS>(q, red[1]) / (double)(n > 1 ? n - 1 : 1);
     const double inv = 1.0 / (sqrt(var) + 1e-5);
-    for (long long i = t; i < n; i += 1024) adv[i] = (float)(((double)adv[i] - mean) * inv);
+#pragma unroll
+    for (int i = 0; i < NRM_ONE_VECS; ++i) {
+        f32x4 y;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) y[e] = (float)(((double)x[i][e] - mean) * inv);
+        store_entries<VEC>(adv, t + i * NRM_ONE_THREADS, n, y);
+    }
+}
+
+// One workgroup's share of the sums about the first entry x_0: part[1 + 2i] = sum (x - x_0), part[2 + 2i] = sum (x - x_0)^2,
+// part[0] = x_0.  var = (q - s^2/n) / (n-1) then cancels little: s^2/n = n (mean - x_0)^2, and x_0's own term already
+// makes the sum of squares about the mean at least (mean - x_0)^2, so at most a factor n of double precision's 2^-53.
+__device__ double normalize_scratch[1 + 2 * NRM_BLOCKS];      // for calls without a context (all of them on the default stream)
+template <bool VEC> __global__ __launch_bounds__(NRM_THREADS) void normalize_sums_kernel(const float *__restrict__ adv, long long n,
+                                                                                         double *part)
+{
+    __shared__ double red[2][NRM_THREADS / 64];
+    if (!part) part = normalize_scratch;
+    const double x0 = (double)adv[0];
+    const long long stride = (long long)gridDim.x * NRM_THREADS, nv = (n + 3) >> 2;
+    double s = 0.0, q = 0.0;
+    for (long long v = (long long)blockIdx.x * NRM_THREADS + threadIdx.x; v < nv; v += 2 * stride) {
+        const f32x4 x[2] = {load_entries<VEC>(adv, v, n), load_entries<VEC>(adv, v + stride < nv ? v + stride : v, n)};
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const double d = 4 * (v + i * stride) + e < n ? (double)x[i][e] - x0 : 0.0;
+                s += d; q += d * d;
+            }
+    }
+    const double bs = block_sum_f64<NRM_THREADS>(s, red[0]), bq = block_sum_f64<NRM_THREADS>(q, red[1]);
+    if (threadIdx.x == 0) {
+        part[1 + 2 * blockIdx.x] = bs; part[2 + 2 * blockIdx.x] = bq;
+        if (blockIdx.x == 0) part[0] = x0;
+    }
+}
+// launched with the grid of the kernel above: every workgroup adds all shares' sums in the same order
+template <bool VEC> __global__ __launch_bounds__(NRM_THREADS) void normalize_apply_kernel(float *__restrict__ adv, long long n,
+                                                                                          const double *part)
+{
+    static_assert(NRM_BLOCKS <= NRM_THREADS, "one share per thread");
+    __shared__ double red[2][NRM_THREADS / 64];
+    if (!part) part = normalize_scratch;
+    const long long stride = (long long)gridDim.x * NRM_THREADS, nv = (n + 3) >> 2;
+    const long long v0 = (long long)blockIdx.x * NRM_THREADS + threadIdx.x;
+    f32x4 x = load_entries<VEC>(adv, v0 < nv ? v0 : 0, n);
+    const int t = threadIdx.x;
+    const double x0 = part[0], ps = t < (int)gridDim.x ? part[1 + 2 * t] : 0.0, pq = t < (int)gridDim.x ? part[2 + 2 * t] : 0.0;
+    const double s = block_sum_f64<NRM_THREADS>(ps, red[0]), q = block_sum_f64<NRM_THREADS>(pq, red[1]);
+    const double mean = x0 + s / (double)n, var = fmax(q - s * (s / (double)n), 0.0) / (double)(n - 1);
+    const double inv = 1.0 / (sqrt(var) + 1e-5);
+    for (long long v = v0; v < nv; v += stride) {
+        const f32x4 next = load_entries<VEC>(adv, v + stride < nv ? v + stride : v, n);
+        f32x4 y;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) y[e] = (float)(((double)x[e] - mean) * inv);
+        store_entries<VEC>(adv, v, n, y);
+        x = next;
+    }
 }
 
 hipError_t launch_normalize(Ctx *c, hipStream_t s, float *adv, long long n)
 {
     Ctx dummy;
     SiteTimer tm(c ? *c : dummy, SITE_NORMALIZE);
-    hipLaunchKernelGGL(normalize_kernel, dim3(1), dim3(1024), 0, s, adv, n);
+    const bool vec = !((uintptr_t)adv & 15u);
+    if (n <= NRM_ONE) {
+        hipLaunchKernelGGL(vec ? normalize_one_kernel<true> : normalize_one_kernel<false>, dim3(1), dim3(NRM_ONE_THREADS), 0, s, adv, (int)n);
+        return hipGetLastError();
+    }
+    double *part = c ? c->ws.adv_part : nullptr;
+    const long long need = ((n + 3) / 4 + NRM_THREADS - 1) / NRM_THREADS;
+    const dim3 grid((unsigned)(need < NRM_BLOCKS ? need : NRM_BLOCKS));
+    hipLaunchKernelGGL(vec ? normalize_sums_kernel<true> : normalize_sums_kernel<false>, grid, dim3(NRM_THREADS), 0, s, adv, n, part);
+    hipLaunchKernelGGL(vec ? normalize_apply_kernel<true> : normalize_apply_kernel<false>, grid, dim3(NRM_THREADS), 0, s, adv, n, part);
     return hipGetLastError();
 }
 
