@@ -694,48 +694,74 @@ __global__ __launch_bounds__(64) void gae_kernel(const float *__restrict__ r, co
     }
 }
 
-// Time-chunked form for short-and-narrow storages (few environments): a workgroup owns 32 columns and cuts time into
-// TC chunks, one wavefront-row per chunk.  A_t = delta_t + c_t A_{t+1} is affine in the carry entering a chunk, so
-// pass 1 reduces every chunk to (S, P) with A_first = S + P * carry, the carries are chained through LDS in chunk
-// order, and pass 2 replays each chunk from its true carry and writes the outputs.  Double precision throughout, so
-// the result equals the one-lane-per-column recurrence to well below binary32 rounding.
-constexpr int GAE_COLS = 32, GAE_MAX_TC = 16;
-__global__ __launch_bounds__(GAE_COLS * GAE_MAX_TC) void gae_chunked_kernel(
+// Time-chunked form: a workgroup owns COLS columns and walks time backwards in spans
+// of TC chunks of GAE_L steps, one chunk per thread, 64 / COLS chunks per wavefront.  A thread holds its chunk in registers
+// (one memory round trip per span).  A_t = delta_t + c_t A_{t+1} is affine in the advantage entering a chunk, so every
+// chunk is first reduced to a map (S, P), A_first = S + P * A_entering; the maps are composed by lane shifts inside a
+// wavefront and through LDS across wavefronts, and every chunk is then replayed from what truly enters it.  Double
+// precision throughout, so the result equals the one-lane-per-column recurrence to well below binary32 rounding.
+// Steps before t = 0 (a last, partial span) have S = 0 and P = 1 and write nothing.
+constexpr int GAE_L = 8, GAE_MAX_WAVES = 8;
+template <int COLS> __global__ __launch_bounds__(64 * GAE_MAX_WAVES) void gae_chunked_kernel(
     const float *__restrict__ r, const float *__restrict__ v, const uint8_t *__restrict__ d, float gamma, float lambda,
-    int T, int N, int TC, int L, float *__restrict__ adv, float *__restrict__ ret)
+    int T, int N, float *__restrict__ adv, float *__restrict__ ret)
 {
-    __shared__ double sS[GAE_MAX_TC][GAE_COLS], sP[GAE_MAX_TC][GAE_COLS];
-    const int cx = threadIdx.x % GAE_COLS, cc = threadIdx.x / GAE_COLS;
-    const int n = blockIdx.x * GAE_COLS + cx;
-    const int t0 = cc * L, t1 = min(T, t0 + L);                 // this thread's chunk [t0, t1)
-    const bool live = n < N && t0 < t1;
+    __shared__ double sS[2][GAE_MAX_WAVES][COLS], sP[2][GAE_MAX_WAVES][COLS];
+    const int waves = blockDim.x >> 6, TC = blockDim.x / COLS;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, cx = threadIdx.x % COLS, cc = threadIdx.x / COLS;
+    const int n = blockIdx.x * COLS + cx;
+    const bool live = n < N;
+    const long long col = live ? n : N - 1;
     const double g = (double)gamma, gl = (double)gamma * (double)lambda;
-    double S = 0.0, P = 1.0;
-    if (live) {
-        double vnext = (double)v[(long long)t1 * N + n];
-        for (int t = t1 - 1; t >= t0; --t) {
-            const long long o = (long long)t * N + n;
-            const double vt = (double)v[o], nd = d[o] ? 0.0 : 1.0;
-            const double delta = (double)r[o] + g * nd * vnext - vt, ct = gl * nd;
-            S = delta + ct * S;
-            P = ct * P;
-            vnext = vt;
+    double enter = 0.0;                                          // advantage entering the span from later times
+    int buf = 0;
+    for (int tend = T; tend > 0; tend -= TC * GAE_L, buf ^= 1) {
+        const int t0 = tend - (TC - cc) * GAE_L;                 // this thread's chunk [t0, t0 + GAE_L); negative steps do not exist
+        float rr[GAE_L], vv[GAE_L + 1];
+        uint8_t dd[GAE_L];
+#pragma unroll
+        for (int i = 0; i < GAE_L; ++i) {
+            const long long o = (long long)max(t0 + i, 0) * N + col;
+            rr[i] = r[o]; vv[i] = v[o]; dd[i] = d[o];
         }
-    }
-    sS[cc][cx] = S; sP[cc][cx] = P;
-    __syncthreads();
-    if (!live) return;
-    double a = 0.0;                                              // advantage entering this chunk from later times
-    for (int q = TC - 1; q > cc; --q) a = sS[q][cx] + sP[q][cx] * a;
-    double vnext = (double)v[(long long)t1 * N + n];
-    for (int t = t1 - 1; t >= t0; --t) {
-        const long long o = (long long)t * N + n;
-        const double vt = (double)v[o], nd = d[o] ? 0.0 : 1.0;
-        const double delta = (double)r[o] + g * nd * vnext - vt;
-        a = delta + gl * nd * a;
-        adv[o] = (float)a;
-        ret[o] = (float)(a + vt);
-        vnext = vt;
+        vv[GAE_L] = v[(long long)max(t0 + GAE_L, 0) * N + col];
+        double S = 0.0, P = 1.0;
+#pragma unroll
+        for (int i = GAE_L - 1; i >= 0; --i) {
+            const double nd = dd[i] ? 0.0 : 1.0;
+            const double delta = (double)rr[i] + g * nd * (double)vv[i + 1] - (double)vv[i], ct = gl * nd;
+            if (t0 + i >= 0) { S = delta + ct * S; P = ct * P; }
+        }
+        // this chunk's map composed with those of the later chunks of the wavefront, then the later chunks' alone
+#pragma unroll
+        for (int o = COLS; o < 64; o <<= 1) {
+            const double Sl = __shfl_down(S, o, 64), Pl = __shfl_down(P, o, 64);
+            if (lane + o < 64) { S = S + P * Sl; P = P * Pl; }
+        }
+        if (lane < COLS) { sS[buf][w][lane] = S; sP[buf][w][lane] = P; }
+        double Se = 0.0, Pe = 1.0;
+        if constexpr (COLS < 64) {
+            const double Sl = __shfl_down(S, COLS, 64), Pl = __shfl_down(P, COLS, 64);
+            if (lane + COLS < 64) { Se = Sl; Pe = Pl; }
+        }
+        __syncthreads();
+        double a = enter, all = enter;                           // entering this wavefront's chunks; leaving the span
+#pragma unroll
+        for (int q = GAE_MAX_WAVES - 1; q >= 0; --q) {
+            const double Sq = q < waves ? sS[buf][q][cx] : 0.0, Pq = q < waves ? sP[buf][q][cx] : 1.0;
+            all = Sq + Pq * all;
+            if (q > w) a = all;
+        }
+        enter = all;
+        a = Se + Pe * a;
+#pragma unroll
+        for (int i = GAE_L - 1; i >= 0; --i) {
+            const double nd = dd[i] ? 0.0 : 1.0;
+            const double delta = (double)rr[i] + g * nd * (double)vv[i + 1] - (double)vv[i];
+            a = delta + gl * nd * a;
+            const long long o = (long long)(t0 + i) * N + col;
+            if (live && t0 + i >= 0) { adv[o] = (float)a; ret[o] = (float)(a + (double)vv[i]); }
+        }
     }
 }
 
@@ -744,17 +770,22 @@ hipError_t launch_gae(Ctx *c, hipStream_t s, const float *r, const float *v, con
 {
     Ctx dummy;
     SiteTimer tm(c ? *c : dummy, SITE_GAE);
-    // enough columns to hide each lane's serial walk behind other wavefronts -> plain kernel; otherwise split time as
-    // well (measured at T = 128: 16384 columns 27.7 us plain, 7.9 us chunked; break-even near 65536 columns)
-    if ((long long)N >= 65536 || T < 16) {
+    // Kernel time by rocprofv3, us: plain / 4 / 16 / 64 columns a workgroup
+    //   5x16 1.7/3.2/2.6/2.3, 6x262147 6.8/55/18/8.6: one chunk of time has nothing to split -> plain
+    //   128x262144 107/641/222/114, 128x70000 40/147/45/31: enough columns hide a lane's serial walk -> plain from 131072
+    //   512x16 64/4.1/5.8/17, 512x100 66/4.7/6.7/18: few workgroups, so every chunk of a long unroll in one span -> 4
+    //   128x32 17/3.9/3.5/5.3, 128x4096 18/11/4.9/6.7, 512x1024 65/11/7.2/18 -> 16
+    //   128x16384 29/39/13/8.0, 30x16384 6.5/12/4.8/4.3: whole cache lines per load -> 64
+    // (with a chunk's rows fetched twice and one at a time, 32 columns: 512x16 12.2, 128x4096 8.0)
+    if (T <= GAE_L || N >= 131072) {
         hipLaunchKernelGGL(gae_kernel, dim3((N + 63) / 64), dim3(64), 0, s, r, v, d, gamma, lambda, T, N, adv, ret);
     } else {
-        int TC = T / 8;                       // chunks of at least 8 steps
-        if (TC > GAE_MAX_TC) TC = GAE_MAX_TC;
-        if (TC < 2) TC = 2;
-        const int L = (T + TC - 1) / TC;
-        hipLaunchKernelGGL(gae_chunked_kernel, dim3((N + GAE_COLS - 1) / GAE_COLS), dim3(GAE_COLS * TC), 0, s, r, v, d,
-                           gamma, lambda, T, N, TC, L, adv, ret);
+        const int cols = N > 8192 ? 64 : T > 256 && N <= 512 ? 4 : 16;
+        const int per_wave = 64 / cols, chunks = (T + GAE_L - 1) / GAE_L;
+        int waves = (chunks + per_wave - 1) / per_wave;
+        if (waves > GAE_MAX_WAVES) waves = GAE_MAX_WAVES;
+        auto kern = cols == 4 ? gae_chunked_kernel<4> : cols == 16 ? gae_chunked_kernel<16> : gae_chunked_kernel<64>;
+        hipLaunchKernelGGL(kern, dim3((N + cols - 1) / cols), dim3(64 * waves), 0, s, r, v, d, gamma, lambda, T, N, adv, ret);
     }
     return hipGetLastError();
 }

@@ -24,3 +24,22 @@ def test_normalize_edges(hts, oracle, n, shift):  # noqa: F811
     assert (got[:shift] == 7.0).all() and (got[shift + n:] == 7.0).all()
     np.testing.assert_allclose(got[shift:shift + n], oracle.normalize_adv(a), rtol=3e-7, atol=3e-7)
     ctx.close()
+
+
+# plain / chunked kernels (8 steps; 131072 columns), each column width (4, 16, 64), spans that end exactly at, one step
+# before and one step after a multiple of the span, a last workgroup with dead columns.  The tolerance of the oracle's
+# other returns tests: one binary32 rounding of a float64 recurrence.
+@pytest.mark.parametrize("T,N", [(8, 3), (9, 1), (257, 5), (513, 512), (512, 513), (256, 17), (255, 16), (65, 8193),
+                                 (64, 8192), (1025, 2), (9, 131071), (9, 131072)])
+def test_gae_edges(hts, oracle, T, N):  # noqa: F811
+    ctx = hts.Context(4, 84, 84, 6, max_act_batch=1)
+    r, v = syn.normal_f32(T + N, syn.S_REW, (T, N)), syn.normal_f32(T * 7 + N, syn.S_VAL, (T + 1, N))
+    d = syn.dones_bernoulli(T + N, T, N, 0.02)
+    adv, ret = torch.zeros(T, N, device="cuda"), torch.zeros(T, N, device="cuda")
+    ctx.hts_returns_gae(dev(r), dev(v), dev(d), 0.99, 0.95, adv, ret)
+    torch.cuda.synchronize()
+    a_ref, r_ref = oracle.gae(r, v, d, np.float32(0.99), np.float32(0.95))
+    for got, want in ((adv, a_ref), (ret, r_ref)):
+        err = np.abs(got.cpu().numpy().astype(np.float64) - want) / np.maximum(1.0, np.abs(want))
+        assert float(err.max()) <= 1e-6
+    ctx.close()
