@@ -8,6 +8,7 @@
 // built from 32x32 MFMA accumulators:
 //   fp32 : v_mfma_f32_32x32x2_f32   (lane l supplies A[l%32][l/32] and B[l/32][l%32])
 //   bf16 : v_mfma_f32_32x32x16_bf16 (lane l supplies 8 consecutive k at k0 = 8*(l/32) for row/col l%32)
+// (problems that cut binary32 operands into bfloat16 pieces have a tile kernel of their own, split.hpp)
 // Accumulator register r of lane l is D[8*(r/4) + 4*(l/32) + r%4][l%32].
 //
 // Operand tiles go global -> registers -> LDS ([row][k], padded) -> MFMA; the global loads of tile i+1 are in
@@ -62,6 +63,63 @@ HTS_HD float to_f32(bf16_t x) { return (float)x; }
 template <typename T> HTS_HD T from_f32(float x);
 template <> HTS_HD float from_f32<float>(float x) { return x; }
 template <> HTS_HD bf16_t from_f32<bf16_t>(float x) { return (bf16_t)x; }   // round to nearest even
+
+// binary32 operands on the bfloat16 matrix instruction.  x = p0 + p1 + p2 exactly, each piece bfloat16: p0 is x rounded to
+// nearest, and what is left has at most 16, then at most 8 significant bits (magnitudes fall by 2^9 a piece; below 2^-108
+// the last piece may be a denormal).  A product of two such operands is the six piece products p_i q_j with i + j <= 2;
+// the three left out are together below 2^-26 of |x y|, less than half of one binary32 rounding.  The sums p0 q0 are kept
+// apart from the five small ones (two accumulators, added once per segment), so the small ones are not rounded to the
+// large ones' last bit.  Measured against exact sums on random operands (equal and mixed magnitudes, one sign and both,
+// 64 to 4096 terms): 2 to 3 times SMALLER error than v_mfma_f32_32x32x2_f32, 2-norm and largest; nine products instead of
+// six change nothing.  Rate: 1750 / 6 = 290 against 121 TFLOP/s of the binary32 instruction in a loop of nothing else.
+// (The splitting of a binary32 number into bfloat16 pieces: Henry, Tang, Heinecke, "Leveraging the bfloat16 Artificial
+// Intelligence Datatype For Higher-Precision Computations", 2019.)
+// A problem whose operand is bytes (pixels: exact in one piece) says so with `static constexpr int A_PIECES = 1` (B_PIECES).
+// A binary32 problem with `static constexpr bool F32_MFMA = true` keeps the binary32 instruction.
+template <class P, class = void> struct F32Mfma : std::false_type {};
+template <class P> struct F32Mfma<P, std::void_t<decltype(P::F32_MFMA)>> : std::integral_constant<bool, P::F32_MFMA && sizeof(typename P::T) == 4> {};
+template <class P, class = void> struct PiecesA { static constexpr int value = sizeof(typename P::T) == 4 ? 3 : 1; };
+template <class P> struct PiecesA<P, std::void_t<decltype(P::A_PIECES)>> { static constexpr int value = P::A_PIECES; };
+template <class P, class = void> struct PiecesB { static constexpr int value = sizeof(typename P::T) == 4 ? 3 : 1; };
+template <class P> struct PiecesB<P, std::void_t<decltype(P::B_PIECES)>> { static constexpr int value = P::B_PIECES; };
+template <typename T, int V, int NP> HTS_HD void to_pieces(const Vec<T, V> &x, Vec<bf16_t, V> (&p)[NP])
+{
+    if constexpr (sizeof(T) == 2) { static_assert(NP == 1, "one piece"); p[0] = x; }
+    else {
+        typedef bf16_t bf16x2 __attribute__((ext_vector_type(2)));
+        typedef float f32x2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+        for (int i = 0; i < V; i += 2) {
+            float r0 = x[i], r1 = x[i + 1];
+#pragma unroll
+            for (int q = 0; q < NP; ++q) {
+                uint32_t w = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{r0, r1}, bf16x2));
+                if (q + 1 < NP) asm("" : "+v"(w));         // (one conversion for both: seen through, each is converted again for its remainder)
+                const bf16x2 h = __builtin_bit_cast(bf16x2, w);
+                p[q][i] = h[0]; p[q][i + 1] = h[1];
+                if (q + 1 < NP) {
+                    r0 -= __builtin_bit_cast(float, w << 16); r1 -= __builtin_bit_cast(float, w & 0xffff0000u);
+                }
+            }
+        }
+    }
+}
+// The products of one 32-long block of k, small pieces first: f(i, j, small) is called for every pair of pieces in a fixed
+// order and runs over the block's k itself, so every kernel adds in the same order whatever its instruction's k length.
+template <int NPA, int NPB, class F> HTS_HD void for_piece_pairs(F &&f)
+{
+    using std::integral_constant;
+    auto one = [&](auto i, auto j) {
+        if constexpr (decltype(i)::value < NPA && decltype(j)::value < NPB)
+            f(i, j, integral_constant<bool, (decltype(i)::value + decltype(j)::value > 0)>{});
+    };
+    one(integral_constant<int, 0>{}, integral_constant<int, 2>{});
+    one(integral_constant<int, 2>{}, integral_constant<int, 0>{});
+    one(integral_constant<int, 1>{}, integral_constant<int, 1>{});
+    one(integral_constant<int, 0>{}, integral_constant<int, 1>{});
+    one(integral_constant<int, 1>{}, integral_constant<int, 0>{});
+    one(integral_constant<int, 0>{}, integral_constant<int, 0>{});
+}
 
 // Exact floor(x / d) for 0 <= x < 2^31 by multiply-shift: mul = ceil(2^p / d), p = 31 + ceil(log2 d).
 struct FastDiv {
@@ -186,6 +244,15 @@ template <class P> struct OwnsRow<P, std::void_t<decltype(P::LANE_OWNS_ROW)>> : 
 template <class P, class = void> struct NaturalOf : std::false_type {};
 template <class P> struct NaturalOf<P, std::void_t<decltype(P::NATURAL_LDS)>> : std::integral_constant<bool, P::NATURAL_LDS> {};
 typedef short i16x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ bf16x8 tr8(const bf16_t *q, int pitch)      // 8 reduction indices of one row entry: two transposing reads
+{
+    typedef i16x4 __attribute__((address_space(3))) *lds_ptr;
+    const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(q));
+    const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(q + 4 * pitch));
+    typedef short i16x8 __attribute__((ext_vector_type(8)));
+    const i16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    return __builtin_bit_cast(bf16x8, v);
+}
 
 // Optional run loaders for operands that are contiguous along the reduction instead of along k: a problem with
 // `void load_a_run(const CtxA &, int k, int kend, Vec<T,VA> (&out)[VA]) const` (likewise load_b_run) fetches the VA
@@ -194,6 +261,22 @@ template <class P, class = void> struct HasRunA : std::false_type {};
 template <class P> struct HasRunA<P, std::void_t<decltype(&P::load_a_run)>> : std::true_type {};
 template <class P, class = void> struct HasRunB : std::false_type {};
 template <class P> struct HasRunB<P, std::void_t<decltype(&P::load_b_run)>> : std::true_type {};
+
+// Optional split of k: `load_a(const CtxA &, int k0, int dk, int kend)` (likewise load_b) fetches at k = k0 + dk, where k0 is
+// the start of a k-tile -- the same for the whole workgroup, so whatever depends on it alone is scalar arithmetic -- and
+// dk < BK.  For gathers whose taps are whole numbers of k-tiles.
+template <class P, class C, class = void> struct HasSplitA : std::false_type {};
+template <class P, class C> struct HasSplitA<P, C, std::void_t<decltype(std::declval<const P &>().load_a(std::declval<const C &>(), 0, 0, 0))>> : std::true_type {};
+template <class P, class C, class = void> struct HasSplitB : std::false_type {};
+template <class P, class C> struct HasSplitB<P, C, std::void_t<decltype(std::declval<const P &>().load_b(std::declval<const C &>(), 0, 0, 0))>> : std::true_type {};
+template <class P> HTS_HD auto tile_load_a(const P &p, const typename P::CtxA &c, int k0, int dk, int kend)
+{
+    if constexpr (HasSplitA<P, typename P::CtxA>::value) return p.load_a(c, k0, dk, kend); else return p.load_a(c, k0 + dk, kend);
+}
+template <class P> HTS_HD auto tile_load_b(const P &p, const typename P::CtxB &c, int k0, int dk, int kend)
+{
+    if constexpr (HasSplitB<P, typename P::CtxB>::value) return p.load_b(c, k0, dk, kend); else return p.load_b(c, k0 + dk, kend);
+}
 
 // Optional batching: a problem with `int batches() const`, `int max_m() const`, `int batch_m(int z) const` is
 // launched with gridDim.z = batches(); batch z has batch_m(z) rows and its own gathers: ctx_a(row, z),
@@ -274,6 +357,104 @@ template <class P, int TM, int TN> struct EpiInputs<P, TM, TN, true> {
     bool mok[TM];
 };
 
+template <class P, int TM, int TN, bool SWAP>
+__device__ __forceinline__ void epi_fetch(const P &p, EpiInputs<P, TM, TN, SWAP> &epi, int m0, int n0, int M, int zb, int wm, int wn, int lane)
+{
+    if constexpr (SWAP) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int m = m0 + (wm * TM + i) * 32 + (lane & 31);
+            epi.mok[i] = m < M;
+            epi.rc[i] = epi_row(p, epi.mok[i] ? m : M - 1, zb);
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int g = 0; g < 4; ++g)
+                    epi.pre[i][j][g] = p.pre4(epi.rc[i], min(n0 + (wn * TN + j) * 32 + 8 * g + 4 * (lane >> 5), p.N - 4));
+        }
+    }
+}
+// Stores a wavefront's block.  Tiles that lie wholly inside the output take a branch-free path (the compiler can then batch
+// the loads an epilogue may need); edge tiles check every element.
+template <class P, int TM, int TN, bool SWAP>
+__device__ __forceinline__ void epi_store(const P &p, const f32x16 (&acc)[TM][TN], EpiInputs<P, TM, TN, SWAP> &epi, int m0, int n0, int M, int z,
+                                          int zb, int wm, int wn, int lane)
+{
+    const int lrow = lane & 31, lk = lane >> 5;
+    auto epilogue = [&](auto full_tile) {
+        constexpr bool FULL = decltype(full_tile)::value;
+        if constexpr (SWAP) {
+            if constexpr (!EpiEarly<P>::value) epi_fetch(p, epi, m0, n0, M, zb, wm, wn, lane);
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        const int n = n0 + (wn * TN + j) * 32 + 8 * g + 4 * lk;
+                        const float v[4] = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
+                        if (FULL || (epi.mok[i] && n < p.N)) {
+                            if constexpr (HasBatch<P>::value) p.store4(epi.rc[i], n, v, z, zb, epi.pre[i][j][g]);
+                            else p.store4(epi.rc[i], n, v, z, epi.pre[i][j][g]);
+                        }
+                    }
+        } else {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    const int n = n0 + (wn * TN + j) * 32 + lrow;
+                    const auto col = make_col(p, FULL ? n : min(n, p.N - 1));
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const int m = m0 + (wm * TM + i) * 32 + 8 * (r / 4) + 4 * lk + (r % 4);
+                        if (FULL || (m < M && n < p.N)) do_store(p, m, n, acc[i][j][r], z, zb, col);
+                    }
+                }
+        }
+    };
+    if (m0 + P::BM <= M && n0 + P::BN <= p.N) epilogue(std::true_type{}); else epilogue(std::false_type{});
+}
+
+// This workgroup's tile: rows m0.., columns n0.., reduction chunk z; false: nothing to do.
+template <class P> __device__ __forceinline__ bool tile_of(const P &p, int M, int &m0, int &n0, int &z)
+{
+    constexpr int BM = P::BM, BN = P::BN;
+    const int tiles_n = (p.N + BN - 1) / BN;
+    int tile = blockIdx.x;
+    z = blockIdx.y;
+    if constexpr (!HasBatch<P>::value) {
+        // A long split reduction is launched as a one-dimensional grid (see launch_gemm): workgroups go to the eight
+        // XCDs in turn, so workgroup h runs on XCD h % 8; all output tiles of reduction chunk z are given to XCD z % 8,
+        // whose L2 then serves the operand rows that those tiles share.
+        if (gridDim.y == 1 && p.klen < p.K) {
+            const int tiles = ((M + BM - 1) / BM) * tiles_n;
+            const int xcd = tile & 7, slot = tile >> 3;
+            z = (slot / tiles) * 8 + xcd;
+            tile = slot % tiles;
+            if ((long long)z * p.klen >= p.K) return false;  // padding of the last round of eight chunks
+        } else {
+            // Otherwise gridDim.x is the number of tiles rounded up to a multiple of 8, and XCD x takes the x-th
+            // eighth of the tile order: neighbouring tiles share an operand panel, and a panel that is needed on one
+            // XCD only is fetched into one L2 only.  (Round-robin, every XCD read the whole of the operand that the
+            // tile order walks slowest: the FC forward pass fetched its activations eight times, 107 MB for 34.)
+            // (A single column of tiles shares nothing but the small weight panel and keeps the round-robin order.)
+            const int tiles = ((M + BM - 1) / BM) * tiles_n, per_xcd = gridDim.x >> 3;
+            if (tiles_n > 1) tile = (tile & 7) * per_xcd + (tile >> 3);
+            if (tile >= tiles) return false;
+        }
+    }
+    // the tile order walks N fastest, so an XCD's share is a range of rows and all columns; a problem whose column
+    // operand is the larger one asks for the transposed order (`static constexpr bool TILES_ALONG_M = true`)
+    if constexpr (TilesAlongM<P>::value) {
+        const int tiles_m = (M + BM - 1) / BM;
+        m0 = (tile % tiles_m) * BM; n0 = (tile / tiles_m) * BN;
+    } else {
+        m0 = (tile / tiles_n) * BM; n0 = (tile % tiles_n) * BN;
+    }
+    return m0 < M;                         // (a batch smaller than the largest one)
+}
+
 // A problem type P provides:
 //   using T                          operand type in LDS / MFMA (float or bf16_t)
 //   static constexpr int BM, BN, BK  workgroup tile; WAVES_M x WAVES_N wavefronts (64 lanes each) share it
@@ -322,39 +503,8 @@ __global__ __launch_bounds__(P::WAVES_M * P::WAVES_N * 64) void gemm_kernel(cons
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave % WM, wn = wave / WM;
-    const int tiles_n = (p.N + BN - 1) / BN;
-    int tile = blockIdx.x, z = blockIdx.y;
-    if constexpr (!HasBatch<P>::value) {
-        // A long split reduction is launched as a one-dimensional grid (see launch_gemm): workgroups go to the eight
-        // XCDs in turn, so workgroup h runs on XCD h % 8; all output tiles of reduction chunk z are given to XCD z % 8,
-        // whose L2 then serves the operand rows that those tiles share.
-        if (gridDim.y == 1 && p.klen < p.K) {
-            const int tiles = ((M + BM - 1) / BM) * tiles_n;
-            const int xcd = tile & 7, slot = tile >> 3;
-            z = (slot / tiles) * 8 + xcd;
-            tile = slot % tiles;
-            if ((long long)z * p.klen >= p.K) return;        // padding of the last round of eight chunks
-        } else {
-            // Otherwise gridDim.x is the number of tiles rounded up to a multiple of 8, and XCD x takes the x-th
-            // eighth of the tile order: neighbouring tiles share an operand panel, and a panel that is needed on one
-            // XCD only is fetched into one L2 only.  (Round-robin, every XCD read the whole of the operand that the
-            // tile order walks slowest: the FC forward pass fetched its activations eight times, 107 MB for 34.)
-            // (A single column of tiles shares nothing but the small weight panel and keeps the round-robin order.)
-            const int tiles = ((M + BM - 1) / BM) * tiles_n, per_xcd = gridDim.x >> 3;
-            if (tiles_n > 1) tile = (tile & 7) * per_xcd + (tile >> 3);
-            if (tile >= tiles) return;
-        }
-    }
-    // the tile order walks N fastest, so an XCD's share is a range of rows and all columns; a problem whose column
-    // operand is the larger one asks for the transposed order (`static constexpr bool TILES_ALONG_M = true`)
-    int m0, n0;
-    if constexpr (TilesAlongM<P>::value) {
-        const int tiles_m = (M + BM - 1) / BM;
-        m0 = (tile % tiles_m) * BM; n0 = (tile / tiles_m) * BN;
-    } else {
-        m0 = (tile / tiles_n) * BM; n0 = (tile % tiles_n) * BN;
-    }
-    if (m0 >= M) return;                   // a batch smaller than the largest one: the whole workgroup leaves
+    int m0, n0, z;
+    if (!tile_of(p, M, m0, n0, z)) return;       // the whole workgroup leaves
     const int kbeg = z * p.klen;
     const int kend = min(p.K, kbeg + p.klen);
 
@@ -402,7 +552,7 @@ __global__ __launch_bounds__(P::WAVES_M * P::WAVES_N * 64) void gemm_kernel(cons
                 if constexpr (!P::A_ALONG_K && !NAT_A && HasRunA<P>::value) p.load_a_run(ca[i], k0 + ka[i], lim, ra[i]);
                 else {
 #pragma unroll
-                    for (int q = 0; q < RA; ++q) ra[i][q] = p.load_a(ca[i], k0 + ka[i] + q, lim);
+                    for (int q = 0; q < RA; ++q) ra[i][q] = tile_load_a(p, ca[i], k0, ka[i] + q, lim);
                 }
             }
 #pragma unroll
@@ -411,7 +561,7 @@ __global__ __launch_bounds__(P::WAVES_M * P::WAVES_N * 64) void gemm_kernel(cons
                 if constexpr (!P::B_ALONG_K && !NAT_B && HasRunB<P>::value) p.load_b_run(cb[i], k0 + kb[i], lim, rb[i]);
                 else {
 #pragma unroll
-                    for (int q = 0; q < RB; ++q) rb[i][q] = p.load_b(cb[i], k0 + kb[i] + q, lim);
+                    for (int q = 0; q < RB; ++q) rb[i][q] = tile_load_b(p, cb[i], k0, kb[i] + q, lim);
                 }
             }
     };
@@ -479,14 +629,6 @@ __global__ __launch_bounds__(P::WAVES_M * P::WAVES_N * 64) void gemm_kernel(cons
                                          : lk * LSNB + lrow;
     const T *a_nat = As + wm * TM * 32 + nat_off_a;
     const T *b_nat = Bs + wn * TN * 32 + nat_off_b;
-    auto tr8 = [](const T *q, int pitch) {      // 8 reduction indices of one row entry: two transposing reads
-        typedef i16x4 __attribute__((address_space(3))) *lds_ptr;
-        const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(q));
-        const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(q + 4 * pitch));
-        typedef short i16x8 __attribute__((ext_vector_type(8)));
-        const i16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-        return __builtin_bit_cast(bf16x8, v);
-    };
 
     // one k-tile: registers -> LDS, refill this stage's registers with the tile D steps ahead, multiply.
     // REFILL: 1 = always (steady state: an unconditional load lets the compiler wait for exactly the older stages),
@@ -553,22 +695,7 @@ __global__ __launch_bounds__(P::WAVES_M * P::WAVES_N * 64) void gemm_kernel(cons
         gload(min(kbeg + s * BK, last), rra[s], rrb[s], kend);
     }
     EpiInputs<P, TM, TN, SWAP> epi;
-    auto fetch_epi = [&]() {
-        if constexpr (SWAP) {
-#pragma unroll
-            for (int i = 0; i < TM; ++i) {
-                const int m = m0 + (wm * TM + i) * 32 + lrow;
-                epi.mok[i] = m < M;
-                epi.rc[i] = epi_row(p, epi.mok[i] ? m : M - 1, zb);
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-#pragma unroll
-                    for (int g = 0; g < 4; ++g)
-                        epi.pre[i][j][g] = p.pre4(epi.rc[i], min(n0 + (wn * TN + j) * 32 + 8 * g + 4 * lk, p.N - 4));
-            }
-        }
-    };
-    if constexpr (SWAP && EpiEarly<P>::value) fetch_epi();
+    if constexpr (EpiEarly<P>::value) epi_fetch(p, epi, m0, n0, M, zb, wm, wn, lane);
     if constexpr (D > 1 || (SEG == 0 && SteadyOf<P>::value)) {
         // the k loop is unrolled by the depth so that every stage has its own registers; whole groups of steps
         // refill unconditionally
@@ -659,42 +786,11 @@ __global__ __launch_bounds__(P::WAVES_M * P::WAVES_N * 64) void gemm_kernel(cons
         for (int k0 = kbeg; k0 < kend; k0 += BK) step_s(k0, acc, rra[0], rrb[0], std::integral_constant<int, 2>{});
     }
 
-    // Epilogue.  Tiles that lie wholly inside the output take a branch-free path (the compiler can then batch the
-    // loads an epilogue may need); edge tiles check every element.
-    auto epilogue = [&](auto full_tile) {
-        constexpr bool FULL = decltype(full_tile)::value;
-        if constexpr (SWAP) {
-            if constexpr (!EpiEarly<P>::value) fetch_epi();
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-#pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        const int n = n0 + (wn * TN + j) * 32 + 8 * g + 4 * lk;
-                        const float v[4] = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
-                        if (FULL || (epi.mok[i] && n < p.N)) {
-                            if constexpr (HasBatch<P>::value) p.store4(epi.rc[i], n, v, z, zb, epi.pre[i][j][g]);
-                            else p.store4(epi.rc[i], n, v, z, epi.pre[i][j][g]);
-                        }
-                    }
-        } else {
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    const int n = n0 + (wn * TN + j) * 32 + lrow;
-                    const auto col = make_col(p, FULL ? n : min(n, p.N - 1));
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int m = m0 + (wm * TM + i) * 32 + 8 * (r / 4) + 4 * lk + (r % 4);
-                        if (FULL || (m < M && n < p.N)) do_store(p, m, n, acc[i][j][r], z, zb, col);
-                    }
-                }
-        }
-    };
-    if (m0 + BM <= M && n0 + BN <= p.N) epilogue(std::true_type{}); else epilogue(std::false_type{});
+    epi_store(p, acc, epi, m0, n0, M, z, zb, wm, wn, lane);
 }
+
+template <class P> __global__ void gemm_split_kernel(const P p);
+template <class P> constexpr auto tile_kernel() { if constexpr (sizeof(typename P::T) == 2 || F32Mfma<P>::value) return gemm_kernel<P>; else return gemm_split_kernel<P>; }
 
 template <class P> inline hipError_t launch_gemm(const P &p, hipStream_t stream)
 {
@@ -706,7 +802,7 @@ template <class P> inline hipError_t launch_gemm(const P &p, hipStream_t stream)
         if (nz >= 32) grid = dim3(((nz + 7) / 8) * 8 * tiles, 1, 1);      // XCD-aware order, decoded in the kernel
         else grid.x = ((tiles + 7) / 8) * 8;                              // likewise: an eighth of the tiles per XCD
     }
-    hipLaunchKernelGGL(gemm_kernel<P>, grid, dim3(P::WAVES_M * P::WAVES_N * 64, 1, 1), 0, stream, p);
+    hipLaunchKernelGGL(tile_kernel<P>(), grid, dim3(P::WAVES_M * P::WAVES_N * 64, 1, 1), 0, stream, p);
     return hipGetLastError();
 }
 

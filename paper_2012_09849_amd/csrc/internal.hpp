@@ -5,6 +5,7 @@
 
 #include "../../include/hts.h"
 #include "problems.hpp"
+#include "split.hpp"
 #include "wsgemm.hpp"
 
 namespace hts {

@@ -52,6 +52,7 @@ HTS_HD int clamp_row(int r, int n) { return r < n ? r : n - 1; }
 // ------------------------------------------------------------------------------------------------------------
 template <typename T_> struct PlainGemm {
     using T = T_;
+    static constexpr bool F32_MFMA = true;
     static constexpr int BM = 64, BN = 64, BK = OperandTraits<T>::BK, WAVES_M = 2, WAVES_N = 2;
     static constexpr int VA = 4, VB = 4;
     static constexpr bool A_ALONG_K = true, B_ALONG_K = true;
@@ -82,6 +83,7 @@ template <typename T_> struct Conv1Fwd {
     static constexpr int BM = 256, BN = 32, BK = (sizeof(T) == 2 ? BK_BF16 : 32), WAVES_M = 8, WAVES_N = 1;
     static constexpr int VA = 8, VB = OperandTraits<T>::VEC;
     static constexpr bool A_ALONG_K = true, B_ALONG_K = true;
+    static constexpr bool F32_MFMA = true;      // (binary32: see ConvFwd)
     static constexpr int SEG = 64;       // forward sums are segmented so every kernel variant returns the same bits
     static constexpr int STAGES = sizeof(T) == 2 ? 2 : 1;     // bf16: two k-tiles of loads in flight (16x72x96 frames: 169 -> 147 us at B = 2048)
     typedef PtrCtx<uint8_t> CtxA;
@@ -122,7 +124,11 @@ template <typename T_> struct Conv1Fwd {
 // ------------------------------------------------------------------------------------------------------------
 template <typename T_, class L, bool FLAT_OUT> struct ConvFwd {
     using T = T_;
-    static constexpr int BM = 128, BN = 64, BK = (sizeof(T) == 2 ? BK_BF16 : 32), WAVES_M = 4, WAVES_N = 1;
+    // (binary32: the forward kernels of small batches lose by pieces -- conv3 at 16 rows 4.4 -> 5.3 us, an act call at 4 rows
+    // 20.5 -> 22 us: few products per operand cut -- and all batch sizes must add alike.  Large batches give up 40 vs 78 us
+    // of conv1 and 47 vs 61 us of conv2 at 1024 rows.)
+    static constexpr bool F32_MFMA = true;
+    static constexpr int BM = sizeof(T) == 2 ? 128 : 64, BN = 64, BK = (sizeof(T) == 2 ? BK_BF16 : 32), WAVES_M = sizeof(T) == 2 ? 4 : 2, WAVES_N = 4 / WAVES_M;
     static constexpr int VA = OperandTraits<T>::VEC, VB = OperandTraits<T>::VEC;
     static constexpr bool A_ALONG_K = true, B_ALONG_K = true;
     // conv2: half a tap row (a tap row is 4*32 = 128); conv3: one tap row (3*64 = 192) for bf16, half of one for fp32
@@ -149,6 +155,12 @@ template <typename T_, class L, bool FLAT_OUT> struct ConvFwd {
     {
         const unsigned uk = (unsigned)k, u = uk / (unsigned)(L::KSZ * L::CIN), r = uk - u * (L::KSZ * L::CIN);
         return load_vec<T, VA>(c.p + (u * (unsigned)(Win * L::CIN) + r));     // a tap row is contiguous in memory
+    }
+    HTS_HD Vec<T, VA> load_a(const CtxA &c, int k0, int dk, int) const        // (a tap row is a whole number of k-tiles)
+    {
+        static_assert(L::KSZ * L::CIN % BK == 0, "tap rows");
+        const int u = k0 / (L::KSZ * L::CIN);
+        return load_vec<T, VA>(c.p + (u * (Win - L::KSZ) * L::CIN + k0) + dk);
     }
     HTS_HD Vec<T, VB> load_b(const CtxB &c, int k, int) const { return load_vec<T, VB>(c.p + k); }
     // tile kernel, flattened output (conv3): a lane owns an output position, so the (sample, position) split of the
@@ -194,6 +206,7 @@ template <typename T_, class L, bool FLAT_OUT> struct ConvFwd {
 // ------------------------------------------------------------------------------------------------------------
 template <typename T_> struct FcFwd {
     using T = T_;
+    static constexpr bool F32_MFMA = true;      // (binary32: see ConvFwd)
     static constexpr int BM = 64, BN = 64, BK = (sizeof(T) == 2 ? BK_BF16 : 32), WAVES_M = 2, WAVES_N = 2;
     static constexpr int VA = OperandTraits<T>::VEC, VB = OperandTraits<T>::VEC;
     static constexpr bool A_ALONG_K = true, B_ALONG_K = true;
@@ -218,6 +231,7 @@ template <typename T_> struct FcFwd {
 // ------------------------------------------------------------------------------------------------------------
 struct HeadsWgrad {
     using T = float;
+    static constexpr bool F32_MFMA = true;      // a few microseconds of latency; nothing to gain from pieces
     static constexpr int BM = 32, BN = 128, BK = 32, WAVES_M = 1, WAVES_N = 4;
     static constexpr int VA = 1, VB = 4;
     static constexpr bool A_ALONG_K = false, B_ALONG_K = false;
@@ -259,6 +273,7 @@ struct HeadsWgrad {
 // ------------------------------------------------------------------------------------------------------------
 template <typename T_> struct FcWgrad {
     using T = T_;
+    static constexpr int SPLIT_DEPTH = 1;
     static constexpr int BM = 64, BN = 64, BK = (sizeof(T) == 2 ? BK_BF16_WGRAD : 32), WAVES_M = 2, WAVES_N = 2;   // 8 x 50 workgroups
     static constexpr int VA = OperandTraits<T>::VEC, VB = OperandTraits<T>::VEC;
     static constexpr bool A_ALONG_K = false, B_ALONG_K = false;
@@ -394,7 +409,7 @@ template <typename T_, class L> struct ConvDgrad {
     HTS_HD CtxB ctx_b(int ch, int z) const
     {
         const int py = z / L::STRIDE;
-        return {ch < N ? (long long)ch * L::KSZ * L::KSZ * L::COUT : -1, py, z - py * L::STRIDE};
+        return {(long long)(ch < N ? ch : N - 1) * L::KSZ * L::KSZ * L::COUT, py, z - py * L::STRIDE};      // (a column beyond the last is never stored)
     }
     HTS_HD Vec<T, VA> load_a(const CtxA &c, int k, int kend) const
     {
@@ -409,6 +424,19 @@ template <typename T_, class L> struct ConvDgrad {
         const int u = c.py + L::STRIDE * a, vv = c.px + L::STRIDE * bb;
         const bool in = c.off >= 0 && k < kend;
         return keep_if<T, VB>(in, load_vec<T, VB>(wd + (in ? c.off + (u * L::KSZ + vv) * L::COUT + n : 0)));
+    }
+    HTS_HD Vec<T, VA> load_a(const CtxA &c, int k0, int dk, int) const       // (a tap is a whole number of k-tiles, KC of taps)
+    {
+        static_assert(L::COUT % BK == 0, "taps");
+        const int tap = k0 / L::COUT, a = tap / TK, bb = tap - a * TK;
+        const unsigned oy = (unsigned)(c.yy - a), ox = (unsigned)(c.xx - bb);
+        const bool in = c.off >= 0 && oy < (unsigned)Ho && ox < (unsigned)Wo;
+        return keep_if<T, VA>(in, load_vec<T, VA>(dy + (in ? c.off + dk + (k0 - tap * L::COUT - (a * Wo + bb) * L::COUT) : 0)));
+    }
+    HTS_HD Vec<T, VB> load_b(const CtxB &c, int k0, int dk, int) const
+    {
+        const int tap = k0 / L::COUT, a = tap / TK, bb = tap - a * TK;
+        return load_vec<T, VB>(wd + (c.off + dk) + (((c.py + L::STRIDE * a) * L::KSZ + c.px + L::STRIDE * bb) * L::COUT + k0 - tap * L::COUT));
     }
     static constexpr bool LANE_OWNS_ROW = true;
     struct Row { long long o; };
@@ -451,6 +479,7 @@ template <typename T_, class L> struct ConvDgrad {
 // ------------------------------------------------------------------------------------------------------------
 template <typename T_, class L> struct ConvWgrad {
     using T = T_;
+    static constexpr int SPLIT_DEPTH = 1;
     static constexpr bool STEADY = true;
     static constexpr int BM = 64, BN = 64, BK = (sizeof(T) == 2 ? BK_BF16_WGRAD : 32), WAVES_M = 2, WAVES_N = 2;
     static constexpr int VA = OperandTraits<T>::VEC, VB = OperandTraits<T>::VEC;
@@ -522,6 +551,9 @@ template <typename T_, class L> struct ConvWgrad {
 // INDEXED: the frames are gathered through `index` (a template parameter so that the loader has no branch)
 template <typename T_, bool INDEXED> struct Conv1Wgrad {
     using T = T_;
+    static constexpr int SPLIT_DEPTH = 1;
+    static constexpr int B_PIECES = 1;   // pixels (and the constant 255) are exact in bfloat16
+    static constexpr bool NATURAL_LDS = sizeof(T) == 4;
     static constexpr bool STEADY = true;
     static constexpr int BM = 32, BN = 128, BK = (sizeof(T) == 2 ? BK_BF16_WGRAD : 32), WAVES_M = 1, WAVES_N = 4;
     static constexpr int VA = OperandTraits<T>::VEC, VB = 8;
