@@ -219,15 +219,14 @@ __device__ __forceinline__ float lane_value(float x, int src)
 }
 
 // ------------------------------------------------------------------------------------------------------------
-// heads: one wavefront per sample.  Lane j (< A) ends up holding logit j; every lane holds the value.
+// heads: the policy and value heads of a sample, then its action (actor) or its loss gradient (learner)
 // ------------------------------------------------------------------------------------------------------------
 struct HeadsArgs {
     const float *fc_part;      // h = relu(fc_bias + sum_g fc_part[g][B][512]), groups added in order, is formed here ...
     const float *fc_bias;
-    float *h_out;              // ... and written out for the backward pass when not null
+    float *h_out;              // ... and (learner) written out for the backward pass
     int nseg;                  // number of groups
     const float *wpi, *bpi, *wv, *bv;
-    const float *logits_in;    // optional: skip the head product and sample from these
     int B, A;
     // actor outputs
     uint64_t seed; uint32_t step; int env_offset;
@@ -238,248 +237,270 @@ struct HeadsArgs {
     bf16_t *dh16;              // not null: dL/dh is written here in bfloat16 (the operand type of the FC layer's backward
 };                             // kernels, which then fetch half the bytes; they rounded it the same way as they loaded it)
 
-template <bool LEARN>
-__global__ __launch_bounds__(256) void heads_kernel(const HeadsArgs a)
+// The last steps of one sample, by one wavefront: lane j (< A) holds logit j.
+// A wavefront runs alone on its SIMD here, so every dependent instruction costs its full latency, and the steps over
+// the actions are kept to one instruction each: the maximum by lane shifts (six steps), the running sums by a shift
+// and an add per action; lanes >= A hold neutral values (-inf for the maximum, +0 for the sums).  (Phase stamps:
+// with one lane read and two or three instructions per action 2.3 of the kernel's 9.6 thousand clock ticks were
+// spent here.)
+__device__ __forceinline__ void sample_action(const HeadsArgs &a, int b, int lane, float mylogit, float u01)
 {
-    extern __shared__ float heads_lds[];          // [wavefronts of the workgroup][A][65]
-    const int lane = threadIdx.x & 63;
-    const int b = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);     // one sample per wavefront
-    if (b >= a.B) return;                        // whole wavefront leaves together; no block-level barrier below
     const int A = a.A;
-
-    float hv[8];
-    constexpr int HEAD_CHUNK = 20;
-    float wv8[8], wrow[HEAD_CHUNK][8];     // value head and (up to) HEAD_CHUNK rows of pi.w: this lane's 8 columns
-    float mylogit = 0.0f, value = 0.0f;
-    float u01 = 0.0f;          // the sample's uniform: needs nothing from memory, so it is formed while the loads travel
-    if constexpr (!LEARN) u01 = seeded_uniform(a.seed, (uint32_t)(a.env_offset + b), a.step);
-    if (a.logits_in) {
-        if (lane < A) mylogit = a.logits_in[(long long)b * A + lane];
-    } else {
-        // Everything this wavefront needs from the weights is requested before the FC partial sums are waited for
-        // (they are independent): value head, FC bias and the first HEAD_CHUNK rows of pi.w.
-        float bv8[8];
-        const float head_bias = lane < A ? a.bpi[lane] : 0.0f, value_bias = a.bv[0];
-        load_vec(a.wv + lane * 8, wv8);
-        load_vec(a.fc_bias + lane * 8, bv8);
-#pragma unroll
-        for (int q = 0; q < HEAD_CHUNK; ++q)
-            if (q < A) load_vec(a.wpi + (long long)q * 512 + lane * 8, wrow[q]);
-        {
-            // add the FC layer's group sums in group order, then bias + ReLU
-#pragma unroll
-            for (int i = 0; i < 8; ++i) hv[i] = 0.0f;
-            const float *src = a.fc_part + (long long)b * 512 + lane * 8;
-            const long long sstride = (long long)a.B * 512;
-            for (int s = 0; s < a.nseg; s += 8) {          // eight groups' loads in flight, added in group order
-                float pv[8][8];
-#pragma unroll
-                for (int q = 0; q < 8; ++q)
-                    if (s + q < a.nseg) load_vec(src + (s + q) * sstride, pv[q]);
-#pragma unroll
-                for (int q = 0; q < 8; ++q)
-                    if (s + q < a.nseg)
-#pragma unroll
-                        for (int i = 0; i < 8; ++i) hv[i] += pv[q][i];
-            }
-#pragma unroll
-            for (int i = 0; i < 8; ++i) { const float y = hv[i] + bv8[i]; hv[i] = y > 0.0f ? y : 0.0f; }
-            if (a.h_out) {
-                f32x4 o0, o1;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) { o0[i] = hv[i]; o1[i] = hv[4 + i]; }
-                f32x4 *dst = reinterpret_cast<f32x4 *>(a.h_out + (long long)b * 512 + lane * 8);
-                dst[0] = o0; dst[1] = o1;
-            }
-        }
-        // A dot products of length 512 for the logits: every lane forms its 8-element partial of each, the partials
-        // go through this wavefront's LDS panel [A][65] and are added row by row in a fixed order (no barrier is
-        // needed because a wavefront's LDS operations execute in order).  The value head is one more dot product,
-        // reduced by a butterfly.
-        float *panel = heads_lds + (threadIdx.x >> 6) * A * 65;
-        {
-            float sv = 0.0f;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) sv = __builtin_fmaf(hv[i], wv8[i], sv);
-            value = wave_sum(sv) + value_bias;
-        }
-        for (int j0 = 0; j0 < A; j0 += HEAD_CHUNK) {
-            if (j0 > 0) {
-#pragma unroll
-                for (int q = 0; q < HEAD_CHUNK; ++q)
-                    if (j0 + q < A) load_vec(a.wpi + (long long)(j0 + q) * 512 + lane * 8, wrow[q]);
-            }
-#pragma unroll
-            for (int q = 0; q < HEAD_CHUNK; ++q)
-                if (j0 + q < A) {
-                    float sj = 0.0f;
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) sj = __builtin_fmaf(hv[i], wrow[q][i], sj);
-                    panel[(j0 + q) * 65 + lane] = sj;
-                }
-        }
-        __builtin_amdgcn_wave_barrier();
-        // row sums: with A <= 32 (<= 16) rows, two (four) lanes share a row, each adding a contiguous half (quarter)
-        // in lane order; the parts are then added in part order
-        const int parts = A <= 16 ? 4 : (A <= 32 ? 2 : 1);
-        const int rows_per = 64 / parts, len = 64 / parts;
-        const int row = lane & (rows_per - 1), part = lane / rows_per;
-        float rowsum = 0.0f;
-        if (row < A) {
-            const float *rp = panel + row * 65 + part * len;
-            for (int t = 0; t < len; t += 16) {
-                float tv[16];
-#pragma unroll
-                for (int u = 0; u < 16; ++u) tv[u] = rp[t + u];
-#pragma unroll
-                for (int u = 0; u < 16; ++u) rowsum += tv[u];
-            }
-        }
-        float tot = rowsum;
-        for (int q = 1; q < parts; ++q) tot += __shfl(rowsum, row + q * rows_per, 64);
-        if (lane < A) mylogit = tot + head_bias;
+    const float m = wave_max(lane < A ? mylogit : -INFINITY);
+    // binary32 inverse CDF: lane j evaluates e_j once; the running sums c_j are formed sequentially in index order
+    // along the lanes; lane j keeps c_j, and the action is the
+    // first j with c_j > u * c_{A-1} (A-1 if there is none)
+    // (c_j = c_{j-1} + e_j along the lanes: every step each lane takes its left neighbour's value -- lane 0 takes
+    // +0 -- and adds its own e_j.  After k steps lanes 0..k hold their c_j and keep it, so A - 1 steps of one
+    // instruction give every lane its running sum in index order; lane reads into scalar registers cost three
+    // instructions per action.)
+    const float ej = lane < A ? sampler_exp(mylogit - m) : 0.0f;
+    float mine = ej;
+    for (int k = 1; k < A; ++k)
+        mine = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(mine), 0x138 /* wave_shr:1 */, 0xF, 0xF, true)) + ej;
+    const float total = lane_value(mine, A - 1);
+    const float thr = u01 * total;
+    const unsigned long long above = __ballot(lane < A && mine > thr);
+    const int act = above ? __ffsll((long long)above) - 1 : A - 1;
+    const float la = lane_value(mylogit, act);
+    if (lane == 0) {
+        a.actions[b] = act;
+        a.logp[b] = (la - m) - logf(total);
     }
+    if (a.logits_out && lane < A) a.logits_out[(long long)b * A + lane] = mylogit;
+}
 
-    // A wavefront runs alone on its SIMD here, so every dependent instruction costs its full latency, and the steps over
-    // the actions are kept to one instruction each: the maximum by lane shifts (six steps), the running sums by a shift
-    // and an add per action; lanes >= A hold neutral values (-inf for the maximum, +0 for the sums).  (Phase stamps:
-    // with one lane read and two or three instructions per action 2.3 of the kernel's 9.6 thousand clock ticks were
-    // spent here.)
-    const float lg = lane < A ? mylogit : -INFINITY;
-    const float m = wave_max(lg);
-
-    if constexpr (!LEARN) {
-        // binary32 inverse CDF: lane j evaluates e_j once; the running sums c_j are formed sequentially in index order
-        // along the lanes; lane j keeps c_j, and the action is the
-        // first j with c_j > u * c_{A-1} (A-1 if there is none)
-        // (c_j = c_{j-1} + e_j along the lanes: every step each lane takes its left neighbour's value -- lane 0 takes
-        // +0 -- and adds its own e_j.  After k steps lanes 0..k hold their c_j and keep it, so A - 1 steps of one
-        // instruction give every lane its running sum in index order; lane reads into scalar registers cost three
-        // instructions per action.)
-        const float ej = lane < A ? sampler_exp(mylogit - m) : 0.0f;
-        float mine = ej;
-        for (int k = 1; k < A; ++k)
-            mine = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(mine), 0x138 /* wave_shr:1 */, 0xF, 0xF, true)) + ej;
-        const float total = lane_value(mine, A - 1);
-        const float thr = u01 * total;
-        const unsigned long long above = __ballot(lane < A && mine > thr);
-        const int act = above ? __ffsll((long long)above) - 1 : A - 1;
-        const float la = lane_value(mylogit, act);
-        if (lane == 0) {
-            a.actions[b] = act;
-            a.logp[b] = (la - m) - logf(total);
-            if (a.values) a.values[b] = value;
-        }
-        if (a.logits_out && lane < A) a.logits_out[(long long)b * A + lane] = mylogit;
+// policy terms of one sample's loss: lane j (< A) receives dL/dlogit j (other lanes 0)
+__device__ __forceinline__ float policy_gradient(const HeadsArgs &a, int b, int lane, float mylogit)
+{
+    const int A = a.A;
+    const float m = wave_max(lane < A ? mylogit : -INFINITY);
+    const long long row = a.la.index ? a.la.index[b] : b;
+    const float e = lane < A ? expf(mylogit - m) : 0.0f;
+    const float lse = m + logf(wave_sum(e));
+    const float lsm = lane < A ? mylogit - lse : 0.0f;
+    const float p = lane < A ? expf(lsm) : 0.0f;
+    const float ent = -wave_sum(p * lsm);
+    const int act = a.la.actions[row];
+    const float logp = lane_value(lsm, act);
+    const float adv = a.la.adv[row];
+    const float invB = 1.0f / (float)a.B;
+    float dlogp, pi_term, clipped = 0.0f, kl = 0.0f;
+    if (a.la.algo == HTS_ALGO_A2C) {
+        pi_term = -logp * adv;
+        dlogp = -adv * invB;
+    } else if (a.la.algo == HTS_ALGO_A2C_TIS) {
+        // truncated importance weight, a constant in the derivative
+        const float old = a.la.old_logp[row];
+        const float rho = expf(logp - old);
+        const float w = fminf(rho, a.la.rho_bar);
+        pi_term = -w * logp * adv;
+        dlogp = -w * adv * invB;
+        clipped = rho > a.la.rho_bar ? 1.0f : 0.0f;
+        kl = old - logp;
     } else {
-        const long long row = a.la.index ? a.la.index[b] : b;
-        const float e = lane < A ? expf(mylogit - m) : 0.0f;
-        const float lse = m + logf(wave_sum(e));
-        const float lsm = lane < A ? mylogit - lse : 0.0f;
-        const float p = lane < A ? expf(lsm) : 0.0f;
-        const float ent = -wave_sum(p * lsm);
-        const int act = a.la.actions[row];
-        const float logp = lane_value(lsm, act);
-        const float adv = a.la.adv[row], R = a.la.ret[row];
-        const float invB = 1.0f / (float)a.B;
-        float dlogp, pi_term, clipped = 0.0f, kl = 0.0f;
-        if (a.la.algo == HTS_ALGO_A2C) {
-            pi_term = -logp * adv;
-            dlogp = -adv * invB;
-        } else if (a.la.algo == HTS_ALGO_A2C_TIS) {
-            // truncated importance weight, a constant in the derivative
-            const float old = a.la.old_logp[row];
-            const float rho = expf(logp - old);
-            const float w = fminf(rho, a.la.rho_bar);
-            pi_term = -w * logp * adv;
-            dlogp = -w * adv * invB;
-            clipped = rho > a.la.rho_bar ? 1.0f : 0.0f;
-            kl = old - logp;
-        } else {
-            const float old = a.la.old_logp[row];
-            const float rho = expf(logp - old);
-            const float lo = 1.0f - a.la.clip_eps, hi = 1.0f + a.la.clip_eps;
-            const float rc = fminf(fmaxf(rho, lo), hi);
-            pi_term = -fminf(rho * adv, rc * adv);
-            const bool cut = (adv > 0.0f && rho > hi) || (adv < 0.0f && rho < lo);
-            dlogp = cut ? 0.0f : -adv * rho * invB;
-            clipped = (rho > hi || rho < lo) ? 1.0f : 0.0f;
-            kl = old - logp;
+        const float old = a.la.old_logp[row];
+        const float rho = expf(logp - old);
+        const float lo = 1.0f - a.la.clip_eps, hi = 1.0f + a.la.clip_eps;
+        const float rc = fminf(fmaxf(rho, lo), hi);
+        pi_term = -fminf(rho * adv, rc * adv);
+        const bool cut = (adv > 0.0f && rho > hi) || (adv < 0.0f && rho < lo);
+        dlogp = cut ? 0.0f : -adv * rho * invB;
+        clipped = (rho > hi || rho < lo) ? 1.0f : 0.0f;
+        kl = old - logp;
+    }
+    const float dl = lane < A ? dlogp * ((lane == act ? 1.0f : 0.0f) - p) + a.la.ent_coef * invB * p * (lsm + ent)
+                              : 0.0f;
+    if (lane < A) a.dz[(long long)b * (A + 1) + lane] = dl;
+    if (lane == 0) {
+        float *t = a.terms + (long long)b * N_TERMS;
+        t[0] = pi_term; t[2] = ent; t[3] = clipped; t[4] = kl;
+    }
+    return dl;
+}
+
+// value term of one sample's loss; returns dL/dvalue
+__device__ __forceinline__ float value_gradient(const HeadsArgs &a, int b, int lane, float value)
+{
+    const long long row = a.la.index ? a.la.index[b] : b;
+    const float R = a.la.ret[row], invB = 1.0f / (float)a.B;
+    float v_term = (R - value) * (R - value), dv_row = 2.0f * (value - R);
+    if (a.la.value_clip > 0.0f) {
+        // clipped value loss: the larger of the plain term and the term of the value held within a radius of
+        // the stored estimate; a value held at the radius does not move with the network's output
+        const float ov = a.la.old_values[row];
+        const float d = value - ov;
+        const float dc = fminf(fmaxf(d, -a.la.value_clip), a.la.value_clip);
+        const float vc = ov + dc;
+        const float c_term = (vc - R) * (vc - R);
+        if (c_term > v_term) {
+            v_term = c_term;
+            dv_row = dc == d ? 2.0f * (vc - R) : 0.0f;
         }
-        const float dl = lane < A ? dlogp * ((lane == act ? 1.0f : 0.0f) - p) + a.la.ent_coef * invB * p * (lsm + ent)
-                                  : 0.0f;
-        float v_term = (R - value) * (R - value), dv_row = 2.0f * (value - R);
-        if (a.la.value_clip > 0.0f) {
-            // clipped value loss: the larger of the plain term and the term of the value held within a radius of
-            // the stored estimate; a value held at the radius does not move with the network's output
-            const float ov = a.la.old_values[row];
-            const float d = value - ov;
-            const float dc = fminf(fmaxf(d, -a.la.value_clip), a.la.value_clip);
-            const float vc = ov + dc;
-            const float c_term = (vc - R) * (vc - R);
-            if (c_term > v_term) {
-                v_term = c_term;
-                dv_row = dc == d ? 2.0f * (vc - R) : 0.0f;
+    }
+    const float dv = a.la.vf_coef * dv_row * invB;
+    if (lane == 0) {
+        a.dz[(long long)b * (a.A + 1) + a.A] = dv;
+        a.terms[(long long)b * N_TERMS + 1] = v_term;
+    }
+    return dv;
+}
+
+// One workgroup of 8 wavefronts per S samples.  Thread t owns hidden unit t: it adds the unit's FC group sums, bias and ReLU
+// into LDS.  A wavefront then forms its share of the A + 1 dot products of every sample, at most HEADS_ROWS at a time (lane l:
+// the 8-element partial of units 8 l .. 8 l + 7, into the sample's LDS panel [A + 1][65]); wavefront s adds the panel's rows
+// of sample s in a fixed order and finishes its policy head, wavefront 4 + s its value head.  (learner) Thread t
+// forms dL/d(pre-activation) of unit t.  Everything a workgroup needs from memory is requested before anything is waited for.
+// What bounds it: with few samples one memory round trip and the chain of dependent steps (one wavefront per sample did all
+// of it alone, a few thousand instructions at full latency each: 5.0 us at 16 rows against 3.9); with many the fetches --
+// the heads are 40 KB a workgroup, whatever S (actor at 1024 / 4096 rows, with
+// one wavefront per sample and a fetch of its own: 6.9 / 18 us, now 5.7 / 9.0; learner at 2048: 18.4, now 12.8).
+constexpr int HEADS_WAVES = 8, HEADS_ROWS = 3;
+template <bool LEARN, int S>
+__global__ __launch_bounds__(64 * HEADS_WAVES) void heads_kernel(const HeadsArgs a)
+{
+    __shared__ __attribute__((aligned(16))) float h_lds[S][512], row_lds[S][HTS_MAX_ACTIONS + 4];
+    extern __shared__ float heads_panels[];            // [S][A + 1][65]
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), A = a.A;
+    const int b0 = blockIdx.x * S;
+    float wrow[HEADS_ROWS][8];
+    auto fetch_rows = [&](int j0) {                    // rows j0, j0 + 8, ... of the heads (row A: value head)
+#pragma unroll
+        for (int i = 0; i < HEADS_ROWS; ++i) {
+            const int j = min(j0 + i * HEADS_WAVES, A);
+            load_vec((j < A ? a.wpi + (long long)j * 512 : a.wv) + lane * 8, wrow[i]);
+        }
+    };
+    fetch_rows(w);
+    const long long gstride = (long long)a.B * 512;
+    constexpr int GQ = S > 2 ? 4 : 8;                  // group sums of a unit in flight per sample
+    float pv[S][GQ];
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+        for (int q = 0; q < GQ; ++q) pv[s][q] = a.fc_part[(long long)min(b0 + s, a.B - 1) * 512 + tid + min(q, a.nseg - 1) * gstride];
+    const float bias = a.fc_bias[tid];
+    const float head_bias = lane < A ? a.bpi[lane] : 0.0f, value_bias = a.bv[0];
+    constexpr int HELD = 20;                           // rows of the heads whose column `tid` is held in registers for dL/dh
+    float wcol[LEARN ? HELD : 1], wvt = 0.0f;
+    if constexpr (LEARN) {
+        wvt = a.wv[tid];
+#pragma unroll
+        for (int j = 0; j < HELD; ++j) wcol[j] = a.wpi[min(j, A - 1) * 512 + tid];
+    }
+    float u01 = 0.0f;          // the sample's uniform: needs nothing from memory, so it is formed while the loads travel
+    if constexpr (!LEARN) { if (w < S) u01 = seeded_uniform(a.seed, (uint32_t)(a.env_offset + b0 + w), a.step); }
+    float h[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) {                      // groups added in group order, then bias + ReLU
+        const int b = min(b0 + s, a.B - 1);
+        float x = 0.0f;
+#pragma unroll
+        for (int q = 0; q < GQ; ++q) if (q < a.nseg) x += pv[s][q];
+        for (int q0 = GQ; q0 < a.nseg; q0 += GQ) {
+            float more[GQ];
+#pragma unroll
+            for (int q = 0; q < GQ; ++q) more[q] = a.fc_part[(long long)b * 512 + tid + min(q0 + q, a.nseg - 1) * gstride];
+#pragma unroll
+            for (int q = 0; q < GQ; ++q) if (q0 + q < a.nseg) x += more[q];
+        }
+        x += bias;
+        h[s] = x > 0.0f ? x : 0.0f;
+        h_lds[s][tid] = h[s];
+        if constexpr (LEARN) { if (b0 + s < a.B) a.h_out[(long long)b * 512 + tid] = h[s]; }
+    }
+    __syncthreads();
+    for (int j0 = w; j0 <= A; j0 += HEADS_ROWS * HEADS_WAVES) {
+        if (j0 != w) fetch_rows(j0);
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            const f32x4 h0 = *reinterpret_cast<const f32x4 *>(&h_lds[s][lane * 8]), h1 = *reinterpret_cast<const f32x4 *>(&h_lds[s][lane * 8 + 4]);
+            float d[HEADS_ROWS];
+#pragma unroll
+            for (int i = 0; i < HEADS_ROWS; ++i) {
+                d[i] = 0.0f;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) d[i] = __builtin_fmaf(h0[e], wrow[i][e], d[i]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) d[i] = __builtin_fmaf(h1[e], wrow[i][4 + e], d[i]);
             }
+#pragma unroll
+            for (int i = 0; i < HEADS_ROWS; ++i)
+                if (j0 + i * HEADS_WAVES <= A) heads_panels[(s * (A + 1) + j0 + i * HEADS_WAVES) * 65 + lane] = d[i];
         }
-        const float dv = a.la.vf_coef * dv_row * invB;
-        if (lane < A) a.dz[(long long)b * (A + 1) + lane] = dl;
-        if (lane == 0) {
-            a.dz[(long long)b * (A + 1) + A] = dv;
-            float *t = a.terms + (long long)b * N_TERMS;
-            t[0] = pi_term; t[1] = v_term; t[2] = ent; t[3] = clipped; t[4] = kl;
-        }
-        // dL/d(FC pre-activation) for this lane's 8 hidden units.  With at most HEAD_CHUNK actions the rows of pi.w are
-        // still in the registers the logits were formed from (fetching them a second time was nearly half of what a
-        // wavefront pulls through its L1, and that is what bounds this kernel); same products in the same order.
-        float acc[8];
-        const bool rows_held = !a.logits_in && A <= HEAD_CHUNK;
-        if (!rows_held || a.logits_in) load_vec(a.wv + lane * 8, wv8);
+    }
+    __syncthreads();
+    static_assert(S <= 4 && HEADS_WAVES == 8, "wavefronts 0-3: policy heads, 4-7: value heads");
+    const int ws = w & 3, b = b0 + ws;
+    if (ws < S && b < a.B) {
+        const float *panel = heads_panels + ws * (A + 1) * 65;
+        if (w < 4) {
+            // row sums: with A <= 32 (<= 16) rows, two (four) lanes share a row, each adding a contiguous half (quarter)
+            // in lane order; the parts are then added in part order
+            const int parts = A <= 16 ? 4 : (A <= 32 ? 2 : 1);
+            const int rows_per = 64 / parts, len = 64 / parts;
+            const int row = lane & (rows_per - 1), part = lane / rows_per;
+            float rowsum = 0.0f;
+            if (row < A) {
+                const float *rp = panel + row * 65 + part * len;
+                for (int t = 0; t < len; t += 16) {
+                    float tv[16];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i] = dv * wv8[i];
-        if (rows_held) {
+                    for (int u = 0; u < 16; ++u) tv[u] = rp[t + u];
 #pragma unroll
-            for (int q = 0; q < HEAD_CHUNK; ++q)
-                if (q < A) {
-                    const float dj = lane_value(dl, q);
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) acc[i] = __builtin_fmaf(dj, wrow[q][i], acc[i]);
+                    for (int u = 0; u < 16; ++u) rowsum += tv[u];
                 }
+            }
+            float tot = rowsum;
+            for (int q = 1; q < parts; ++q) tot += __shfl(rowsum, row + q * rows_per, 64);
+            const float logit = lane < A ? tot + head_bias : 0.0f;
+            if constexpr (!LEARN) sample_action(a, b, lane, logit, u01);
+            else {
+                const float dl = policy_gradient(a, b, lane, logit);
+                if (lane < A) row_lds[ws][lane] = dl;
+            }
         } else {
-            for (int j = 0; j < A; ++j) {
-                const float dj = lane_value(dl, j);
-                float w8[8];
-                load_vec(a.wpi + (long long)j * 512 + lane * 8, w8);
-#pragma unroll
-                for (int i = 0; i < 8; ++i) acc[i] = __builtin_fmaf(dj, w8[i], acc[i]);
+            const float value = wave_sum(panel[A * 65 + lane]) + value_bias;
+            if constexpr (!LEARN) { if (lane == 0) a.values[b] = value; }
+            else {
+                const float dv = value_gradient(a, b, lane, value);
+                if (lane == 0) row_lds[ws][A] = dv;
             }
         }
-        f32x4 o0, o1;
+    }
+    if constexpr (LEARN) {
+        __syncthreads();
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            o0[i] = hv[i] > 0.0f ? acc[i] : 0.0f;
-            o1[i] = hv[4 + i] > 0.0f ? acc[4 + i] : 0.0f;
-        }
-        if (a.dh16) {
-            bf16x8 o;
+        for (int s = 0; s < S; ++s) {
+            if (b0 + s >= a.B) break;
+            const float *row = row_lds[s];
+            float acc = row[A] * wvt;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) { o[i] = from_f32<bf16_t>(o0[i]); o[4 + i] = from_f32<bf16_t>(o1[i]); }
-            *reinterpret_cast<bf16x8 *>(a.dh16 + (long long)b * 512 + lane * 8) = o;
-        } else {
-            f32x4 *dst = reinterpret_cast<f32x4 *>(a.dh + (long long)b * 512 + lane * 8);
-            dst[0] = o0; dst[1] = o1;
+            for (int j = 0; j < HELD; ++j) if (j < A) acc = __builtin_fmaf(row[j], wcol[j], acc);
+            for (int j = HELD; j < A; ++j) acc = __builtin_fmaf(row[j], a.wpi[j * 512 + tid], acc);
+            acc = h[s] > 0.0f ? acc : 0.0f;
+            if (a.dh16) a.dh16[(long long)(b0 + s) * 512 + tid] = from_f32<bf16_t>(acc); else a.dh[(long long)(b0 + s) * 512 + tid] = acc;
         }
     }
 }
 
-// Wavefronts per workgroup.  A wavefront fetches about 40 KB (the policy head's weights and its sample's FC partial
-// sums); with few samples one wavefront per workgroup spreads those fetches over as many compute units as there are
-// samples instead of queueing four wavefronts' worth behind one L1.
-static int heads_waves(int rows) { return rows <= 512 ? 1 : 4; }
-static size_t heads_lds_bytes(int A, int waves) { return (size_t)waves * A * 65 * sizeof(float); }
-static hipError_t raise_lds_limit(const void *fn, size_t bytes)
+// sampling alone, from given logits: one wavefront per sample
+__global__ __launch_bounds__(64) void sample_kernel(const HeadsArgs a, const float *__restrict__ logits)
 {
-    return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    const int lane = threadIdx.x, b = blockIdx.x;
+    const float logit = lane < a.A ? logits[(long long)b * a.A + lane] : 0.0f;
+    sample_action(a, b, lane, logit, seeded_uniform(a.seed, (uint32_t)(a.env_offset + b), a.step));
+}
+
+template <bool LEARN> static hipError_t launch_heads(const HeadsArgs &a, hipStream_t stream)
+{
+    // Kernel time at S = 1 / 2 / 4, us: actor 16 rows 3.8/4.2/5.7, 700 4.6/5.6/6.2, 1024 5.7/5.6/6.8, 2048 9.0/8.2/9.3, 4096
+    // 16.2/12.5/9.0 (one slice of FC sums there); learner 512 6.3/6.4/8.9, 1024 10.6/8.6/11.2, 2048 16.8/14.5/12.8: a second
+    // sample per workgroup pays once every compute unit has about four workgroups of its own.
+    const int S = a.A > 32 || a.B <= (LEARN ? 512 : 1024) ? 1 : a.B < (LEARN ? 2048 : 3072) ? 2 : 4;
+    auto kern = S == 1 ? heads_kernel<LEARN, 1> : S == 2 ? heads_kernel<LEARN, 2> : heads_kernel<LEARN, 4>;
+    hipLaunchKernelGGL(kern, dim3((a.B + S - 1) / S), dim3(64 * HEADS_WAVES), (size_t)S * (a.A + 1) * 65 * sizeof(float), stream, a);
+    return hipGetLastError();
 }
 
 static void heads_network(const Ctx &c, HeadsArgs &a)
@@ -495,16 +516,15 @@ hipError_t launch_heads_act(Ctx &c, const float *logits_in, uint64_t seed, uint3
 {
     SiteTimer tm(c, SITE_HEADS_ACT);
     HeadsArgs a = {};
-    a.logits_in = logits_in;
-    if (!logits_in) heads_network(c, a);
     a.B = N; a.A = c.g.A;
     a.seed = seed; a.step = step; a.env_offset = env_offset;
     a.actions = actions; a.logp = logp; a.values = values; a.logits_out = logits_out;
-    const int wv = heads_waves(N);
-    const size_t lds = heads_lds_bytes(c.g.A, wv);
-    if (lds > 65536) { const hipError_t e = raise_lds_limit(reinterpret_cast<const void *>(heads_kernel<false>), lds); if (e != hipSuccess) return e; }
-    hipLaunchKernelGGL(heads_kernel<false>, dim3((N + wv - 1) / wv), dim3(64 * wv), lds, c.stream, a);
-    return hipGetLastError();
+    if (logits_in) {
+        hipLaunchKernelGGL(sample_kernel, dim3(N), dim3(64), 0, c.stream, a, logits_in);
+        return hipGetLastError();
+    }
+    heads_network(c, a);
+    return launch_heads<false>(a, c.stream);
 }
 
 hipError_t launch_heads_learn(Ctx &c, const LossArgs &la, int B)
@@ -517,11 +537,7 @@ hipError_t launch_heads_learn(Ctx &c, const LossArgs &la, int B)
     a.la = la;
     a.dz = c.ws.dz; a.terms = c.ws.terms;
     if (c.desc.precision == HTS_PRECISION_BF16) a.dh16 = reinterpret_cast<bf16_t *>(c.ws.dh); else a.dh = c.ws.dh;
-    const int wv = heads_waves(B);
-    const size_t lds = heads_lds_bytes(c.g.A, wv);
-    if (lds > 65536) { const hipError_t e = raise_lds_limit(reinterpret_cast<const void *>(heads_kernel<true>), lds); if (e != hipSuccess) return e; }
-    hipLaunchKernelGGL(heads_kernel<true>, dim3((B + wv - 1) / wv), dim3(64 * wv), lds, c.stream, a);
-    return hipGetLastError();
+    return launch_heads<true>(a, c.stream);
 }
 
 // ------------------------------------------------------------------------------------------------------------
