@@ -138,8 +138,13 @@ extern "C" int32_t hts_create(const hts_net_desc *desc, int32_t max_act_batch, i
     c.tile16_below = 128;
     if (const char *t16 = getenv("HTS_TILE16_BELOW")) c.tile16_below = atoi(t16);   // tuning knob, same bits either way
     if (const char *fr = getenv("HTS_FC_FOLD_ROWS")) c.fc_fold_rows = atoi(fr);   // tuning knob, same bits either way
-    c.conv1_slab_rows = 256;
-    if (const char *sr = getenv("HTS_CONV1_SLAB_ROWS")) c.conv1_slab_rows = atoi(sr);   // tuning knob, same bits either way
+    // conv1 by the slab kernel against the wave-per-segment kernel, us: 16x72x96 frames 16 rows 6.5 / 5.6 (196 workgroups), 24
+    // rows 6.8 / 8 (two rounds of workgroups from 21 rows on), 64 rows 7.7 / 16.8; 4x84x84 32 rows 5.5 / 4.8, 64 6.0 / 6.2, 100 6.9 / 9.5
+    c.conv1_slab_rows = g.C == 16 ? 21 : 64;
+    c.conv1_wgrad_slab_rows = 256;
+    // (against the wave-per-segment kernel, us: 4x84x84 frames 32 rows 6.7 / 6.6, 64 6.9 / 9.9; 16x72x96 32 14.8 / 14.1, 64 15.2 / 21.3)
+    c.conv1_wgrad_image_rows = 33;
+    if (const char *sr = getenv("HTS_CONV1_SLAB_ROWS")) c.conv1_slab_rows = c.conv1_wgrad_slab_rows = atoi(sr);   // tuning knob, same bits either way
     c.ws = Workspace();
     Carver size_pass;
     carve(c, size_pass);

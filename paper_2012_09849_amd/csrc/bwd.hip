@@ -606,10 +606,14 @@ template <typename T> static hipError_t backward_t(Ctx &c, const uint8_t *obs, c
     // partial buffers of the three conv weight gradients live side by side in ws.part
     const SplitK s3 = split_for((long long)B * g.P3, MAXZ3), s2 = split_for((long long)B * g.P2, MAXZ2),
                  s1 = split_for((long long)B * g.P1, MAXZ1);
+    const bool lds1 = sizeof(T) == 2 && ((B >= c.conv1_wgrad_slab_rows && conv1_wgrad_slab_fits(g, obs)) || (B >= c.conv1_wgrad_image_rows && conv1_wgrad_image_fits(g, obs)));
+    // conv2/conv3 weight gradients, us, wave-per-segment / tile kernel: bf16 at 16 rows of 84x84 frames 8.8 / 5.4 and 10.1 / 5.9,
+    // at 128 rows 12.0 / 5.8 and 12.1 / 6.6; binary32 at 16 rows 9.1 / 10.5 and 8.7 / 11.3, at 96 rows 14.0 / 13.8 and 13.1 / 12.8
+    const bool smallw = small && sizeof(T) == 4;
     int spg3 = 0, spg2 = 0, spg1 = 0;
-    const int nz3 = small ? groups_for((long long)B * g.P3, &spg3, 32, 8) : s3.nz;
-    const int nz2 = small ? groups_for((long long)B * g.P2, &spg2, 32, 8) : s2.nz;
-    int nz1 = small ? groups_for((long long)B * g.P1, &spg1, 56, 4) : s1.nz;   // long reduction, tiny output
+    const int nz3 = smallw ? groups_for((long long)B * g.P3, &spg3, 32, 8) : s3.nz;
+    const int nz2 = smallw ? groups_for((long long)B * g.P2, &spg2, 32, 8) : s2.nz;
+    int nz1 = small && !lds1 ? groups_for((long long)B * g.P1, &spg1, 56, 4) : s1.nz;   // long reduction, tiny output
     float *part3 = c.ws.part;
     float *part2 = part3 + (size_t)nz3 * 64 * 577;
     float *part1 = part2 + (size_t)nz2 * 64 * 513;
@@ -621,7 +625,8 @@ template <typename T> static hipError_t backward_t(Ctx &c, const uint8_t *obs, c
         p.dPo = FastDiv::make(g.P3); p.dWo = FastDiv::make(g.W3);
         {
             SiteTimer tm(c, SITE_CONV3_WGRAD);
-            e = small ? launch_wsgemm<ConvWgrad<T, Layer3>, 4, 64, false>(p, c.stream, spg3) : launch_gemm(p, c.stream);
+            if constexpr (sizeof(T) == 4) e = smallw ? launch_wsgemm<ConvWgrad<T, Layer3>, 4, 64, false>(p, c.stream, spg3) : launch_gemm(p, c.stream);
+            else e = launch_gemm(p, c.stream);
         }
         if (e != hipSuccess) return e;
     }
@@ -660,7 +665,8 @@ template <typename T> static hipError_t backward_t(Ctx &c, const uint8_t *obs, c
         p.dPo = FastDiv::make(g.P2); p.dWo = FastDiv::make(g.W2);
         {
             SiteTimer tm(c, SITE_CONV2_WGRAD);
-            e = small ? launch_wsgemm<ConvWgrad<T, Layer2>, 4, 64, false>(p, c.stream, spg2) : launch_gemm(p, c.stream);
+            if constexpr (sizeof(T) == 4) e = smallw ? launch_wsgemm<ConvWgrad<T, Layer2>, 4, 64, false>(p, c.stream, spg2) : launch_gemm(p, c.stream);
+            else e = launch_gemm(p, c.stream);
         }
         if (e != hipSuccess) return e;
     }
@@ -696,8 +702,8 @@ template <typename T> static hipError_t backward_t(Ctx &c, const uint8_t *obs, c
             SiteTimer tm(c, SITE_CONV1_WGRAD);
             return small ? launch_wsgemm<decltype(p), 4, 64, false>(p, c.stream, spg1) : launch_gemm(p, c.stream);
         };
-        if (!small && sizeof(T) == 2 && B >= c.conv1_slab_rows && conv1_wgrad_slab_fits(g, obs) && conv1_wgrad_slab_batch_fits(B, s1.nz)) e = launch_conv1_wgrad_slab(c, obs, index, B, part1, s1.nz, &nz1);
-        else if (!small && sizeof(T) == 2 && conv1_wgrad_image_fits(g, obs)) e = launch_conv1_wgrad_image(c, obs, index, B, part1, s1.nz, &nz1);
+        if (sizeof(T) == 2 && B >= c.conv1_wgrad_slab_rows && conv1_wgrad_slab_fits(g, obs) && conv1_wgrad_slab_batch_fits(B, s1.nz)) e = launch_conv1_wgrad_slab(c, obs, index, B, part1, s1.nz, &nz1);
+        else if (sizeof(T) == 2 && B >= c.conv1_wgrad_image_rows && conv1_wgrad_image_fits(g, obs)) e = launch_conv1_wgrad_image(c, obs, index, B, part1, s1.nz, &nz1);
         else e = index ? conv1_wgrad(Conv1Wgrad<T, true>{}) : conv1_wgrad(Conv1Wgrad<T, false>{});
         if (e != hipSuccess) return e;
     }

@@ -194,6 +194,7 @@ struct Conv1SlabArgs {
     const float *bias;
     bf16_t *out;            // [B][P1][32]
     int B, W1, P1;
+    int parts;              // workgroups that share an observation (more than one: at most one observation per workgroup)
 };
 constexpr int C1S_THREADS = 512, C1S_PRODUCERS = 256;
 constexpr int C1S_MAX_SAMPLES = 64;       // observations per workgroup (their row indices are read once, into LDS)
@@ -205,19 +206,28 @@ template <int H, int W> constexpr size_t conv1_slab_lds() { return (size_t)2 * (
 
 // (LDS admits one workgroup per compute unit, two wavefronts per SIMD: the register budget is stated, or the compiler
 // aims at three and keeps fewer loads in flight -- 107 -> 96 us)
-template <int NG, int H, int W> __global__ __launch_bounds__(C1S_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void conv1_slab_kernel(const Conv1SlabArgs a)
+template <int NG, int H, int W, bool SHARED> __global__ __launch_bounds__(C1S_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void conv1_slab_kernel(const Conv1SlabArgs a)
 {
-    constexpr int C = 4 * NG, K = 64 * C, SLAB = 4 * H * W, NV = SLAB / 16, PT = C1S_PRODUCERS, NP = (NV + PT - 1) / PT;
+    constexpr int C = 4 * NG, K = 64 * C, SLAB = 4 * H * W, NV = SLAB / 16, PT = C1S_PRODUCERS;
+    // (shared: half an observation's tiles reach over at most two thirds of its rows)
+    constexpr int NP = ((SHARED ? NV * 2 / 3 : NV) + PT - 1) / PT;
     constexpr int IMG = 2 * SLAB;          // bytes of one bf16 image
-    constexpr int D = 2;                   // slabs in flight in the producers' registers (four: no faster, 99 vs 96 us)
+    // slabs in flight in the producers' registers (walking a batch, four are no faster: 99 vs 96 us; with one observation per
+    // workgroup all of it is requested at once)
+    constexpr int D = SHARED && NG > 2 ? NG : 2;
     static_assert(SLAB % 16 == 0 && (NG == 1 || NG % D == 0), "slab shape");
     extern __shared__ __attribute__((aligned(16))) unsigned char c1s_smem[];
     unsigned char *wl = c1s_smem + 2 * IMG;
     float *lbias = reinterpret_cast<float *>(wl + 2 * C1S_WBUF);
     int *rowid = reinterpret_cast<int *>(lbias + 32);
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), lrow = lane & 31, lk = lane >> 5;
-    const int nsamp = (a.B - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;
-    if (tid < nsamp) { const int b = blockIdx.x + tid * gridDim.x; rowid[tid] = a.index ? a.index[b] : b; }
+    // this workgroup's observations b0, b0 + bstep, ... and its share of their position tiles; of an image it needs the rows
+    // under those tiles only
+    const int parts = SHARED ? a.parts : 1;
+    const int b0 = (int)blockIdx.x / parts, part = (int)blockIdx.x % parts, bstep = (int)gridDim.x / parts;
+    const int alltiles = (a.P1 + 31) >> 5, tile0 = SHARED ? alltiles * part / parts : 0, ntiles = SHARED ? alltiles * (part + 1) / parts - tile0 : alltiles;
+    const int nsamp = SHARED ? 1 : (a.B - b0 + bstep - 1) / bstep;
+    if (tid < nsamp) { const int b = b0 + tid * bstep; rowid[tid] = a.index ? a.index[b] : b; }
     if (tid >= 64 && tid < 96) lbias[tid - 64] = a.bias[tid - 64];
     __syncthreads();
     const int nphase = nsamp * NG;          // slab q: observation q / NG of this workgroup, channels 4 (q % NG) .. + 3
@@ -229,8 +239,19 @@ template <int NG, int H, int W> __global__ __launch_bounds__(C1S_THREADS) __attr
         // A thread's byte offsets inside a slab / a weight slice never change; what changes per slab is the same for the
         // whole workgroup and is kept in scalar registers, so a fetch is loads and nothing else.
         uint32_t ioff[NP], woffs[NWV ? NWV : 1];
+        // the slab's vectors in order; for a share of an observation those of the rows it needs of each channel.  A vector
+        // behind the last one repeats it.
+        int nv = NV;
+        if constexpr (SHARED) {
+            const int oy0 = 32 * tile0 / a.W1, oy1 = (min(32 * (tile0 + ntiles), a.P1) - 1) / a.W1;
+            const int first = 4 * oy0 * W / 16, span = ((4 * oy1 + 8) * W + 15) / 16 - first;       // vectors per channel
+            nv = 4 * span;
 #pragma unroll
-        for (int i = 0; i < NP; ++i) { const int v = pt + i * PT; ioff[i] = 16u * (uint32_t)(NV % PT == 0 ? v : min(v, NV - 1)); }   // a vector behind the slab's end repeats its last one
+            for (int i = 0; i < NP; ++i) { const int v = min(pt + i * PT, nv - 1); ioff[i] = 16u * (uint32_t)((v / span) * (H * W / 16) + first + v % span); }
+        } else {
+#pragma unroll
+            for (int i = 0; i < NP; ++i) { const int v = pt + i * PT; ioff[i] = 16u * (uint32_t)(NV % PT == 0 ? v : min(v, NV - 1)); }
+        }
 #pragma unroll
         for (int i = 0; i < NWV; ++i) { const int v = pt + i * PT; woffs[i] = (uint32_t)((v >> 5) * (2 * K) + (v & 31) * 16); }       // row v / 32, 16-byte column v % 32 of the 32 x 256 slice
         auto fetch = [&](int q, uint4 (&r)[NP + NWV]) {
@@ -238,7 +259,7 @@ template <int NG, int H, int W> __global__ __launch_bounds__(C1S_THREADS) __attr
             const long long row = __builtin_amdgcn_readfirstlane(rowid[s]);
             const uint8_t *src = a.obs + (row * C + 4 * cg) * (H * W);
 #pragma unroll
-            for (int i = 0; i < NP; ++i) r[i] = *reinterpret_cast<const uint4 *>(src + ioff[i]);
+            for (int i = 0; i < NP; ++i) if (!SHARED || i * PT < nv) r[i] = *reinterpret_cast<const uint4 *>(src + ioff[i]);
             if constexpr (NG > 1) {
                 const unsigned char *wsrc = reinterpret_cast<const unsigned char *>(a.w) + cg * 512;
 #pragma unroll
@@ -246,10 +267,11 @@ template <int NG, int H, int W> __global__ __launch_bounds__(C1S_THREADS) __attr
             }
         };
         auto convert = [&](const uint4 (&r)[NP + NWV], int buf) {
-            unsigned char *dst = c1s_smem + buf * IMG + 32 * pt;
+            unsigned char *dst = c1s_smem + buf * IMG + (SHARED ? 0 : 32 * pt);
 #pragma unroll
             for (int i = 0; i < NP; ++i) {
-                if (NV % PT != 0 && pt + i * PT >= NV) continue;
+                if ((SHARED || NV % PT != 0) && pt + i * PT >= nv) continue;
+                const uint32_t at = SHARED ? 2 * ioff[i] : i * PT * 32;
                 const uint32_t x[4] = {r[i].x, r[i].y, r[i].z, r[i].w};
                 bf16x8 lo, hi;
 #pragma unroll
@@ -259,8 +281,8 @@ template <int NG, int H, int W> __global__ __launch_bounds__(C1S_THREADS) __attr
                     hi[e] = from_f32<bf16_t>((float)((x[2] >> (8 * e)) & 0xFFu));
                     hi[4 + e] = from_f32<bf16_t>((float)((x[3] >> (8 * e)) & 0xFFu));
                 }
-                *reinterpret_cast<bf16x8 *>(dst + i * PT * 32) = lo;
-                *reinterpret_cast<bf16x8 *>(dst + i * PT * 32 + 16) = hi;
+                *reinterpret_cast<bf16x8 *>(dst + at) = lo;
+                *reinterpret_cast<bf16x8 *>(dst + at + 16) = hi;
             }
             if constexpr (NG > 1) {
 #pragma unroll
@@ -288,12 +310,11 @@ template <int NG, int H, int W> __global__ __launch_bounds__(C1S_THREADS) __attr
         return;
     }
     // ---- consumers ----
-    const int ntiles = (a.P1 + 31) >> 5;
     uint32_t toff[C1S_TILES];
     int tm[C1S_TILES];
 #pragma unroll
     for (int i = 0; i < C1S_TILES; ++i) {
-        const int m = (w + 4 * i) * 32 + lrow, mc = m < a.P1 ? m : a.P1 - 1;
+        const int m = (tile0 + min(w + 4 * i, ntiles - 1)) * 32 + lrow, mc = m < a.P1 ? m : a.P1 - 1;
         const int oy = mc / a.W1, ox = mc - oy * a.W1;
         toff[i] = 2u * (uint32_t)((4 * oy + lk) * W + 4 * ox);      // image row u = 2t + lk of the patch, t = 0
         tm[i] = m;
@@ -427,7 +448,7 @@ template <int NG, int H, int W> __global__ __launch_bounds__(C1S_THREADS) __attr
     };
     __syncthreads();
     for (int s = 0; s < nsamp; ++s) {
-        const int b = blockIdx.x + s * gridDim.x;
+        const int b = b0 + s * bstep;
 #pragma unroll
         for (int cg = 0; cg < NG; ++cg) {
             const int buf = (s * NG + cg) & 1;
@@ -453,15 +474,23 @@ static hipError_t launch_conv1_slab(Ctx &c, const uint8_t *obs, const int32_t *i
     a.obs = obs; a.index = index; a.w = (const bf16_t *)c.ws.w1s; a.bias = c.ws.hb + c.sh.b1; a.out = (bf16_t *)c.ws.act1;
     a.B = B; a.W1 = g.W1; a.P1 = g.P1;
     const bool football = g.C == 16;
-    void (*kern)(const Conv1SlabArgs) = football ? conv1_slab_kernel<4, 72, 96> : conv1_slab_kernel<1, 84, 84>;
+    // Fewer observations than half the compute units: each goes to as many workgroups as there are compute units for it (at
+    // most one per position tile).  Kernel time at 16x72x96 frames, us, one workgroup per observation / shared: 16 rows 12.4 /
+    // 6.5, 32 12.4 / 6.8, 64 12.6 / 7.7, 128 13.5 / 11.4; 4x84x84: 64 7.7 / 6.0, 128 8.6 / 7.3.
+    a.parts = B < 128 ? 256 / B : B == 128 ? 2 : 1;
+    if (a.parts > (g.P1 + 31) / 32) a.parts = (g.P1 + 31) / 32;
+    const bool shared = a.parts > 1;
+    void (*kern)(const Conv1SlabArgs) = football ? (shared ? conv1_slab_kernel<4, 72, 96, true> : conv1_slab_kernel<4, 72, 96, false>)
+                                                 : (shared ? conv1_slab_kernel<1, 84, 84, true> : conv1_slab_kernel<1, 84, 84, false>);
     const size_t lds = football ? conv1_slab_lds<72, 96>() : conv1_slab_lds<84, 84>();
-    static std::atomic<bool> attr_set[2] = {};      // raise the dynamic-LDS limit once per instantiation (setting it twice is harmless)
-    if (!attr_set[football ? 1 : 0].load(std::memory_order_acquire)) {
+    static std::atomic<bool> attr_set[4] = {};      // raise the dynamic-LDS limit once per instantiation (setting it twice is harmless)
+    std::atomic<bool> &set = attr_set[(football ? 1 : 0) + (shared ? 2 : 0)];
+    if (!set.load(std::memory_order_acquire)) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
-        attr_set[football ? 1 : 0].store(true, std::memory_order_release);
+        set.store(true, std::memory_order_release);
     }
-    int grid = B < 256 ? B : 256;                    // one workgroup per compute unit (its LDS), walking the batch
+    int grid = B * a.parts < 256 ? B * a.parts : 256;                    // one workgroup per compute unit (its LDS), walking the batch
     const int least = (B + C1S_MAX_SAMPLES - 1) / C1S_MAX_SAMPLES;
     if (grid < least) grid = least;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(C1S_THREADS), lds, c.stream, a);
@@ -500,11 +529,11 @@ template <typename T> static hipError_t forward_t(Ctx &c, const uint8_t *obs, co
                 }
             }
             if (done) {}
+            else if (sizeof(T) == 2 && B >= c.conv1_slab_rows && conv1_slab_fits(g, obs)) e = launch_conv1_slab(c, obs, index, B);
             else if (small) e = g.K1 >= 1024 ? launch_wsgemm<Conv1Fwd<T>, 16, Conv1Fwd<T>::SEG, false, (sizeof(T) == 4)>(p, c.stream)
                                         : launch_wsgemm<Conv1Fwd<T>, 4, Conv1Fwd<T>::SEG, false>(p, c.stream);
             // (four-channel frames too: against the LDS-image kernel of that shape, conv1 at 1024 rows of 4x84x84
             // 21.7 -> 19.0 us, an act call at 256 / 4096 rows 38.8 -> 36.7 / 203 -> 188 us)
-            else if (sizeof(T) == 2 && B >= c.conv1_slab_rows && conv1_slab_fits(g, obs)) e = launch_conv1_slab(c, obs, index, B);
             else if (sizeof(T) == 2 && conv1_image_fits(g, obs)) e = launch_conv1_image(c, obs, index, B);
             else e = launch_gemm(p, c.stream);
         }
