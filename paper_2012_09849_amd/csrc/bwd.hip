@@ -3,6 +3,7 @@
 // each chunk writes its own partial, and wgrad_reduce adds the partials in chunk order -- no atomics, so the
 // gradient is bit-identical from run to run.
 #include "internal.hpp"
+#include "dmagemm.hpp"
 #include "imgconv.hpp"
 
 namespace hts {
@@ -546,6 +547,17 @@ static hipError_t launch_conv1_wgrad_slab(Ctx &c, const uint8_t *obs, const int3
     return hipGetLastError();
 }
 
+// bf16: gemm_dma_kernel.  Kernel time, us, register-staged tile kernel / 64x64 tiles of 3 stages / 64x128 of 2: 203 rows of 16x72x96
+// frames (160 workgroups of 64x64) 6.8 / 6.0 / 8.6, 512 rows of 4x84x84 (392) 8.7 / 8.6 / 9.7, 700 rows (539) 10.6 / 11.0 / 10.6,
+// 1024 rows (784) 14.1 / 13.7 / 11.8, 2048 rows of 16x72x96 19.6 / 19.1 / 18.2.
+static hipError_t launch_fc_dgrad(const FcDgrad<float> &p, hipStream_t s) { return launch_gemm(p, s); }
+static hipError_t launch_fc_dgrad(const FcDgrad<bf16_t> &p, hipStream_t s)
+{
+    typedef FcDgrad<bf16_t> P;
+    if (dma_workgroups(p, 64, 64) <= 512) return launch_dma(DmaTiles<P, 64, 64, 2, 2, 3>(p), s);
+    return launch_dma(DmaTiles<P, 64, 128, 2, 2, 2>(p), s);
+}
+
 template <typename T> static hipError_t backward_t(Ctx &c, const uint8_t *obs, const int32_t *index, int B, float *grads)
 {
     const Geom &g = c.g;
@@ -599,7 +611,7 @@ template <typename T> static hipError_t backward_t(Ctx &c, const uint8_t *obs, c
         p.dh = (const T *)c.ws.dh; p.wfcd = (const T *)c.ws.wfcd; p.a3n = (const T *)c.ws.a3n; p.dy3 = (T *)c.ws.dy3;
         {
             SiteTimer tm(c, SITE_FC_DGRAD);
-            e = small ? launch_wsgemm<FcDgrad<T>, 4, 64, false>(p, c.stream) : launch_gemm(p, c.stream);
+            e = small ? launch_wsgemm<FcDgrad<T>, 4, 64, false>(p, c.stream) : launch_fc_dgrad(p, c.stream);
         }
         if (e != hipSuccess) return e;
     }

@@ -1,0 +1,168 @@
+// Tile kernel for bfloat16 problems whose operands are contiguous along k and need no masking, for large batches:
+// gemm.hpp's contractions with the operand tiles copied from memory straight into LDS (buffer_load ... lds, 16 bytes a lane),
+// up to DMA_STAGES - 1 k-tiles ahead, one barrier per k-tile.  The register-staged kernel writes every operand byte to LDS
+// from registers (the slowest LDS operation), keeps one k-tile in flight and takes two barriers per k-tile; this one has
+// no staging registers, so larger tiles fit, and the address of a copy is a fixed lane offset plus a scalar.  Same k order
+// and segments, hence the same bits.  What bounds it now: batches of a few hundred rows by the memory latency of the first
+// k-tiles; large ones by filling a compute unit's L1 (24 KB per k-tile of 128x64, about 380 ticks, against 256 ticks of
+// products) and, conv2, by HBM (4096 rows: 147 MB in 41.5 us).  Not kept: 4 to 8 stages (128 KB of LDS: 6.6-7.2 us where 3
+// stages take 5.5-5.8), 256-row tiles of conv2 (44 us against 41.5 at 4096 rows), 128x128 tiles of FC (11.4 against 10.4 at 1024).
+#pragma once
+#include "gemm.hpp"
+
+namespace hts {
+
+typedef __attribute__((address_space(3))) void *lds_void;
+
+// A problem offers `int dma_k(int k0) const`: where k-tile k0 starts in an A row, in elements from ctx_a(row).p; a B row is
+// contiguous.  K and klen are whole numbers of k-tiles of 64, rows start at multiples of 16 bytes, and ctx_a(row).p does not
+// decrease with the row (a tile's rows are addressed from its first one with 32 bits).
+
+// 16 bytes per lane, memory -> LDS: lane l's bytes land at dst + 16 l (dst: one address for the wavefront)
+__device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t src, uint32_t lane_off, uint32_t wave_off, const bf16_t *dst)
+{
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (lds_void)dst, 16, (int)lane_off, (int)wave_off, 0, 0);
+}
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t dma_source(const void *p, uint32_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes, 0x00020000);
+}
+
+// problem P on tiles of another shape
+template <class P, int BM_, int BN_, int WM_, int WN_, int STAGES_, int GROUP_ = 0> struct DmaTiles : P {
+    static constexpr int BM = BM_, BN = BN_, WAVES_M = WM_, WAVES_N = WN_, DMA_STAGES = STAGES_, GROUP = GROUP_;
+    explicit DmaTiles(const P &p) : P(p) {}
+};
+
+constexpr int wait_imm(int vm) { return (vm & 15) | ((vm >> 4) << 14) | (7 << 4); }       // vmcnt(vm) lgkmcnt(0)
+
+// waits until at most min(ahead, AHEAD) k-tiles' copies (PER a tile) of this wavefront are under way, and for its LDS reads
+template <int AHEAD, int PER> __device__ __forceinline__ void wait_tiles(int ahead)
+{
+    static_assert(AHEAD * PER < 64, "vmcnt");
+    if constexpr (AHEAD > 0) {
+        if (ahead < AHEAD) { wait_tiles<AHEAD - 1, PER>(ahead); return; }
+    }
+    __builtin_amdgcn_s_waitcnt(wait_imm(AHEAD * PER));
+}
+
+template <class P>
+__global__ __launch_bounds__(P::WAVES_M * P::WAVES_N * 64, 2) void gemm_dma_kernel(const P p)
+{
+    constexpr int BM = P::BM, BN = P::BN, BK = 64, NS = P::DMA_STAGES;
+    constexpr int WM = P::WAVES_M, WN = P::WAVES_N, NT = WM * WN * 64, NW = WM * WN;
+    constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
+    constexpr int SEG = SegOf<P>::value, GROUP = GroupOf<P>::value;
+    constexpr bool SWAP = OwnsRow<P>::value;
+    constexpr int NA = BM / 8 / NW, NB = BN / 8 / NW;          // copies of 8 rows per wavefront and k-tile
+    constexpr int STAGE = (BM + BN) * BK;                       // elements
+    static_assert(sizeof(typename P::T) == 2 && P::A_ALONG_K && P::B_ALONG_K && (SEG == 0 || SEG == BK) && (GROUP == 0 || GROUP % BK == 0), "problem");
+    static_assert(NA * 8 * NW == BM && NB * 8 * NW == BN && TM * 32 * WM == BM && TN * 32 * WN == BN, "tile shape");
+    __shared__ __attribute__((aligned(1024))) bf16_t tile[NS * STAGE];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave % WM, wn = wave / WM, lrow = lane & 31, lk = lane >> 5;
+    int m0, n0, z;
+    if (!tile_of(p, p.M, m0, n0, z)) return;       // the whole workgroup leaves
+    const int kbeg = z * p.klen, nt = (min(p.K, kbeg + p.klen) - kbeg) / BK;
+
+    // LDS rows of 64 k: 16-byte slot s of row r holds k-vector s ^ ((r >> 1) & 7), so the sixteen rows of an operand read
+    // fall into different banks; a copy of 8 rows is contiguous in LDS and takes whole 128-byte lines from memory
+    const bf16_t *abase = p.ctx_a(m0).p, *bbase = p.ctx_b(n0).p;
+    const __amdgpu_buffer_rsrc_t ra = dma_source(abase, 0xfffffffcu), rb = dma_source(bbase, 0xfffffffcu);
+    uint32_t oa[NA], ob[NB];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+        const int r = (wave * NA + i) * 8 + (lane >> 3);
+        oa[i] = (uint32_t)((const char *)p.ctx_a(m0 + r).p - (const char *)abase) + 16u * ((lane & 7) ^ ((r >> 1) & 7));
+    }
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        const int r = (wave * NB + i) * 8 + (lane >> 3);
+        ob[i] = (uint32_t)((const char *)p.ctx_b(n0 + r).p - (const char *)bbase) + 16u * ((lane & 7) ^ ((r >> 1) & 7));
+    }
+    auto fetch = [&](int t, int s) {
+        const int k0 = kbeg + t * BK;
+        const uint32_t wa = 2u * (uint32_t)p.dma_k(k0), wb = 2u * (uint32_t)k0;
+#pragma unroll
+        for (int i = 0; i < NA; ++i) dma16(ra, oa[i], wa, tile + s * STAGE + (wave * NA + i) * 8 * BK);
+#pragma unroll
+        for (int i = 0; i < NB; ++i) dma16(rb, ob[i], wb, tile + s * STAGE + BM * BK + (wave * NB + i) * 8 * BK);
+    };
+    // A segment is one k-tile.  Its sums are added to the running ones while the next k-tile's products are formed, hence two
+    // sets of accumulators, taken in turn.
+    f32x16 acc[SEG > 0 ? 2 : 1][TM][TN], tot[SEG > 0 ? TM : 1][SEG > 0 ? TN : 1], grp[GROUP > 0 ? TM : 1][GROUP > 0 ? TN : 1];
+    auto clear = [&](auto &x) {
+        for (auto &r : x) for (auto &c : r)
+#pragma unroll
+            for (int q = 0; q < 16; ++q) c[q] = 0.0f;
+    };
+    clear(acc[0]);
+    if constexpr (SEG > 0) { clear(acc[1]); clear(tot); }
+    if constexpr (GROUP > 0) clear(grp);
+    auto add = [&](auto &x, const auto &y) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) x[i][j] += y[i][j];
+    };
+    const int sw = (lrow >> 1) & 7;
+    auto use = [&](int s, int t, auto parity) {
+        constexpr int PAR = SEG > 0 ? decltype(parity)::value : 0;
+        const bf16_t *as = tile + s * STAGE + (wm * TM * 32 + lrow) * BK, *bs = tile + s * STAGE + BM * BK + (wn * TN * 32 + lrow) * BK;
+        const f32x16 zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+            const int slot = 8 * ((2 * kk + lk) ^ sw);
+            bf16x8 av[TM], bv[TN];
+#pragma unroll
+            for (int i = 0; i < TM; ++i) av[i] = *reinterpret_cast<const bf16x8 *>(as + i * 32 * BK + slot);
+#pragma unroll
+            for (int j = 0; j < TN; ++j) bv[j] = *reinterpret_cast<const bf16x8 *>(bs + j * 32 * BK + slot);
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    const f32x16 &c = SEG > 0 && kk == 0 ? zero : acc[PAR][i][j];
+                    acc[PAR][i][j] = SWAP ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(bv[j], av[i], c, 0, 0, 0)
+                                          : __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[i], bv[j], c, 0, 0, 0);
+                }
+            if constexpr (SEG > 0) if (kk == 0) add(tot, acc[1 - PAR]);
+        }
+        if constexpr (GROUP > 0) if (t > 0 && t % (GROUP / BK) == 0) { add(grp, tot); clear(tot); }
+    };
+    EpiInputs<P, TM, TN, SWAP> epi;
+    if constexpr (EpiEarly<P>::value) epi_fetch(p, epi, m0, n0, p.M, 0, wm, wn, lane);
+#pragma unroll
+    for (int s = 0; s < NS - 1; ++s) if (s < nt) fetch(s, s);
+    int s = 0;
+    auto step = [&](int t, auto parity) {
+        // this wavefront's copies of tile t have landed (later tiles' may be in flight); its reads of tile t-1 are done
+        wait_tiles<NS - 2, NA + NB>(nt - 1 - t);
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();               // everybody's
+        asm volatile("" ::: "memory");
+        if (t + NS - 1 < nt) fetch(t + NS - 1, s == 0 ? NS - 1 : s - 1);
+        use(s, t, parity);
+        s = s + 1 == NS ? 0 : s + 1;
+    };
+    for (int t = 0; t < nt; t += 2) {
+        step(t, std::integral_constant<int, 0>{});
+        if (t + 1 < nt) step(t + 1, std::integral_constant<int, 1>{});
+    }
+    if constexpr (SEG > 0) { if (nt & 1) add(tot, acc[0]); else add(tot, acc[1]); }
+    if constexpr (GROUP > 0) add(grp, tot);
+    if constexpr (GROUP > 0) epi_store(p, grp, epi, m0, n0, p.M, z, 0, wm, wn, lane);
+    else if constexpr (SEG > 0) epi_store(p, tot, epi, m0, n0, p.M, z, 0, wm, wn, lane);
+    else epi_store(p, acc[0], epi, m0, n0, p.M, z, 0, wm, wn, lane);
+}
+
+template <class P> inline int dma_workgroups(const P &p, int bm, int bn) { return ((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn) * ((p.K + p.klen - 1) / p.klen); }
+template <class P> inline hipError_t launch_dma(const P &p, hipStream_t stream)
+{
+    const int tiles = ((p.M + P::BM - 1) / P::BM) * ((p.N + P::BN - 1) / P::BN), nz = (p.K + p.klen - 1) / p.klen;
+    hipLaunchKernelGGL(gemm_dma_kernel<P>, dim3(((tiles + 7) / 8) * 8, nz), dim3(P::WAVES_M * P::WAVES_N * 64), 0, stream, p);
+    return hipGetLastError();
+}
+
+}  // namespace hts

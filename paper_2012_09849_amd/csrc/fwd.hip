@@ -1,6 +1,7 @@
 // Forward pass of the policy/value network (appendix "Implementation Details") as four tiled contractions:
 // conv1 (uint8 gather, 1/255 folded in), conv2, conv3, FC.  The heads run in misc.hip.
 #include "internal.hpp"
+#include "dmagemm.hpp"
 #include "imgconv.hpp"
 
 #include <atomic>
@@ -497,6 +498,29 @@ static hipError_t launch_conv1_slab(Ctx &c, const uint8_t *obs, const int32_t *i
     return hipGetLastError();
 }
 
+// bf16 conv2 and FC of large batches: gemm_dma_kernel, tile and stages by the number of workgroups.  Kernel time, us, register-
+// staged tile kernel / 3 stages / 2 stages.  conv2: 16x72x96 frames, 203 rows (112 workgroups) 8.6 / 7.1 / 8.1, 512 rows (280)
+// 10.4 / 9.6 / 9.8; 4x84x84, 1024 rows (648) 15.0 / 15.5 / 13.5, 4096 rows 45.9 / 49 / 41.5.
+template <class L> static hipError_t launch_rows(const ConvFwd<bf16_t, L, false> &p, hipStream_t s)
+{
+    typedef ConvFwd<bf16_t, L, false> P;
+    if (dma_workgroups(p, 128, 64) <= 512) return launch_dma(DmaTiles<P, 128, 64, 2, 2, 3>(p), s);
+    return launch_dma(DmaTiles<P, 128, 64, 2, 2, 2>(p), s);
+}
+// FC, 64x64 tiles: 203 rows of 16x72x96 frames (160 workgroups) 7.1 / 5.7 / -, 700 rows of 4x84x84 (616) 9.9 / 10.2 / 9.2; 128x64
+// tiles instead of 64x64: 1024 rows (896) 11.0 / 11.4 -> 10.4, 2048 rows of 16x72x96 22.1 / 20.5 -> 18.5; 4096 rows with the groups
+// added in the kernel 36.5 / 32.6 -> 29.2 (2 stages 36).
+static hipError_t launch_rows(const FcFwd<bf16_t> &p, hipStream_t s)
+{
+    typedef FcFwd<bf16_t> P;
+    if (p.klen > FC_GROUP_K) return launch_dma(DmaTiles<P, 128, 64, 2, 2, 3, FC_GROUP_K>(p), s);
+    const int wgs = dma_workgroups(p, 64, 64);
+    if (wgs <= 512) return launch_dma(DmaTiles<P, 64, 64, 2, 2, 3>(p), s);
+    if (wgs < 896) return launch_dma(DmaTiles<P, 64, 64, 2, 2, 2>(p), s);
+    return launch_dma(DmaTiles<P, 128, 64, 2, 2, 2>(p), s);
+}
+template <class P> static hipError_t launch_rows(const P &p, hipStream_t s) { return launch_gemm(p, s); }
+
 template <typename T> static hipError_t forward_t(Ctx &c, const uint8_t *obs, const int32_t *index, int B, bool learn)
 {
     const Geom &g = c.g;
@@ -555,7 +579,7 @@ template <typename T> static hipError_t forward_t(Ctx &c, const uint8_t *obs, co
                 e = launch_wsgemm16<ConvFwd<T, Layer2, false>, 8, ConvFwd<T, Layer2, false>::SEG>(p, c.stream);
             else
             e = small ? launch_wsgemm<ConvFwd<T, Layer2, false>, 8, ConvFwd<T, Layer2, false>::SEG, false>(p, c.stream)
-                      : launch_gemm(p, c.stream);
+                      : launch_rows(p, c.stream);
         }
         if (e != hipSuccess) return e;
     }
@@ -603,7 +627,7 @@ template <typename T> static hipError_t forward_t(Ctx &c, const uint8_t *obs, co
                 e = launch_wsgemm16<FcFwd<T>, 8, FcFwd<T>::SEG>(p, c.stream, FC_GROUP_K / FcFwd<T>::SEG);
             else
             e = small ? launch_wsgemm<FcFwd<T>, 8, FcFwd<T>::SEG, false>(p, c.stream, FC_GROUP_K / FcFwd<T>::SEG)
-                      : launch_gemm(p, c.stream);
+                      : launch_rows(p, c.stream);
         }
         if (e != hipSuccess) return e;
     }

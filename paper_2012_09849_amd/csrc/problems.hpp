@@ -163,6 +163,7 @@ template <typename T_, class L, bool FLAT_OUT> struct ConvFwd {
         return load_vec<T, VA>(c.p + (u * (Win - L::KSZ) * L::CIN + k0) + dk);
     }
     HTS_HD Vec<T, VB> load_b(const CtxB &c, int k, int) const { return load_vec<T, VB>(c.p + k); }
+    HTS_HD int dma_k(int k0) const { return (k0 / (L::KSZ * L::CIN)) * (Win - L::KSZ) * L::CIN + k0; }     // A's offset of k-tile k0 from its row
     // tile kernel, flattened output (conv3): a lane owns an output position, so the (sample, position) split of the
     // row index is done once per lane instead of once per element (the plain layout measured no faster that way)
     static constexpr bool LANE_OWNS_ROW = FLAT_OUT;
@@ -222,6 +223,7 @@ template <typename T_> struct FcFwd {
     // K = F = 64*P3 and the group length are whole numbers of k-tiles and segments: no end-of-range checks
     HTS_HD Vec<T, VA> load_a(const CtxA &c, int k, int) const { return load_vec<T, VA>(c.p + k); }
     HTS_HD Vec<T, VB> load_b(const CtxB &c, int k, int) const { return load_vec<T, VB>(c.p + k); }
+    HTS_HD int dma_k(int k0) const { return k0; }
     HTS_HD void store(int m, int n, float acc, int grp) const { part[((long long)grp * M + m) * N + n] = acc; }
 };
 
@@ -326,6 +328,7 @@ template <typename T_> struct FcDgrad {
     // K = 512 is a whole number of k-tiles and segments: no end-of-range checks
     HTS_HD Vec<T, VA> load_a(const CtxA &c, int k, int) const { return load_vec<T, VA>(c.p + k); }
     HTS_HD Vec<T, VB> load_b(const CtxB &c, int k, int) const { return load_vec<T, VB>(c.p + k); }
+    HTS_HD int dma_k(int k0) const { return k0; }
     static constexpr bool LANE_OWNS_ROW = true;
     struct Row { long long o; };
     HTS_HD Row row(int b) const { return {(long long)b * N}; }

@@ -1,0 +1,52 @@
+"""conv2, FC and the FC input gradient of large bf16 batches, whose operand tiles are copied straight into LDS: batches that
+end inside a tile, on either side of each change of tile or stages, against the wave-per-segment kernels bit for bit; and the
+gradient where the input gradient changes tiles."""
+import numpy as np
+import pytest
+import torch
+
+from test_gpu_parity import ATARI, FOOT, _act, _rollout, _split, dev, hts  # noqa: F401
+import hts_synth as syn
+
+pytestmark = pytest.mark.gpu
+
+
+# workgroups of 64x64 FC tiles at these sizes (84x84): 168, 504, 560, 840, 896, 952; 4100 rows add the groups in the kernel
+@pytest.mark.parametrize("shape,A,sizes", [(ATARI, 18, (129, 576, 577, 960, 961, 1030, 4100)), (FOOT, 19, (129, 203, 833, 1409)),
+                                           ((3, 44, 52), 7, (129, 500, 2113))])
+def test_large_batches_agree_bitwise(hts, shape, A, sizes, monkeypatch):  # noqa: F811
+    n = max(sizes)
+    params = dev(syn.init_params(31, *shape, A, bias_scale=0.05))
+    g = torch.Generator(device="cuda").manual_seed(32)
+    obs = torch.randint(0, 256, (n, *shape), device="cuda", generator=g, dtype=torch.uint8)
+    monkeypatch.setenv("HTS_SMALL_BATCH", "1000000")
+    ctx = hts.Context(*shape, A, precision=1, max_act_batch=n)
+    want = _act(ctx, obs, params, 5, 1, 0, A)
+    ctx.close()
+    monkeypatch.delenv("HTS_SMALL_BATCH")
+    ctx = hts.Context(*shape, A, precision=1, max_act_batch=n)
+    for k in sizes:
+        got = _act(ctx, obs[n - k:].contiguous(), params, 5, 1, n - k, A)
+        assert all(np.array_equal(x[n - k:], y) for x, y in zip(want, got)), k
+    ctx.close()
+
+
+# As for small minibatches (twice the rows, half the weight of each): binary32 sums of at most n = 700 * 400 terms in another
+# order, sqrt(n) 2^-24 = 3.2e-5.  350 rows take 64x64 tiles of the FC input gradient, 700 rows 64x128.
+@pytest.mark.parametrize("shape,A,B", [(ATARI, 18, 350), ((3, 44, 52), 7, 150)])
+def test_gradient_is_the_mean_of_its_halves(hts, oracle, shape, A, B):  # noqa: F811
+    _, params, obs, actions, old_logp, adv, ret = _rollout(oracle, shape, A, 2 * B, 900 + B, False)
+    ctx = hts.Context(*shape, A, precision=1, max_learn_batch=2 * B)
+
+    def gradient(lo, hi):
+        g = torch.full((ctx.P,), float("nan"), device="cuda")
+        rows = [dev(x[lo:hi]) for x in (obs, actions, adv, ret)]
+        ctx.hts_loss_and_grads(rows[0], rows[1], None, rows[2], rows[3], dev(params), hts.HParams(algo=hts.ALGO_A2C), g)
+        torch.cuda.synchronize()
+        return _split(g.cpu().numpy().astype(np.float64), shape, A)
+
+    whole, first, second = gradient(0, 2 * B), gradient(0, B), gradient(B, 2 * B)
+    for name, w in whole.items():
+        mean = 0.5 * (first[name] + second[name])
+        assert np.linalg.norm(w - mean) <= 3.2e-5 * np.linalg.norm(mean), name
+    ctx.close()
