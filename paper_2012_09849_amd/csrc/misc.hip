@@ -845,34 +845,34 @@ template <bool VEC> __device__ __forceinline__ void store_entries(float *adv, lo
     for (int e = 0; e < 4; ++e) if (4 * v + e < n) adv[4 * v + e] = x[e];
 }
 
-template <bool VEC> __global__ __launch_bounds__(NRM_ONE_THREADS) void normalize_one_kernel(float *__restrict__ adv, int n)
+template <bool VEC, int NT> __global__ __launch_bounds__(NT) void normalize_one_kernel(float *__restrict__ adv, int n)
 {
-    __shared__ double red[2][NRM_ONE_THREADS / 64];
+    __shared__ double red[2][NT / 64];
     const int t = threadIdx.x;
     f32x4 x[NRM_ONE_VECS];
 #pragma unroll
-    for (int i = 0; i < NRM_ONE_VECS; ++i) x[i] = load_entries<VEC>(adv, t + i * NRM_ONE_THREADS, n);
+    for (int i = 0; i < NRM_ONE_VECS; ++i) x[i] = load_entries<VEC>(adv, t + i * NT, n);
     double s = 0.0, q = 0.0;
 #pragma unroll
     for (int i = 0; i < NRM_ONE_VECS; ++i)
 #pragma unroll
         for (int e = 0; e < 4; ++e) s += (double)x[i][e];
-    const double mean = block_sum_f64<NRM_ONE_THREADS>(s, red[0]) / (double)n;
+    const double mean = block_sum_f64<NT>(s, red[0]) / (double)n;
 #pragma unroll
     for (int i = 0; i < NRM_ONE_VECS; ++i)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const double d = 4 * (t + i * NRM_ONE_THREADS) + e < n ? (double)x[i][e] - mean : 0.0;
+            const double d = 4 * (t + i * NT) + e < n ? (double)x[i][e] - mean : 0.0;
             q += d * d;
         }
-    const double var = block_sum_f64<NRM_ONE_THREADS>(q, red[1]) / (double)(n > 1 ? n - 1 : 1);
+    const double var = block_sum_f64<NT>(q, red[1]) / (double)(n > 1 ? n - 1 : 1);
     const double inv = 1.0 / (sqrt(var) + 1e-5);
 #pragma unroll
     for (int i = 0; i < NRM_ONE_VECS; ++i) {
         f32x4 y;
 #pragma unroll
         for (int e = 0; e < 4; ++e) y[e] = (float)(((double)x[i][e] - mean) * inv);
-        store_entries<VEC>(adv, t + i * NRM_ONE_THREADS, n, y);
+        store_entries<VEC>(adv, t + i * NT, n, y);
     }
 }
 
@@ -935,7 +935,12 @@ hipError_t launch_normalize(Ctx *c, hipStream_t s, float *adv, long long n)
     SiteTimer tm(c ? *c : dummy, SITE_NORMALIZE);
     const bool vec = !((uintptr_t)adv & 15u);
     if (n <= NRM_ONE) {
-        hipLaunchKernelGGL(vec ? normalize_one_kernel<true> : normalize_one_kernel<false>, dim3(1), dim3(NRM_ONE_THREADS), 0, s, adv, (int)n);
+        // four wavefronts while they hold the array: with sixteen, the launch and the two reductions take 4.8 us at any size,
+        // with four 3.0-3.3
+        const bool few = n <= NRM_ONE / 4;
+        auto kern = few ? (vec ? normalize_one_kernel<true, NRM_ONE_THREADS / 4> : normalize_one_kernel<false, NRM_ONE_THREADS / 4>)
+                        : (vec ? normalize_one_kernel<true, NRM_ONE_THREADS> : normalize_one_kernel<false, NRM_ONE_THREADS>);
+        hipLaunchKernelGGL(kern, dim3(1), dim3(few ? NRM_ONE_THREADS / 4 : NRM_ONE_THREADS), 0, s, adv, (int)n);
         return hipGetLastError();
     }
     double *part = c ? c->ws.adv_part : nullptr;

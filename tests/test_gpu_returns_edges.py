@@ -9,10 +9,10 @@ from test_gpu_parity import dev, hts  # noqa: F401
 pytestmark = pytest.mark.gpu
 
 
-# one workgroup / several (16384 entries), remainders of a 4-entry vector, a pointer that is not 16-byte aligned.
+# four or sixteen wavefronts (4096 entries) / several workgroups (16384), remainders of a 4-entry vector, a pointer that is not 16-byte aligned.
 # The kernels work in float64 and round once: half an ulp of binary32 (6e-8) relative, 3e-7 allowed for the float64 sums'
 # effect on a value near zero.
-@pytest.mark.parametrize("n,shift", [(1, 0), (5, 1), (16383, 0), (16384, 2), (16385, 0), (65537, 3), (528387, 0)])
+@pytest.mark.parametrize("n,shift", [(1, 0), (5, 1), (4096, 0), (4097, 1), (16383, 0), (16384, 2), (16385, 0), (65537, 3), (528387, 0)])
 def test_normalize_edges(hts, oracle, n, shift):  # noqa: F811
     ctx = hts.Context(4, 84, 84, 6, max_act_batch=1)
     a = (syn.normal_f32(n, syn.S_MISC, (n,)) * 3 + 100).astype(np.float32)
