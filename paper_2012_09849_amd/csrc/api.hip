@@ -122,9 +122,7 @@ extern "C" int32_t hts_create(const hts_net_desc *desc, int32_t max_act_batch, i
     c.desc = *desc; c.g = g; c.stream = (hipStream_t)hip_stream;
     c.max_act = max_act_batch; c.max_learn = max_learn_batch;
     c.max_b = max_act_batch > max_learn_batch ? max_act_batch : max_learn_batch;
-    // (binary32: an update of 96 rows of 84x84 frames takes 182 us either way; 128 rows 204 us by the small-batch kernels,
-    // 191 us by the tile kernels)
-    c.small_b = desc->precision == HTS_PRECISION_BF16 ? 128 : 96;
+    c.small_b = 128;
     c.fc_groups = (g.F + FC_GROUP_K - 1) / FC_GROUP_K;
     c.synced = false; c.synced_learn = false; c.track_params = false; c.shadow_of = nullptr;
     {

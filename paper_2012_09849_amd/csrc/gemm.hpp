@@ -8,7 +8,6 @@
 // built from 32x32 MFMA accumulators:
 //   fp32 : v_mfma_f32_32x32x2_f32   (lane l supplies A[l%32][l/32] and B[l/32][l%32])
 //   bf16 : v_mfma_f32_32x32x16_bf16 (lane l supplies 8 consecutive k at k0 = 8*(l/32) for row/col l%32)
-// (problems that cut binary32 operands into bfloat16 pieces have a tile kernel of their own, split.hpp)
 // Accumulator register r of lane l is D[8*(r/4) + 4*(l/32) + r%4][l%32].
 //
 // Operand tiles go global -> registers -> LDS ([row][k], padded) -> MFMA; the global loads of tile i+1 are in
@@ -63,63 +62,6 @@ HTS_HD float to_f32(bf16_t x) { return (float)x; }
 template <typename T> HTS_HD T from_f32(float x);
 template <> HTS_HD float from_f32<float>(float x) { return x; }
 template <> HTS_HD bf16_t from_f32<bf16_t>(float x) { return (bf16_t)x; }   // round to nearest even
-
-// binary32 operands on the bfloat16 matrix instruction.  x = p0 + p1 + p2 exactly, each piece bfloat16: p0 is x rounded to
-// nearest, and what is left has at most 16, then at most 8 significant bits (magnitudes fall by 2^9 a piece; below 2^-108
-// the last piece may be a denormal).  A product of two such operands is the six piece products p_i q_j with i + j <= 2;
-// the three left out are together below 2^-26 of |x y|, less than half of one binary32 rounding.  The sums p0 q0 are kept
-// apart from the five small ones (two accumulators, added once per segment), so the small ones are not rounded to the
-// large ones' last bit.  Measured against exact sums on random operands (equal and mixed magnitudes, one sign and both,
-// 64 to 4096 terms): 2 to 3 times SMALLER error than v_mfma_f32_32x32x2_f32, 2-norm and largest; nine products instead of
-// six change nothing.  Rate: 1750 / 6 = 290 against 121 TFLOP/s of the binary32 instruction in a loop of nothing else.
-// (The splitting of a binary32 number into bfloat16 pieces: Henry, Tang, Heinecke, "Leveraging the bfloat16 Artificial
-// Intelligence Datatype For Higher-Precision Computations", 2019.)
-// A problem whose operand is bytes (pixels: exact in one piece) says so with `static constexpr int A_PIECES = 1` (B_PIECES).
-// A binary32 problem with `static constexpr bool F32_MFMA = true` keeps the binary32 instruction.
-template <class P, class = void> struct F32Mfma : std::false_type {};
-template <class P> struct F32Mfma<P, std::void_t<decltype(P::F32_MFMA)>> : std::integral_constant<bool, P::F32_MFMA && sizeof(typename P::T) == 4> {};
-template <class P, class = void> struct PiecesA { static constexpr int value = sizeof(typename P::T) == 4 ? 3 : 1; };
-template <class P> struct PiecesA<P, std::void_t<decltype(P::A_PIECES)>> { static constexpr int value = P::A_PIECES; };
-template <class P, class = void> struct PiecesB { static constexpr int value = sizeof(typename P::T) == 4 ? 3 : 1; };
-template <class P> struct PiecesB<P, std::void_t<decltype(P::B_PIECES)>> { static constexpr int value = P::B_PIECES; };
-template <typename T, int V, int NP> HTS_HD void to_pieces(const Vec<T, V> &x, Vec<bf16_t, V> (&p)[NP])
-{
-    if constexpr (sizeof(T) == 2) { static_assert(NP == 1, "one piece"); p[0] = x; }
-    else {
-        typedef bf16_t bf16x2 __attribute__((ext_vector_type(2)));
-        typedef float f32x2 __attribute__((ext_vector_type(2)));
-#pragma unroll
-        for (int i = 0; i < V; i += 2) {
-            float r0 = x[i], r1 = x[i + 1];
-#pragma unroll
-            for (int q = 0; q < NP; ++q) {
-                uint32_t w = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{r0, r1}, bf16x2));
-                if (q + 1 < NP) asm("" : "+v"(w));         // (one conversion for both: seen through, each is converted again for its remainder)
-                const bf16x2 h = __builtin_bit_cast(bf16x2, w);
-                p[q][i] = h[0]; p[q][i + 1] = h[1];
-                if (q + 1 < NP) {
-                    r0 -= __builtin_bit_cast(float, w << 16); r1 -= __builtin_bit_cast(float, w & 0xffff0000u);
-                }
-            }
-        }
-    }
-}
-// The products of one 32-long block of k, small pieces first: f(i, j, small) is called for every pair of pieces in a fixed
-// order and runs over the block's k itself, so every kernel adds in the same order whatever its instruction's k length.
-template <int NPA, int NPB, class F> HTS_HD void for_piece_pairs(F &&f)
-{
-    using std::integral_constant;
-    auto one = [&](auto i, auto j) {
-        if constexpr (decltype(i)::value < NPA && decltype(j)::value < NPB)
-            f(i, j, integral_constant<bool, (decltype(i)::value + decltype(j)::value > 0)>{});
-    };
-    one(integral_constant<int, 0>{}, integral_constant<int, 2>{});
-    one(integral_constant<int, 2>{}, integral_constant<int, 0>{});
-    one(integral_constant<int, 1>{}, integral_constant<int, 1>{});
-    one(integral_constant<int, 0>{}, integral_constant<int, 1>{});
-    one(integral_constant<int, 1>{}, integral_constant<int, 0>{});
-    one(integral_constant<int, 0>{}, integral_constant<int, 0>{});
-}
 
 // Exact floor(x / d) for 0 <= x < 2^31 by multiply-shift: mul = ceil(2^p / d), p = 31 + ceil(log2 d).
 struct FastDiv {
@@ -281,6 +223,15 @@ template <class P> HTS_HD auto tile_load_b(const P &p, const typename P::CtxB &c
 // Optional batching: a problem with `int batches() const`, `int max_m() const`, `int batch_m(int z) const` is
 // launched with gridDim.z = batches(); batch z has batch_m(z) rows and its own gathers: ctx_a(row, z),
 // ctx_b(col, z) and store(m, n, acc, split, z) receive the batch index (the problem object stays read-only).
+// Optional bias column: a naturally staged binary32 problem with `static constexpr float BIAS_COL = x` whose last column N - 1
+// has B = x at every k (a weight gradient's bias) has one wavefront add that column up from the row operands in LDS, k by k,
+// instead of giving it a tile of columns of its own.  The same bits: v_mfma_f32_32x32x2_f32 equals a sequential fma chain.
+// 1024 rows of 84x84 frames: conv2, 9 column tiles -> 8 and with them 576 workgroups -> 512, two per compute unit, 91 -> 69 us;
+// conv1, 3 tiles -> 2, 133 -> 100.  (FC's 50 tiles -> 49 gain less than the wavefront's chain costs: 48.6 -> 53 us; not taken.)
+template <class P, class = void> struct BiasCol : std::false_type {};
+template <class P> struct BiasCol<P, std::void_t<decltype(P::BIAS_COL)>> : std::integral_constant<bool, sizeof(typename P::T) == 4 && NaturalOf<P>::value> {};
+template <class P> HTS_HD int tile_cols(const P &p) { return p.N - (BiasCol<P>::value ? 1 : 0); }       // columns that the tiles cover
+
 // Optional tile order (see the kernel): N slowest instead of M slowest.
 template <class P, class = void> struct TilesAlongM : std::false_type {};
 template <class P> struct TilesAlongM<P, std::void_t<decltype(P::TILES_ALONG_M)>> : std::integral_constant<bool, P::TILES_ALONG_M> {};
@@ -380,7 +331,7 @@ template <class P, int TM, int TN, bool SWAP>
 __device__ __forceinline__ void epi_store(const P &p, const f32x16 (&acc)[TM][TN], EpiInputs<P, TM, TN, SWAP> &epi, int m0, int n0, int M, int z,
                                           int zb, int wm, int wn, int lane)
 {
-    const int lrow = lane & 31, lk = lane >> 5;
+    const int lrow = lane & 31, lk = lane >> 5, N = tile_cols(p);
     auto epilogue = [&](auto full_tile) {
         constexpr bool FULL = decltype(full_tile)::value;
         if constexpr (SWAP) {
@@ -393,7 +344,7 @@ __device__ __forceinline__ void epi_store(const P &p, const f32x16 (&acc)[TM][TN
                     for (int g = 0; g < 4; ++g) {
                         const int n = n0 + (wn * TN + j) * 32 + 8 * g + 4 * lk;
                         const float v[4] = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
-                        if (FULL || (epi.mok[i] && n < p.N)) {
+                        if (FULL || (epi.mok[i] && n < N)) {
                             if constexpr (HasBatch<P>::value) p.store4(epi.rc[i], n, v, z, zb, epi.pre[i][j][g]);
                             else p.store4(epi.rc[i], n, v, z, epi.pre[i][j][g]);
                         }
@@ -404,23 +355,23 @@ __device__ __forceinline__ void epi_store(const P &p, const f32x16 (&acc)[TM][TN
 #pragma unroll
                 for (int j = 0; j < TN; ++j) {
                     const int n = n0 + (wn * TN + j) * 32 + lrow;
-                    const auto col = make_col(p, FULL ? n : min(n, p.N - 1));
+                    const auto col = make_col(p, FULL ? n : min(n, N - 1));
 #pragma unroll
                     for (int r = 0; r < 16; ++r) {
                         const int m = m0 + (wm * TM + i) * 32 + 8 * (r / 4) + 4 * lk + (r % 4);
-                        if (FULL || (m < M && n < p.N)) do_store(p, m, n, acc[i][j][r], z, zb, col);
+                        if (FULL || (m < M && n < N)) do_store(p, m, n, acc[i][j][r], z, zb, col);
                     }
                 }
         }
     };
-    if (m0 + P::BM <= M && n0 + P::BN <= p.N) epilogue(std::true_type{}); else epilogue(std::false_type{});
+    if (m0 + P::BM <= M && n0 + P::BN <= N) epilogue(std::true_type{}); else epilogue(std::false_type{});
 }
 
 // This workgroup's tile: rows m0.., columns n0.., reduction chunk z; false: nothing to do.
 template <class P> __device__ __forceinline__ bool tile_of(const P &p, int M, int &m0, int &n0, int &z)
 {
     constexpr int BM = P::BM, BN = P::BN;
-    const int tiles_n = (p.N + BN - 1) / BN;
+    const int tiles_n = (tile_cols(p) + BN - 1) / BN;
     int tile = blockIdx.x;
     z = blockIdx.y;
     if constexpr (!HasBatch<P>::value) {
@@ -630,6 +581,10 @@ __global__ __launch_bounds__(P::WAVES_M * P::WAVES_N * 64) void gemm_kernel(cons
     const T *a_nat = As + wm * TM * 32 + nat_off_a;
     const T *b_nat = Bs + wn * TN * 32 + nat_off_b;
 
+    constexpr bool BIAS = BiasCol<P>::value;
+    static_assert(!BIAS || (NAT_A && BM <= 64), "bias column: a row per lane");
+    float bias = 0.0f;                           // of row lane % BM, in the last wavefront of the workgroups of the first columns
+
     // one k-tile: registers -> LDS, refill this stage's registers with the tile D steps ahead, multiply.
     // REFILL: 1 = always (steady state: an unconditional load lets the compiler wait for exactly the older stages),
     // 0 = never, 2 = if that tile exists
@@ -671,6 +626,15 @@ __global__ __launch_bounds__(P::WAVES_M * P::WAVES_N * 64) void gemm_kernel(cons
                     for (int j = 0; j < TN; ++j)
                         acc[i][j] = SWAP ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(bv[j], av[i], acc[i][j], 0, 0, 0)
                                          : __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[i], bv[j], acc[i][j], 0, 0, 0);
+            }
+        }
+        if constexpr (BIAS) {
+            if (n0 == 0 && wave == WM * WN - 1) {
+                float a[BK];
+#pragma unroll
+                for (int k = 0; k < BK; ++k) a[k] = As[k * LSNA + lane % BM];
+#pragma unroll
+                for (int k = 0; k < BK; ++k) bias = __builtin_fmaf(a[k], P::BIAS_COL, bias);
             }
         }
         __syncthreads();
@@ -786,15 +750,15 @@ __global__ __launch_bounds__(P::WAVES_M * P::WAVES_N * 64) void gemm_kernel(cons
         for (int k0 = kbeg; k0 < kend; k0 += BK) step_s(k0, acc, rra[0], rrb[0], std::integral_constant<int, 2>{});
     }
 
+    if constexpr (BIAS) {
+        if (n0 == 0 && wave == WM * WN - 1 && lane < BM && m0 + lane < M) p.store(m0 + lane, p.N - 1, bias, z);
+    }
     epi_store(p, acc, epi, m0, n0, M, z, zb, wm, wn, lane);
 }
 
-template <class P> __global__ void gemm_split_kernel(const P p);
-template <class P> constexpr auto tile_kernel() { if constexpr (sizeof(typename P::T) == 2 || F32Mfma<P>::value) return gemm_kernel<P>; else return gemm_split_kernel<P>; }
-
 template <class P> inline hipError_t launch_gemm(const P &p, hipStream_t stream)
 {
-    const int tiles = ((grid_rows(p) + P::BM - 1) / P::BM) * ((p.N + P::BN - 1) / P::BN);
+    const int tiles = ((grid_rows(p) + P::BM - 1) / P::BM) * ((tile_cols(p) + P::BN - 1) / P::BN);
     const int nz = (p.K + p.klen - 1) / p.klen;
     if (tiles <= 0 || nz <= 0) return hipSuccess;
     dim3 grid(tiles, nz, grid_batches(p));
@@ -802,7 +766,7 @@ template <class P> inline hipError_t launch_gemm(const P &p, hipStream_t stream)
         if (nz >= 32) grid = dim3(((nz + 7) / 8) * 8 * tiles, 1, 1);      // XCD-aware order, decoded in the kernel
         else grid.x = ((tiles + 7) / 8) * 8;                              // likewise: an eighth of the tiles per XCD
     }
-    hipLaunchKernelGGL(tile_kernel<P>(), grid, dim3(P::WAVES_M * P::WAVES_N * 64, 1, 1), 0, stream, p);
+    hipLaunchKernelGGL(gemm_kernel<P>, grid, dim3(P::WAVES_M * P::WAVES_N * 64, 1, 1), 0, stream, p);
     return hipGetLastError();
 }
 

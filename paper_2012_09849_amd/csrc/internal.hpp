@@ -5,7 +5,6 @@
 
 #include "../../include/hts.h"
 #include "problems.hpp"
-#include "split.hpp"
 #include "wsgemm.hpp"
 
 namespace hts {

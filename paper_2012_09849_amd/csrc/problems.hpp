@@ -52,7 +52,6 @@ HTS_HD int clamp_row(int r, int n) { return r < n ? r : n - 1; }
 // ------------------------------------------------------------------------------------------------------------
 template <typename T_> struct PlainGemm {
     using T = T_;
-    static constexpr bool F32_MFMA = true;
     static constexpr int BM = 64, BN = 64, BK = OperandTraits<T>::BK, WAVES_M = 2, WAVES_N = 2;
     static constexpr int VA = 4, VB = 4;
     static constexpr bool A_ALONG_K = true, B_ALONG_K = true;
@@ -83,7 +82,6 @@ template <typename T_> struct Conv1Fwd {
     static constexpr int BM = 256, BN = 32, BK = (sizeof(T) == 2 ? BK_BF16 : 32), WAVES_M = 8, WAVES_N = 1;
     static constexpr int VA = 8, VB = OperandTraits<T>::VEC;
     static constexpr bool A_ALONG_K = true, B_ALONG_K = true;
-    static constexpr bool F32_MFMA = true;      // (binary32: see ConvFwd)
     static constexpr int SEG = 64;       // forward sums are segmented so every kernel variant returns the same bits
     static constexpr int STAGES = sizeof(T) == 2 ? 2 : 1;     // bf16: two k-tiles of loads in flight (16x72x96 frames: 169 -> 147 us at B = 2048)
     typedef PtrCtx<uint8_t> CtxA;
@@ -124,10 +122,6 @@ template <typename T_> struct Conv1Fwd {
 // ------------------------------------------------------------------------------------------------------------
 template <typename T_, class L, bool FLAT_OUT> struct ConvFwd {
     using T = T_;
-    // (binary32: the forward kernels of small batches lose by pieces -- conv3 at 16 rows 4.4 -> 5.3 us, an act call at 4 rows
-    // 20.5 -> 22 us: few products per operand cut -- and all batch sizes must add alike.  Large batches give up 40 vs 78 us
-    // of conv1 and 47 vs 61 us of conv2 at 1024 rows.)
-    static constexpr bool F32_MFMA = true;
     static constexpr int BM = sizeof(T) == 2 ? 128 : 64, BN = 64, BK = (sizeof(T) == 2 ? BK_BF16 : 32), WAVES_M = sizeof(T) == 2 ? 4 : 2, WAVES_N = 4 / WAVES_M;
     static constexpr int VA = OperandTraits<T>::VEC, VB = OperandTraits<T>::VEC;
     static constexpr bool A_ALONG_K = true, B_ALONG_K = true;
@@ -207,7 +201,6 @@ template <typename T_, class L, bool FLAT_OUT> struct ConvFwd {
 // ------------------------------------------------------------------------------------------------------------
 template <typename T_> struct FcFwd {
     using T = T_;
-    static constexpr bool F32_MFMA = true;      // (binary32: see ConvFwd)
     static constexpr int BM = 64, BN = 64, BK = (sizeof(T) == 2 ? BK_BF16 : 32), WAVES_M = 2, WAVES_N = 2;
     static constexpr int VA = OperandTraits<T>::VEC, VB = OperandTraits<T>::VEC;
     static constexpr bool A_ALONG_K = true, B_ALONG_K = true;
@@ -233,7 +226,6 @@ template <typename T_> struct FcFwd {
 // ------------------------------------------------------------------------------------------------------------
 struct HeadsWgrad {
     using T = float;
-    static constexpr bool F32_MFMA = true;      // a few microseconds of latency; nothing to gain from pieces
     static constexpr int BM = 32, BN = 128, BK = 32, WAVES_M = 1, WAVES_N = 4;
     static constexpr int VA = 1, VB = 4;
     static constexpr bool A_ALONG_K = false, B_ALONG_K = false;
@@ -275,7 +267,6 @@ struct HeadsWgrad {
 // ------------------------------------------------------------------------------------------------------------
 template <typename T_> struct FcWgrad {
     using T = T_;
-    static constexpr int SPLIT_DEPTH = 1;
     static constexpr int BM = 64, BN = 64, BK = (sizeof(T) == 2 ? BK_BF16_WGRAD : 32), WAVES_M = 2, WAVES_N = 2;   // 8 x 50 workgroups
     static constexpr int VA = OperandTraits<T>::VEC, VB = OperandTraits<T>::VEC;
     static constexpr bool A_ALONG_K = false, B_ALONG_K = false;
@@ -482,7 +473,7 @@ template <typename T_, class L> struct ConvDgrad {
 // ------------------------------------------------------------------------------------------------------------
 template <typename T_, class L> struct ConvWgrad {
     using T = T_;
-    static constexpr int SPLIT_DEPTH = 1;
+    static constexpr float BIAS_COL = 1.0f;
     static constexpr bool STEADY = true;
     static constexpr int BM = 64, BN = 64, BK = (sizeof(T) == 2 ? BK_BF16_WGRAD : 32), WAVES_M = 2, WAVES_N = 2;
     static constexpr int VA = OperandTraits<T>::VEC, VB = OperandTraits<T>::VEC;
@@ -554,8 +545,7 @@ template <typename T_, class L> struct ConvWgrad {
 // INDEXED: the frames are gathered through `index` (a template parameter so that the loader has no branch)
 template <typename T_, bool INDEXED> struct Conv1Wgrad {
     using T = T_;
-    static constexpr int SPLIT_DEPTH = 1;
-    static constexpr int B_PIECES = 1;   // pixels (and the constant 255) are exact in bfloat16
+    static constexpr float BIAS_COL = 255.0f;
     static constexpr bool NATURAL_LDS = sizeof(T) == 4;
     static constexpr bool STEADY = true;
     static constexpr int BM = 32, BN = 128, BK = (sizeof(T) == 2 ? BK_BF16_WGRAD : 32), WAVES_M = 1, WAVES_N = 4;

@@ -19,8 +19,6 @@
 
 namespace hts {
 
-template <class P, int SEG> constexpr int ws_pitch() { return SEG + (sizeof(typename P::T) == 2 ? 8 : F32Mfma<P>::value ? 1 : 4); }
-
 // BDIR = true (needs B_ALONG_K): the B operand (a weight matrix, rows contiguous in k) skips LDS -- every lane
 // loads the k-vectors of its own column straight into registers and picks the elements its MFMA slot needs.  That
 // halves the LDS footprint, so twice as many wavefronts (segments) fit in one workgroup.
@@ -31,11 +29,7 @@ __global__ __launch_bounds__(WAVES * 64) void wsgemm_kernel(const P p, const int
     const int zb = blockIdx.z, M = rows_of(p, zb);
     using T = typename P::T;
     using Tr = OperandTraits<T>;
-    // binary32 panels stay binary32 in LDS; a lane cuts what it reads into bfloat16 pieces (every entry of a panel is read
-    // by one lane only).  Their row pitch keeps rows 16-byte aligned and four banks apart.
-    constexpr int NPA = PiecesA<P>::value, NPB = PiecesB<P>::value;
-    constexpr bool F32 = F32Mfma<P>::value, SPLIT = !F32 && NPA * NPB > 1;
-    constexpr int LS = ws_pitch<P, SEG>();
+    constexpr int LS = SEG + Tr::PAD;
     constexpr int VA = P::VA, VB = P::VB;
     // work items per operand panel: a k-contiguous vector (ALONG_K); otherwise (operand contiguous along its rows) a
     // V x V block to transpose in registers (bfloat16: LDS rows are then written 16 bytes at a time), or for binary32 a
@@ -46,7 +40,7 @@ __global__ __launch_bounds__(WAVES * 64) void wsgemm_kernel(const P p, const int
     constexpr int CB = P::B_ALONG_K ? 32 * SEG / VB : NAT_B ? (32 / VB) * SEG : (32 / VB) * (SEG / VB);
     constexpr int NA = (CA + 63) / 64, NB = (CB + 63) / 64;
     constexpr int RA = (P::A_ALONG_K || NAT_A) ? 1 : VA, RB = (P::B_ALONG_K || NAT_B) ? 1 : VB;
-    static_assert(SEG % (F32 ? 2 : 16) == 0 && (!SPLIT || SEG % 32 == 0) && SEG % VA == 0 && SEG % VB == 0 && 32 % VA == 0 && 32 % VB == 0, "segment shape");
+    static_assert(SEG % Tr::KINST == 0 && SEG % VA == 0 && SEG % VB == 0 && 32 % VA == 0 && 32 % VB == 0, "segment shape");
     constexpr size_t PANEL_BYTES = (size_t)(BDIR ? 1 : 2) * 32 * LS * sizeof(T);   // operand panel(s) of one wavefront
     static_assert(PARTIAL || PANEL_BYTES >= 4096, "the fold reuses a wavefront's panels for its 32x32 partial tile");
 
@@ -95,9 +89,9 @@ __global__ __launch_bounds__(WAVES * 64) void wsgemm_kernel(const P p, const int
         if (ROWS_B && i % (NB / 2 > 0 ? NB / 2 : 1) != 0) cb[i] = cb[i - 1];
         else cb[i] = make_ctx_b(p, n0 + r, zb);
     }
-    constexpr bool VEC_LDS = !F32;
+    constexpr bool VEC_LDS = sizeof(T) == 2;
     const typename P::CtxB cbd = make_ctx_b(p, n0 + lrow, zb);      // this lane's own column (direct B operands)
-    constexpr int NBD = BDIR ? (F32 ? SEG / VB : (SEG / 16) * (8 / VB)) : 1;
+    constexpr int NBD = BDIR ? (sizeof(T) == 4 ? SEG / VB : (SEG / 16) * (8 / VB)) : 1;
 
     auto segment_sum = [&](int seg) -> f32x16 {
         const int kbeg = seg * SEG, kend = min(p.K, kbeg + SEG);
@@ -105,7 +99,7 @@ __global__ __launch_bounds__(WAVES * 64) void wsgemm_kernel(const P p, const int
         Vec<T, VB> rb[BDIR ? 1 : NB][RB];
         Vec<T, VB> rbd[NBD];
         if constexpr (BDIR) {
-            if constexpr (F32) {
+            if constexpr (sizeof(T) == 4) {
 #pragma unroll
                 for (int q = 0; q < NBD; ++q) rbd[q] = p.load_b(cbd, kbeg + q * VB, kend);
             } else {        // slot t of this lane covers k = 16 t + 8 lk .. +7
@@ -186,48 +180,32 @@ __global__ __launch_bounds__(WAVES * 64) void wsgemm_kernel(const P p, const int
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
         const T *a = As + lrow * LS, *b = Bs + lrow * LS;
-        if constexpr (F32 && BDIR) {
+        if constexpr (!BDIR) {
+#pragma unroll 8
+            for (int kk = 0; kk < SEG; kk += Tr::KINST) {
+                if constexpr (sizeof(T) == 4)
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[kk + lk], b[kk + lk], acc, 0, 0, 0);
+                else
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8 *>(a + kk + lk * 8),
+                                                                  *reinterpret_cast<const bf16x8 *>(b + kk + lk * 8), acc, 0, 0, 0);
+            }
+        } else if constexpr (sizeof(T) == 4) {
 #pragma unroll
             for (int t = 0; t < SEG / 2; ++t) {          // slot t needs k = 2 t + lk: one of two neighbours in a vector
                 const float b0 = rbd[(2 * t) / VB][(2 * t) % VB], b1 = rbd[(2 * t + 1) / VB][(2 * t + 1) % VB];
                 acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[2 * t + lk], lk ? b1 : b0, acc, 0, 0, 0);
             }
-        } else if constexpr (F32) {
-#pragma unroll 8
-            for (int kk = 0; kk < SEG; kk += 2) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[kk + lk], b[kk + lk], acc, 0, 0, 0);
         } else {
-            auto b_at = [&](int t) {                     // this lane's 8 consecutive k of slot t
-                if constexpr (!BDIR) return *reinterpret_cast<const Vec<T, 8> *>(b + 16 * t + lk * 8);
-                else if constexpr (VB == 8) return rbd[t];
+#pragma unroll
+            for (int t = 0; t < SEG / 16; ++t) {
+                bf16x8 bv;
+                if constexpr (VB == 8) bv = rbd[t];
                 else {
-                    Vec<T, 8> v;
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) v[e] = rbd[t * (8 / VB) + e / VB][e % VB];
-                    return v;
+                    for (int e = 0; e < 8; ++e) bv[e] = rbd[t * (8 / VB) + e / VB][e % VB];
                 }
-            };
-            constexpr int KB = SPLIT ? 2 : 1;
-            f32x16 small;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) small[r] = 0.0f;
-#pragma unroll
-            for (int t = 0; t < SEG / 16; t += KB) {
-                bf16x8 av[KB][NPA], bv[KB][NPB];
-#pragma unroll
-                for (int h = 0; h < KB; ++h) {
-                    to_pieces<T, 8>(*reinterpret_cast<const Vec<T, 8> *>(a + 16 * (t + h) + lk * 8), av[h]);
-                    to_pieces<T, 8>(b_at(t + h), bv[h]);
-                }
-                for_piece_pairs<NPA, NPB>([&](auto pa, auto pb, auto is_small) {
-                    f32x16 &d = decltype(is_small)::value ? small : acc;
-#pragma unroll
-                    for (int h = 0; h < KB; ++h)
-                        d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[h][decltype(pa)::value], bv[h][decltype(pb)::value], d, 0, 0, 0);
-                });
-            }
-            if constexpr (SPLIT) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[r] += small[r];
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8 *>(a + 16 * t + lk * 8), bv,
+                                                              acc, 0, 0, 0);
             }
         }
         return acc;
@@ -336,7 +314,7 @@ __global__ __launch_bounds__(WAVES * 64) void wsgemm16_kernel(const P p, const i
     using Tr = OperandTraits<T>;
     constexpr int VA = P::VA, VB = P::VB;
     constexpr int KI = sizeof(T) == 4 ? 4 : 32;          // k per matrix instruction
-    static_assert(P::A_ALONG_K && P::B_ALONG_K && (sizeof(T) == 2 || F32Mfma<P>::value), "k-contiguous operands, not cut into pieces");
+    static_assert(P::A_ALONG_K && P::B_ALONG_K, "k-contiguous operands");
     static_assert(WAVES >= 4 && SEG % KI == 0 && SEG % (4 * VA) == 0 && SEG % (4 * VB) == 0,
                   "four wavefronts own the fold; four lanes share a panel row");
     constexpr int LS = SEG + Tr::VEC;         // row pitch: a 16-byte step per row, so the 64 lanes of an operand read
@@ -448,8 +426,7 @@ inline hipError_t launch_wsgemm(const P &p, hipStream_t stream, int segs_per_gro
     const int tiles = ((grid_rows(p) + 31) / 32) * ((p.N + 31) / 32);
     const int nseg = (p.K + SEG - 1) / SEG;
     if (tiles <= 0 || nseg <= 0) return hipSuccess;
-    const size_t lds = (size_t)WAVES * (BDIR ? 1 : 2) * 32 * ws_pitch<P, SEG>() * sizeof(T);
-    static_assert((size_t)WAVES * (BDIR ? 1 : 2) * 32 * ws_pitch<P, SEG>() * sizeof(T) <= 160 * 1024, "LDS");
+    const size_t lds = (size_t)WAVES * (BDIR ? 1 : 2) * 32 * (SEG + OperandTraits<T>::PAD) * sizeof(T);
     auto kern = wsgemm_kernel<P, WAVES, SEG, PARTIAL, BDIR>;
     static std::atomic<bool> attr_set{false};       // raise the dynamic-LDS limit once per instantiation (setting it twice is harmless)
     if (!attr_set.load(std::memory_order_acquire)) {

@@ -1,6 +1,6 @@
 """conv2, FC and the FC input gradient of large bf16 batches, whose operand tiles are copied straight into LDS: batches that
-end inside a tile, on either side of each change of tile or stages, against the wave-per-segment kernels bit for bit; and the
-gradient where the input gradient changes tiles."""
+end inside a tile, on either side of each change of tile or stages, against the wave-per-segment kernels bit for bit; and
+gradients where the input gradient changes tiles and where a bias is summed beside the column tiles (binary32)."""
 import numpy as np
 import pytest
 import torch
@@ -32,11 +32,12 @@ def test_large_batches_agree_bitwise(hts, shape, A, sizes, monkeypatch):  # noqa
 
 
 # As for small minibatches (twice the rows, half the weight of each): binary32 sums of at most n = 700 * 400 terms in another
-# order, sqrt(n) 2^-24 = 3.2e-5.  350 rows take 64x64 tiles of the FC input gradient, 700 rows 64x128.
-@pytest.mark.parametrize("shape,A,B", [(ATARI, 18, 350), ((3, 44, 52), 7, 150)])
-def test_gradient_is_the_mean_of_its_halves(hts, oracle, shape, A, B):  # noqa: F811
+# order, sqrt(n) 2^-24 = 3.2e-5.  350 rows take 64x64 tiles of the FC input gradient, 700 rows 64x128.  Three channels end
+# conv1's weight gradient inside a column tile, whose bias column is binary32's to sum beside the tiles.
+@pytest.mark.parametrize("shape,A,B,precision", [(ATARI, 18, 350, 1), ((3, 44, 52), 7, 150, 1), (ATARI, 18, 330, 0), ((3, 44, 52), 7, 150, 0)])
+def test_gradient_is_the_mean_of_its_halves(hts, oracle, shape, A, B, precision):  # noqa: F811
     _, params, obs, actions, old_logp, adv, ret = _rollout(oracle, shape, A, 2 * B, 900 + B, False)
-    ctx = hts.Context(*shape, A, precision=1, max_learn_batch=2 * B)
+    ctx = hts.Context(*shape, A, precision=precision, max_learn_batch=2 * B)
 
     def gradient(lo, hi):
         g = torch.full((ctx.P,), float("nan"), device="cuda")

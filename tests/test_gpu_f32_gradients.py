@@ -1,4 +1,4 @@
-"""binary32 backward kernels on bfloat16 pieces: gradients at the edges of their tiles and of the two kernel families, and
+"""binary32 backward kernels: gradients at the edges of their tiles, and
 over operands whose magnitudes spread over many binades, against the oracle's float64 gradient."""
 import numpy as np
 import pytest
@@ -10,14 +10,13 @@ from test_gpu_parity import ATARI, _rollout, _split, dev, hts, oracle_hp  # noqa
 pytestmark = pytest.mark.gpu
 
 
-# 96 / 97 rows: last of the wave-per-segment, first of the tile kernels; 65 = one row more than a 64-row tile; 3x44x52 and
-# 2x36x36 frames have feature counts that end inside a tile.  A sum of n products of binary32 numbers in binary32 is off by
-# about sqrt(n) 2^-24 of its size: n is at most B * P1 = 97 * 400 positions, so 1.2e-5; the pieces' own error (2^-26 a
-# product) is below that.  Rows of `adv` scaled over 2^-20 .. 2^20 leave the gradient to a few rows and the small ones to
-# the last pieces.
-@pytest.mark.parametrize("shape,A,B,spread", [((3, 44, 52), 7, 65, 0), ((3, 44, 52), 7, 96, 20), ((3, 44, 52), 7, 97, 20),
+# 128 / 129 rows: last of the wave-per-segment, first of the tile kernels; 65 = one row more than a 64-row tile; 3x44x52 and
+# 2x36x36 frames have feature counts that end inside a tile, and conv1 columns that end inside one beside the bias column.  A
+# sum of n products of binary32 numbers in binary32 is off by about sqrt(n) 2^-24 of its size: n is at most B * P1 = 129 * 120
+# (3x44x52) or 97 * 400 positions, so 1.2e-5.  Rows of `adv` scaled over 2^-20 .. 2^20 leave the gradient to a few rows.
+@pytest.mark.parametrize("shape,A,B,spread", [((3, 44, 52), 7, 65, 0), ((3, 44, 52), 7, 96, 20), ((3, 44, 52), 7, 97, 20), ((3, 44, 52), 7, 129, 20),
                                               ((2, 36, 36), 5, 129, 0), (ATARI, 18, 97, 0)])
-def test_gradient_on_pieces(hts, oracle, shape, A, B, spread):  # noqa: F811
+def test_f32_gradient(hts, oracle, shape, A, B, spread):  # noqa: F811
     Cc, H, W = shape
     net, params, obs, actions, old_logp, adv, ret = _rollout(oracle, shape, A, B, 300 + B, False)
     adv = (adv * 2.0 ** np.linspace(-spread, spread, B)).astype(np.float32)
