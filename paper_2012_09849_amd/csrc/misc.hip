@@ -917,7 +917,9 @@ template <bool VEC> __global__ __launch_bounds__(NRM_THREADS) void normalize_app
     const int t = threadIdx.x;
     const double x0 = part[0], ps = t < (int)gridDim.x ? part[1 + 2 * t] : 0.0, pq = t < (int)gridDim.x ? part[2 + 2 * t] : 0.0;
     const double s = block_sum_f64<NRM_THREADS>(ps, red[0]), q = block_sum_f64<NRM_THREADS>(pq, red[1]);
-    const double mean = x0 + s / (double)n, var = fmax(q - s * (s / (double)n), 0.0) / (double)(n - 1);
+    // (rounding may leave a sum of squares just below zero; a NaN, from an infinity or a NaN among the entries, stays one and
+    // makes every result NaN, as the one-workgroup kernel's two passes do)
+    const double sq = q - s * (s / (double)n), mean = x0 + s / (double)n, var = (sq < 0.0 ? 0.0 : sq) / (double)(n - 1);
     const double inv = 1.0 / (sqrt(var) + 1e-5);
     for (long long v = v0; v < nv; v += stride) {
         const f32x4 next = load_entries<VEC>(adv, v + stride < nv ? v + stride : v, n);

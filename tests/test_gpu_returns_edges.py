@@ -26,6 +26,23 @@ def test_normalize_edges(hts, oracle, n, shift):  # noqa: F811
     ctx.close()
 
 
+# One infinity or NaN makes the mean or the deviation infinite or NaN, and with it every result NaN: in the one-workgroup
+# kernels (4 and 16 wavefronts) and in the several workgroups of larger arrays, wherever it stands (entry 0 is the point
+# about which the latter sum).
+@pytest.mark.parametrize("n", [5, 4096, 8192, 16384, 16385, 70000])
+@pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan")])
+def test_normalize_nonfinite(hts, n, value):  # noqa: F811
+    ctx = hts.Context(4, 84, 84, 6, max_act_batch=1)
+    for at in (0, n // 2, n - 1):
+        a = syn.normal_f32(n, syn.S_MISC, (n,)).astype(np.float32)
+        a[at] = value
+        buf = dev(a)
+        ctx.hts_normalize_advantages(buf)
+        torch.cuda.synchronize()
+        assert bool(torch.isnan(buf).all()), at
+    ctx.close()
+
+
 # plain / chunked kernels (8 steps; 131072 columns), each column width (4, 16, 64), spans that end exactly at, one step
 # before and one step after a multiple of the span, a last workgroup with dead columns.  The tolerance of the oracle's
 # other returns tests: one binary32 rounding of a float64 recurrence.
