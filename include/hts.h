@@ -114,7 +114,8 @@ int32_t hts_sample_from_logits(hts_ctx *ctx, const float *logits, uint64_t seed,
 int32_t hts_returns_gae(hts_ctx *ctx, const float *rewards, const float *values, const uint8_t *dones, float gamma,
                         float lambda, int32_t T, int32_t N, float *advantages, float *returns);
 
-/* In-place (A - mean) / (std + 1e-5) over n entries, std with the n-1 divisor; fixed-shape reduction. */
+/* In-place (A - mean) / (std + 1e-5) over n entries, std with the n-1 divisor; fixed-shape reduction.  ctx may be NULL only
+ * if stream 0 is intended; such calls may be made by several threads at a time. */
 int32_t hts_normalize_advantages(hts_ctx *ctx, float *adv, int64_t n);
 
 /* One storage as the learner reads it: `count` rows (= T*N, time-major), of which the minibatch is the B rows

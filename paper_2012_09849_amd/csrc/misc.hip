@@ -879,7 +879,10 @@ template <bool VEC, int NT> __global__ __launch_bounds__(NT) void normalize_one_
 // One workgroup's share of the sums about the first entry x_0: part[1 + 2i] = sum (x - x_0), part[2 + 2i] = sum (x - x_0)^2,
 // part[0] = x_0.  var = (q - s^2/n) / (n-1) then cancels little: s^2/n = n (mean - x_0)^2, and x_0's own term already
 // makes the sum of squares about the mean at least (mean - x_0)^2, so at most a factor n of double precision's 2^-53.
-__device__ double normalize_scratch[1 + 2 * NRM_BLOCKS];      // for calls without a context (all of them on the default stream)
+// Calls without a context have no workspace and share one array per GPU.  All of them go to the default stream, which keeps a
+// call's two launches in order; normalize_mutex keeps another thread's from coming between them.
+__device__ double normalize_scratch[1 + 2 * NRM_BLOCKS];
+static std::mutex normalize_mutex;
 template <bool VEC> __global__ __launch_bounds__(NRM_THREADS) void normalize_sums_kernel(const float *__restrict__ adv, long long n,
                                                                                          double *part)
 {
@@ -946,6 +949,8 @@ hipError_t launch_normalize(Ctx *c, hipStream_t s, float *adv, long long n)
         return hipGetLastError();
     }
     double *part = c ? c->ws.adv_part : nullptr;
+    std::unique_lock<std::mutex> pair(normalize_mutex, std::defer_lock);
+    if (!part) pair.lock();
     const long long need = ((n + 3) / 4 + NRM_THREADS - 1) / NRM_THREADS;
     const dim3 grid((unsigned)(need < NRM_BLOCKS ? need : NRM_BLOCKS));
     hipLaunchKernelGGL(vec ? normalize_sums_kernel<true> : normalize_sums_kernel<false>, grid, dim3(NRM_THREADS), 0, s, adv, n, part);

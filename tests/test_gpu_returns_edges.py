@@ -1,4 +1,7 @@
 """Returns and advantage normalisation at the edges of their kernels' ranges, against the oracle."""
+import ctypes as C
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -40,6 +43,38 @@ def test_normalize_nonfinite(hts, n, value):  # noqa: F811
         ctx.hts_normalize_advantages(buf)
         torch.cuda.synchronize()
         assert bool(torch.isnan(buf).all()), at
+    ctx.close()
+
+
+# Without a context the call goes to stream 0 and, beyond 16384 entries, its two launches pass their sums through one array of
+# the library: calls of several threads with other sizes and means must come out as they do with a context, bit for bit.
+def test_normalize_without_a_context_from_several_threads(hts):  # noqa: F811
+    calls, sizes = 60, (4097, 16385, 70000, 300001)
+    ctx = hts.Context(4, 84, 84, 6, max_act_batch=1, stream=torch.cuda.default_stream())
+    lib = hts.binding.load_library()
+    bufs, wants = [], []
+    for i, n in enumerate(sizes):
+        x = dev(syn.normal_f32(n, syn.S_MISC, (n,)) * (i + 1) + 10 * i)
+        bufs.append([x.clone() for _ in range(calls)])
+        ctx.hts_normalize_advantages(x)
+        wants.append(x)
+    torch.cuda.synchronize()
+    codes, start = [], threading.Barrier(len(sizes))
+
+    def work(mine, n):
+        start.wait()
+        for b in mine:
+            codes.append(lib.hts_normalize_advantages(None, C.c_void_p(b.data_ptr()), n))
+
+    threads = [threading.Thread(target=work, args=(b, n)) for b, n in zip(bufs, sizes)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert codes == [0] * (calls * len(sizes))
+    for mine, want in zip(bufs, wants):
+        assert all(torch.equal(b, want) for b in mine)
     ctx.close()
 
 
