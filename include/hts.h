@@ -110,7 +110,8 @@ int32_t hts_sample_from_logits(hts_ctx *ctx, const float *logits, uint64_t seed,
  *   rewards f32 [T,N]   values f32 [T+1,N] (row T = value of the state after the last step)
  *   dones u8 [T,N] (1 = the action at step t ended the episode)
  *   delta_t = r_t + gamma (1-d_t) V_{t+1} - V_t;  A_t = delta_t + gamma lambda (1-d_t) A_{t+1}, A_T = 0;
- *   advantages f32 [T,N] = A;   returns f32 [T,N] = A + V.   ctx may be NULL only if stream 0 is intended. */
+ *   advantages f32 [T,N] = A;   returns f32 [T,N] = A + V; each may take the place of rewards or of values' first T rows.
+ * ctx may be NULL only if stream 0 is intended. */
 int32_t hts_returns_gae(hts_ctx *ctx, const float *rewards, const float *values, const uint8_t *dones, float gamma,
                         float lambda, int32_t T, int32_t N, float *advantages, float *returns);
 

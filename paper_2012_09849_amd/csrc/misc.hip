@@ -669,6 +669,8 @@ hipError_t launch_wgrad_reduce(Ctx &c, const ReduceSpec (&spec)[REDUCE_JOBS], fl
 constexpr int GAE_U = 8;
 // The recurrence runs in double precision inside the lane (inputs and outputs are fp32), so a long unroll does not
 // accumulate binary32 rounding: each output is the correctly rounded result of an almost exact recurrence.
+// (Outputs in the place of inputs are fine: what is stored to a row depends on everything that is read of it, and no row is
+// read twice.  Without __restrict__ 128x262144 takes 128 us instead of 111.)
 __global__ __launch_bounds__(64) void gae_kernel(const float *__restrict__ r, const float *__restrict__ v,
                                                  const uint8_t *__restrict__ d, float gamma, float lambda, int T, int N,
                                                  float *__restrict__ adv, float *__restrict__ ret)
@@ -717,12 +719,14 @@ __global__ __launch_bounds__(64) void gae_kernel(const float *__restrict__ r, co
 // wavefront and through LDS across wavefronts, and every chunk is then replayed from what truly enters it.  Double
 // precision throughout, so the result equals the one-lane-per-column recurrence to well below binary32 rounding.
 // Steps before t = 0 (a last, partial span) have S = 0 and P = 1 and write nothing.
+// The outputs may take the place of inputs (no __restrict__): a span reads all of its rows before it writes any, and the value
+// behind a span's last step, whose row the span after it in time has written already, comes through LDS from the thread that read it.
 constexpr int GAE_L = 8, GAE_MAX_WAVES = 8;
 template <int COLS> __global__ __launch_bounds__(64 * GAE_MAX_WAVES) void gae_chunked_kernel(
-    const float *__restrict__ r, const float *__restrict__ v, const uint8_t *__restrict__ d, float gamma, float lambda,
-    int T, int N, float *__restrict__ adv, float *__restrict__ ret)
+    const float *r, const float *v, const uint8_t *d, float gamma, float lambda, int T, int N, float *adv, float *ret)
 {
     __shared__ double sS[2][GAE_MAX_WAVES][COLS], sP[2][GAE_MAX_WAVES][COLS];
+    __shared__ float sV[2][COLS];                                // value of the span's first step
     const int waves = blockDim.x >> 6, TC = blockDim.x / COLS;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, cx = threadIdx.x % COLS, cc = threadIdx.x / COLS;
     const int n = blockIdx.x * COLS + cx;
@@ -741,6 +745,7 @@ template <int COLS> __global__ __launch_bounds__(64 * GAE_MAX_WAVES) void gae_ch
             rr[i] = r[o]; vv[i] = v[o]; dd[i] = d[o];
         }
         vv[GAE_L] = v[(long long)max(t0 + GAE_L, 0) * N + col];
+        if (tend != T && cc == TC - 1) vv[GAE_L] = sV[buf ^ 1][cx];
         double S = 0.0, P = 1.0;
 #pragma unroll
         for (int i = GAE_L - 1; i >= 0; --i) {
@@ -760,6 +765,7 @@ template <int COLS> __global__ __launch_bounds__(64 * GAE_MAX_WAVES) void gae_ch
             const double Sl = __shfl_down(S, COLS, 64), Pl = __shfl_down(P, COLS, 64);
             if (lane + COLS < 64) { Se = Sl; Pe = Pl; }
         }
+        if (cc == 0) sV[buf][cx] = vv[0];
         __syncthreads();
         double a = enter, all = enter;                           // entering this wavefront's chunks; leaving the span
 #pragma unroll

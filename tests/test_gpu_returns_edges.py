@@ -95,3 +95,22 @@ def test_gae_edges(hts, oracle, T, N):  # noqa: F811
         err = np.abs(got.cpu().numpy().astype(np.float64) - want) / np.maximum(1.0, np.abs(want))
         assert float(err.max()) <= 1e-6
     ctx.close()
+
+
+# The outputs may be written over the inputs (advantages over the rewards, returns over the first T rows of the values, or the
+# other way round): plain kernel (T, N at either end of its range) and chunked kernels of each column width, with one span of
+# time and with several, the last one partial.
+@pytest.mark.parametrize("T,N", [(5, 33), (8, 40), (13, 131072), (9, 17), (30, 300), (130, 40), (300, 700), (700, 1030), (1100, 5), (2048, 6), (64, 8200), (135, 8200)])
+def test_gae_in_place(hts, T, N):  # noqa: F811
+    ctx = hts.Context(4, 84, 84, 6, max_act_batch=1)
+    r, v = dev(syn.normal_f32(T + N, syn.S_REW, (T, N))), dev(syn.normal_f32(T * 7 + N, syn.S_VAL, (T + 1, N)))
+    d = dev(syn.dones_bernoulli(T + N, T, N, 0.02))
+    adv, ret = torch.zeros(T, N, device="cuda"), torch.zeros(T, N, device="cuda")
+    ctx.hts_returns_gae(r, v, d, 0.99, 0.95, adv, ret)
+    for swap in (False, True):
+        r2, v2 = r.clone(), v.clone()
+        outs = (v2[:T], r2) if swap else (r2, v2[:T])
+        ctx.hts_returns_gae(r2, v2, d, 0.99, 0.95, *outs)
+        torch.cuda.synchronize()
+        assert torch.equal(outs[0], adv) and torch.equal(outs[1], ret) and torch.equal(v2[T], v[T]), swap
+    ctx.close()
