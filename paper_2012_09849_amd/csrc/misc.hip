@@ -793,16 +793,22 @@ hipError_t launch_gae(Ctx *c, hipStream_t s, const float *r, const float *v, con
     Ctx dummy;
     SiteTimer tm(c ? *c : dummy, SITE_GAE);
     // Kernel time by rocprofv3, us: plain / 4 / 16 / 64 columns a workgroup
-    //   5x16 1.7/3.2/2.6/2.3, 6x262147 6.8/55/18/8.6: one chunk of time has nothing to split -> plain
-    //   128x262144 107/641/222/114, 128x70000 40/147/45/31: enough columns hide a lane's serial walk -> plain from 131072
-    //   512x16 64/4.1/5.8/17, 512x100 66/4.7/6.7/18: few workgroups, so every chunk of a long unroll in one span -> 4
-    //   128x32 17/3.9/3.5/5.3, 128x4096 18/11/4.9/6.7, 512x1024 65/11/7.2/18 -> 16
-    //   128x16384 29/39/13/8.0, 30x16384 6.5/12/4.8/4.3: whole cache lines per load -> 64
+    //   plain to 11 steps (a second chunk is mostly padding): 5x16 1.7/3.2/2.6/2.3, 9x48 2.4/4.0/3.5/2.9, 10x300 3.4/4.0/4.0/3.5, 11x70000
+    //   5.8/-/-/5.6, 11x100000 5.6/-/-/6.5; 12x48 2.8/3.9/3.3/2.6, 12x300 3.7/4.0/4.0/3.7, 12x70000 5.9/-/8.0/5.6
+    //   plain from 131072 columns, which hide a lane's serial walk: 128x262144 107/641/222/114, 20x140000 10.8/-/17/11.3, but 128x120000
+    //   58/-/80/49, 256x100000 151/-/136/95; where a workgroup of 64 columns has five to eight wavefronts (33 to 64 steps; 65 to 96 are
+    //   two such spans) few of them fit a compute unit: from 81920 columns on 40x80000 15.0/14.4, 40x90000 15.7/16.9, 80x100000 28/30
+    //   64 columns, whole cache lines per load: 128x16384 29/39/13/8.0, 128x10240 18/-/8.7/7.3, 128x8192 18/-/6.6/7.2; to 40 steps at any
+    //   width: 16x48 3.4/3.9/3.3/2.9, 30x4096 6.2/5.0/4.0/3.9, 40x300 7.2/-/4.2/4.0, 48x16 7.2/-/3.0/3.3
+    //   4 columns beyond 256 steps, the span of 16 columns: 256x16 32/3.8/3.4/9.1, 288x16 37/4.0/5.3/11, 512x16 64/4.1/5.8/17, as long as
+    //   its quarter cache lines don't count; the two meet at 900 columns for 288 steps, 700 for 384, 512 for 512, 450 for 700 and 1024,
+    //   500 for 2048, 700 for 4096 (512x400 5.8/6.9, 512x640 7.9/6.9, 2048x256 18.2/19.8, 2048x900 31/28)
+    //   16 else: 128x32 17/3.9/3.5/5.3, 128x4096 18/11/4.9/6.7, 512x1024 65/11/7.2/18
     // (with a chunk's rows fetched twice and one at a time, 32 columns: 512x16 12.2, 128x4096 8.0)
-    if (T <= GAE_L || N >= 131072) {
+    if (T < 12 || N >= (T > 32 && T <= 96 ? 81920 : 131072)) {
         hipLaunchKernelGGL(gae_kernel, dim3((N + 63) / 64), dim3(64), 0, s, r, v, d, gamma, lambda, T, N, adv, ret);
     } else {
-        const int cols = N > 8192 ? 64 : T > 256 && N <= 512 ? 4 : 16;
+        const int cols = N > 8192 || T <= 40 ? 64 : T > 256 && N <= 512 ? 4 : 16;
         const int per_wave = 64 / cols, chunks = (T + GAE_L - 1) / GAE_L;
         int waves = (chunks + per_wave - 1) / per_wave;
         if (waves > GAE_MAX_WAVES) waves = GAE_MAX_WAVES;

@@ -78,11 +78,30 @@ def test_normalize_without_a_context_from_several_threads(hts):  # noqa: F811
     ctx.close()
 
 
-# plain / chunked kernels (8 steps; 131072 columns), each column width (4, 16, 64), spans that end exactly at, one step
-# before and one step after a multiple of the span, a last workgroup with dead columns.  The tolerance of the oracle's
-# other returns tests: one binary32 rounding of a float64 recurrence.
-@pytest.mark.parametrize("T,N", [(8, 3), (9, 1), (257, 5), (513, 512), (512, 513), (256, 17), (255, 16), (65, 8193),
-                                 (64, 8192), (1025, 2), (9, 131071), (9, 131072)])
+# Infinities and NaN spread backwards in time until the column's first step and never to another column, the same in the
+# plain and the chunked kernels as in the oracle's sequential float64 recurrence (0 * inf at an episode's end is NaN there too).
+@pytest.mark.parametrize("T,N", [(5, 40), (14, 40), (30, 40), (130, 40), (300, 40), (1100, 6), (70, 8200), (13, 131072)])
+def test_gae_nonfinite(hts, oracle, T, N):  # noqa: F811
+    ctx = hts.Context(4, 84, 84, 6, max_act_batch=1)
+    r, v = syn.normal_f32(T + N, syn.S_REW, (T, N)), syn.normal_f32(T * 7 + N, syn.S_VAL, (T + 1, N))
+    d = syn.dones_bernoulli(T + N, T, N, 0.02)
+    r[T // 2, 0], r[T - 1, 1], v[T // 3, 2], v[T, 3], v[0, 4] = np.inf, -np.inf, np.nan, np.inf, np.nan
+    r[T // 2, 5], r[T // 4, 5] = np.inf, -np.inf
+    adv, ret = torch.zeros(T, N, device="cuda"), torch.zeros(T, N, device="cuda")
+    ctx.hts_returns_gae(dev(r), dev(v), dev(d), 0.99, 0.95, adv, ret)
+    torch.cuda.synchronize()
+    with np.errstate(invalid="ignore"):
+        a_ref, r_ref = oracle.gae(r, v, d, np.float32(0.99), np.float32(0.95))
+    for got, want in ((adv, a_ref), (ret, r_ref)):
+        np.testing.assert_allclose(got.cpu().numpy(), want.astype(np.float32), rtol=1e-6, atol=1e-6)
+    ctx.close()
+
+
+# plain / chunked kernels (11 steps; 131072 columns, 81920 for 33 to 96 steps), each column width (4, 16, 64; 64 up to 40 steps),
+# spans that end exactly at, one step before and one step after a multiple of the span, a last workgroup with dead columns.
+# The tolerance of the oracle's other returns tests: one binary32 rounding of a float64 recurrence.
+@pytest.mark.parametrize("T,N", [(8, 3), (9, 1), (11, 100), (12, 1), (12, 70), (40, 65), (41, 65), (257, 5), (513, 512), (512, 513), (256, 17), (255, 16), (65, 8193),
+                                 (64, 8192), (1025, 2), (9, 131071), (9, 131072), (12, 131071), (33, 81919), (33, 81920), (97, 81920)])
 def test_gae_edges(hts, oracle, T, N):  # noqa: F811
     ctx = hts.Context(4, 84, 84, 6, max_act_batch=1)
     r, v = syn.normal_f32(T + N, syn.S_REW, (T, N)), syn.normal_f32(T * 7 + N, syn.S_VAL, (T + 1, N))
@@ -100,7 +119,7 @@ def test_gae_edges(hts, oracle, T, N):  # noqa: F811
 # The outputs may be written over the inputs (advantages over the rewards, returns over the first T rows of the values, or the
 # other way round): plain kernel (T, N at either end of its range) and chunked kernels of each column width, with one span of
 # time and with several, the last one partial.
-@pytest.mark.parametrize("T,N", [(5, 33), (8, 40), (13, 131072), (9, 17), (30, 300), (130, 40), (300, 700), (700, 1030), (1100, 5), (2048, 6), (64, 8200), (135, 8200)])
+@pytest.mark.parametrize("T,N", [(5, 33), (8, 40), (13, 131072), (13, 17), (30, 300), (130, 40), (300, 700), (700, 1030), (1100, 5), (2048, 6), (64, 8200), (135, 8200)])
 def test_gae_in_place(hts, T, N):  # noqa: F811
     ctx = hts.Context(4, 84, 84, 6, max_act_batch=1)
     r, v = dev(syn.normal_f32(T + N, syn.S_REW, (T, N))), dev(syn.normal_f32(T * 7 + N, syn.S_VAL, (T + 1, N)))
