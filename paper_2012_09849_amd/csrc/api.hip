@@ -131,7 +131,6 @@ extern "C" int32_t hts_create(const hts_net_desc *desc, int32_t max_act_batch, i
         s.b1 = 0; s.b2 = 32; s.b3 = 96; s.fcb = 160; s.piw = 672;
         s.pib = s.piw + 512ll * g.A; s.vw = pad4(s.pib + g.A); s.vb = s.vw + 512; s.count = pad4(s.vb + 1);
     }
-    if (const char *sb = getenv("HTS_SMALL_BATCH")) c.small_b = atoi(sb);   // tuning knob: 0 disables the small path
     c.fc_fold_rows = 4096; c.fc_slices = c.fc_groups;
     c.tile16_below = 128;
     if (const char *t16 = getenv("HTS_TILE16_BELOW")) c.tile16_below = atoi(t16);   // tuning knob, same bits either way
@@ -143,6 +142,12 @@ extern "C" int32_t hts_create(const hts_net_desc *desc, int32_t max_act_batch, i
     // (against the wave-per-segment kernel, us: 4x84x84 frames 32 rows 6.7 / 6.6, 64 6.9 / 9.9; 16x72x96 32 14.8 / 14.1, 64 15.2 / 21.3)
     c.conv1_wgrad_image_rows = 33;
     if (const char *sr = getenv("HTS_CONV1_SLAB_ROWS")) c.conv1_slab_rows = c.conv1_wgrad_slab_rows = atoi(sr);   // tuning knob, same bits either way
+    // tuning knob: batches up to it take the wave-per-segment kernels (0: none), bf16's conv1 too, which by itself leaves them at fewer rows
+    if (const char *sb = getenv("HTS_SMALL_BATCH")) {
+        c.small_b = atoi(sb);
+        for (int *rows : {&c.conv1_slab_rows, &c.conv1_wgrad_slab_rows, &c.conv1_wgrad_image_rows})
+            if (*rows <= c.small_b) *rows = c.small_b < (1 << 20) ? c.small_b + 1 : 1 << 20;
+    }
     c.ws = Workspace();
     Carver size_pass;
     carve(c, size_pass);

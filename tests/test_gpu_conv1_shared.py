@@ -48,3 +48,26 @@ def test_small_bf16_minibatch_gradient_is_the_mean_of_its_halves(hts, oracle, sh
         mean = 0.5 * (first[name] + second[name])
         assert np.linalg.norm(w - mean) <= 1.4e-5 * np.linalg.norm(mean), name
     ctx.close()
+
+
+# HTS_SMALL_BATCH asks for the wave-per-segment kernels in every layer that has them.  Up to 32 rows that is the default; at 40 rows
+# of bf16 conv1's weight gradient takes the image kernel by itself: the same products added in another order (binary32 sums of
+# n = 40 * 400 terms, sqrt(n) 2^-24 = 7.6e-6), so some bits must differ, and every other tensor is the same bit for bit.
+@pytest.mark.parametrize("B", [32, 40])
+def test_small_batch_knob_covers_conv1(hts, oracle, B, monkeypatch):  # noqa: F811
+    _, params, obs, actions, _, adv, ret = _rollout(oracle, ATARI, 18, B, 800 + B, False)
+    grads = []
+    for knob in (None, "128"):
+        monkeypatch.delenv("HTS_SMALL_BATCH", raising=False) if knob is None else monkeypatch.setenv("HTS_SMALL_BATCH", knob)
+        ctx = hts.Context(*ATARI, 18, precision=1, max_learn_batch=B)
+        g = torch.full((ctx.P,), float("nan"), device="cuda")
+        ctx.hts_loss_and_grads(dev(obs), dev(actions), None, dev(adv), dev(ret), dev(params), hts.HParams(algo=hts.ALGO_A2C), g)
+        torch.cuda.synchronize()
+        grads.append(_split(g.cpu().numpy(), ATARI, 18))
+        ctx.close()
+    default, forced = grads
+    for name, w in default.items():
+        same = np.array_equal(w, forced[name])
+        assert same or (B == 40 and name in ("conv1.w", "conv1.b")), name
+        assert np.linalg.norm(w.astype(np.float64) - forced[name]) <= 7.6e-6 * np.linalg.norm(w), name
+    assert np.array_equal(default["conv1.w"], forced["conv1.w"]) == (B == 32)

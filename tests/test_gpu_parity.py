@@ -242,6 +242,7 @@ def test_conv1_slab_kernel_agrees_bitwise(hts, shape, A, N, monkeypatch):
     assert all(np.array_equal(x, y) for x, y in zip(*outs))
     # and against the wave-per-segment kernels, 100 observations at a time
     monkeypatch.delenv("HTS_CONV1_SLAB_ROWS", raising=False)
+    monkeypatch.setenv("HTS_SMALL_BATCH", "128")
     ctx = hts.Context(Cc, H, W, A, precision=1, max_act_batch=N)
     for lo in range(0, N, 100):
         part = _act(ctx, obs[lo:lo + 100], params, 5, 1, lo, A)
@@ -765,7 +766,9 @@ def test_bf16_ragged_large_batch_agrees_with_small_batch_kernels(hts, oracle, sh
     every LDS-resident kernel part full and every tile kernel a ragged tail: the large-batch kernels (tile kernels,
     image kernels, split reductions) against the wave-per-segment kernels on the same bf16 problem.  The two differ in
     the order of the backward reductions only (forward bits are identical), so the gradients agree far inside the bf16
-    tolerance; the wave-per-segment kernels are the ones held against the oracle above."""
+    tolerance; the wave-per-segment kernels are the ones held against the oracle above.  The bf16 weight gradients of conv2
+    and conv3 have no wave-per-segment form: they are held against the operand-rounding oracle here (2e-2 and 2.5e-2 of a
+    tensor in the 2-norm, the bounds of the real minibatches: a gate that opens on one side only now and then)."""
     Cc, H, W = shape
     net, params, obs, actions, old_logp, adv, ret = _rollout(oracle, shape, A, count, 900 + count, True)
     index = syn.permutation(8, count)[:B]
@@ -790,3 +793,10 @@ def test_bf16_ragged_large_batch_agrees_with_small_batch_kernels(hts, oracle, sh
     for name, gl in _split(g_large, shape, A).items():
         e = rel_err(gl, _split(g_small, shape, A)[name])
         assert e <= 1e-3, (name, e)
+    qnet = oracle.make_net(Cc, H, W, A, operand_bf16=True)
+    g_q, _ = oracle.loss_grads(qnet, params, obs, actions, old_logp, adv, ret, oracle_hp(oracle, hp), index=index,
+                               threads=oracle.host_threads())
+    for name in ("conv2.w", "conv2.b", "conv3.w", "conv3.b"):
+        want = _split(g_q, shape, A)[name]
+        e = np.linalg.norm(_split(g_large, shape, A)[name] - want) / np.linalg.norm(want)
+        assert e <= (2e-2 if shape == ATARI else 2.5e-2), (name, e)
