@@ -618,14 +618,17 @@ template <typename T> static hipError_t backward_t(Ctx &c, const uint8_t *obs, c
     // partial buffers of the three conv weight gradients live side by side in ws.part
     const SplitK s3 = split_for((long long)B * g.P3, MAXZ3), s2 = split_for((long long)B * g.P2, MAXZ2),
                  s1 = split_for((long long)B * g.P1, MAXZ1);
-    const bool lds1 = sizeof(T) == 2 && ((B >= c.conv1_wgrad_slab_rows && conv1_wgrad_slab_fits(g, obs)) || (B >= c.conv1_wgrad_image_rows && conv1_wgrad_image_fits(g, obs)));
+    // conv1's weight gradient: the kernels with the frame in LDS (bf16) where they fit, else those of the other layers
+    const bool slab1 = sizeof(T) == 2 && B >= c.conv1_wgrad_slab_rows && conv1_wgrad_slab_fits(g, obs) && conv1_wgrad_slab_batch_fits(B, s1.nz);
+    const bool image1 = !slab1 && sizeof(T) == 2 && B >= c.conv1_wgrad_image_rows && conv1_wgrad_image_fits(g, obs);
+    const bool small1 = !slab1 && !image1 && small;
     // conv2/conv3 weight gradients, us, wave-per-segment / tile kernel: bf16 at 16 rows of 84x84 frames 8.8 / 5.4 and 10.1 / 5.9,
     // at 128 rows 12.0 / 5.8 and 12.1 / 6.6; binary32 at 16 rows 9.1 / 10.5 and 8.7 / 11.3, at 96 rows 14.0 / 13.8 and 13.1 / 12.8
     const bool smallw = small && sizeof(T) == 4;
     int spg3 = 0, spg2 = 0, spg1 = 0;
     const int nz3 = smallw ? groups_for((long long)B * g.P3, &spg3, 32, 8) : s3.nz;
     const int nz2 = smallw ? groups_for((long long)B * g.P2, &spg2, 32, 8) : s2.nz;
-    int nz1 = small && !lds1 ? groups_for((long long)B * g.P1, &spg1, 56, 4) : s1.nz;   // long reduction, tiny output
+    int nz1 = small1 ? groups_for((long long)B * g.P1, &spg1, 56, 4) : s1.nz;   // long reduction, tiny output
     float *part3 = c.ws.part;
     float *part2 = part3 + (size_t)nz3 * 64 * 577;
     float *part1 = part2 + (size_t)nz2 * 64 * 513;
@@ -712,10 +715,10 @@ template <typename T> static hipError_t backward_t(Ctx &c, const uint8_t *obs, c
             p.Kc = g.K1; p.C = g.C; p.H = g.H; p.W = g.W; p.W1 = g.W1; p.P1 = g.P1;
             p.dP1 = FastDiv::make(g.P1); p.dW1 = FastDiv::make(g.W1);
             SiteTimer tm(c, SITE_CONV1_WGRAD);
-            return small ? launch_wsgemm<decltype(p), 4, 64, false>(p, c.stream, spg1) : launch_gemm(p, c.stream);
+            return small1 ? launch_wsgemm<decltype(p), 4, 64, false>(p, c.stream, spg1) : launch_gemm(p, c.stream);
         };
-        if (sizeof(T) == 2 && B >= c.conv1_wgrad_slab_rows && conv1_wgrad_slab_fits(g, obs) && conv1_wgrad_slab_batch_fits(B, s1.nz)) e = launch_conv1_wgrad_slab(c, obs, index, B, part1, s1.nz, &nz1);
-        else if (sizeof(T) == 2 && B >= c.conv1_wgrad_image_rows && conv1_wgrad_image_fits(g, obs)) e = launch_conv1_wgrad_image(c, obs, index, B, part1, s1.nz, &nz1);
+        if (slab1) e = launch_conv1_wgrad_slab(c, obs, index, B, part1, s1.nz, &nz1);
+        else if (image1) e = launch_conv1_wgrad_image(c, obs, index, B, part1, s1.nz, &nz1);
         else e = index ? conv1_wgrad(Conv1Wgrad<T, true>{}) : conv1_wgrad(Conv1Wgrad<T, false>{});
         if (e != hipSuccess) return e;
     }
