@@ -205,13 +205,26 @@ constexpr int C1S_TILES = 4;              // position tiles per consumer wavefro
 
 template <int H, int W> constexpr size_t conv1_slab_lds() { return (size_t)2 * (8 * H * W) + 2 * C1S_WBUF + 128 + C1S_MAX_SAMPLES * 4; }
 
+// 16-byte vectors of a slab under the widest share of an observation's position tiles, over every number of sharing workgroups
+constexpr int conv1_slab_share(int H, int W)
+{
+    const int W1 = (W - 8) / 4 + 1, P1 = ((H - 8) / 4 + 1) * W1, tiles = (P1 + 31) / 32;
+    int most = 0;
+    for (int parts = 2; parts <= tiles; ++parts)
+        for (int part = 0; part < parts; ++part) {
+            const int m0 = 32 * (tiles * part / parts), m1 = 32 * (tiles * (part + 1) / parts) < P1 ? 32 * (tiles * (part + 1) / parts) : P1;
+            const int vecs = 4 * (((4 * ((m1 - 1) / W1) + 8) * W + 15) / 16 - 4 * (m0 / W1) * W / 16);
+            most = vecs > most ? vecs : most;
+        }
+    return most;
+}
+
 // (LDS admits one workgroup per compute unit, two wavefronts per SIMD: the register budget is stated, or the compiler
 // aims at three and keeps fewer loads in flight -- 107 -> 96 us)
 template <int NG, int H, int W, bool SHARED> __global__ __launch_bounds__(C1S_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void conv1_slab_kernel(const Conv1SlabArgs a)
 {
     constexpr int C = 4 * NG, K = 64 * C, SLAB = 4 * H * W, NV = SLAB / 16, PT = C1S_PRODUCERS;
-    // (shared: half an observation's tiles reach over at most two thirds of its rows)
-    constexpr int NP = ((SHARED ? NV * 2 / 3 : NV) + PT - 1) / PT;
+    constexpr int NP = ((SHARED ? conv1_slab_share(H, W) : NV) + PT - 1) / PT;
     constexpr int IMG = 2 * SLAB;          // bytes of one bf16 image
     // slabs in flight in the producers' registers (walking a batch, four are no faster: 99 vs 96 us; with one observation per
     // workgroup all of it is requested at once)
@@ -475,10 +488,10 @@ static hipError_t launch_conv1_slab(Ctx &c, const uint8_t *obs, const int32_t *i
     a.obs = obs; a.index = index; a.w = (const bf16_t *)c.ws.w1s; a.bias = c.ws.hb + c.sh.b1; a.out = (bf16_t *)c.ws.act1;
     a.B = B; a.W1 = g.W1; a.P1 = g.P1;
     const bool football = g.C == 16;
-    // Fewer observations than half the compute units: each goes to as many workgroups as there are compute units for it (at
+    // At most half as many observations as compute units: each goes to as many workgroups as there are compute units for it (at
     // most one per position tile).  Kernel time at 16x72x96 frames, us, one workgroup per observation / shared: 16 rows 12.4 /
     // 6.5, 32 12.4 / 6.8, 64 12.6 / 7.7, 128 13.5 / 11.4; 4x84x84: 64 7.7 / 6.0, 128 8.6 / 7.3.
-    a.parts = B < 128 ? 256 / B : B == 128 ? 2 : 1;
+    a.parts = B <= 128 ? 256 / B : 1;
     if (a.parts > (g.P1 + 31) / 32) a.parts = (g.P1 + 31) / 32;
     const bool shared = a.parts > 1;
     void (*kern)(const Conv1SlabArgs) = football ? (shared ? conv1_slab_kernel<4, 72, 96, true> : conv1_slab_kernel<4, 72, 96, false>)
