@@ -511,25 +511,31 @@ static hipError_t launch_conv1_slab(Ctx &c, const uint8_t *obs, const int32_t *i
     return hipGetLastError();
 }
 
-// bf16 conv2 and FC of large batches: gemm_dma_kernel, tile and stages by the number of workgroups.  Kernel time, us, register-
-// staged tile kernel / 3 stages / 2 stages.  conv2: 16x72x96 frames, 203 rows (112 workgroups) 8.6 / 7.1 / 8.1, 512 rows (280)
-// 10.4 / 9.6 / 9.8; 4x84x84, 1024 rows (648) 15.0 / 15.5 / 13.5, 4096 rows 45.9 / 49 / 41.5.
+// bf16 conv2 and FC of large batches: gemm_dma_kernel, tile and stages by the number of workgroups.  Kernel time, us, 3 stages / 2
+// (register-staged tile kernel).
+// conv2: three stages pay while a compute unit has one workgroup, are equal while it has two and cost one beyond.  84x84 and 72x96
+// frames: 112 workgroups 7.2 / 8.4 (8.6), 162 7.4 / 9.8, 243 7.7 / 9.2, 280 9.8 / 9.7 (10.4), 324 10.1 / 9.9, 443 13.2 / 13.1, 482
+// 11.3 / 11.6, 509 13.7 / 13.6, 538 17.9 / 15.5, 648 15.5 / 13.5 (15.0), 4096 rows of 4x84x84 49 / 41.5 (45.9).
 template <class L> static hipError_t launch_rows(const ConvFwd<bf16_t, L, false> &p, hipStream_t s)
 {
     typedef ConvFwd<bf16_t, L, false> P;
     if (dma_workgroups(p, 128, 64) <= 512) return launch_dma(DmaTiles<P, 128, 64, 2, 2, 3>(p), s);
     return launch_dma(DmaTiles<P, 128, 64, 2, 2, 2>(p), s);
 }
-// FC, 64x64 tiles: 203 rows of 16x72x96 frames (160 workgroups) 7.1 / 5.7 / -, 700 rows of 4x84x84 (616) 9.9 / 10.2 / 9.2; 128x64
-// tiles instead of 64x64: 1024 rows (896) 11.0 / 11.4 -> 10.4, 2048 rows of 16x72x96 22.1 / 20.5 -> 18.5; 4096 rows with the groups
-// added in the kernel 36.5 / 32.6 -> 29.2 (2 stages 36).
+// FC by the number of 64x64 tiles: 64x64 tiles of 3 stages / of 2 / 128x64 of 2 (register-staged 64x64).  The third stage pays while
+// a compute unit has one tile and does no harm while it has two: 160 5.7 / 7.2 / - (7.1), 280 6.3 / 7.4 / -, 392 8.1 / 7.8 / -, 504 8.3 / 8.2
+// / -, 520 9.8 / 8.6 / 10.2.  Larger tiles fetch less per product but leave units idle until there are enough of them, on 84x84 frames
+// (seven groups) 616 10.2 / 8.8 / 9.7 (9.9), 840 10.2 / 9.5 / 10.2, 896 11.2 / 9.6 / 10.1 (11.0), 1008 11.9 / 11.1 / 10.8, 1344 13.8 / 15.2
+// / 13.0, on 72x96 (five) 640 10.4 / 10.3 / 11.2, 720 12.0 / 11.4 / 12.1, 800 13.1 / 13.0 / 12.7, 960 16.0 / 14.2 / 13.2, 1280 20.5 / 21.6 /
+// 18.0 (22.1): 896 lies where the two shapes' break-evens meet.  4096 rows with the groups added in the kernel: 128x64, 29.2 with 3 stages, 36
+// with 2 (64x64 32.6, register-staged 36.5).
 static hipError_t launch_rows(const FcFwd<bf16_t> &p, hipStream_t s)
 {
     typedef FcFwd<bf16_t> P;
     if (p.klen > FC_GROUP_K) return launch_dma(DmaTiles<P, 128, 64, 2, 2, 3, FC_GROUP_K>(p), s);
     const int wgs = dma_workgroups(p, 64, 64);
     if (wgs <= 512) return launch_dma(DmaTiles<P, 64, 64, 2, 2, 3>(p), s);
-    if (wgs < 896) return launch_dma(DmaTiles<P, 64, 64, 2, 2, 2>(p), s);
+    if (wgs <= 896) return launch_dma(DmaTiles<P, 64, 64, 2, 2, 2>(p), s);
     return launch_dma(DmaTiles<P, 128, 64, 2, 2, 2>(p), s);
 }
 template <class P> static hipError_t launch_rows(const P &p, hipStream_t s) { return launch_gemm(p, s); }

@@ -11,8 +11,9 @@ import hts_synth as syn
 pytestmark = pytest.mark.gpu
 
 
-# workgroups of 64x64 FC tiles at these sizes (84x84): 168, 504, 560, 840, 896, 952; 4100 rows add the groups in the kernel
-@pytest.mark.parametrize("shape,A,sizes", [(ATARI, 18, (129, 576, 577, 960, 961, 1030, 4100)), (FOOT, 19, (129, 203, 833, 1409)),
+# workgroups of 64x64 FC tiles at these sizes (84x84): 168, 504, 560, 728, 728, 840, 896, 952; 4100 rows add the groups in the
+# kernel; conv2 has 512 workgroups at 809 rows and 513 at 810
+@pytest.mark.parametrize("shape,A,sizes", [(ATARI, 18, (129, 576, 577, 809, 810, 960, 961, 1030, 4100)), (FOOT, 19, (129, 203, 833, 1409)),
                                            ((3, 44, 52), 7, (129, 500, 2113))])
 def test_large_batches_agree_bitwise(hts, shape, A, sizes, monkeypatch):  # noqa: F811
     n = max(sizes)
