@@ -494,10 +494,13 @@ __global__ __launch_bounds__(64) void sample_kernel(const HeadsArgs a, const flo
 
 template <bool LEARN> static hipError_t launch_heads(const HeadsArgs &a, hipStream_t stream)
 {
-    // Kernel time at S = 1 / 2 / 4, us: actor 16 rows 3.8/4.2/5.7, 700 4.6/5.6/6.2, 1024 5.7/5.6/6.8, 2048 9.0/8.2/9.3, 4096
-    // 16.2/12.5/9.0 (one slice of FC sums there); learner 512 6.3/6.4/8.9, 1024 10.6/8.6/11.2, 2048 16.8/14.5/12.8: a second
-    // sample per workgroup pays once every compute unit has about four workgroups of its own.
-    const int S = a.A > 32 || a.B <= (LEARN ? 512 : 1024) ? 1 : a.B < (LEARN ? 2048 : 3072) ? 2 : 4;
+    // Kernel time at S = 1 / 2 / 4, us.  Learner: one round of workgroups of a single sample ends at 768 rows (three fit a compute unit),
+    // of two samples at 1024 (two fit): 512 6.3/6.4/8.9, 768 6.9/7.0/9.2, 832 9.5/7.4/8.7, 1024 10.8/7.5/9.0, 1152 11.4/11.0/10.7, 1536
+    // 12.7/11.8/11.0, 2048 17.9/15.3/13.1 on 84x84 frames (seven slices of FC sums); 1152 12.4/12.8/11.3, 1536 13.7/13.4/11.6 on 72x96 (five).
+    // Actor (more workgroups fit): 16 rows 3.8/4.2/5.7, 768 5.0/5.2/5.8, 1024 5.9/5.8/6.0, 1100 7.4/6.3/7.6, 1536 8.6/6.7/7.8, 2048
+    // 9.4/8.4/8.4, 2560 10.6/9.9/10.0, 3072 12.1/11.3/10.7, 3584 13.9/12.8/13.4, 4096 (one slice) 14.6/12.1/8.2; 72x96: 3072 12.3/11.1/10.4,
+    // 3584 14.0/12.3/13.0: two and four are level from 2048 to 4095 rows, one slice decides for four.
+    const int S = a.A > 32 || a.B <= (LEARN ? 512 : 1024) ? 1 : a.B <= (LEARN ? 1024 : 3072) ? 2 : 4;
     auto kern = S == 1 ? heads_kernel<LEARN, 1> : S == 2 ? heads_kernel<LEARN, 2> : heads_kernel<LEARN, 4>;
     hipLaunchKernelGGL(kern, dim3((a.B + S - 1) / S), dim3(64 * HEADS_WAVES), (size_t)S * (a.A + 1) * 65 * sizeof(float), stream, a);
     return hipGetLastError();

@@ -26,7 +26,7 @@ def test_heads_do_not_depend_on_the_batch(hts, A, N):  # noqa: F811
 
 
 @pytest.mark.parametrize("A", [19, 20, 21])
-@pytest.mark.parametrize("B", [513, 2049])
+@pytest.mark.parametrize("B", [513, 1024, 1025, 2049])
 def test_heads_gradient_of_repeated_rows(hts, A, B):  # noqa: F811
     """B copies of one row: every row's share of the heads gradient is the same number, so pi.w's gradient is B times one
     row's, up to a binary32 chain over B equal terms (B 2^-24 at most) and the 1/B of the mean."""
