@@ -141,7 +141,7 @@ extern "C" int32_t hts_create(const hts_net_desc *desc, int32_t max_act_batch, i
     c.conv1_wgrad_slab_rows = 256;
     // (against the wave-per-segment kernel, us: 4x84x84 frames 32 rows 6.7 / 6.6, 64 6.9 / 9.9; 16x72x96 32 14.8 / 14.1, 64 15.2 / 21.3)
     c.conv1_wgrad_image_rows = 33;
-    if (const char *sr = getenv("HTS_CONV1_SLAB_ROWS")) c.conv1_slab_rows = c.conv1_wgrad_slab_rows = atoi(sr);   // tuning knob, same bits either way
+    if (const char *sr = getenv("HTS_CONV1_SLAB_ROWS")) c.conv1_slab_rows = c.conv1_wgrad_slab_rows = atoi(sr);   // tuning knob, same bits either way but conv1.b's gradient
     // tuning knob: batches up to it take the wave-per-segment kernels (0: none), bf16's conv1 too, which by itself leaves them at fewer rows
     if (const char *sb = getenv("HTS_SMALL_BATCH")) {
         c.small_b = atoi(sb);

@@ -9,7 +9,7 @@
 namespace hts {
 
 // ------------------------------------------------------------------------------------------------------------
-// conv1 weight gradient for large bf16 batches of small frames with 4, 8, 12 or 16 channels (4x84x84, 16x72x96):
+// conv1 weight gradient of bf16 minibatches from 33 rows on, small frames with 4, 8, 12 or 16 channels (4x84x84, 16x72x96):
 // one workgroup walks a share of the observations.  For each one the sample's 32-channel output gradient [P1][32] is
 // copied into LDS, and, four input channels at a time, the frame is converted to bf16 ONCE into an LDS image
 // [(c,y)][W]; wavefront t then owns the 32 weight columns (c = 4*group + t/2, u = 4(t%2)..+3, v = 0..7) and adds
@@ -275,7 +275,7 @@ static hipError_t launch_conv1_wgrad_image(Ctx &c, const uint8_t *obs, const int
 }
 
 // ------------------------------------------------------------------------------------------------------------
-// The same weight gradient for 16-channel frames (16x72x96) with the work split between wavefronts: wavefronts 4-7
+// The same weight gradient for 16-channel frames (16x72x96), from 256 rows on, with the work split between wavefronts: wavefronts 4-7
 // (producers) fetch the next four-channel slab of the frame into registers, convert it into one of TWO LDS images and
 // bring in the next sample's output gradient, while wavefronts 0-3 (consumers, one per SIMD next to a producer)
 // multiply the current slab -- consumer w owns input channel w of the slab, i.e. two column tiles (rows u = 0..3 and

@@ -9,8 +9,9 @@
 namespace hts {
 
 // ------------------------------------------------------------------------------------------------------------
-// conv1 for large batches of small 4-channel frames (bf16, image <= 64 KiB of LDS, e.g. 4x84x84): one workgroup per
-// observation.
+// conv1 of bf16 batches beyond the wave-per-segment kernels, 4-channel frames whose bf16 image takes at most 64 KiB of LDS and
+// that the slab kernel below does not serve: shapes other than 4x84x84, and 4x84x84 frames at an address that is a multiple
+// of 4 but not of 16 bytes.  One workgroup per observation.
 // The frame is converted to bf16 ONCE into an LDS image [(c,y)][Wp] (the tile kernel converts every pixel four times,
 // once per patch that contains it, and spends most of its issue slots on that and on gather addresses); the matrix
 // instruction's position operand is then read straight from the image -- 8 consecutive k of conv1.w's (c,u,v) order
@@ -165,7 +166,7 @@ static hipError_t launch_conv1_image(Ctx &c, const uint8_t *obs, const int32_t *
     a.dGpr = FastDiv::make(g.W / 4); a.dW1 = FastDiv::make(g.W1);
     const size_t lds = (((size_t)g.C * g.H * a.Wp + 7) & ~(size_t)7) * sizeof(bf16_t) + 32 * sizeof(float);      // image + conv1.b
     const int grid = B < 512 ? B : 512;          // resident workgroups walk the batch
-    if (g.H == 84 && g.W == 84 && a.Wp == 84)                 // the Atari frame of the paper's experiments
+    if (g.H == 84 && g.W == 84 && a.Wp == 84)                 // the Atari frame of the paper's experiments (misaligned)
         hipLaunchKernelGGL((conv1_image_kernel<4, 84, 84, 28>), dim3(grid), dim3(C1IMG_THREADS), lds, c.stream, a);
     else
         hipLaunchKernelGGL((conv1_image_kernel<4, 0, 0, C1IMG_MAX_PASSES>), dim3(grid), dim3(C1IMG_THREADS), lds, c.stream, a);
@@ -173,9 +174,9 @@ static hipError_t launch_conv1_image(Ctx &c, const uint8_t *obs, const int32_t *
 }
 
 // ------------------------------------------------------------------------------------------------------------
-// conv1 for large bf16 batches of the two frame shapes of the paper's experiments (16x72x96, and 4x84x84 for the largest
-// batches), whose four-channel slab (4*H*W bytes, about 27 KB) fits twice into LDS as bf16: one workgroup per compute
-// unit walks a share of the observations.
+// conv1 of bf16 batches of the two frame shapes of the paper's experiments (16x72x96 from 21 rows on, 4x84x84 from 64), whose
+// four-channel slab (4*H*W bytes, about 27 KB) fits twice into LDS as bf16: one workgroup per compute unit walks a share of
+// the observations, or, up to 128 of them, several workgroups share one (see launch_conv1_slab).
 // A frame passes in slabs of four channels.  Wavefronts 4-7 (producers) fetch slab q+2 into registers, convert slab q+1
 // to bf16 once into one of two LDS images [(c,y)][W] and copy the 32 x 256 slice of conv1.w that belongs to its
 // channels beside it; meanwhile wavefronts 0-3 (consumers, one per SIMD next to a producer) multiply slab q: position
@@ -575,8 +576,8 @@ template <typename T> static hipError_t forward_t(Ctx &c, const uint8_t *obs, co
             else if (sizeof(T) == 2 && B >= c.conv1_slab_rows && conv1_slab_fits(g, obs)) e = launch_conv1_slab(c, obs, index, B);
             else if (small) e = g.K1 >= 1024 ? launch_wsgemm<Conv1Fwd<T>, 16, Conv1Fwd<T>::SEG, false, (sizeof(T) == 4)>(p, c.stream)
                                         : launch_wsgemm<Conv1Fwd<T>, 4, Conv1Fwd<T>::SEG, false>(p, c.stream);
-            // (four-channel frames too: against the LDS-image kernel of that shape, conv1 at 1024 rows of 4x84x84
-            // 21.7 -> 19.0 us, an act call at 256 / 4096 rows 38.8 -> 36.7 / 203 -> 188 us)
+            // (against the LDS-image kernel, which is left with other four-channel shapes and misaligned frames, conv1 at 1024
+            // rows of 4x84x84 21.7 -> 19.0 us, an act call at 256 / 4096 rows 38.8 -> 36.7 / 203 -> 188 us)
             else if (sizeof(T) == 2 && conv1_image_fits(g, obs)) e = launch_conv1_image(c, obs, index, B);
             else e = launch_gemm(p, c.stream);
         }
