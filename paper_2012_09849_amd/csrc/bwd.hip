@@ -549,7 +549,8 @@ static hipError_t launch_conv1_wgrad_slab(Ctx &c, const uint8_t *obs, const int3
 
 // bf16: gemm_dma_kernel.  Kernel time, us, register-staged tile kernel / 64x64 tiles of 3 stages / 64x128 of 2: 203 rows of 16x72x96
 // frames (160 workgroups of 64x64) 6.8 / 6.0 / 8.6, 512 rows of 4x84x84 (392) 8.7 / 8.6 / 9.7, 700 rows (539) 10.6 / 11.0 / 10.6,
-// 1024 rows (784) 14.1 / 13.7 / 11.8, 2048 rows of 16x72x96 19.6 / 19.1 / 18.2.
+// 1024 rows (784) 14.1 / 13.7 / 11.8, 2048 rows of 16x72x96 19.6 / 19.1 / 18.2.  Around the cut, two 64x64 tiles a compute unit: 490
+// - / 8.4 / 9.4, 520 - / 9.9 / 10.0, 560 - / 10.8 / 10.2, 637 - / 11.2 / 11.1, 720 - / 11.6 / 12.1.
 static hipError_t launch_fc_dgrad(const FcDgrad<float> &p, hipStream_t s) { return launch_gemm(p, s); }
 static hipError_t launch_fc_dgrad(const FcDgrad<bf16_t> &p, hipStream_t s)
 {
