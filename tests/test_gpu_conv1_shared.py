@@ -1,6 +1,7 @@
 """conv1 of bf16 batches at the edges of its kernels: observations shared by 16, 3, 2 and 1 workgroups (each with the image
 rows under its position tiles only), first and last batch of each, against the kernels that serve other batch sizes, bit
-for bit; and the gradient of small bf16 minibatches, whose weight gradients take the large batches' kernels."""
+for bit; the gradient of small bf16 minibatches, whose weight gradients take the large batches' kernels; and the knob that
+sends them to the wave-per-segment ones."""
 import numpy as np
 import pytest
 import torch

@@ -1,5 +1,6 @@
 """binary32 backward kernels: gradients at the edges of their tiles, and
-over operands whose magnitudes spread over many binades, against the oracle's float64 gradient."""
+over operands whose magnitudes spread over many binades, against the oracle's float64 gradient; the order of their sums,
+bit for bit, against chains of fused multiply-adds on the host."""
 import numpy as np
 import pytest
 import torch

@@ -353,7 +353,8 @@ LEARN_CASES = [
     ((2, 36, 36), 21, 30, 23, 1, 0.1, 0.0, 0),
     ((2, 36, 36), 33, 30, None, 0, 0.1, 0.5, 0),
     ((2, 36, 36), 64, 140, 131, 1, 0.1, 0.0, 0),
-    ((2, 36, 36), 64, 560, 530, 1, 0.1, 0.0, 0),   # more than 512 rows: four wavefronts per heads workgroup
+    ((2, 36, 36), 64, 560, 530, 1, 0.1, 0.0, 0),   # more than 512 rows of more than 32 actions: one sample per heads workgroup at any size
+    ((2, 36, 36), 21, 560, 530, 1, 0.1, 0.0, 0),   # two samples per heads workgroup, one column of the heads beyond those in registers
     (FOOT, 19, 50, 48, 1, 0.08, 0.0, 0),           # the multi-agent workload's rows per call as a minibatch
 ]
 
