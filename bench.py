@@ -56,6 +56,7 @@ def site_work(cfg, P):
     w["conv1_wgrad"] = ("flop", B * f["conv1"], B)
     w["fc_wgrad"] = ("flop", B * f["fc"], B)
     w["fc_dgrad"] = ("flop", B * f["fc"], B)
+    w["wgrads"] = ("flop", B * (f["fc"] + f["conv1"] + f["conv2"] + f["conv3"]), B)      # binary32: one launch for all of them
     w["adam"] = ("byte", 28.0 * P, B)
     w["grad_norm"] = ("byte", 4.0 * P, B)
     w["gae"] = ("byte", 17.0 * T * N + 4.0 * N, N)

@@ -390,7 +390,7 @@ extern "C" int32_t hts_profile_end(hts_ctx *ctx, int32_t *launches, double *tota
 static const char *const k_site_names[SITE_COUNT] = {
     "prep", "conv1_fwd", "conv2_fwd", "conv3_fwd", "fc_fwd", "heads_act", "heads_learn", "heads_wgrad", "fc_wgrad",
     "fc_dgrad", "conv3_wgrad", "conv3_dgrad", "conv2_wgrad", "conv2_dgrad", "conv1_wgrad", "wgrad_reduce", "grad_norm",
-    "adam", "gae", "normalize", "stats", "conv1_fwd_learn", "conv2_fwd_learn", "conv3_fwd_learn", "fc_fwd_learn"};
+    "adam", "gae", "normalize", "stats", "conv1_fwd_learn", "conv2_fwd_learn", "conv3_fwd_learn", "fc_fwd_learn", "wgrads"};
 
 extern "C" int32_t hts_profile_site_count(void) { return SITE_COUNT; }
 

@@ -4,6 +4,7 @@
 // gradient is bit-identical from run to run.
 #include "internal.hpp"
 #include "dmagemm.hpp"
+#include "group.hpp"
 #include "imgconv.hpp"
 
 namespace hts {
@@ -578,44 +579,7 @@ template <typename T> static hipError_t backward_t(Ctx &c, const uint8_t *obs, c
         *spg = s;
         return (nseg + s - 1) / s;
     };
-    // heads: pi.w, pi.b, v.w, v.b.  A tiny output and a reduction over the whole minibatch: beyond 512 rows it is cut
-    // into groups of 16 segments (one round of the 16 wavefronts) whose partials join the conv layers' reduction.
-    int nzh = 0;
-    {
-        HeadsWgrad p;
-        p.M = g.A + 1; p.N = 513; p.K = B; p.klen = B;
-        p.dz = c.ws.dz; p.h = c.ws.h; p.g = grads; p.A = g.A; p.part = nullptr;
-        p.piw = g.piw; p.pib = g.pib; p.vw = g.vw; p.vb = g.vb;
-        const int nseg = (B + 31) / 32;
-        int spg = 1 << 30;
-        if (nseg > 16) {
-            spg = 16 * ((nseg + 16 * HEADS_MAXZ - 1) / (16 * HEADS_MAXZ));      // whole rounds, at most HEADS_MAXZ groups
-            nzh = (nseg + spg - 1) / spg;
-            p.part = c.ws.heads_part;
-        }
-        {
-            SiteTimer tm(c, SITE_HEADS_WGRAD);        // 16 wavefronts share each tile
-            e = launch_wsgemm<HeadsWgrad, 16, 32, false>(p, c.stream, spg);
-        }
-        if (e != hipSuccess) return e;
-    }
-    {   // fc.w, fc.b
-        FcWgrad<T> p;
-        p.M = 512; p.N = g.F + 1; p.K = B; p.klen = B;
-        p.dh = (const T *)c.ws.dh; p.a3 = (const T *)c.ws.a3; p.g = grads; p.F = g.F; p.fcw = g.fcw; p.fcb = g.fcb;
-        { SiteTimer tm(c, SITE_FC_WGRAD); e = launch_gemm(p, c.stream); }
-        if (e != hipSuccess) return e;
-    }
-    {   // d(conv3 pre-activation)
-        FcDgrad<T> p;
-        p.M = B; p.N = g.F; p.K = 512; p.klen = 512;
-        p.dh = (const T *)c.ws.dh; p.wfcd = (const T *)c.ws.wfcd; p.a3n = (const T *)c.ws.a3n; p.dy3 = (T *)c.ws.dy3;
-        {
-            SiteTimer tm(c, SITE_FC_DGRAD);
-            e = small ? launch_wsgemm<FcDgrad<T>, 4, 64, false>(p, c.stream) : launch_fc_dgrad(p, c.stream);
-        }
-        if (e != hipSuccess) return e;
-    }
+    // ---- the weight gradients' problems ----
     // partial buffers of the three conv weight gradients live side by side in ws.part
     const SplitK s3 = split_for((long long)B * g.P3, MAXZ3), s2 = split_for((long long)B * g.P2, MAXZ2),
                  s1 = split_for((long long)B * g.P1, MAXZ1);
@@ -633,18 +597,63 @@ template <typename T> static hipError_t backward_t(Ctx &c, const uint8_t *obs, c
     float *part3 = c.ws.part;
     float *part2 = part3 + (size_t)nz3 * 64 * 577;
     float *part1 = part2 + (size_t)nz2 * 64 * 513;
-    {   // conv3.w, conv3.b
-        ConvWgrad<T, Layer3> p;
-        p.M = 64; p.N = 577; p.K = B * g.P3; p.klen = s3.klen;
-        p.dy = (const T *)c.ws.dy3; p.in = (const T *)c.ws.act2; p.part = part3;
-        p.Hin = g.H2; p.Win = g.W2; p.Wo = g.W3; p.Po = g.P3;
-        p.dPo = FastDiv::make(g.P3); p.dWo = FastDiv::make(g.W3);
+    // heads: pi.w, pi.b, v.w, v.b.  A tiny output and a reduction over the whole minibatch: beyond 512 rows it is cut
+    // into groups of 16 segments whose partials join the conv layers' reduction.
+    HeadsWgrad ph;
+    ph.M = g.A + 1; ph.N = 513; ph.K = B; ph.klen = B;
+    ph.dz = c.ws.dz; ph.h = c.ws.h; ph.g = grads; ph.A = g.A; ph.part = nullptr;
+    ph.piw = g.piw; ph.pib = g.pib; ph.vw = g.vw; ph.vb = g.vb;
+    int spgh = 1 << 30, nzh = 0;
+    {
+        const int nseg = (B + 31) / 32;
+        if (nseg > 16) {
+            spgh = 16 * ((nseg + 16 * HEADS_MAXZ - 1) / (16 * HEADS_MAXZ));     // at most HEADS_MAXZ groups
+            nzh = (nseg + spgh - 1) / spgh;
+            ph.part = c.ws.heads_part;
+        }
+    }
+    FcWgrad<T> pf;      // fc.w, fc.b
+    pf.M = 512; pf.N = g.F + 1; pf.K = B; pf.klen = B;
+    pf.dh = (const T *)c.ws.dh; pf.a3 = (const T *)c.ws.a3; pf.g = grads; pf.F = g.F; pf.fcw = g.fcw; pf.fcb = g.fcb;
+    ConvWgrad<T, Layer3> p3;      // conv3.w, conv3.b
+    p3.M = 64; p3.N = 577; p3.K = B * g.P3; p3.klen = s3.klen;
+    p3.dy = (const T *)c.ws.dy3; p3.in = (const T *)c.ws.act2; p3.part = part3;
+    p3.Hin = g.H2; p3.Win = g.W2; p3.Wo = g.W3; p3.Po = g.P3;
+    p3.dPo = FastDiv::make(g.P3); p3.dWo = FastDiv::make(g.W3);
+    ConvWgrad<T, Layer2> p2;      // conv2.w, conv2.b
+    p2.M = 64; p2.N = 513; p2.K = B * g.P2; p2.klen = s2.klen;
+    p2.dy = (const T *)c.ws.dy2; p2.in = (const T *)c.ws.act1; p2.part = part2;
+    p2.Hin = g.H1; p2.Win = g.W1; p2.Wo = g.W2; p2.Po = g.P2;
+    p2.dPo = FastDiv::make(g.P2); p2.dWo = FastDiv::make(g.W2);
+    auto conv1_problem = [&](auto p) {      // conv1.w, conv1.b
+        p.M = 32; p.N = g.K1 + 1; p.K = B * g.P1; p.klen = s1.klen;
+        p.dy = (const T *)c.ws.dy1; p.obs = obs; p.index = index; p.part = part1;
+        p.Kc = g.K1; p.C = g.C; p.H = g.H; p.W = g.W; p.W1 = g.W1; p.P1 = g.P1;
+        p.dP1 = FastDiv::make(g.P1); p.dW1 = FastDiv::make(g.W1);
+        return p;
+    };
+    // ---- launches.  binary32's weight gradients share one launch behind the input gradients: each of them alone has one or two
+    // wavefronts per SIMD (400 to 576 workgroups at 1024 rows of 84x84 frames; 282 us one after the other, 215 together; 51 and 32
+    // at 80 rows).  bfloat16's go out each right behind the input gradient whose output they read, while the caches still hold
+    // it (together 115 us against 90 at 2048 rows of 72x96 frames). ----
+    if constexpr (sizeof(T) == 2) {
+        { SiteTimer tm(c, SITE_HEADS_WGRAD); e = launch_wsgemm<HeadsWgrad, 16, 32, false>(ph, c.stream, spgh); }      // 16 wavefronts share each tile
+        if (e == hipSuccess) { SiteTimer tm(c, SITE_FC_WGRAD); e = launch_gemm(pf, c.stream); }
+        if (e != hipSuccess) return e;
+    }
+    {   // d(conv3 pre-activation)
+        FcDgrad<T> p;
+        p.M = B; p.N = g.F; p.K = 512; p.klen = 512;
+        p.dh = (const T *)c.ws.dh; p.wfcd = (const T *)c.ws.wfcd; p.a3n = (const T *)c.ws.a3n; p.dy3 = (T *)c.ws.dy3;
         {
-            SiteTimer tm(c, SITE_CONV3_WGRAD);
-            if constexpr (sizeof(T) == 4) e = smallw ? launch_wsgemm<ConvWgrad<T, Layer3>, 4, 64, false>(p, c.stream, spg3) : launch_gemm(p, c.stream);
-            else e = launch_gemm(p, c.stream);
+            SiteTimer tm(c, SITE_FC_DGRAD);
+            e = small ? launch_wsgemm<FcDgrad<T>, 4, 64, false>(p, c.stream) : launch_fc_dgrad(p, c.stream);
         }
         if (e != hipSuccess) return e;
+    }
+    if constexpr (sizeof(T) == 2) {
+        SiteTimer tm(c, SITE_CONV3_WGRAD);
+        if ((e = launch_gemm(p3, c.stream)) != hipSuccess) return e;
     }
     {   // d(conv2 pre-activation)
         ConvDgrad<T, Layer3> p;
@@ -673,18 +682,9 @@ template <typename T> static hipError_t backward_t(Ctx &c, const uint8_t *obs, c
         }
         if (e != hipSuccess) return e;
     }
-    {   // conv2.w, conv2.b
-        ConvWgrad<T, Layer2> p;
-        p.M = 64; p.N = 513; p.K = B * g.P2; p.klen = s2.klen;
-        p.dy = (const T *)c.ws.dy2; p.in = (const T *)c.ws.act1; p.part = part2;
-        p.Hin = g.H1; p.Win = g.W1; p.Wo = g.W2; p.Po = g.P2;
-        p.dPo = FastDiv::make(g.P2); p.dWo = FastDiv::make(g.W2);
-        {
-            SiteTimer tm(c, SITE_CONV2_WGRAD);
-            if constexpr (sizeof(T) == 4) e = smallw ? launch_wsgemm<ConvWgrad<T, Layer2>, 4, 64, false>(p, c.stream, spg2) : launch_gemm(p, c.stream);
-            else e = launch_gemm(p, c.stream);
-        }
-        if (e != hipSuccess) return e;
+    if constexpr (sizeof(T) == 2) {
+        SiteTimer tm(c, SITE_CONV2_WGRAD);
+        if ((e = launch_gemm(p2, c.stream)) != hipSuccess) return e;
     }
     {   // d(conv1 pre-activation)
         ConvDgrad<T, Layer2> p;
@@ -709,20 +709,27 @@ template <typename T> static hipError_t backward_t(Ctx &c, const uint8_t *obs, c
         }
         if (e != hipSuccess) return e;
     }
-    {   // conv1.w, conv1.b
-        auto conv1_wgrad = [&](auto p) {
-            p.M = 32; p.N = g.K1 + 1; p.K = B * g.P1; p.klen = s1.klen;
-            p.dy = (const T *)c.ws.dy1; p.obs = obs; p.index = index; p.part = part1;
-            p.Kc = g.K1; p.C = g.C; p.H = g.H; p.W = g.W; p.W1 = g.W1; p.P1 = g.P1;
-            p.dP1 = FastDiv::make(g.P1); p.dW1 = FastDiv::make(g.W1);
-            SiteTimer tm(c, SITE_CONV1_WGRAD);
-            return small1 ? launch_wsgemm<decltype(p), 4, 64, false>(p, c.stream, spg1) : launch_gemm(p, c.stream);
+    if constexpr (sizeof(T) == 4) {
+        SiteTimer tm(c, SITE_WGRADS);
+        auto all = [&](auto p1) {
+            if (small) return launch_group(c.stream, SegmentJob<HeadsWgrad, 32>(ph, spgh), SegmentJob<decltype(p1), 64>(p1, spg1), SegmentJob<ConvWgrad<T, Layer2>, 64>(p2, spg2),
+                                           SegmentJob<ConvWgrad<T, Layer3>, 64>(p3, spg3), TileJob<FcWgrad<T>>(pf));
+            HeadsTiles pt(ph);
+            pt.klen = nzh > 0 ? spgh * 32 : B;
+            return launch_group(c.stream, TileJob<HeadsTiles>(pt), TileJob<decltype(p1)>(p1), TileJob<ConvWgrad<T, Layer2>>(p2), TileJob<FcWgrad<T>>(pf),
+                                TileJob<ConvWgrad<T, Layer3>>(p3));
         };
+        e = index ? all(conv1_problem(Conv1Wgrad<T, true>{})) : all(conv1_problem(Conv1Wgrad<T, false>{}));
+    } else {
         if (slab1) e = launch_conv1_wgrad_slab(c, obs, index, B, part1, s1.nz, &nz1);
         else if (image1) e = launch_conv1_wgrad_image(c, obs, index, B, part1, s1.nz, &nz1);
-        else e = index ? conv1_wgrad(Conv1Wgrad<T, true>{}) : conv1_wgrad(Conv1Wgrad<T, false>{});
-        if (e != hipSuccess) return e;
+        else {
+            SiteTimer tm(c, SITE_CONV1_WGRAD);
+            auto conv1_wgrad = [&](auto p) { return small1 ? launch_wsgemm<decltype(p), 4, 64, false>(p, c.stream, spg1) : launch_gemm(p, c.stream); };
+            e = index ? conv1_wgrad(conv1_problem(Conv1Wgrad<T, true>{})) : conv1_wgrad(conv1_problem(Conv1Wgrad<T, false>{}));
+        }
     }
+    if (e != hipSuccess) return e;
     const long long hstride = (long long)(g.A + 1) * 513;
     const ReduceSpec specs[REDUCE_JOBS] = {
         {part3, nz3, 64, 577, 64, 3, 0, true, 1.0f, g.w3, g.b3},

@@ -63,7 +63,7 @@ __global__ __launch_bounds__(P::WAVES_M * P::WAVES_N * 64, 2) void gemm_dma_kern
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave % WM, wn = wave / WM, lrow = lane & 31, lk = lane >> 5;
     int m0, n0, z;
-    if (!tile_of(p, p.M, m0, n0, z)) return;       // the whole workgroup leaves
+    if (!tile_of(p, launch_at(), p.M, m0, n0, z)) return;       // the whole workgroup leaves
     const int kbeg = z * p.klen, nt = (min(p.K, kbeg + p.klen) - kbeg) / BK;
 
     // LDS rows of 64 k: 16-byte slot s of row r holds k-vector s ^ ((r >> 1) & 7), so the sixteen rows of an operand read

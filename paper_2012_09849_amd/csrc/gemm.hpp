@@ -367,30 +367,34 @@ __device__ __forceinline__ void epi_store(const P &p, const f32x16 (&acc)[TM][TN
     if (m0 + P::BM <= M && n0 + P::BN <= N) epilogue(std::true_type{}); else epilogue(std::false_type{});
 }
 
+// A workgroup's place in its problem's grid: the launch's own indices, or those inside a job of a grouped launch.
+struct WgAt { int x, y, z, nx, ny; };
+__device__ __forceinline__ WgAt launch_at() { return {(int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z, (int)gridDim.x, (int)gridDim.y}; }
+
 // This workgroup's tile: rows m0.., columns n0.., reduction chunk z; false: nothing to do.
-template <class P> __device__ __forceinline__ bool tile_of(const P &p, int M, int &m0, int &n0, int &z)
+template <class P> __device__ __forceinline__ bool tile_of(const P &p, const WgAt &at, int M, int &m0, int &n0, int &z)
 {
     constexpr int BM = P::BM, BN = P::BN;
     const int tiles_n = (tile_cols(p) + BN - 1) / BN;
-    int tile = blockIdx.x;
-    z = blockIdx.y;
+    int tile = at.x;
+    z = at.y;
     if constexpr (!HasBatch<P>::value) {
         // A long split reduction is launched as a one-dimensional grid (see launch_gemm): workgroups go to the eight
         // XCDs in turn, so workgroup h runs on XCD h % 8; all output tiles of reduction chunk z are given to XCD z % 8,
         // whose L2 then serves the operand rows that those tiles share.
-        if (gridDim.y == 1 && p.klen < p.K) {
+        if (at.ny == 1 && p.klen < p.K) {
             const int tiles = ((M + BM - 1) / BM) * tiles_n;
             const int xcd = tile & 7, slot = tile >> 3;
             z = (slot / tiles) * 8 + xcd;
             tile = slot % tiles;
             if ((long long)z * p.klen >= p.K) return false;  // padding of the last round of eight chunks
         } else {
-            // Otherwise gridDim.x is the number of tiles rounded up to a multiple of 8, and XCD x takes the x-th
+            // Otherwise the grid's x extent is the number of tiles rounded up to a multiple of 8, and XCD x takes the x-th
             // eighth of the tile order: neighbouring tiles share an operand panel, and a panel that is needed on one
             // XCD only is fetched into one L2 only.  (Round-robin, every XCD read the whole of the operand that the
             // tile order walks slowest: the FC forward pass fetched its activations eight times, 107 MB for 34.)
             // (A single column of tiles shares nothing but the small weight panel and keeps the round-robin order.)
-            const int tiles = ((M + BM - 1) / BM) * tiles_n, per_xcd = gridDim.x >> 3;
+            const int tiles = ((M + BM - 1) / BM) * tiles_n, per_xcd = at.nx >> 3;
             if (tiles_n > 1) tile = (tile & 7) * per_xcd + (tile >> 3);
             if (tile >= tiles) return false;
         }
@@ -421,21 +425,30 @@ template <class P> __device__ __forceinline__ bool tile_of(const P &p, int M, in
 //   CtxB ctx_b(int col) const,  Vec<T,VB> load_b(const CtxB &, int k, int kend) const
 //   void store(int m, int n, float acc, int z) const          called only for m < M, n < N
 //   optionally Col col(int n) const and store(..., const Col &)   per-column epilogue data, fetched once per lane
+// LDS: operand tiles, k-contiguous rows ([row][k + pad]) or natural staging ([reduction][row + pad]); the latter's pad keeps the row
+// pitch at 64 bytes modulo 128 for bf16 (the four reduction rows a 16-lane group reads at once fall into different banks)
+// and 128 modulo 256 for fp32
+template <class P> struct TileLds {
+    using T = typename P::T;
+    static constexpr bool NAT_A = NaturalOf<P>::value && !P::A_ALONG_K, NAT_B = NaturalOf<P>::value && !P::B_ALONG_K;
+    static constexpr int LS = P::BK + OperandTraits<T>::PAD;
+    static constexpr int LSNA = P::BM + (P::BM % 64 == 0 ? 32 : 0), LSNB = P::BN + (P::BN % 64 == 0 ? 32 : 0);
+    static constexpr int A_ELEMS = NAT_A ? P::BK * LSNA : P::BM * LS, B_ELEMS = NAT_B ? P::BK * LSNB : P::BN * LS;
+    static constexpr size_t A_BYTES = (A_ELEMS * sizeof(T) + 15) & ~(size_t)15, BYTES = A_BYTES + ((B_ELEMS * sizeof(T) + 15) & ~(size_t)15);
+};
+
 template <class P>
-__global__ __launch_bounds__(P::WAVES_M * P::WAVES_N * 64) void gemm_kernel(const P p)
+__device__ __forceinline__ void gemm_tile(const P &p, const WgAt at, typename P::T *As, typename P::T *Bs)
 {
-    const int zb = blockIdx.z, M = rows_of(p, zb);
+    const int zb = at.z, M = rows_of(p, zb);
     using T = typename P::T;
     using Tr = OperandTraits<T>;
     constexpr int BM = P::BM, BN = P::BN, BK = P::BK;
     constexpr int WM = P::WAVES_M, WN = P::WAVES_N, NT = WM * WN * 64;
     constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
-    constexpr int LS = BK + Tr::PAD;
     constexpr int VA = P::VA, VB = P::VB;
-    // natural staging ([reduction][row + pad]); the pad keeps the row pitch at 64 bytes modulo 128 for bf16 (the four
-    // reduction rows a 16-lane group reads at once fall into different banks) and 128 modulo 256 for fp32
-    constexpr bool NAT_A = NaturalOf<P>::value && !P::A_ALONG_K, NAT_B = NaturalOf<P>::value && !P::B_ALONG_K;
-    constexpr int LSNA = BM + (BM % 64 == 0 ? 32 : 0), LSNB = BN + (BN % 64 == 0 ? 32 : 0);
+    constexpr bool NAT_A = TileLds<P>::NAT_A, NAT_B = TileLds<P>::NAT_B;
+    constexpr int LS = TileLds<P>::LS, LSNA = TileLds<P>::LSNA, LSNB = TileLds<P>::LSNB;
     // work items per operand tile: a k-contiguous vector (ALONG_K), a row-contiguous vector at one reduction index
     // (natural staging) or a V x V block to transpose (otherwise)
     constexpr int CA = P::A_ALONG_K ? BM * BK / VA : (NAT_A ? BK * (BM / VA) : (BM / VA) * (BK / VA));
@@ -449,13 +462,10 @@ __global__ __launch_bounds__(P::WAVES_M * P::WAVES_N * 64) void gemm_kernel(cons
     static_assert(SEG % BK == 0, "SEG must be a multiple of BK");
     constexpr bool VEC_LDS = sizeof(T) == 2;      // bf16 rows are 16-byte aligned: whole vectors are stored at once
 
-    __shared__ __attribute__((aligned(16))) T As[NAT_A ? BK * LSNA : BM * LS];
-    __shared__ __attribute__((aligned(16))) T Bs[NAT_B ? BK * LSNB : BN * LS];
-
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave % WM, wn = wave / WM;
     int m0, n0, z;
-    if (!tile_of(p, M, m0, n0, z)) return;       // the whole workgroup leaves
+    if (!tile_of(p, at, M, m0, n0, z)) return;       // the whole workgroup leaves
     const int kbeg = z * p.klen;
     const int kend = min(p.K, kbeg + p.klen);
 
@@ -583,7 +593,7 @@ __global__ __launch_bounds__(P::WAVES_M * P::WAVES_N * 64) void gemm_kernel(cons
 
     constexpr bool BIAS = BiasCol<P>::value;
     static_assert(!BIAS || (NAT_A && BM <= 64), "bias column: a row per lane");
-    float bias = 0.0f;                           // of row lane % BM, in the last wavefront of the workgroups of the first columns
+    float bias = 0.0f, bias_tot = 0.0f;          // of row lane % BM, in the last wavefront of the workgroups of the first columns (segmented: of the segment, before it)
 
     // one k-tile: registers -> LDS, refill this stage's registers with the tile D steps ahead, multiply.
     // REFILL: 1 = always (steady state: an unconditional load lets the compiler wait for exactly the older stages),
@@ -718,6 +728,7 @@ __global__ __launch_bounds__(P::WAVES_M * P::WAVES_N * 64) void gemm_kernel(cons
             clear(sacc);
 #pragma unroll
             for (int s = 0; s < SPS; ++s) step(k0 + s * BK, sacc);
+            if constexpr (BIAS) { bias_tot += bias; bias = 0.0f; }
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -732,6 +743,7 @@ __global__ __launch_bounds__(P::WAVES_M * P::WAVES_N * 64) void gemm_kernel(cons
             f32x16 sacc[TM][TN];
             clear(sacc);
             for (; k0 < kend; k0 += BK) step(k0, sacc);
+            if constexpr (BIAS) { bias_tot += bias; bias = 0.0f; }
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -751,21 +763,34 @@ __global__ __launch_bounds__(P::WAVES_M * P::WAVES_N * 64) void gemm_kernel(cons
     }
 
     if constexpr (BIAS) {
-        if (n0 == 0 && wave == WM * WN - 1 && lane < BM && m0 + lane < M) p.store(m0 + lane, p.N - 1, bias, z);
+        if (n0 == 0 && wave == WM * WN - 1 && lane < BM && m0 + lane < M) p.store(m0 + lane, p.N - 1, SEG > 0 ? bias_tot : bias, z);
     }
     epi_store(p, acc, epi, m0, n0, M, z, zb, wm, wn, lane);
 }
 
-template <class P> inline hipError_t launch_gemm(const P &p, hipStream_t stream)
+template <class P>
+__global__ __launch_bounds__(P::WAVES_M * P::WAVES_N * 64) void gemm_kernel(const P p)
+{
+    __shared__ __attribute__((aligned(16))) typename P::T As[TileLds<P>::A_ELEMS], Bs[TileLds<P>::B_ELEMS];
+    gemm_tile(p, launch_at(), As, Bs);
+}
+
+template <class P> inline dim3 gemm_grid(const P &p)
 {
     const int tiles = ((grid_rows(p) + P::BM - 1) / P::BM) * ((tile_cols(p) + P::BN - 1) / P::BN);
     const int nz = (p.K + p.klen - 1) / p.klen;
-    if (tiles <= 0 || nz <= 0) return hipSuccess;
     dim3 grid(tiles, nz, grid_batches(p));
     if constexpr (!HasBatch<P>::value) {
         if (nz >= 32) grid = dim3(((nz + 7) / 8) * 8 * tiles, 1, 1);      // XCD-aware order, decoded in the kernel
         else grid.x = ((tiles + 7) / 8) * 8;                              // likewise: an eighth of the tiles per XCD
     }
+    return grid;
+}
+
+template <class P> inline hipError_t launch_gemm(const P &p, hipStream_t stream)
+{
+    const dim3 grid = gemm_grid(p);
+    if (grid.x == 0 || grid.y == 0) return hipSuccess;
     hipLaunchKernelGGL(gemm_kernel<P>, grid, dim3(P::WAVES_M * P::WAVES_N * 64, 1, 1), 0, stream, p);
     return hipGetLastError();
 }

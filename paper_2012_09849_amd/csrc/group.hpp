@@ -1,0 +1,99 @@
+// Several independent contractions in one launch: a job is a problem with one of the tile bodies of gemm.hpp / wsgemm.hpp, and a
+// workgroup finds its job by its index.  Each job keeps the grid, the tile order and the bits that it has in a launch of its own.
+#pragma once
+#include "wsgemm.hpp"
+
+namespace hts {
+
+constexpr int GROUP_THREADS = 256;
+
+// A job's workgroups in the order of its own launch's linear index; rounded up to a multiple of eight, so that workgroup i of every
+// job runs on XCD i % 8 as the tile orders assume.
+struct JobGrid {
+    int blocks, total, nx, ny;
+    FastDiv dx, dy;
+    JobGrid() = default;
+    explicit JobGrid(const dim3 &g) : blocks((int)((g.x * g.y * g.z + 7) / 8 * 8)), total((int)(g.x * g.y * g.z)), nx((int)g.x), ny((int)g.y),
+                                      dx(FastDiv::make((int)g.x)), dy(FastDiv::make((int)g.y)) {}
+    __device__ __forceinline__ WgAt at(int i) const
+    {
+        const int r = dx.div(i), z = dy.div(r);
+        return {i - r * nx, r - z * ny, z, nx, ny};
+    }
+};
+
+// the tile kernel's workgroups
+template <class P> struct TileJob {
+    P p;
+    JobGrid grid;
+    static constexpr size_t LDS = TileLds<P>::BYTES;
+    static_assert(P::WAVES_M * P::WAVES_N * 64 == GROUP_THREADS, "workgroup");
+    explicit TileJob(const P &q) : p(q), grid(gemm_grid(q)) {}
+    __device__ __forceinline__ void run(int i, unsigned char *smem) const
+    {
+        using T = typename P::T;
+        gemm_tile(p, grid.at(i), reinterpret_cast<T *>(smem), reinterpret_cast<T *>(smem + TileLds<P>::A_BYTES));
+    }
+};
+
+// the wave-per-segment kernel's (PARTIAL = false), spg segments of SEG per reduction group
+template <class P, int SEG> struct SegmentJob {
+    P p;
+    int spg;
+    JobGrid grid;
+    static constexpr int WAVES = GROUP_THREADS / 64;
+    static constexpr size_t LDS = wsgemm_lds<P, WAVES, SEG, false>();
+    SegmentJob(const P &q, int segs_per_group) : p(q)
+    {
+        const int nseg = (q.K + SEG - 1) / SEG;
+        spg = segs_per_group < nseg ? segs_per_group : nseg;
+        grid = JobGrid(wsgemm_grid<P, WAVES, SEG, false>(q, spg));
+    }
+    __device__ __forceinline__ void run(int i, unsigned char *smem) const { wsgemm_tile<P, WAVES, SEG, false>(p, spg, grid.at(i), smem); }
+};
+
+template <class... J> struct Jobs;
+template <> struct Jobs<> {
+    static constexpr size_t LDS = 0;
+    int blocks() const { return 0; }
+    __device__ __forceinline__ void run(int, unsigned char *) const {}
+};
+template <class H, class... R> struct Jobs<H, R...> {
+    H head;
+    Jobs<R...> rest;
+    static constexpr size_t LDS = H::LDS > Jobs<R...>::LDS ? H::LDS : Jobs<R...>::LDS;
+    explicit Jobs(const H &h, const R &...r) : head(h), rest(r...) {}
+    int blocks() const { return head.grid.blocks + rest.blocks(); }
+    __device__ __forceinline__ void run(int i, unsigned char *smem) const
+    {
+        if (i >= head.grid.blocks) rest.run(i - head.grid.blocks, smem);
+        else if (i < head.grid.total) head.run(i, smem);
+    }
+};
+
+template <class G> __global__ __launch_bounds__(GROUP_THREADS) void group_kernel(const G g)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    g.run((int)blockIdx.x, smem);
+}
+
+// jobs in the order in which their workgroups should start
+template <class... J> inline hipError_t launch_group(hipStream_t stream, const J &...jobs)
+{
+    typedef Jobs<J...> G;
+    const G g(jobs...);
+    static_assert(sizeof(G) <= 4096, "kernel arguments");
+    auto kern = group_kernel<G>;
+    if constexpr (G::LDS > 65536) {
+        static std::atomic<bool> attr_set{false};       // raise the dynamic-LDS limit once per instantiation (setting it twice is harmless)
+        if (!attr_set.load(std::memory_order_acquire)) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)G::LDS);
+            if (e != hipSuccess) return e;
+            attr_set.store(true, std::memory_order_release);
+        }
+    }
+    hipLaunchKernelGGL(kern, dim3(g.blocks()), dim3(GROUP_THREADS), G::LDS, stream, g);
+    return hipGetLastError();
+}
+
+}  // namespace hts

@@ -46,7 +46,9 @@ enum Site {
     SITE_CONV2_DGRAD, SITE_CONV1_WGRAD, SITE_WGRAD_REDUCE, SITE_GRAD_NORM, SITE_ADAM, SITE_GAE, SITE_NORMALIZE,
     SITE_STATS,
     // the learner's forward pass runs other kernels than an actor call of a few rows: its launches are sites of their own
-    SITE_CONV1_FWD_LEARN, SITE_CONV2_FWD_LEARN, SITE_CONV3_FWD_LEARN, SITE_FC_FWD_LEARN, SITE_COUNT
+    SITE_CONV1_FWD_LEARN, SITE_CONV2_FWD_LEARN, SITE_CONV3_FWD_LEARN, SITE_FC_FWD_LEARN,
+    SITE_WGRADS,      // the weight gradients that share a launch
+    SITE_COUNT
 };
 constexpr int PROF_CAP = 4096;     // event pairs kept per profiling window
 

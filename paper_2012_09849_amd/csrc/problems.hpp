@@ -264,6 +264,12 @@ struct HeadsWgrad {
     }
 };
 
+// the same on the tile kernel (klen a whole number of segments): segments of 32 rows, as the wave-per-segment kernel forms them
+struct HeadsTiles : HeadsWgrad {
+    static constexpr int SEG = 32;
+    explicit HeadsTiles(const HeadsWgrad &p) : HeadsWgrad(p) {}
+};
+
 // ------------------------------------------------------------------------------------------------------------
 // FC weight gradient: D[j][f] = sum_b dh[b][j] * (f < F ? a3[b][f] : 1); column F is fc.b
 // ------------------------------------------------------------------------------------------------------------

@@ -23,10 +23,10 @@ namespace hts {
 // loads the k-vectors of its own column straight into registers and picks the elements its MFMA slot needs.  That
 // halves the LDS footprint, so twice as many wavefronts (segments) fit in one workgroup.
 template <class P, int WAVES, int SEG, bool PARTIAL, bool BDIR = false>
-__global__ __launch_bounds__(WAVES * 64) void wsgemm_kernel(const P p, const int spg)
+__device__ __forceinline__ void wsgemm_tile(const P &p, const int spg, const WgAt at, unsigned char *smem)
 {
     static_assert(!BDIR || P::B_ALONG_K, "direct B operands must be contiguous along k");
-    const int zb = blockIdx.z, M = rows_of(p, zb);
+    const int zb = at.z, M = rows_of(p, zb);
     using T = typename P::T;
     using Tr = OperandTraits<T>;
     constexpr int LS = SEG + Tr::PAD;
@@ -44,11 +44,10 @@ __global__ __launch_bounds__(WAVES * 64) void wsgemm_kernel(const P p, const int
     constexpr size_t PANEL_BYTES = (size_t)(BDIR ? 1 : 2) * 32 * LS * sizeof(T);   // operand panel(s) of one wavefront
     static_assert(PARTIAL || PANEL_BYTES >= 4096, "the fold reuses a wavefront's panels for its 32x32 partial tile");
 
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     T *As = reinterpret_cast<T *>(smem + (size_t)w * PANEL_BYTES), *Bs = As + 32 * LS;
     const int tiles_n = (p.N + 31) / 32;
-    const int m0 = (blockIdx.x / tiles_n) * 32, n0 = (blockIdx.x % tiles_n) * 32;
+    const int m0 = (at.x / tiles_n) * 32, n0 = (at.x % tiles_n) * 32;
     if (m0 >= M) return;
     const int nseg = (p.K + SEG - 1) / SEG;
     const int lrow = lane & 31, lk = lane >> 5;
@@ -212,7 +211,7 @@ __global__ __launch_bounds__(WAVES * 64) void wsgemm_kernel(const P p, const int
     };
 
     if constexpr (PARTIAL) {
-        const int seg = blockIdx.y * WAVES + w;
+        const int seg = at.y * WAVES + w;
         if (seg >= nseg) return;
         const f32x16 acc = segment_sum(seg);
         const int n = n0 + lrow;
@@ -244,7 +243,7 @@ __global__ __launch_bounds__(WAVES * 64) void wsgemm_kernel(const P p, const int
         float total[PER];
 #pragma unroll
         for (int e = 0; e < PER; ++e) total[e] = 0.0f;
-        const int gbeg = blockIdx.y * spg, gend = min(nseg, gbeg + spg);
+        const int gbeg = at.y * spg, gend = min(nseg, gbeg + spg);
         const int rounds = (gend - gbeg + WAVES - 1) / WAVES;
         for (int rd = 0; rd < rounds; ++rd) {
             const int seg = gbeg + rd * WAVES + w;
@@ -279,7 +278,7 @@ __global__ __launch_bounds__(WAVES * 64) void wsgemm_kernel(const P p, const int
             for (int e = 0; e < PER; ++e) {
                 const int r = e * WAVES + w;
                 if constexpr (PRE1) p.store1(pre[e], total[e]);
-                else do_store(p, m0 + 8 * (r / 4) + 4 * lk + (r % 4), n, total[e], (int)blockIdx.y, zb, col);
+                else do_store(p, m0 + 8 * (r / 4) + 4 * lk + (r % 4), n, total[e], at.y, zb, col);
             }
         } else {
 #pragma unroll
@@ -288,11 +287,18 @@ __global__ __launch_bounds__(WAVES * 64) void wsgemm_kernel(const P p, const int
                 const int m = m0 + 8 * (r / 4) + 4 * lk + (r % 4);
                 if (m < M && n < p.N) {
                     if constexpr (PRE1) p.store1(pre[e], total[e]);
-                    else do_store(p, m, n, total[e], (int)blockIdx.y, zb, col);
+                    else do_store(p, m, n, total[e], at.y, zb, col);
                 }
             }
         }
     }
+}
+
+template <class P, int WAVES, int SEG, bool PARTIAL, bool BDIR = false>
+__global__ __launch_bounds__(WAVES * 64) void wsgemm_kernel(const P p, const int spg)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    wsgemm_tile<P, WAVES, SEG, PARTIAL, BDIR>(p, spg, launch_at(), smem);
 }
 
 // ------------------------------------------------------------------------------------------------------------
@@ -419,14 +425,22 @@ template <class P, int WAVES, int SEG> inline hipError_t launch_wsgemm16(const P
     return hipGetLastError();
 }
 
+template <class P, int WAVES, int SEG, bool BDIR> constexpr size_t wsgemm_lds()
+{
+    return (size_t)WAVES * (BDIR ? 1 : 2) * 32 * (SEG + OperandTraits<typename P::T>::PAD) * sizeof(typename P::T);
+}
+template <class P, int WAVES, int SEG, bool PARTIAL> inline dim3 wsgemm_grid(const P &p, int spg)
+{
+    const int tiles = ((grid_rows(p) + 31) / 32) * ((p.N + 31) / 32), nseg = (p.K + SEG - 1) / SEG;
+    return dim3(tiles, PARTIAL ? (nseg + WAVES - 1) / WAVES : (nseg + spg - 1) / spg, grid_batches(p));
+}
+
 template <class P, int WAVES, int SEG, bool PARTIAL, bool BDIR = false>
 inline hipError_t launch_wsgemm(const P &p, hipStream_t stream, int segs_per_group = 1 << 30)
 {
-    using T = typename P::T;
-    const int tiles = ((grid_rows(p) + 31) / 32) * ((p.N + 31) / 32);
     const int nseg = (p.K + SEG - 1) / SEG;
-    if (tiles <= 0 || nseg <= 0) return hipSuccess;
-    const size_t lds = (size_t)WAVES * (BDIR ? 1 : 2) * 32 * (SEG + OperandTraits<T>::PAD) * sizeof(T);
+    if (grid_rows(p) <= 0 || p.N <= 0 || nseg <= 0) return hipSuccess;
+    const size_t lds = wsgemm_lds<P, WAVES, SEG, BDIR>();
     auto kern = wsgemm_kernel<P, WAVES, SEG, PARTIAL, BDIR>;
     static std::atomic<bool> attr_set{false};       // raise the dynamic-LDS limit once per instantiation (setting it twice is harmless)
     if (!attr_set.load(std::memory_order_acquire)) {
@@ -436,8 +450,8 @@ inline hipError_t launch_wsgemm(const P &p, hipStream_t stream, int segs_per_gro
         attr_set.store(true, std::memory_order_release);
     }
     const int spg = segs_per_group < nseg ? segs_per_group : nseg;
-    const int gy = PARTIAL ? (nseg + WAVES - 1) / WAVES : (nseg + spg - 1) / spg;
-    hipLaunchKernelGGL(kern, dim3(tiles, gy, grid_batches(p)), dim3(WAVES * 64, 1, 1), lds, stream, p, spg);
+    const dim3 grid = wsgemm_grid<P, WAVES, SEG, PARTIAL>(p, spg);
+    hipLaunchKernelGGL(kern, grid, dim3(WAVES * 64, 1, 1), lds, stream, p, spg);
     return hipGetLastError();
 }
 
