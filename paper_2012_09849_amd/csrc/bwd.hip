@@ -633,8 +633,8 @@ template <typename T> static hipError_t backward_t(Ctx &c, const uint8_t *obs, c
         return p;
     };
     // ---- launches.  binary32's weight gradients share one launch behind the input gradients: each of them alone has one or two
-    // wavefronts per SIMD (400 to 576 workgroups at 1024 rows of 84x84 frames; 282 us one after the other, 215 together; 51 and 32
-    // at 80 rows).  bfloat16's go out each right behind the input gradient whose output they read, while the caches still hold
+    // wavefronts per SIMD (400 to 576 workgroups of tiles at 1024 rows of 84x84 frames; 282 us one after the other, 215 together, 183 with their
+    // operands in registers; 51 and 32 at 80 rows).  bfloat16's go out each right behind the input gradient whose output they read, while the caches still hold
     // it (together 115 us against 90 at 2048 rows of 72x96 frames). ----
     if constexpr (sizeof(T) == 2) {
         { SiteTimer tm(c, SITE_HEADS_WGRAD); e = launch_wsgemm<HeadsWgrad, 16, 32, false>(ph, c.stream, spgh); }      // 16 wavefronts share each tile
@@ -716,8 +716,16 @@ template <typename T> static hipError_t backward_t(Ctx &c, const uint8_t *obs, c
                                            SegmentJob<ConvWgrad<T, Layer3>, 64>(p3, spg3), TileJob<FcWgrad<T>>(pf));
             HeadsTiles pt(ph);
             pt.klen = nzh > 0 ? spgh * 32 : B;
-            return launch_group(c.stream, TileJob<HeadsTiles>(pt), TileJob<decltype(p1)>(p1), TileJob<ConvWgrad<T, Layer2>>(p2), TileJob<FcWgrad<T>>(pf),
-                                TileJob<ConvWgrad<T, Layer3>>(p3));
+            typedef RegConv1Wgrad<decltype(p1)::GATHERED> Reg1;
+            typedef RegConvWgrad<Layer2> Reg2;
+            typedef RegConvWgrad<Layer3> Reg3;
+            const Reg1 r1(p1);
+            const Reg2 r2(p2);
+            const Reg3 r3(p3);
+            const RegFcWgrad rf(pf);
+            // (the long tasks first, the short bias columns last)
+            return launch_group(c.stream, TileJob<HeadsTiles>(pt), RegJob<Reg1>(r1), RegJob<Reg2>(r2), RegJob<RegFcWgrad>(rf), RegJob<Reg3>(r3),
+                                RegJob<Reg1, true>(r1), RegJob<Reg2, true>(r2), RegJob<Reg3, true>(r3), RegJob<RegFcWgrad, true>(rf));
         };
         e = index ? all(conv1_problem(Conv1Wgrad<T, true>{})) : all(conv1_problem(Conv1Wgrad<T, false>{}));
     } else {

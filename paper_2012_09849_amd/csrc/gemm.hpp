@@ -223,15 +223,6 @@ template <class P> HTS_HD auto tile_load_b(const P &p, const typename P::CtxB &c
 // Optional batching: a problem with `int batches() const`, `int max_m() const`, `int batch_m(int z) const` is
 // launched with gridDim.z = batches(); batch z has batch_m(z) rows and its own gathers: ctx_a(row, z),
 // ctx_b(col, z) and store(m, n, acc, split, z) receive the batch index (the problem object stays read-only).
-// Optional bias column: a naturally staged binary32 problem with `static constexpr float BIAS_COL = x` whose last column N - 1
-// has B = x at every k (a weight gradient's bias) has one wavefront add that column up from the row operands in LDS, k by k,
-// instead of giving it a tile of columns of its own.  The same bits: v_mfma_f32_32x32x2_f32 equals a sequential fma chain.
-// 1024 rows of 84x84 frames: conv2, 9 column tiles -> 8 and with them 576 workgroups -> 512, two per compute unit, 91 -> 69 us;
-// conv1, 3 tiles -> 2, 133 -> 100.  (FC's 50 tiles -> 49 gain less than the wavefront's chain costs: 48.6 -> 53 us; not taken.)
-template <class P, class = void> struct BiasCol : std::false_type {};
-template <class P> struct BiasCol<P, std::void_t<decltype(P::BIAS_COL)>> : std::integral_constant<bool, sizeof(typename P::T) == 4 && NaturalOf<P>::value> {};
-template <class P> HTS_HD int tile_cols(const P &p) { return p.N - (BiasCol<P>::value ? 1 : 0); }       // columns that the tiles cover
-
 // Optional tile order (see the kernel): N slowest instead of M slowest.
 template <class P, class = void> struct TilesAlongM : std::false_type {};
 template <class P> struct TilesAlongM<P, std::void_t<decltype(P::TILES_ALONG_M)>> : std::integral_constant<bool, P::TILES_ALONG_M> {};
@@ -331,7 +322,7 @@ template <class P, int TM, int TN, bool SWAP>
 __device__ __forceinline__ void epi_store(const P &p, const f32x16 (&acc)[TM][TN], EpiInputs<P, TM, TN, SWAP> &epi, int m0, int n0, int M, int z,
                                           int zb, int wm, int wn, int lane)
 {
-    const int lrow = lane & 31, lk = lane >> 5, N = tile_cols(p);
+    const int lrow = lane & 31, lk = lane >> 5, N = p.N;
     auto epilogue = [&](auto full_tile) {
         constexpr bool FULL = decltype(full_tile)::value;
         if constexpr (SWAP) {
@@ -375,7 +366,7 @@ __device__ __forceinline__ WgAt launch_at() { return {(int)blockIdx.x, (int)bloc
 template <class P> __device__ __forceinline__ bool tile_of(const P &p, const WgAt &at, int M, int &m0, int &n0, int &z)
 {
     constexpr int BM = P::BM, BN = P::BN;
-    const int tiles_n = (tile_cols(p) + BN - 1) / BN;
+    const int tiles_n = (p.N + BN - 1) / BN;
     int tile = at.x;
     z = at.y;
     if constexpr (!HasBatch<P>::value) {
@@ -591,10 +582,6 @@ __device__ __forceinline__ void gemm_tile(const P &p, const WgAt at, typename P:
     const T *a_nat = As + wm * TM * 32 + nat_off_a;
     const T *b_nat = Bs + wn * TN * 32 + nat_off_b;
 
-    constexpr bool BIAS = BiasCol<P>::value;
-    static_assert(!BIAS || (NAT_A && BM <= 64), "bias column: a row per lane");
-    float bias = 0.0f, bias_tot = 0.0f;          // of row lane % BM, in the last wavefront of the workgroups of the first columns (segmented: of the segment, before it)
-
     // one k-tile: registers -> LDS, refill this stage's registers with the tile D steps ahead, multiply.
     // REFILL: 1 = always (steady state: an unconditional load lets the compiler wait for exactly the older stages),
     // 0 = never, 2 = if that tile exists
@@ -636,15 +623,6 @@ __device__ __forceinline__ void gemm_tile(const P &p, const WgAt at, typename P:
                     for (int j = 0; j < TN; ++j)
                         acc[i][j] = SWAP ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(bv[j], av[i], acc[i][j], 0, 0, 0)
                                          : __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[i], bv[j], acc[i][j], 0, 0, 0);
-            }
-        }
-        if constexpr (BIAS) {
-            if (n0 == 0 && wave == WM * WN - 1) {
-                float a[BK];
-#pragma unroll
-                for (int k = 0; k < BK; ++k) a[k] = As[k * LSNA + lane % BM];
-#pragma unroll
-                for (int k = 0; k < BK; ++k) bias = __builtin_fmaf(a[k], P::BIAS_COL, bias);
             }
         }
         __syncthreads();
@@ -728,7 +706,6 @@ __device__ __forceinline__ void gemm_tile(const P &p, const WgAt at, typename P:
             clear(sacc);
 #pragma unroll
             for (int s = 0; s < SPS; ++s) step(k0 + s * BK, sacc);
-            if constexpr (BIAS) { bias_tot += bias; bias = 0.0f; }
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -743,7 +720,6 @@ __device__ __forceinline__ void gemm_tile(const P &p, const WgAt at, typename P:
             f32x16 sacc[TM][TN];
             clear(sacc);
             for (; k0 < kend; k0 += BK) step(k0, sacc);
-            if constexpr (BIAS) { bias_tot += bias; bias = 0.0f; }
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -762,9 +738,6 @@ __device__ __forceinline__ void gemm_tile(const P &p, const WgAt at, typename P:
         for (int k0 = kbeg; k0 < kend; k0 += BK) step_s(k0, acc, rra[0], rrb[0], std::integral_constant<int, 2>{});
     }
 
-    if constexpr (BIAS) {
-        if (n0 == 0 && wave == WM * WN - 1 && lane < BM && m0 + lane < M) p.store(m0 + lane, p.N - 1, SEG > 0 ? bias_tot : bias, z);
-    }
     epi_store(p, acc, epi, m0, n0, M, z, zb, wm, wn, lane);
 }
 
@@ -777,7 +750,7 @@ __global__ __launch_bounds__(P::WAVES_M * P::WAVES_N * 64) void gemm_kernel(cons
 
 template <class P> inline dim3 gemm_grid(const P &p)
 {
-    const int tiles = ((grid_rows(p) + P::BM - 1) / P::BM) * ((tile_cols(p) + P::BN - 1) / P::BN);
+    const int tiles = ((grid_rows(p) + P::BM - 1) / P::BM) * ((p.N + P::BN - 1) / P::BN);
     const int nz = (p.K + p.klen - 1) / p.klen;
     dim3 grid(tiles, nz, grid_batches(p));
     if constexpr (!HasBatch<P>::value) {

@@ -1,6 +1,7 @@
 // Several independent contractions in one launch: a job is a problem with one of the tile bodies of gemm.hpp / wsgemm.hpp, and a
 // workgroup finds its job by its index.  Each job keeps the grid, the tile order and the bits that it has in a launch of its own.
 #pragma once
+#include "regwgrad.hpp"
 #include "wsgemm.hpp"
 
 namespace hts {
@@ -27,6 +28,7 @@ template <class P> struct TileJob {
     P p;
     JobGrid grid;
     static constexpr size_t LDS = TileLds<P>::BYTES;
+    static constexpr bool WIDE = false;
     static_assert(P::WAVES_M * P::WAVES_N * 64 == GROUP_THREADS, "workgroup");
     explicit TileJob(const P &q) : p(q), grid(gemm_grid(q)) {}
     __device__ __forceinline__ void run(int i, unsigned char *smem) const
@@ -43,6 +45,7 @@ template <class P, int SEG> struct SegmentJob {
     JobGrid grid;
     static constexpr int WAVES = GROUP_THREADS / 64;
     static constexpr size_t LDS = wsgemm_lds<P, WAVES, SEG, false>();
+    static constexpr bool WIDE = false;
     SegmentJob(const P &q, int segs_per_group) : p(q)
     {
         const int nseg = (q.K + SEG - 1) / SEG;
@@ -52,9 +55,38 @@ template <class P, int SEG> struct SegmentJob {
     __device__ __forceinline__ void run(int i, unsigned char *smem) const { wsgemm_tile<P, WAVES, SEG, false>(p, spg, grid.at(i), smem); }
 };
 
+// register-operand weight gradient: a task per wavefront, the row tiles of a column tile next to each other.  XCD x takes the
+// reduction chunks x, x + 8, ... or, where there is only one, the column tiles x, x + 8, ...  BIAS: the bias columns instead (short
+// tasks: a workgroup of their own kind, or the other wavefronts' SIMDs wait).
+template <class W, bool BIAS = false> struct RegJob {
+    W p;
+    struct { int blocks, total; } grid;
+    int nz;
+    FastDiv dtasks;
+    static constexpr int WAVES = GROUP_THREADS / 64;
+    static constexpr size_t LDS = WAVES * RW_BLOCK * 8;
+    static constexpr bool WIDE = true;
+    explicit RegJob(const W &q) : p(q)
+    {
+        nz = (q.K + q.klen - 1) / q.klen;
+        const int cols = BIAS ? 1 : q.col_tiles(), tasks = W::CHUNKED ? cols * W::ROW_TILES : W::ROW_TILES, outer = W::CHUNKED ? nz : cols;
+        dtasks = FastDiv::make(tasks);
+        grid.blocks = grid.total = 8 * (((outer + 7) / 8 * tasks + WAVES - 1) / WAVES);
+    }
+    __device__ __forceinline__ void run(int i, unsigned char *smem) const
+    {
+        const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), t = (i >> 3) * WAVES + w, o = dtasks.div(t), inner = t - o * dtasks.d, outer = o * 8 + (i & 7);
+        uint32_t *table = reinterpret_cast<uint32_t *>(smem) + w * RW_BLOCK * 2;
+        if (outer >= (W::CHUNKED ? nz : BIAS ? 1 : p.col_tiles())) return;
+        const int rt = inner % W::ROW_TILES, c = W::CHUNKED ? inner / W::ROW_TILES : outer;
+        regwgrad_task<W, BIAS>(p, rt, c, W::CHUNKED ? outer : 0, table);
+    }
+};
+
 template <class... J> struct Jobs;
 template <> struct Jobs<> {
     static constexpr size_t LDS = 0;
+    static constexpr bool WIDE = false;
     int blocks() const { return 0; }
     __device__ __forceinline__ void run(int, unsigned char *) const {}
 };
@@ -62,6 +94,7 @@ template <class H, class... R> struct Jobs<H, R...> {
     H head;
     Jobs<R...> rest;
     static constexpr size_t LDS = H::LDS > Jobs<R...>::LDS ? H::LDS : Jobs<R...>::LDS;
+    static constexpr bool WIDE = H::WIDE || Jobs<R...>::WIDE;
     explicit Jobs(const H &h, const R &...r) : head(h), rest(r...) {}
     int blocks() const { return head.grid.blocks + rest.blocks(); }
     __device__ __forceinline__ void run(int i, unsigned char *smem) const
@@ -71,6 +104,13 @@ template <class H, class... R> struct Jobs<H, R...> {
     }
 };
 
+// (for the register-operand jobs four wavefronts per SIMD at most: without the bound the compiler keeps their blocks in accumulation
+// registers and moves them to and fro.  Fewer, by asking for LDS: 183 us with four, 195 with two, 230 with one)
+template <class G> __global__ __launch_bounds__(GROUP_THREADS) __attribute__((amdgpu_waves_per_eu(2, 4))) void group_wide_kernel(const G g)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    g.run((int)blockIdx.x, smem);
+}
 template <class G> __global__ __launch_bounds__(GROUP_THREADS) void group_kernel(const G g)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -83,7 +123,8 @@ template <class... J> inline hipError_t launch_group(hipStream_t stream, const J
     typedef Jobs<J...> G;
     const G g(jobs...);
     static_assert(sizeof(G) <= 4096, "kernel arguments");
-    auto kern = group_kernel<G>;
+    void (*kern)(const G);
+    if constexpr (G::WIDE) kern = group_wide_kernel<G>; else kern = group_kernel<G>;
     if constexpr (G::LDS > 65536) {
         static std::atomic<bool> attr_set{false};       // raise the dynamic-LDS limit once per instantiation (setting it twice is harmless)
         if (!attr_set.load(std::memory_order_acquire)) {

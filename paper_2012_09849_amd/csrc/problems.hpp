@@ -481,7 +481,6 @@ template <typename T_, class L> struct ConvDgrad {
 // ------------------------------------------------------------------------------------------------------------
 template <typename T_, class L> struct ConvWgrad {
     using T = T_;
-    static constexpr float BIAS_COL = 1.0f;
     static constexpr bool STEADY = true;
     static constexpr int BM = 64, BN = 64, BK = (sizeof(T) == 2 ? BK_BF16_WGRAD : 32), WAVES_M = 2, WAVES_N = 2;
     static constexpr int VA = OperandTraits<T>::VEC, VB = OperandTraits<T>::VEC;
@@ -553,8 +552,7 @@ template <typename T_, class L> struct ConvWgrad {
 // INDEXED: the frames are gathered through `index` (a template parameter so that the loader has no branch)
 template <typename T_, bool INDEXED> struct Conv1Wgrad {
     using T = T_;
-    static constexpr float BIAS_COL = 255.0f;
-    static constexpr bool NATURAL_LDS = sizeof(T) == 4;
+    static constexpr bool GATHERED = INDEXED;
     static constexpr bool STEADY = true;
     static constexpr int BM = 32, BN = 128, BK = (sizeof(T) == 2 ? BK_BF16_WGRAD : 32), WAVES_M = 1, WAVES_N = 4;
     static constexpr int VA = OperandTraits<T>::VEC, VB = 8;
