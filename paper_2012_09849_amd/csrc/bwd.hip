@@ -678,7 +678,7 @@ template <typename T> static hipError_t backward_t(Ctx &c, const uint8_t *obs, c
             // weight column touches 32 cache lines per load instruction, and with sixteen wavefronts on a compute unit
             // the L1's address processing was the whole issue phase (24.2 -> 19.3 us at 80 rows).  bfloat16 rows are
             // half as long and the direct form stays faster there (11.6 vs 17.2 us).
-            e = small ? launch_wsgemm<ConvDgrad<T, Layer3>, (sizeof(T) == 4 ? 8 : 4), (sizeof(T) == 2 ? 192 : 72), false, (sizeof(T) == 2)>(p, c.stream) : launch_gemm(p, c.stream);
+            e = small ? launch_wsgemm<ConvDgrad<T, Layer3>, (sizeof(T) == 4 ? 8 : 4), (sizeof(T) == 2 ? 192 : 72), false, (sizeof(T) == 2)>(p, c.stream) : launch_gemm(ConvDgradByPosition<T, Layer3>(p), c.stream);
         }
         if (e != hipSuccess) return e;
     }
@@ -705,7 +705,7 @@ template <typename T> static hipError_t backward_t(Ctx &c, const uint8_t *obs, c
                 a.out = (bf16_t *)c.ws.dy1; a.B = B;
                 e = launch_imgconv<ImgDgrad<32, 4, 2, 17, 23, 4>>(a, c.stream);
             } else
-            e = small ? launch_wsgemm<ConvDgrad<T, Layer2>, 4, 64, false>(p, c.stream) : launch_gemm(p, c.stream);
+            e = small ? launch_wsgemm<ConvDgrad<T, Layer2>, 4, 64, false>(p, c.stream) : launch_gemm(ConvDgradByPosition<T, Layer2>(p), c.stream);
         }
         if (e != hipSuccess) return e;
     }

@@ -223,6 +223,12 @@ template <class P> HTS_HD auto tile_load_b(const P &p, const typename P::CtxB &c
 // Optional batching: a problem with `int batches() const`, `int max_m() const`, `int batch_m(int z) const` is
 // launched with gridDim.z = batches(); batch z has batch_m(z) rows and its own gathers: ctx_a(row, z),
 // ctx_b(col, z) and store(m, n, acc, split, z) receive the batch index (the problem object stays read-only).
+// Optional taps: a batched problem (without SEG) with `uint32_t live_taps(int m0, int batch) const` has bit t set where the k in
+// [t TAP_K, (t+1) TAP_K) (a whole number of k-tiles) may differ from zero for the tile of rows from m0 on; the others are left
+// out: a zero product changes no sum.
+template <class P, class = void> struct HasTaps : std::false_type {};
+template <class P> struct HasTaps<P, std::void_t<decltype(&P::live_taps)>> : std::true_type {};
+
 // Optional tile order (see the kernel): N slowest instead of M slowest.
 template <class P, class = void> struct TilesAlongM : std::false_type {};
 template <class P> struct TilesAlongM<P, std::void_t<decltype(P::TILES_ALONG_M)>> : std::integral_constant<bool, P::TILES_ALONG_M> {};
@@ -582,15 +588,15 @@ __device__ __forceinline__ void gemm_tile(const P &p, const WgAt at, typename P:
     const T *a_nat = As + wm * TM * 32 + nat_off_a;
     const T *b_nat = Bs + wn * TN * 32 + nat_off_b;
 
-    // one k-tile: registers -> LDS, refill this stage's registers with the tile D steps ahead, multiply.
+    // one k-tile: registers -> LDS, refill this stage's registers with the tile at `next` (D steps ahead), multiply.
     // REFILL: 1 = always (steady state: an unconditional load lets the compiler wait for exactly the older stages),
     // 0 = never, 2 = if that tile exists
-    auto step_s = [&](int k0, f32x16 (&acc)[TM][TN], Vec<T, VA> (&ra)[NA][RA], Vec<T, VB> (&rb)[NB][RB], auto refill) {
+    auto step_s = [&](int next, f32x16 (&acc)[TM][TN], Vec<T, VA> (&ra)[NA][RA], Vec<T, VB> (&rb)[NB][RB], auto refill) {
         constexpr int REFILL = decltype(refill)::value;
         sstore(ra, rb);
         __syncthreads();
-        if constexpr (REFILL == 1) gload(k0 + D * BK, ra, rb, 0x7fffffff);
-        else if constexpr (REFILL == 2) { if (k0 + D * BK < kend) gload(k0 + D * BK, ra, rb, kend); }
+        if constexpr (REFILL == 1) gload(next, ra, rb, 0x7fffffff);
+        else if constexpr (REFILL == 2) { if (next < kend) gload(next, ra, rb, kend); }
 #pragma unroll
         for (int kk = 0; kk < BK; kk += Tr::KINST) {
             if constexpr (sizeof(T) == 4) {
@@ -638,13 +644,20 @@ __device__ __forceinline__ void gemm_tile(const P &p, const WgAt at, typename P:
 
     f32x16 acc[TM][TN];
     clear(acc);
+    uint32_t live = 0xffffffffu;
+    int first = kbeg;
+    if constexpr (HasTaps<P>::value) {
+        static_assert(D == 1 && SEG == 0 && P::TAP_K % BK == 0, "taps");
+        live = p.live_taps(m0, zb);
+        first = live ? __builtin_ctz(live) * P::TAP_K : 0;
+    }
     // (unconditional: a stage beyond the end of a short reduction range fetches the range's last k-tile once more and
     // is never consumed -- a branch here leaves the compiler unsure how many loads are outstanding when the k loop
     // starts, and it then waits for all of them at the top of every iteration)
 #pragma unroll
     for (int s = 0; s < D; ++s) {
         const int last = kbeg + ((kend - kbeg - 1) / BK) * BK;
-        gload(min(kbeg + s * BK, last), rra[s], rrb[s], kend);
+        gload(min(first + s * BK, last), rra[s], rrb[s], kend);
     }
     EpiInputs<P, TM, TN, SWAP> epi;
     if constexpr (EpiEarly<P>::value) epi_fetch(p, epi, m0, n0, M, zb, wm, wn, lane);
@@ -668,7 +681,7 @@ __device__ __forceinline__ void gemm_tile(const P &p, const WgAt at, typename P:
         for (; kg + 2 * D * BK <= kend; kg += D * BK) {
 #pragma unroll
             for (int s = 0; s < D; ++s) {
-                step_s(kg + s * BK, sacc, rra[s], rrb[s], std::integral_constant<int, 1>{});
+                step_s(kg + (s + D) * BK, sacc, rra[s], rrb[s], std::integral_constant<int, 1>{});
                 fold(kg + s * BK);
             }
         }
@@ -678,12 +691,12 @@ __device__ __forceinline__ void gemm_tile(const P &p, const WgAt at, typename P:
             for (int s = 0; s < D; ++s) {
                 const int k0 = kg + s * BK;
                 if (k0 >= kend) break;                 // uniform over the workgroup
-                step_s(k0, sacc, rra[s], rrb[s], std::integral_constant<int, 2>{});
+                step_s(k0 + D * BK, sacc, rra[s], rrb[s], std::integral_constant<int, 2>{});
                 fold(k0);
             }
         }
     } else if constexpr (SEG > 0) {
-        auto step = [&](int k0, f32x16 (&a)[TM][TN]) { step_s(k0, a, rra[0], rrb[0], std::integral_constant<int, 2>{}); };
+        auto step = [&](int k0, f32x16 (&a)[TM][TN]) { step_s(k0 + BK, a, rra[0], rrb[0], std::integral_constant<int, 2>{}); };
         // one fresh accumulator per segment (it only lives inside the segment), folded into the running total
         constexpr int SPS = SEG / BK;            // k-tiles per segment
         constexpr int GROUP = GroupOf<P>::value;
@@ -734,8 +747,18 @@ __device__ __forceinline__ void gemm_tile(const P &p, const WgAt at, typename P:
 #pragma unroll
                 for (int j = 0; j < TN; ++j) acc[i][j] = tot[i][j];
         }
+    } else if constexpr (HasTaps<P>::value) {
+        for (int k0 = live ? first : kend; k0 < kend;) {
+            int next = k0 + BK;
+            if (next % P::TAP_K == 0) {
+                const uint32_t later = next < kend ? live >> (next / P::TAP_K) : 0u;
+                next = later ? next + __builtin_ctz(later) * P::TAP_K : kend;
+            }
+            step_s(next, acc, rra[0], rrb[0], std::integral_constant<int, 2>{});
+            k0 = next;
+        }
     } else {
-        for (int k0 = kbeg; k0 < kend; k0 += BK) step_s(k0, acc, rra[0], rrb[0], std::integral_constant<int, 2>{});
+        for (int k0 = kbeg; k0 < kend; k0 += BK) step_s(k0 + BK, acc, rra[0], rrb[0], std::integral_constant<int, 2>{});
     }
 
     epi_store(p, acc, epi, m0, n0, M, z, zb, wm, wn, lane);
