@@ -3,7 +3,7 @@
 // each chunk writes its own partial, and wgrad_reduce adds the partials in chunk order -- no atomics, so the
 // gradient is bit-identical from run to run.
 #include "internal.hpp"
-#include "dmagemm.hpp"
+#include "dmawgrad.hpp"
 #include "group.hpp"
 #include "imgconv.hpp"
 
@@ -587,8 +587,8 @@ template <typename T> static hipError_t backward_t(Ctx &c, const uint8_t *obs, c
     const bool slab1 = sizeof(T) == 2 && B >= c.conv1_wgrad_slab_rows && conv1_wgrad_slab_fits(g, obs) && conv1_wgrad_slab_batch_fits(B, s1.nz);
     const bool image1 = !slab1 && sizeof(T) == 2 && B >= c.conv1_wgrad_image_rows && conv1_wgrad_image_fits(g, obs);
     const bool small1 = !slab1 && !image1 && small;
-    // conv2/conv3 weight gradients, us, wave-per-segment / tile kernel: bf16 at 16 rows of 84x84 frames 8.8 / 5.4 and 10.1 / 5.9,
-    // at 128 rows 12.0 / 5.8 and 12.1 / 6.6; binary32 at 16 rows 9.1 / 10.5 and 8.7 / 11.3, at 96 rows 14.0 / 13.8 and 13.1 / 12.8
+    // conv2/conv3 weight gradients, us, wave-per-segment / copying kernel: bf16 at 16 rows of 84x84 frames 8.8 / 5.5 and 10.1 / 4.7,
+    // at 128 rows 12.0 / 5.3 and 12.1 / 5.5; wave-per-segment / tile kernel: binary32 at 16 rows 9.1 / 10.5 and 8.7 / 11.3, at 96 rows 14.0 / 13.8 and 13.1 / 12.8
     const bool smallw = small && sizeof(T) == 4;
     int spg3 = 0, spg2 = 0, spg1 = 0;
     const int nz3 = smallw ? groups_for((long long)B * g.P3, &spg3, 32, 8) : s3.nz;
@@ -635,10 +635,10 @@ template <typename T> static hipError_t backward_t(Ctx &c, const uint8_t *obs, c
     // ---- launches.  binary32's weight gradients share one launch behind the input gradients: each of them alone has one or two
     // wavefronts per SIMD (400 to 576 workgroups of tiles at 1024 rows of 84x84 frames; 282 us one after the other, 215 together, 183 with their
     // operands in registers; 51 and 32 at 80 rows).  bfloat16's go out each right behind the input gradient whose output they read, while the caches still hold
-    // it (together 115 us against 90 at 2048 rows of 72x96 frames). ----
+    // it (on the tile kernel, together 115 us against 90 at 2048 rows of 72x96 frames). ----
     if constexpr (sizeof(T) == 2) {
         { SiteTimer tm(c, SITE_HEADS_WGRAD); e = launch_wsgemm<HeadsWgrad, 16, 32, false>(ph, c.stream, spgh); }      // 16 wavefronts share each tile
-        if (e == hipSuccess) { SiteTimer tm(c, SITE_FC_WGRAD); e = launch_gemm(pf, c.stream); }
+        if (e == hipSuccess) { SiteTimer tm(c, SITE_FC_WGRAD); e = launch_wgrad_dma<1, 3, 2>(DmaFcWgrad(pf), c.stream); }
         if (e != hipSuccess) return e;
     }
     {   // d(conv3 pre-activation)
@@ -653,7 +653,7 @@ template <typename T> static hipError_t backward_t(Ctx &c, const uint8_t *obs, c
     }
     if constexpr (sizeof(T) == 2) {
         SiteTimer tm(c, SITE_CONV3_WGRAD);
-        if ((e = launch_gemm(p3, c.stream)) != hipSuccess) return e;
+        if ((e = launch_wgrad_dma<1, 3, 2>(DmaConvWgrad<Layer3>(p3), c.stream)) != hipSuccess) return e;
     }
     {   // d(conv2 pre-activation)
         ConvDgrad<T, Layer3> p;
@@ -684,7 +684,7 @@ template <typename T> static hipError_t backward_t(Ctx &c, const uint8_t *obs, c
     }
     if constexpr (sizeof(T) == 2) {
         SiteTimer tm(c, SITE_CONV2_WGRAD);
-        if ((e = launch_gemm(p2, c.stream)) != hipSuccess) return e;
+        if ((e = launch_wgrad_dma<2, 3, 4>(DmaConvWgrad<Layer2>(p2), c.stream)) != hipSuccess) return e;
     }
     {   // d(conv1 pre-activation)
         ConvDgrad<T, Layer2> p;

@@ -177,12 +177,11 @@ template <class P> struct SteadyOf<P, std::void_t<decltype(P::STEADY)>> { static
 template <class P, class = void> struct OwnsRow : std::false_type {};
 template <class P> struct OwnsRow<P, std::void_t<decltype(P::LANE_OWNS_ROW)>> : std::integral_constant<bool, P::LANE_OWNS_ROW> {};
 
-// Optional natural staging of operands that are contiguous along the row index instead of along the reduction (the
+// Optional natural staging of fp32 operands that are contiguous along the row index instead of along the reduction (the
 // weight gradients): a problem with `static constexpr bool NATURAL_LDS = true` has such an operand loaded by threads
 // whose neighbours take neighbouring row vectors at ONE reduction index (whole cache lines per load instruction), kept in
-// LDS as it lies in memory ([reduction][row], padded), and brought into the matrix instruction's lane layout by the
-// transposing LDS read (bf16) or by plain element reads (fp32).  No register transposes; same operand values in the
-// same lanes as the default staging, hence the same bits.
+// LDS as it lies in memory ([reduction][row], padded), and read element by element into the matrix instruction's lane
+// layout.  No register transposes; same operand values in the same lanes as the default staging, hence the same bits.
 template <class P, class = void> struct NaturalOf : std::false_type {};
 template <class P> struct NaturalOf<P, std::void_t<decltype(P::NATURAL_LDS)>> : std::integral_constant<bool, P::NATURAL_LDS> {};
 typedef short i16x4 __attribute__((ext_vector_type(4)));
@@ -423,11 +422,11 @@ template <class P> __device__ __forceinline__ bool tile_of(const P &p, const WgA
 //   void store(int m, int n, float acc, int z) const          called only for m < M, n < N
 //   optionally Col col(int n) const and store(..., const Col &)   per-column epilogue data, fetched once per lane
 // LDS: operand tiles, k-contiguous rows ([row][k + pad]) or natural staging ([reduction][row + pad]); the latter's pad keeps the row
-// pitch at 64 bytes modulo 128 for bf16 (the four reduction rows a 16-lane group reads at once fall into different banks)
-// and 128 modulo 256 for fp32
+// pitch at 128 bytes modulo 256
 template <class P> struct TileLds {
     using T = typename P::T;
     static constexpr bool NAT_A = NaturalOf<P>::value && !P::A_ALONG_K, NAT_B = NaturalOf<P>::value && !P::B_ALONG_K;
+    static_assert(sizeof(T) == 4 || !(NAT_A || NAT_B), "natural staging");
     static constexpr int LS = P::BK + OperandTraits<T>::PAD;
     static constexpr int LSNA = P::BM + (P::BM % 64 == 0 ? 32 : 0), LSNB = P::BN + (P::BN % 64 == 0 ? 32 : 0);
     static constexpr int A_ELEMS = NAT_A ? P::BK * LSNA : P::BM * LS, B_ELEMS = NAT_B ? P::BK * LSNB : P::BN * LS;
@@ -577,16 +576,8 @@ __device__ __forceinline__ void gemm_tile(const P &p, const WgAt at, typename P:
     const int lrow = lane & 31, lk = lane >> 5;
     const T *a_base = As + (wm * TM * 32 + lrow) * LS;
     const T *b_base = Bs + (wn * TN * 32 + lrow) * LS;
-    // Natural staging, bf16: the transposing read works on groups of 16 lanes; lane 4j+q of a group points at 4 row
-    // entries (4q..4q+3 of the group's 16) of reduction index j (< 4) and receives the 4 reduction indices of row
-    // entry (lane % 16).  Groups 0,1 cover rows 0-15 and 16-31 at reduction 0-7 (two reads), groups 2,3 at 8-15.
-    // fp32: lane (row, k) reads its element.
-    const int nat_off_a = sizeof(T) == 2 ? (8 * (lane >> 5) + ((lane & 15) >> 2)) * LSNA + 16 * ((lane >> 4) & 1) + 4 * (lane & 3)
-                                         : lk * LSNA + lrow;
-    const int nat_off_b = sizeof(T) == 2 ? (8 * (lane >> 5) + ((lane & 15) >> 2)) * LSNB + 16 * ((lane >> 4) & 1) + 4 * (lane & 3)
-                                         : lk * LSNB + lrow;
-    const T *a_nat = As + wm * TM * 32 + nat_off_a;
-    const T *b_nat = Bs + wn * TN * 32 + nat_off_b;
+    const T *a_nat = As + wm * TM * 32 + lk * LSNA + lrow;      // natural staging: lane (row, k) reads its element
+    const T *b_nat = Bs + wn * TN * 32 + lk * LSNB + lrow;
 
     // one k-tile: registers -> LDS, refill this stage's registers with the tile at `next` (D steps ahead), multiply.
     // REFILL: 1 = always (steady state: an unconditional load lets the compiler wait for exactly the older stages),
@@ -614,15 +605,9 @@ __device__ __forceinline__ void gemm_tile(const P &p, const WgAt at, typename P:
             } else {
                 bf16x8 av[TM], bv[TN];
 #pragma unroll
-                for (int i = 0; i < TM; ++i) {
-                    if constexpr (NAT_A) av[i] = tr8(a_nat + kk * LSNA + i * 32, LSNA);
-                    else av[i] = *reinterpret_cast<const bf16x8 *>(a_base + i * 32 * LS + kk + lk * 8);
-                }
+                for (int i = 0; i < TM; ++i) av[i] = *reinterpret_cast<const bf16x8 *>(a_base + i * 32 * LS + kk + lk * 8);
 #pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    if constexpr (NAT_B) bv[j] = tr8(b_nat + kk * LSNB + j * 32, LSNB);
-                    else bv[j] = *reinterpret_cast<const bf16x8 *>(b_base + j * 32 * LS + kk + lk * 8);
-                }
+                for (int j = 0; j < TN; ++j) bv[j] = *reinterpret_cast<const bf16x8 *>(b_base + j * 32 * LS + kk + lk * 8);
 #pragma unroll
                 for (int i = 0; i < TM; ++i)
 #pragma unroll

@@ -275,7 +275,7 @@ struct HeadsTiles : HeadsWgrad {
 // ------------------------------------------------------------------------------------------------------------
 template <typename T_> struct FcWgrad {
     using T = T_;
-    static constexpr int BM = 64, BN = 64, BK = (sizeof(T) == 2 ? BK_BF16_WGRAD : 32), WAVES_M = 2, WAVES_N = 2;   // 8 x 50 workgroups
+    static constexpr int BM = 64, BN = 64, BK = 32, WAVES_M = 2, WAVES_N = 2;   // 8 x 50 workgroups
     static constexpr int VA = OperandTraits<T>::VEC, VB = OperandTraits<T>::VEC;
     static constexpr bool A_ALONG_K = false, B_ALONG_K = false;
     static constexpr bool NATURAL_LDS = true;
@@ -521,11 +521,9 @@ template <typename T_, class L> struct ConvDgradByPosition : ConvDgrad<T_, L> {
 // ------------------------------------------------------------------------------------------------------------
 template <typename T_, class L> struct ConvWgrad {
     using T = T_;
-    static constexpr bool STEADY = true;
-    static constexpr int BM = 64, BN = 64, BK = (sizeof(T) == 2 ? BK_BF16_WGRAD : 32), WAVES_M = 2, WAVES_N = 2;
+    static constexpr int BM = 64, BN = 64, BK = 32, WAVES_M = 2, WAVES_N = 2;
     static constexpr int VA = OperandTraits<T>::VEC, VB = OperandTraits<T>::VEC;
     static constexpr bool A_ALONG_K = false, B_ALONG_K = false;
-    static constexpr bool NATURAL_LDS = true;
     struct CtxA { int n; };
     struct CtxB { long long goff; };   // offset of (u,v,c) inside a patch; -1: bias column; -2: beyond the last column
     int M, N, K, klen;     // M = Cout (64), N = L::K + 1, K = B*Po
@@ -555,32 +553,6 @@ template <typename T_, class L> struct ConvWgrad {
         Vec<T, VB> v = keep_if<T, VB>(inside, load_vec<T, VB>(in + off));
         v[0] = (m < kend && c.goff == -1) ? from_f32<T>(1.0f) : v[0];
         return v;
-    }
-    // VB consecutive reduction indices m, m+1, ...: one (b, oy, ox) decomposition, advanced position by position.
-    // Loads are issued for every column (the bias and padding columns read column 0 and discard it), so that a k-tile
-    // known to lie inside the range has only unconditional loads.
-    HTS_HD void load_b_run(const CtxB &c, int m, int kend, Vec<T, VB> (&out)[VB]) const
-    {
-        const int Ho = dWo.div(Po);
-        const int mm = m < K ? m : K - 1;
-        const int b = dPo.div(mm), p = mm - b * Po;
-        int oy = dWo.div(p), ox = p - oy * Wo;
-        const T *src = in + (((long long)b * Hin + oy * L::STRIDE) * Win + ox * L::STRIDE) * L::CIN + (c.goff >= 0 ? c.goff : 0);
-        const T *first = src;                                                  // a valid address for positions past the range
-        const int row_adv = (L::STRIDE * Win - Wo * L::STRIDE) * L::CIN;      // from the end of an output row to the next
-        const int img_adv = (Hin - Ho * L::STRIDE) * Win * L::CIN;            // from the last output row to the next sample
-        const T one = from_f32<T>(c.goff == -1 ? 1.0f : 0.0f);
-#pragma unroll
-        for (int q = 0; q < VB; ++q) {
-            const bool live = m + q < kend;
-            out[q] = keep_if<T, VB>(live && c.goff >= 0, load_vec<T, VB>(live ? src : first));
-            out[q][0] = (live && c.goff < 0) ? one : out[q][0];
-            src += L::STRIDE * L::CIN;
-            if (++ox == Wo) {
-                ox = 0; src += row_adv;
-                if (++oy == Ho) { oy = 0; src += img_adv; }
-            }
-        }
     }
     HTS_HD void store(int n, int kcol, float acc, int z) const
     {
@@ -627,7 +599,9 @@ template <typename T_, bool INDEXED> struct Conv1Wgrad {
         v[0] = (m < kend && c.goff == -1) ? from_f32<T>(255.0f) : v[0];   // the 1/255 of the input scaling is applied
         return v;                                                          // when the partials are combined
     }
-    // As ConvWgrad::load_b_run; a run of VB positions touches at most two samples (P1 >= 16), whose storage rows are
+    // VB consecutive reduction indices m, m+1, ...: one (b, oy, ox) decomposition, advanced position by position.  Loads are issued for
+    // every column (the bias and padding columns read column 0 and discard it), so that a k-tile known to lie inside the range has
+    // only unconditional loads.  A run of VB positions touches at most two samples (P1 >= 16), whose storage rows are
     // both looked up before the loads.
     HTS_HD void load_b_run(const CtxB &c, int m, int kend, Vec<T, VB> (&out)[VB]) const
     {
