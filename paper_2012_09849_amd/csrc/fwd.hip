@@ -3,6 +3,7 @@
 #include "internal.hpp"
 #include "dmagemm.hpp"
 #include "imgconv.hpp"
+#include "regconv.hpp"
 
 #include <atomic>
 
@@ -593,8 +594,15 @@ template <typename T> static hipError_t forward_t(Ctx &c, const uint8_t *obs, co
         p.dPo = FastDiv::make(g.P2); p.dWo = FastDiv::make(g.W2);
         {
             SiteTimer tm(c, learn ? SITE_CONV2_FWD_LEARN : SITE_CONV2_FWD);
-            // (the LDS-resident kernel of imgconv.hpp measured slower here than the tile kernel: 20.4 vs 17.8 us at
-            // B = 1024 -- this layer streams the large conv1 output once either way)
+            // (the kernel of imgconv.hpp, weights in LDS and rows staged in registers, measured slower than either: 20.4 us at B = 1024)
+            // Weights in registers, from where the machine's rate outweighs the 7 us until the first products.  us, LDS-copy tiles / this,
+            // 84x84 frames: 256 rows 7.3 / 8.4, 1024 13.8 / 15.0, 1536 19.4 / 19.4, 2048 24.4 / 23.2, 4096 43.5 / 38.2, 8192 105 / 80;
+            // 72x96: 2048 22.6 / 23.8, 3072 34.4 / 31.6, 4096 43.9 / 40.7
+            RegConvArgs r = {};
+            r.in = (const bf16_t *)c.ws.act1; r.w = (const bf16_t *)c.ws.wf2; r.bias = hb + c.sh.b2; r.out = (bf16_t *)c.ws.act2; r.B = B;
+            if (sizeof(T) == 2 && !small && atari_grid && B >= 2048) e = launch_regconv<RegConv<Layer2, 20, 20, ConvFwd<bf16_t, Layer2, false>::SEG>>(r, c.stream);
+            else if (sizeof(T) == 2 && !small && foot_grid && B >= 3072) e = launch_regconv<RegConv<Layer2, 17, 23, ConvFwd<bf16_t, Layer2, false>::SEG>>(r, c.stream);
+            else
             if (small && few32(((p.M + 31) / 32) * 2))
                 e = launch_wsgemm16<ConvFwd<T, Layer2, false>, 8, ConvFwd<T, Layer2, false>::SEG>(p, c.stream);
             else

@@ -1,0 +1,28 @@
+"""conv2 of large bf16 batches, its weights in registers and its samples in LDS: on either side of its first sizes, with an odd sample
+at the end and with unequal numbers of groups per workgroup, against the wave-per-segment kernels bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from test_gpu_parity import ATARI, FOOT, _act, dev, hts  # noqa: F401
+import hts_synth as syn
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("shape,A,sizes", [(ATARI, 18, (2047, 2048, 2049, 2561)), (FOOT, 19, (3071, 3072, 3075))])
+def test_rows_agree_bitwise(hts, shape, A, sizes, monkeypatch):  # noqa: F811
+    n = max(sizes)
+    params = dev(syn.init_params(41, *shape, A, bias_scale=0.05))
+    g = torch.Generator(device="cuda").manual_seed(42)
+    obs = torch.randint(0, 256, (n, *shape), device="cuda", generator=g, dtype=torch.uint8)
+    monkeypatch.setenv("HTS_SMALL_BATCH", "1000000")
+    ctx = hts.Context(*shape, A, precision=1, max_act_batch=n)
+    want = _act(ctx, obs, params, 5, 1, 0, A)
+    ctx.close()
+    monkeypatch.delenv("HTS_SMALL_BATCH")
+    ctx = hts.Context(*shape, A, precision=1, max_act_batch=n)
+    for k in sizes:
+        got = _act(ctx, obs[n - k:].contiguous(), params, 5, 1, n - k, A)
+        assert all(np.array_equal(x[n - k:], y) for x, y in zip(want, got)), k
+    ctx.close()
