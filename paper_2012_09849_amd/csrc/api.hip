@@ -88,7 +88,6 @@ void carve(Ctx &c, Carver &cv)
     cv.take(w.wfc, (size_t)512 * g.F * ts); cv.take(w.hb, (size_t)c.sh.count * 4);
     cv.take(w.act1, mb * g.P1 * 32 * ts); cv.take(w.act2, mb * g.P2 * 64 * ts); cv.take(w.a3, mb * g.F * ts);
     cv.take(w.fc_part, (size_t)c.fc_groups * mb * 512 * 4);
-    cv.take(w.clip, 2 * 4);
     cv.take(w.adv_part, (1 + 2 * NRM_BLOCKS) * 8);
     cv.take(w.norm_part, (size_t)((g.P + NORM_CHUNK - 1) / NORM_CHUNK) * 4);
     if (ml > 0) {
@@ -300,15 +299,15 @@ extern "C" int32_t hts_loss_and_grads(hts_ctx *ctx, const hts_buffer *buf, const
     const int32_t rc2 = loss_and_grads(c, buf, params, hp, grads);
     if (rc2 != HTS_OK) return rc2;
     if (stats_or_null) {
-        HIP_TRY(launch_grad_norm(c, grads, c.g.P, 0.0f, true));
+        HIP_TRY(launch_grad_norm(c, grads, c.g.P));
         HIP_TRY(launch_stats(c, buf->B, stats_or_null));
     }
     return HTS_OK;
 }
 
-// have_norm: 0 = nothing computed yet, 1 = the per-chunk sums of squares are in the workspace, 2 = the clip factor too
+// have_norm: the per-chunk sums of squares are in the workspace already
 static int32_t adam_apply(Ctx &c, float *params, const float *grads, hts_opt_state *opt, const hts_hparams *hp,
-                          long long P, int have_norm)
+                          long long P, bool have_norm)
 {
     const int64_t t = opt->step + 1;
     if (hp->optimizer != HTS_OPT_ADAM && hp->optimizer != HTS_OPT_RMSPROP) return HTS_EINVAL;
@@ -318,15 +317,15 @@ static int32_t adam_apply(Ctx &c, float *params, const float *grads, hts_opt_sta
     const float bc1 = rms ? 1.0f : (float)(1.0 - pow((double)hp->beta1, (double)t));
     const float bc2 = rms ? 1.0f : (float)(1.0 - pow((double)hp->beta2, (double)t));
     const bool clip = hp->max_grad_norm > 0.0f;
-    // the optimiser kernel forms the clip factor from the per-chunk sums itself unless it already exists
-    if (clip && have_norm == 0) { HIP_TRY(launch_grad_norm(c, grads, P, hp->max_grad_norm, false)); have_norm = 1; }
-    const float *scale = clip && have_norm == 2 ? c.ws.clip : nullptr, *parts = clip && have_norm == 1 ? c.ws.norm_part : nullptr;
+    // the optimiser kernel forms the clip factor from the per-chunk sums itself
+    if (clip && !have_norm) HIP_TRY(launch_grad_norm(c, grads, P));
+    const float *parts = clip ? c.ws.norm_part : nullptr;
     if (c.track_params && P == c.g.P) {
         // the optimiser kernel rewrites the workspace copy from the new values: it stays in step with the caller's vector
-        HIP_TRY(launch_adam_shadow(c, params, grads, opt->m, opt->v, scale, parts, hp->max_grad_norm, hp->lr, b1, b2,
+        HIP_TRY(launch_adam_shadow(c, params, grads, opt->m, opt->v, parts, hp->max_grad_norm, hp->lr, b1, b2,
                                    hp->adam_eps, bc1, bc2, c.max_learn > 0));
     } else {
-        HIP_TRY(launch_adam(c, params, grads, opt->m, opt->v, P, scale, parts, hp->max_grad_norm, hp->lr, b1, b2,
+        HIP_TRY(launch_adam(c, params, grads, opt->m, opt->v, P, parts, hp->max_grad_norm, hp->lr, b1, b2,
                             hp->adam_eps, bc1, bc2));
         c.synced = false; c.synced_learn = false;     // the caller's vector has moved on; the workspace copy has not
     }
@@ -344,11 +343,10 @@ static int32_t learner_step(hts_ctx *ctx, const hts_buffer *buf, const float *pa
     Ctx &c = ctx->c;
     const int32_t rc2 = loss_and_grads(c, buf, params_grad, hp, c.ws.grads);
     if (rc2 != HTS_OK) return rc2;
-    // statistics need the norm itself; without them the optimiser kernel finishes the clip factor
     const bool need_norm = hp->max_grad_norm > 0.0f || stats_or_null;
-    if (need_norm) HIP_TRY(launch_grad_norm(c, c.ws.grads, c.g.P, hp->max_grad_norm, stats_or_null != nullptr));
+    if (need_norm) HIP_TRY(launch_grad_norm(c, c.ws.grads, c.g.P));
     if (stats_or_null) HIP_TRY(launch_stats(c, buf->B, stats_or_null));
-    return adam_apply(c, params, c.ws.grads, opt, hp, c.g.P, need_norm ? (stats_or_null ? 2 : 1) : 0);
+    return adam_apply(c, params, c.ws.grads, opt, hp, c.g.P, need_norm);
 }
 
 extern "C" int32_t hts_learner_step(hts_ctx *ctx, const hts_buffer *buf, float *params, hts_opt_state *opt,

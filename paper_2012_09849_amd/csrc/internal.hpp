@@ -32,7 +32,7 @@ struct Workspace {
     float *h;                 // learner only: FC output [B][512], written by the heads kernel for the backward pass
     float *fc_part;           // [fc_groups][B][512] partial sums of the FC layer, one per group of FC_GROUP_K inputs
     // backward
-    float *dz, *dh, *terms, *grads, *part, *norm_part, *clip;   // clip[0] = scale, clip[1] = ||g||
+    float *dz, *dh, *terms, *grads, *part, *norm_part;
     double *adv_part;         // [1 + 2 NRM_BLOCKS] sums of the advantage normalisation
     float *heads_part;        // [HEADS_MAXZ][A+1][513] partials of the heads weight gradient (large minibatches)
     void *dy3, *dy2, *dy1;    // T
@@ -148,12 +148,12 @@ constexpr int HEADS_MAXZ = 16;      // most chunks the heads weight gradient's r
 hipError_t launch_gae(Ctx *c, hipStream_t s, const float *r, const float *v, const uint8_t *d, float gamma, float lambda, int T,
                       int N, float *adv, float *ret);
 hipError_t launch_normalize(Ctx *c, hipStream_t s, float *adv, long long n);
-hipError_t launch_grad_norm(Ctx &c, const float *g, long long P, float max_norm, bool finalize);
-hipError_t launch_adam(Ctx &c, float *theta, const float *g, float *m, float *v, long long P, const float *scale_or_null,
+hipError_t launch_grad_norm(Ctx &c, const float *g, long long P);
+hipError_t launch_adam(Ctx &c, float *theta, const float *g, float *m, float *v, long long P,
                        const float *norm_part_or_null, float max_norm, float lr, float b1, float b2, float eps, float bc1,
                        float bc2);
 // the same update of the whole network's vector, which also rewrites the workspace copy of the network from the new values
-hipError_t launch_adam_shadow(Ctx &c, float *theta, const float *g, float *m, float *v, const float *scale_or_null,
+hipError_t launch_adam_shadow(Ctx &c, float *theta, const float *g, float *m, float *v,
                               const float *norm_part_or_null, float max_norm, float lr, float b1, float b2, float eps,
                               float bc1, float bc2, bool learn);
 

@@ -543,39 +543,62 @@ hipError_t launch_heads_learn(Ctx &c, const LossArgs &la, int B)
     return launch_heads<true>(a, c.stream);
 }
 
+// Sum over a workgroup of 256 threads, in thread 0: pairs 128, 64, ... 1 apart, one barrier (the last six steps are lane shifts of the first
+// wavefront)
+__device__ __forceinline__ float block_sum_256(float x, float *red)
+{
+    const int t = threadIdx.x;
+    red[t] = x;
+    __syncthreads();
+    if (t < 64) {
+        x = (red[t] + red[t + 128]) + (red[t + 64] + red[t + 192]);
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) x += __shfl_down(x, o, 64);
+    }
+    return x;
+}
+
+// ||g|| from the per-chunk sums, added in a fixed order by one workgroup of 256 threads (every thread gets the result)
+__device__ __forceinline__ float norm_from_parts(const float *__restrict__ part, int nparts, float *red)
+{
+    const int t = threadIdx.x;
+    float s = 0.0f;
+    for (int i = t; i < nparts; i += 256) s += part[i];
+    s = block_sum_256(s, red);
+    __syncthreads();
+    if (t == 0) red[0] = s;
+    __syncthreads();
+    return sqrtf(red[0]);
+}
+
 // ------------------------------------------------------------------------------------------------------------
 // loss statistics: one workgroup, fixed strided sums then a fixed LDS tree
 // ------------------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void stats_kernel(const float *__restrict__ terms, int B, const float *clip,
+// (the norm from its per-chunk sums, as the optimiser kernel forms it: a launch for it alone took 4.7 us)
+__global__ __launch_bounds__(256) void stats_kernel(const float *__restrict__ terms, int B, const float *__restrict__ norm_part, int nparts,
                                                     hts_stats *stats)
 {
-    __shared__ float red[N_TERMS][256];
+    __shared__ float red[N_TERMS + 1][256];
     const int t = threadIdx.x;
     float s[N_TERMS];
 #pragma unroll
     for (int i = 0; i < N_TERMS; ++i) s[i] = 0.0f;
+#pragma unroll 4
     for (int b = t; b < B; b += 256)
 #pragma unroll
         for (int i = 0; i < N_TERMS; ++i) s[i] += terms[(long long)b * N_TERMS + i];
 #pragma unroll
-    for (int i = 0; i < N_TERMS; ++i) red[i][t] = s[i];
-    __syncthreads();
-    for (int w = 128; w >= 1; w >>= 1) {
-        if (t < w)
-#pragma unroll
-            for (int i = 0; i < N_TERMS; ++i) red[i][t] += red[i][t + w];
-        __syncthreads();
-    }
+    for (int i = 0; i < N_TERMS; ++i) s[i] = block_sum_256(s[i], red[i]);
+    const float gn = norm_from_parts(norm_part, nparts, red[N_TERMS]);
     if (t == 0) {
         const float invB = 1.0f / (float)B;
-        stats->policy_loss = red[0][0] * invB;
-        stats->value_loss = red[1][0] * invB;
-        stats->entropy = red[2][0] * invB;
-        stats->clip_frac = red[3][0] * invB;
-        stats->approx_kl = red[4][0] * invB;
-        const float gn = clip ? clip[1] : 0.0f;
+        stats->policy_loss = s[0] * invB;
+        stats->value_loss = s[1] * invB;
+        stats->entropy = s[2] * invB;
+        stats->clip_frac = s[3] * invB;
+        stats->approx_kl = s[4] * invB;
         stats->grad_norm = gn;
-        const float chk = red[0][0] + red[1][0] + red[2][0] + gn;
+        const float chk = s[0] + s[1] + s[2] + gn;
         stats->nonfinite = (chk - chk == 0.0f) ? 0 : 1;
     }
 }
@@ -583,7 +606,8 @@ __global__ __launch_bounds__(256) void stats_kernel(const float *__restrict__ te
 hipError_t launch_stats(Ctx &c, int B, hts_stats *stats)
 {
     SiteTimer tm(c, SITE_STATS);
-    hipLaunchKernelGGL(stats_kernel, dim3(1), dim3(256), 0, c.stream, c.ws.terms, B, c.ws.clip, stats);
+    hipLaunchKernelGGL(stats_kernel, dim3(1), dim3(256), 0, c.stream, c.ws.terms, B, c.ws.norm_part,
+                       (int)((c.g.P + NORM_CHUNK - 1) / NORM_CHUNK), stats);
     return hipGetLastError();
 }
 
@@ -825,7 +849,7 @@ hipError_t launch_gae(Ctx *c, hipStream_t s, const float *r, const float *v, con
 // advantage normalisation: double-precision sums of fixed shape.  Up to NRM_ONE entries one workgroup holds the array in
 // registers (one launch); beyond that up to NRM_BLOCKS workgroups each reduce a share and a second launch combines
 // their sums and rescales.  Kernel times by rocprofv3: 512x16 entries 6.2 us as three strided passes of one workgroup over
-// memory, 4.8 us from registers (launch, one memory round trip, two reductions across 16 wavefronts); 128x4096 entries
+// memory, 3.3 us from registers (launch, one memory round trip, two reductions across 8 wavefronts); 128x4096 entries
 // 281 us with one workgroup (2 MB through one compute unit three times), 3.3 + 3.9 us (two launches; 6 MB moved).
 // ------------------------------------------------------------------------------------------------------------
 constexpr int NRM_ONE_THREADS = 1024, NRM_ONE_VECS = 4;                       // 4-entry vectors per thread, one workgroup
@@ -955,12 +979,12 @@ hipError_t launch_normalize(Ctx *c, hipStream_t s, float *adv, long long n)
     SiteTimer tm(c ? *c : dummy, SITE_NORMALIZE);
     const bool vec = !((uintptr_t)adv & 15u);
     if (n <= NRM_ONE) {
-        // four wavefronts while they hold the array: with sixteen, the launch and the two reductions take 4.8 us at any size,
-        // with four 3.0-3.3
-        const bool few = n <= NRM_ONE / 4;
-        auto kern = few ? (vec ? normalize_one_kernel<true, NRM_ONE_THREADS / 4> : normalize_one_kernel<false, NRM_ONE_THREADS / 4>)
-                        : (vec ? normalize_one_kernel<true, NRM_ONE_THREADS> : normalize_one_kernel<false, NRM_ONE_THREADS>);
-        hipLaunchKernelGGL(kern, dim3(1), dim3(few ? NRM_ONE_THREADS / 4 : NRM_ONE_THREADS), 0, s, adv, (int)n);
+        // as few wavefronts as hold the array, four, eight or sixteen: the launch and the two reductions take 3.0, 3.3 and 4.8 us
+        const int nt = n <= NRM_ONE / 4 ? NRM_ONE_THREADS / 4 : n <= NRM_ONE / 2 ? NRM_ONE_THREADS / 2 : NRM_ONE_THREADS;
+        auto kern = nt == NRM_ONE_THREADS / 4   ? (vec ? normalize_one_kernel<true, NRM_ONE_THREADS / 4> : normalize_one_kernel<false, NRM_ONE_THREADS / 4>)
+                    : nt == NRM_ONE_THREADS / 2 ? (vec ? normalize_one_kernel<true, NRM_ONE_THREADS / 2> : normalize_one_kernel<false, NRM_ONE_THREADS / 2>)
+                                                : (vec ? normalize_one_kernel<true, NRM_ONE_THREADS> : normalize_one_kernel<false, NRM_ONE_THREADS>);
+        hipLaunchKernelGGL(kern, dim3(1), dim3(nt), 0, s, adv, (int)n);
         return hipGetLastError();
     }
     double *part = c ? c->ws.adv_part : nullptr;
@@ -974,57 +998,31 @@ hipError_t launch_normalize(Ctx *c, hipStream_t s, float *adv, long long n)
 }
 
 // ------------------------------------------------------------------------------------------------------------
-// gradient norm: per-chunk sums of squares (fixed chunking), then one workgroup combines them in index order
+// gradient norm: per-chunk sums of squares (fixed chunking), combined in index order where they are used
 // ------------------------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void sumsq_kernel(const float *__restrict__ g, long long P, float *__restrict__ part)
 {
     __shared__ float red[256];
     const int t = threadIdx.x;
     const long long base = (long long)blockIdx.x * NORM_CHUNK;
+    // all of a thread's loads at once, one memory round trip (P = 1.7 M: 5.5 -> 4.6 us)
+    float x[NORM_CHUNK / 256];
+#pragma unroll
+    for (int i = 0; i < NORM_CHUNK / 256; ++i) {
+        const long long o = base + t + 256 * i;
+        const float v = g[o < P ? o : P - 1];
+        x[i] = o < P ? v : 0.0f;
+    }
     float s = 0.0f;
-#pragma unroll 4
-    for (int i = t; i < NORM_CHUNK; i += 256) {
-        const long long o = base + i;
-        const float x = o < P ? g[o] : 0.0f;
-        s = __builtin_fmaf(x, x, s);
-    }
-    red[t] = s;
-    __syncthreads();
-    for (int w = 128; w >= 1; w >>= 1) {
-        if (t < w) red[t] += red[t + w];
-        __syncthreads();
-    }
-    if (t == 0) part[blockIdx.x] = red[0];
+#pragma unroll
+    for (int i = 0; i < NORM_CHUNK / 256; ++i) s = __builtin_fmaf(x[i], x[i], s);
+    s = block_sum_256(s, red);
+    if (t == 0) part[blockIdx.x] = s;
 }
 
-// ||g|| from the per-chunk sums, added in a fixed order by one workgroup of 256 threads (every thread gets the result)
-__device__ __forceinline__ float norm_from_parts(const float *__restrict__ part, int nparts, float *red)
-{
-    const int t = threadIdx.x;
-    float s = 0.0f;
-    for (int i = t; i < nparts; i += 256) s += part[i];
-    red[t] = s;
-    __syncthreads();
-    for (int w = 128; w >= 1; w >>= 1) {
-        if (t < w) red[t] += red[t + w];
-        __syncthreads();
-    }
-    return sqrtf(red[0]);
-}
 __device__ __forceinline__ float clip_scale(float nrm, float max_norm)
 {
     return max_norm > 0.0f ? fminf(1.0f, max_norm / (nrm + 1e-6f)) : 1.0f;
-}
-
-__global__ __launch_bounds__(256) void clip_finalize_kernel(const float *__restrict__ part, int nparts, float max_norm,
-                                                            float *__restrict__ clip)
-{
-    __shared__ float red[256];
-    const float nrm = norm_from_parts(part, nparts, red);
-    if (threadIdx.x == 0) {
-        clip[0] = clip_scale(nrm, max_norm);
-        clip[1] = nrm;
-    }
 }
 
 static void enqueue_sumsq(hipStream_t stream, const float *g, long long P, float *norm_part)
@@ -1033,16 +1031,12 @@ static void enqueue_sumsq(hipStream_t stream, const float *g, long long P, float
     hipLaunchKernelGGL(sumsq_kernel, dim3(nparts), dim3(256), 0, stream, g, P, norm_part);
 }
 
-// finalize = false leaves the per-chunk sums in the workspace for the optimiser kernel, which then forms the norm and the
-// clip factor itself (the same additions in the same order, in every workgroup): one launch less per update
-hipError_t launch_grad_norm(Ctx &c, const float *g, long long P, float max_norm, bool finalize)
+// the statistics and the optimiser kernel form the norm and the clip factor from these sums themselves (the same additions in the same
+// order, in every workgroup)
+hipError_t launch_grad_norm(Ctx &c, const float *g, long long P)
 {
     SiteTimer tm(c, SITE_GRAD_NORM);
-    const int nparts = (int)((P + NORM_CHUNK - 1) / NORM_CHUNK);
     enqueue_sumsq(c.stream, g, P, c.ws.norm_part);
-    if (finalize)
-        hipLaunchKernelGGL(clip_finalize_kernel, dim3(1), dim3(256), 0, c.stream, c.ws.norm_part, nparts, max_norm,
-                           c.ws.clip);
     return hipGetLastError();
 }
 
@@ -1061,15 +1055,14 @@ __device__ __forceinline__ void adam_one(float &th, float g, float &m, float &v,
 template <bool VEC4>
 __global__ __launch_bounds__(256) void adam_kernel(float *__restrict__ theta, const float *__restrict__ g,
                                                    float *__restrict__ m, float *__restrict__ v, long long P,
-                                                   const float *__restrict__ scale, const float *__restrict__ norm_part,
+                                                   const float *__restrict__ norm_part,
                                                    int nparts, float max_norm, float lr, float b1, float b2,
                                                    float eps, float ibc1, float ibc2)
 {
-    // the clip factor: given (scale), or formed here from the per-chunk sums of squares (norm_part), or none
+    // the clip factor, formed here from the per-chunk sums of squares, or none
     __shared__ float red[256];
     float gs = 1.0f;
     if (norm_part) gs = clip_scale(norm_from_parts(norm_part, nparts, red), max_norm);
-    else if (scale) gs = scale[0];
     const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
     if constexpr (VEC4) {
         const long long o = i * 4;
@@ -1107,7 +1100,7 @@ struct AdamShadowArgs {
     float *theta;
     const float *g;
     float *m, *v;
-    const float *scale, *norm_part;
+    const float *norm_part;
     int nparts;
     float max_norm, lr, b1, b2, eps, ibc1, ibc2;
 };
@@ -1117,8 +1110,9 @@ template <typename T> __global__ __launch_bounds__(256) void adam_shadow_kernel(
     __shared__ float tile[64][65];
     __shared__ float red[256];
     float gs = 1.0f;
-    if (a.norm_part) gs = clip_scale(norm_from_parts(a.norm_part, a.nparts, red), a.max_norm);
-    else if (a.scale) gs = a.scale[0];
+    auto find_scale = [&]() {
+        if (a.norm_part) gs = clip_scale(norm_from_parts(a.norm_part, a.nparts, red), a.max_norm);
+    };
     float *__restrict__ theta = a.theta;
     const float *__restrict__ g = a.g;
     float *__restrict__ m = a.m, *__restrict__ v = a.v;
@@ -1148,6 +1142,7 @@ template <typename T> __global__ __launch_bounds__(256) void adam_shadow_kernel(
                 th[i] = *reinterpret_cast<const f32x4 *>(theta + idx); gg[i] = *reinterpret_cast<const f32x4 *>(g + idx);
                 mm[i] = *reinterpret_cast<const f32x4 *>(m + idx); vv[i] = *reinterpret_cast<const f32x4 *>(v + idx);
             }
+            find_scale();                    // while they travel
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int r = rr + 16 * i;
@@ -1167,6 +1162,7 @@ template <typename T> __global__ __launch_bounds__(256) void adam_shadow_kernel(
                 *reinterpret_cast<Vec<T, 4> *>(wfc + o) = w4;
             }
         } else {
+            find_scale();
             float th[16], gg[16], mm[16], vv[16];
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
@@ -1196,6 +1192,7 @@ template <typename T> __global__ __launch_bounds__(256) void adam_shadow_kernel(
         return;
     }
     blk -= p.nb_fc;
+    find_scale();
     if (blk < p.nb_conv) {
         const int i = blk * 256 + t;
         T *wf2 = (T *)p.wf2, *wf3 = (T *)p.wf3, *wd2 = (T *)p.wd2, *wd3 = (T *)p.wd3;
@@ -1238,7 +1235,7 @@ template <typename T> __global__ __launch_bounds__(256) void adam_shadow_kernel(
 }
 
 static void enqueue_adam(hipStream_t stream, float *theta, const float *g, float *m, float *v, long long P,
-                         const float *scale, const float *norm_part, float max_norm, float lr, float b1, float b2,
+                         const float *norm_part, float max_norm, float lr, float b1, float b2,
                          float eps, float bc1, float bc2)
 {
     const int nparts = (int)((P + NORM_CHUNK - 1) / NORM_CHUNK);
@@ -1247,29 +1244,29 @@ static void enqueue_adam(hipStream_t stream, float *theta, const float *g, float
     if (aligned) {
         const long long nthreads = (P + 3) / 4;
         hipLaunchKernelGGL(adam_kernel<true>, dim3((unsigned)((nthreads + 255) / 256)), dim3(256), 0, stream, theta, g,
-                           m, v, P, scale, norm_part, nparts, max_norm, lr, b1, b2, eps, ibc1, ibc2);
+                           m, v, P, norm_part, nparts, max_norm, lr, b1, b2, eps, ibc1, ibc2);
     } else {
         hipLaunchKernelGGL(adam_kernel<false>, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, stream, theta, g, m, v,
-                           P, scale, norm_part, nparts, max_norm, lr, b1, b2, eps, ibc1, ibc2);
+                           P, norm_part, nparts, max_norm, lr, b1, b2, eps, ibc1, ibc2);
     }
 }
 
-hipError_t launch_adam(Ctx &c, float *theta, const float *g, float *m, float *v, long long P, const float *scale,
+hipError_t launch_adam(Ctx &c, float *theta, const float *g, float *m, float *v, long long P,
                        const float *norm_part, float max_norm, float lr, float b1, float b2, float eps, float bc1, float bc2)
 {
     SiteTimer tm(c, SITE_ADAM);
-    enqueue_adam(c.stream, theta, g, m, v, P, scale, norm_part, max_norm, lr, b1, b2, eps, bc1, bc2);
+    enqueue_adam(c.stream, theta, g, m, v, P, norm_part, max_norm, lr, b1, b2, eps, bc1, bc2);
     return hipGetLastError();
 }
 
-hipError_t launch_adam_shadow(Ctx &c, float *theta, const float *g, float *m, float *v, const float *scale,
+hipError_t launch_adam_shadow(Ctx &c, float *theta, const float *g, float *m, float *v,
                               const float *norm_part, float max_norm, float lr, float b1, float b2, float eps, float bc1,
                               float bc2, bool learn)
 {
     SiteTimer tm(c, SITE_ADAM);
     AdamShadowArgs a;
     a.pa = prep_args(c, nullptr, learn);
-    a.theta = theta; a.g = g; a.m = m; a.v = v; a.scale = scale; a.norm_part = norm_part;
+    a.theta = theta; a.g = g; a.m = m; a.v = v; a.norm_part = norm_part;
     a.nparts = (int)((c.g.P + NORM_CHUNK - 1) / NORM_CHUNK);
     a.max_norm = max_norm; a.lr = lr; a.b1 = b1; a.b2 = b2; a.eps = eps; a.ibc1 = 1.0f / bc1; a.ibc2 = 1.0f / bc2;
     const int nb = a.pa.nb_fc + a.pa.nb_conv + a.pa.nb_w1 + a.pa.nb_hb;
@@ -1339,7 +1336,7 @@ extern "C" int32_t hts_adam_apply_static(float *params, const float *grads, hts_
     const bool clip = hp->max_grad_norm > 0.0f;
     // every partial sum the optimiser kernel reads is written by the pass before it: nothing has to start at zero
     if (clip) enqueue_sumsq(stream, grads, P, part);
-    enqueue_adam(stream, params, grads, opt->m, opt->v, P, nullptr, clip ? part : nullptr, hp->max_grad_norm, hp->lr, b1,
+    enqueue_adam(stream, params, grads, opt->m, opt->v, P, clip ? part : nullptr, hp->max_grad_norm, hp->lr, b1,
                  b2, hp->adam_eps, bc1, bc2);
     e = hipGetLastError();
     if (e != hipSuccess) { note_hip_error(e); return HTS_EHIP; }
