@@ -634,11 +634,11 @@ template <typename T> static hipError_t backward_t(Ctx &c, const uint8_t *obs, c
     };
     // ---- launches.  binary32's weight gradients share one launch behind the input gradients: each of them alone has one or two
     // wavefronts per SIMD (400 to 576 workgroups of tiles at 1024 rows of 84x84 frames; 282 us one after the other, 215 together, 183 with their
-    // operands in registers; 51 and 32 at 80 rows).  bfloat16's go out each right behind the input gradient whose output they read, while the caches still hold
+    // operands in registers; 51 and 32 at 80 rows).  bfloat16's conv layers go out each right behind the input gradient whose output they read, while the caches still hold
     // it (on the tile kernel, together 115 us against 90 at 2048 rows of 72x96 frames). ----
     if constexpr (sizeof(T) == 2) {
-        { SiteTimer tm(c, SITE_HEADS_WGRAD); e = launch_wsgemm<HeadsWgrad, 16, 32, false>(ph, c.stream, spgh); }      // 16 wavefronts share each tile
-        if (e == hipSuccess) { SiteTimer tm(c, SITE_FC_WGRAD); e = launch_wgrad_dma<1, 3, 2>(DmaFcWgrad(pf), c.stream); }
+        SiteTimer tm(c, SITE_FC_WGRAD);
+        e = launch_group(c.stream, SegmentJob<HeadsWgrad, 32>(ph, spgh), DmaJob<DmaFcWgrad, 1, 3>(DmaFcWgrad(pf)));
         if (e != hipSuccess) return e;
     }
     {   // d(conv3 pre-activation)

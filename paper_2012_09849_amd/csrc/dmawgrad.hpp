@@ -36,18 +36,16 @@ __device__ __forceinline__ void copy16(const rsrc_words &src, uint32_t lane_off,
 }
 
 // WN: wavefronts along the columns, two of them along the rows.  Conv2's eight halves go in pairs, with eight wavefronts; conv3's nine and
-// FC's few one by one, for more workgroups.
+// FC's few one by one, for more workgroups.  block: index in the grid; tile: wgrad_dma_lds bytes of LDS.
 // W offers: A_PITCH, bytes between its rows of dy; `From from(kbeg, kend, rt)`, the chunk's buffers; halves(), how many 64-column halves
 // there are; outer(HALVES) and inner(HALVES): sets of workgroups, each of them on one XCD, and workgroups of a set, with
 // place(outer, inner, &rt, &ct, &z); b_row(k, kend, From) and b_half(half), byte offsets of a position's row and of a half's columns;
 // store(n, col, value, z), store_bias(n, value, z).
-template <class W, int HALVES, int STAGES, int WN>
-__global__ __launch_bounds__(128 * WN, 2) void wgrad_dma_kernel(const W p)
+template <class W, int HALVES, int STAGES, int WN> __device__ __forceinline__ void wgrad_dma_tile(const W &p, const int block, unsigned char *tile)
 {
     constexpr int TN = 2 * HALVES / WN, ROWS = 32 / WN, STAGE = (1 + HALVES) * DW_TILE, PER = ROWS / 8 * (1 + HALVES);      // columns of 32 a wavefront; copies a k-tile
-    __shared__ __attribute__((aligned(1024))) unsigned char tile[STAGES * STAGE];
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wm = w & 1, wn = w >> 1;
-    const int per = p.inner(HALVES), slot = (int)blockIdx.x >> 3, outer = (slot / per) * 8 + ((int)blockIdx.x & 7), inner = slot - (slot / per) * per;
+    const int per = p.inner(HALVES), slot = block >> 3, outer = (slot / per) * 8 + (block & 7), inner = slot - (slot / per) * per;
     if (outer >= p.outer(HALVES)) return;
     int rt, ct, z;
     p.place(outer, inner, rt, ct, z);
@@ -133,6 +131,13 @@ __global__ __launch_bounds__(128 * WN, 2) void wgrad_dma_kernel(const W p)
     }
 }
 
+template <int HALVES, int STAGES> constexpr size_t wgrad_dma_lds() { return (size_t)STAGES * (1 + HALVES) * DW_TILE; }
+template <class W, int HALVES, int STAGES, int WN> __global__ __launch_bounds__(128 * WN, 2) void wgrad_dma_kernel(const W p)
+{
+    __shared__ __attribute__((aligned(1024))) unsigned char tile[wgrad_dma_lds<HALVES, STAGES>()];
+    wgrad_dma_tile<W, HALVES, STAGES, WN>(p, (int)blockIdx.x, tile);
+}
+
 template <class L> struct DmaConvWgrad {
     static constexpr int A_PITCH = DW_ROW;
     struct From { rsrc_words a, b; int b0; };
@@ -185,9 +190,10 @@ struct DmaFcWgrad {
     __device__ __forceinline__ void store_bias(int j, float v, int) const { w.g[w.fcb + j] = v; }
 };
 
+template <int HALVES, class W> inline int wgrad_dma_blocks(const W &p) { return 8 * ((p.outer(HALVES) + 7) / 8) * p.inner(HALVES); }
 template <int HALVES, int STAGES, int WN, class W> inline hipError_t launch_wgrad_dma(const W &p, hipStream_t stream)
 {
-    const int blocks = 8 * ((p.outer(HALVES) + 7) / 8) * p.inner(HALVES);
+    const int blocks = wgrad_dma_blocks<HALVES>(p);
     hipLaunchKernelGGL((wgrad_dma_kernel<W, HALVES, STAGES, WN>), dim3(blocks), dim3(128 * WN), 0, stream, p);
     return hipGetLastError();
 }

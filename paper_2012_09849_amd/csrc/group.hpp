@@ -1,6 +1,7 @@
 // Several independent contractions in one launch: a job is a problem with one of the tile bodies of gemm.hpp / wsgemm.hpp, and a
 // workgroup finds its job by its index.  Each job keeps the grid, the tile order and the bits that it has in a launch of its own.
 #pragma once
+#include "dmawgrad.hpp"
 #include "regwgrad.hpp"
 #include "wsgemm.hpp"
 
@@ -83,6 +84,18 @@ template <class W, bool BIAS = false> struct RegJob {
     }
 };
 
+// bfloat16 weight gradient on LDS copies.  FC's shares a launch with the heads', whose 17 to 68 workgroups leave the chip idle: one
+// after the other 16.2 us at 1024 rows of 84x84 frames, 24.4 at 2048 of 72x96, 10.1 at 128 of 84x84; together 13.0, 19.2 and 6.0.
+// (WIDE: 13.4 and 20.1 with the accumulators in accumulation registers.)
+template <class W, int HALVES, int STAGES> struct DmaJob {
+    W p;
+    struct { int blocks, total; } grid;
+    static constexpr size_t LDS = wgrad_dma_lds<HALVES, STAGES>();
+    static constexpr bool WIDE = true;
+    explicit DmaJob(const W &q) : p(q) { grid.blocks = grid.total = wgrad_dma_blocks<HALVES>(q); }
+    __device__ __forceinline__ void run(int i, unsigned char *smem) const { wgrad_dma_tile<W, HALVES, STAGES, GROUP_THREADS / 128>(p, i, smem); }
+};
+
 template <class... J> struct Jobs;
 template <> struct Jobs<> {
     static constexpr size_t LDS = 0;
@@ -104,16 +117,16 @@ template <class H, class... R> struct Jobs<H, R...> {
     }
 };
 
-// (for the register-operand jobs four wavefronts per SIMD at most: without the bound the compiler keeps their blocks in accumulation
-// registers and moves them to and fro.  Fewer, by asking for LDS: 183 us with four, 195 with two, 230 with one)
+// (for the jobs that say WIDE four wavefronts per SIMD at most: without the bound the compiler keeps their blocks in accumulation
+// registers and moves them to and fro.  Register-operand weight gradients, fewer, by asking for LDS: 183 us with four, 195 with two, 230 with one)
 template <class G> __global__ __launch_bounds__(GROUP_THREADS) __attribute__((amdgpu_waves_per_eu(2, 4))) void group_wide_kernel(const G g)
 {
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     g.run((int)blockIdx.x, smem);
 }
 template <class G> __global__ __launch_bounds__(GROUP_THREADS) void group_kernel(const G g)
 {
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     g.run((int)blockIdx.x, smem);
 }
 
