@@ -13,7 +13,7 @@
 // Operand tiles go global -> registers -> LDS ([row][k], padded) -> MFMA; the global loads of tile i+1 are in
 // flight while tile i is multiplied.  Gathers are separable: the part of an address that depends on the tile row
 // (batch / y / x decomposition, done with multiply-shift division) is computed once per thread before the K loop
-// (ctx_a / ctx_b); the part that depends on k is cheap.  blockIdx.y selects a contiguous K range of length p.klen
+// (ctx_a / ctx_b); the part that depends on k is cheap.  a workgroup takes one contiguous K range of length p.klen
 // (split-K); the problem's store() receives that index so partial sums go to distinct slots and are later combined
 // in a fixed order (no atomics anywhere).
 #pragma once
