@@ -39,7 +39,8 @@ __device__ __forceinline__ void copy16(const rsrc_words &src, uint32_t lane_off,
 // FC's few one by one, for more workgroups.  block: index in the grid; tile: wgrad_dma_lds bytes of LDS.
 // W offers: A_PITCH, bytes between its rows of dy; `From from(kbeg, kend, rt)`, the chunk's buffers; halves(), how many 64-column halves
 // there are; outer(HALVES) and inner(HALVES): sets of workgroups, each of them on one XCD, and workgroups of a set, with
-// place(outer, inner, &rt, &ct, &z); b_row(k, kend, From) and b_half(half), byte offsets of a position's row and of a half's columns;
+// place(outer, inner, &rt, &ct, &z); b_source(k0, From), the buffer of the k-tile from k0 on, b_row(k0, r, kend, From) and b_half(half),
+// byte offsets of its row r and of a half's columns in it;
 // store(n, col, value, z), store_bias(n, value, z).
 template <class W, int HALVES, int STAGES, int WN> __device__ __forceinline__ void wgrad_dma_tile(const W &p, const int block, unsigned char *tile)
 {
@@ -62,13 +63,14 @@ template <class W, int HALVES, int STAGES, int WN> __device__ __forceinline__ vo
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)tile;
     auto fetch = [&](int t, int s) {
         const uint32_t dst = lds0 + (uint32_t)(s * STAGE + ROWS * w * DW_ROW);
+        const rsrc_words b = p.b_source(kbeg + t * 64, from);
 #pragma unroll
         for (int i = 0; i < ROWS / 8; ++i) {
             const int r = ROWS * w + 8 * i + lr;
             copy16(from.a, (uint32_t)(r * W::A_PITCH) + src16, (uint32_t)(t * 64 * W::A_PITCH), dst + 8 * i * DW_ROW);
-            const uint32_t row = p.b_row(kbeg + t * 64 + r, kend, from) + src16;
+            const uint32_t row = p.b_row(kbeg + t * 64, r, kend, from) + src16;
 #pragma unroll
-            for (int h = 0; h < HALVES; ++h) copy16(from.b, row, half_off[h], dst + (1 + h) * DW_TILE + 8 * i * DW_ROW);
+            for (int h = 0; h < HALVES; ++h) copy16(b, row, half_off[h], dst + (1 + h) * DW_TILE + 8 * i * DW_ROW);
         }
     };
     // transposing reads: lane 4j + q of a 16-lane group points at four columns of reduction row j and receives the four rows of its column
@@ -154,9 +156,10 @@ template <class L> struct DmaConvWgrad {
         const int b0 = w.dPo.div(kbeg);
         return {copy_source(w.dy + (long long)kbeg * 64, (uint32_t)(kend - kbeg) * DW_ROW), copy_source(w.in + (long long)b0 * w.Hin * w.Win * L::CIN, 0x80000000u), b0};
     }
-    __device__ __forceinline__ uint32_t b_row(int k, int kend, const From &f) const
+    __device__ __forceinline__ rsrc_words b_source(int, const From &f) const { return f.b; }
+    __device__ __forceinline__ uint32_t b_row(int k0, int r, int kend, const From &f) const
     {
-        const int m = min(k, kend - 1), b = w.dPo.div(m), pos = m - b * w.Po, oy = w.dWo.div(pos), ox = pos - oy * w.Wo;
+        const int k = k0 + r, m = min(k, kend - 1), b = w.dPo.div(m), pos = m - b * w.Po, oy = w.dWo.div(pos), ox = pos - oy * w.Wo;
         return k < kend ? 2u * (((uint32_t)(b - f.b0) * w.Hin + oy * L::STRIDE) * w.Win + ox * L::STRIDE) * L::CIN : 0x80000000u;
     }
     __device__ __forceinline__ uint32_t b_half(int h) const
@@ -171,7 +174,7 @@ template <class L> struct DmaConvWgrad {
 
 struct DmaFcWgrad {
     static constexpr int A_PITCH = 1024;
-    struct From { rsrc_words a, b; };
+    struct From { rsrc_words a; };
     FcWgrad<bf16_t> w;
     int K, klen;
     explicit DmaFcWgrad(const FcWgrad<bf16_t> &p) : w(p), K(p.K), klen(p.K) {}
@@ -179,12 +182,14 @@ struct DmaFcWgrad {
     HTS_HD int inner(int) const { return 8; }
     HTS_HD int halves() const { return w.F / 64; }
     __device__ __forceinline__ void place(int outer, int inner, int &rt, int &ct, int &z) const { rt = inner; ct = outer; z = 0; }
-    // (both buffers end with the last sample; fewer than 2^31 activations at the largest minibatch)
-    __device__ __forceinline__ From from(int, int, int rt) const
+    // (both buffers end with the last sample.  The activations can be more than 4 GB, 43008 rows of 256x256 frames, say: a buffer for
+    // every k-tile, of at most 2 GB, as a frame of at most 2^24 values leaves at most as many features)
+    __device__ __forceinline__ From from(int, int, int rt) const { return {copy_source(w.dh + rt * 64, (uint32_t)K * A_PITCH - (uint32_t)rt * DW_ROW)}; }
+    __device__ __forceinline__ rsrc_words b_source(int k0, const From &) const
     {
-        return {copy_source(w.dh + rt * 64, (uint32_t)K * A_PITCH - (uint32_t)rt * DW_ROW), copy_source(w.a3, (uint32_t)K * (uint32_t)w.F * 2u)};
+        return copy_source(w.a3 + (long long)k0 * w.F, (uint32_t)min(K - k0, 64) * (uint32_t)w.F * 2u);
     }
-    __device__ __forceinline__ uint32_t b_row(int k, int, const From &) const { return (uint32_t)k * (uint32_t)w.F * 2u; }
+    __device__ __forceinline__ uint32_t b_row(int, int r, int, const From &) const { return (uint32_t)r * (uint32_t)w.F * 2u; }
     __device__ __forceinline__ uint32_t b_half(int h) const { return (uint32_t)h * DW_ROW; }
     __device__ __forceinline__ void store(int j, int f, float v, int) const { w.g[w.fcw + (long long)j * w.F + f] = v; }
     __device__ __forceinline__ void store_bias(int j, float v, int) const { w.g[w.fcb + j] = v; }
