@@ -22,17 +22,22 @@ constexpr int DW_ROW = 128, DW_TILE = 64 * DW_ROW;       // bytes of a row of 64
 
 // A buffer as the instruction takes it, and the copy itself: written out, because the compiler makes every transposing LDS read wait
 // for all copies under way (it cannot tell their tiles apart), which leaves nothing of the stages.  The copy has no result; the kernel
-// waits for it before the barrier that hands the tile over.  (m0: the LDS address, one wait state ahead.)
+// waits for it before the barrier that hands the tile over.  The compiler keeps no distances to what is inside: m0, the LDS address, is
+// written one wait state ahead; a buffer's words, which lane reads write, have their five wait states where they are made; the offsets come
+// from scalar instructions, which need none.  (Five wait states in every copy: conv2's weight gradient 21.1 -> 21.7 us at 2048 rows of
+// 72x96 frames.  A value brought back from a spill by a lane read would need them; tests/test_copy_wait_states.py finds one in the built library.)
 typedef __attribute__((ext_vector_type(4))) int rsrc_words;
 __device__ __forceinline__ rsrc_words copy_source(const void *p, uint32_t bytes)
 {
     const unsigned long long a = (unsigned long long)p;
-    return {__builtin_amdgcn_readfirstlane((int)a), __builtin_amdgcn_readfirstlane((int)(a >> 32) & 0xffff), __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000};
+    rsrc_words r = {__builtin_amdgcn_readfirstlane((int)a), __builtin_amdgcn_readfirstlane((int)(a >> 32) & 0xffff), __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000};
+    asm volatile("s_nop 4" : "+s"(r));
+    return r;
 }
 __device__ __forceinline__ void copy16(const rsrc_words &src, uint32_t lane_off, uint32_t wave_off, uint32_t lds)
 {
     asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
-                 :: "v"(lane_off), "s"(src), "s"(wave_off), "s"(lds) : "memory");
+                 :: "v"(lane_off), "s"(src), "s"(wave_off), "s"(lds) : "memory", "m0");
 }
 
 // WN: wavefronts along the columns, two of them along the rows.  Conv2's eight halves go in pairs, with eight wavefronts; conv3's nine and

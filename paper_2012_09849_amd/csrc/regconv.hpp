@@ -104,7 +104,7 @@ template <class C> __global__ __launch_bounds__(512) __attribute__((amdgpu_waves
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         fetch(grp + 2 * step, s == 0 ? 2 : s - 1);
-        const rsrc_words to = copy_source(a.out + (long long)grp * C::ROWS * 64, (uint32_t)(min(C::G, a.B - grp * C::G) * C::POUT * 128));
+        const __amdgpu_buffer_rsrc_t to = dma_source(a.out + (long long)grp * C::ROWS * 64, (uint32_t)(min(C::G, a.B - grp * C::G) * C::POUT * 128));
         for (int t = w >> 1; t < C::TILES; t += 4) {
             const int idx = t * 32 + lrow, ic = min(idx, C::ROWS - 1), g = ic / C::POUT, p = ic - g * C::POUT, oy = p / C::WO, ox = p - oy * C::WO;
             // A window's pixel (u, v) lies at a constant distance, and its swizzle differs from that of (u % 2, v / 2) by a constant: four
@@ -159,7 +159,7 @@ template <class C> __global__ __launch_bounds__(512) __attribute__((amdgpu_waves
                 got.x = __shfl_xor(send.x, 32, 64);
                 got.y = __shfl_xor(send.y, 32, 64);
                 const u32x4 v = kg ? u32x4{got.x, got.y, mine.x, mine.y} : u32x4{mine.x, mine.y, got.x, got.y};
-                asm volatile("buffer_store_dwordx4 %0, %1, %2, 0 offen" :: "v"(v), "v"(o + 16 * h), "s"(to) : "memory");
+                __builtin_amdgcn_raw_buffer_store_b128(v, to, (int)(o + 16 * h), 0, 0);
             }
         }
         s = s + 1 == C::STAGES ? 0 : s + 1;
