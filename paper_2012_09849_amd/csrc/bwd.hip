@@ -560,6 +560,31 @@ static hipError_t launch_fc_dgrad(const FcDgrad<bf16_t> &p, hipStream_t s)
     return launch_dma(DmaTiles<P, 64, 128, 2, 2, 2>(p), s);
 }
 
+// The tile kernel's input gradients in sample order or, with the taps that a position lacks left out, by position.  us, sample / position:
+// conv3, where a launch of no more tiles than compute units takes as long as a tile with all nine taps and leaving out pays beyond, or where the
+//   output is so small that no position has nine.  binary32 84x84 frames 200 rows (253 tiles) 21.6 / 21.7, 224 (284) 28.8 / 22.4, 1024 69.1 /
+//   43.4; 72x96 224 (245) 21.8 / 22.6, 256 28.7 / 20.3; 104x104 160 (303) 28.9 / 21.8; 128x128 129 (395) 29.5 / 30.0, 192 39.8 / 31.8; 64x64 256
+//   (144) 21.6 / 19.7; 44x52 (output 2x3) 129 20.6 / 15.5.  bf16 80x80 129 9.2 / 10.0, 200 9.7 / 10.2, 256 9.6 / 9.5, 500 10.6 / 12.1, 1000 15.4 / 13.9;
+//   96x96 200 (313) 11.9 / 10.7, 1024 23.2 / 17.9; 128x128 129 11.1 / 12.6, 256 14.9 / 13.1; 44x52 129 9.9 / 7.7.
+// conv2, binary32, at any batch: 84x84 200 rows 23.9 / 23.8, 256 27.4 / 24.0, 320 29.0 / 29.6, 512 44.0 / 40.2, 1000 77.8 / 70.7; 72x96 200 23.3 / 23.4,
+//   224 23.8 / 21.7, 1000 75.5 / 63.5; 128x128 129 30.0 / 29.6, 192 43.8 / 39.0, 512 92.0 / 85.8.  bf16, by the size of the input: up to 27x27 gains of up
+//   to 19 % at any batch (64x64 frames 129 rows 7.3 / 6.8, 1900 29.4 / 24.3; 96x96 200 12.4 / 12.8, 1536 51.4 / 48.1; 112x112 256 16.8 / 16.3, 768 37.4 /
+//   37.9, 1024 48.4 / 44.5), 31x31 19.8 / 19.7 at 256, 32.6 / 41.7 at 500, 62.5 / 61.7 at 1024, 129 / 133 at 2048: a position's 64-byte rows lie a
+//   sample apart.
+template <typename T> static bool by_position(const ConvDgrad<T, Layer3> &p)
+{
+    const int tiles = (p.max_m() + p.BM - 1) / p.BM;
+    return p.Ho < 3 || p.Wo < 3 || p.Bn >= 256 || (tiles > 256 && (sizeof(T) == 4 || p.Bn >= 192));
+}
+static bool by_position(const ConvDgrad<float, Layer2> &) { return true; }
+static bool by_position(const ConvDgrad<bf16_t, Layer2> &p) { return p.Hin * p.Win <= 27 * 27; }
+template <typename T, class L> static hipError_t launch_conv_dgrad(const ConvDgrad<T, L> &p, hipStream_t s)
+{
+    typedef ConvDgradByPosition<T, L> ByPosition;
+    if (ByPosition::fits(p) && by_position(p)) return launch_gemm(ByPosition(p), s);
+    return launch_gemm(p, s);
+}
+
 template <typename T> static hipError_t backward_t(Ctx &c, const uint8_t *obs, const int32_t *index, int B, float *grads)
 {
     const Geom &g = c.g;
@@ -678,7 +703,7 @@ template <typename T> static hipError_t backward_t(Ctx &c, const uint8_t *obs, c
             // weight column touches 32 cache lines per load instruction, and with sixteen wavefronts on a compute unit
             // the L1's address processing was the whole issue phase (24.2 -> 19.3 us at 80 rows).  bfloat16 rows are
             // half as long and the direct form stays faster there (11.6 vs 17.2 us).
-            e = small ? launch_wsgemm<ConvDgrad<T, Layer3>, (sizeof(T) == 4 ? 8 : 4), (sizeof(T) == 2 ? 192 : 72), false, (sizeof(T) == 2)>(p, c.stream) : launch_gemm(ConvDgradByPosition<T, Layer3>(p), c.stream);
+            e = small ? launch_wsgemm<ConvDgrad<T, Layer3>, (sizeof(T) == 4 ? 8 : 4), (sizeof(T) == 2 ? 192 : 72), false, (sizeof(T) == 2)>(p, c.stream) : launch_conv_dgrad(p, c.stream);
         }
         if (e != hipSuccess) return e;
     }
@@ -705,7 +730,7 @@ template <typename T> static hipError_t backward_t(Ctx &c, const uint8_t *obs, c
                 a.out = (bf16_t *)c.ws.dy1; a.B = B;
                 e = launch_imgconv<ImgDgrad<32, 4, 2, 17, 23, 4>>(a, c.stream);
             } else
-            e = small ? launch_wsgemm<ConvDgrad<T, Layer2>, 4, 64, false>(p, c.stream) : launch_gemm(ConvDgradByPosition<T, Layer2>(p), c.stream);
+            e = small ? launch_wsgemm<ConvDgrad<T, Layer2>, 4, 64, false>(p, c.stream) : launch_conv_dgrad(p, c.stream);
         }
         if (e != hipSuccess) return e;
     }

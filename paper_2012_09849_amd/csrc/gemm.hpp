@@ -222,9 +222,12 @@ template <class P> HTS_HD auto tile_load_b(const P &p, const typename P::CtxB &c
 // Optional batching: a problem with `int batches() const`, `int max_m() const`, `int batch_m(int z) const` is
 // launched with gridDim.z = batches(); batch z has batch_m(z) rows and its own gathers: ctx_a(row, z),
 // ctx_b(col, z) and store(m, n, acc, split, z) receive the batch index (the problem object stays read-only).
-// Optional taps: a batched problem (without SEG) with `uint32_t live_taps(int m0, int batch) const` has bit t set where the k in
-// [t TAP_K, (t+1) TAP_K) (a whole number of k-tiles) may differ from zero for the tile of rows from m0 on; the others are left
-// out: a zero product changes no sum.
+// Optional tiles: a batched problem (one column of tiles, one reduction chunk) with `struct Tile` and `bool tile(int i, int batch, Tile &) const`
+// numbers its rows tile by tile; Tile is the problem of the (at most BM) rows of one.
+template <class P, class = void> struct HasTile : std::false_type {};
+template <class P> struct HasTile<P, std::void_t<typename P::Tile>> : std::true_type {};
+// Optional taps: such a Tile (without SEG) with `uint32_t live_taps() const` has bit t set where the k in [t TAP_K, (t+1) TAP_K) (a whole
+// number of k-tiles) may differ from zero; the others are left out: a zero product changes no sum.
 template <class P, class = void> struct HasTaps : std::false_type {};
 template <class P> struct HasTaps<P, std::void_t<decltype(&P::live_taps)>> : std::true_type {};
 
@@ -633,7 +636,8 @@ __device__ __forceinline__ void gemm_tile(const P &p, const WgAt at, typename P:
     int first = kbeg;
     if constexpr (HasTaps<P>::value) {
         static_assert(D == 1 && SEG == 0 && P::TAP_K % BK == 0, "taps");
-        live = p.live_taps(m0, zb);
+        live = p.live_taps();
+        __builtin_amdgcn_sched_barrier(0);       // (or the compiler mixes this with the row contexts and takes registers that cost a wavefront per SIMD)
         first = live ? __builtin_ctz(live) * P::TAP_K : 0;
     }
     // (unconditional: a stage beyond the end of a short reduction range fetches the range's last k-tile once more and
@@ -753,7 +757,10 @@ template <class P>
 __global__ __launch_bounds__(P::WAVES_M * P::WAVES_N * 64) void gemm_kernel(const P p)
 {
     __shared__ __attribute__((aligned(16))) typename P::T As[TileLds<P>::A_ELEMS], Bs[TileLds<P>::B_ELEMS];
-    gemm_tile(p, launch_at(), As, Bs);
+    if constexpr (HasTile<P>::value) {
+        typename P::Tile t(p);
+        if (p.tile((int)blockIdx.x, (int)blockIdx.z, t)) gemm_tile(t, WgAt{0, 0, (int)blockIdx.z, 1, 1}, As, Bs);
+    } else gemm_tile(p, launch_at(), As, Bs);
 }
 
 template <class P> inline dim3 gemm_grid(const P &p)

@@ -477,41 +477,72 @@ template <typename T_, class L> struct ConvDgrad {
 
 // The same with the rows in another order, all samples of one input position after another, for the tile kernel: the taps that reach
 // a tile's one or two positions are known, and the others -- structural zeros; 41 % of conv3's products on a 9x9 input, 19 % of
-// conv2's on 20x20 -- are left out.  An XCD's tiles are the same samples throughout.
+// conv2's on 20x20 -- are left out.  The samples are cut into 8, 4, 2 or 1 runs of at least BM, whose tiles take turns, so that an XCD
+// keeps to one run and finds its operands in its L2 from position to position.
 template <typename T_, class L> struct ConvDgradByPosition : ConvDgrad<T_, L> {
     typedef ConvDgrad<T_, L> P;
-    static constexpr int TAP_K = L::COUT;
-    FastDiv dB;
-    explicit ConvDgradByPosition(const P &p) : P(p), dB(FastDiv::make(p.Bn)) {}
-    HTS_HD typename P::CtxA ctx_a(int m, int z) const
+    int lg, q, r;                  // 2^lg runs, the first r of q + 1 samples, the others of q
+    FastDiv dq, dq1;
+    static bool fits(const P &p) { return p.Bn >= P::BM; }
+    explicit ConvDgradByPosition(const P &p) : P(p), lg(3)
     {
-        const typename P::Cls c = this->cls(z);
-        if (m >= c.M) return {-1, 0, 0};
-        const int pos = dB.div(m), b = m - pos * this->Bn, yy = c.dW.div(pos), xx = pos - yy * c.Wc;
-        return {(((long long)b * this->Ho + yy) * this->Wo + xx) * L::COUT, yy, xx};
+        while (lg > 0 && (P::BM << lg) > p.Bn) --lg;
+        q = p.Bn >> lg; r = p.Bn - (q << lg);
+        dq = FastDiv::make(q); dq1 = FastDiv::make(q + 1);
     }
-    HTS_HD typename P::Row row(int m, int z) const
-    {
-        const typename P::Cls c = this->cls(z);
-        const int pos = dB.div(m), b = m - pos * this->Bn, yy = c.dW.div(pos), xx = pos - yy * c.Wc;
-        return {((((long long)b * this->Hin + yy * L::STRIDE + c.py) * this->Win) + xx * L::STRIDE + c.px) * this->N};
-    }
-    HTS_HD uint32_t live_taps(int m0, int z) const
-    {
-        constexpr uint32_t ALL = (1u << (P::TK * P::TK)) - 1u;
-        const typename P::Cls c = this->cls(z);
-        const int last = m0 + P::BM < c.M ? m0 + P::BM - 1 : c.M - 1, p0 = dB.div(m0), p1 = dB.div(last);
-        if (p1 - p0 > 2) return ALL;
-        uint32_t live = 0;
-        for (int pos = p0; pos <= p1; ++pos) {
-            const int yy = c.dW.div(pos), xx = pos - yy * c.Wc;
+    HTS_HD int max_m() const { return (((P::max_m() / this->Bn) * (q + (r > 0)) + P::BM - 1) / P::BM * P::BM) << lg; }
+
+    // One tile: its rows are samples x0, x0 + 1, ... of its run at position (ya, xa), then samples 0, 1, ... at the next one, (yb, xb).
+    struct Tile : P {
+        static constexpr int TAP_K = L::COUT;
+        int rows, first, x0, cnt, ya, xa, yb, xb;
+        explicit HTS_HD Tile(const P &p) : P(p) {}
+        HTS_HD int batch_m(int) const { return rows; }
+        struct At { int b, yy, xx; };
+        HTS_HD At at(int m) const
+        {
+            const int x = x0 + m;
+            const bool next = x >= cnt;
+            return {first + x - (next ? cnt : 0), next ? yb : ya, next ? xb : xa};
+        }
+        HTS_HD typename P::CtxA ctx_a(int m, int) const
+        {
+            const At t = at(m);
+            if (m >= rows) return {-1, 0, 0};
+            return {(((long long)t.b * this->Ho + t.yy) * this->Wo + t.xx) * L::COUT, t.yy, t.xx};
+        }
+        HTS_HD typename P::Row row(int m, int z) const
+        {
+            const At t = at(m);
+            const int py = z / L::STRIDE, px = z - py * L::STRIDE;
+            return {((((long long)t.b * this->Hin + t.yy * L::STRIDE + py) * this->Win) + t.xx * L::STRIDE + px) * this->N};
+        }
+        HTS_HD uint32_t live_taps() const
+        {
+            uint32_t live = 0;
+            const bool two = x0 + rows > cnt;
 #pragma unroll
             for (int t = 0; t < P::TK * P::TK; ++t) {
-                const int oy = yy - t / P::TK, ox = xx - t % P::TK;
-                if (oy >= 0 && oy < this->Ho && ox >= 0 && ox < this->Wo) live |= 1u << t;
+                const int a = t / P::TK, bb = t % P::TK;
+                const auto reached = [&](int yy, int xx) { return (unsigned)(yy - a) < (unsigned)this->Ho && (unsigned)(xx - bb) < (unsigned)this->Wo; };
+                if (reached(ya, xa) || (two && reached(yb, xb))) live |= 1u << t;
             }
+            return live;
         }
-        return live;
+    };
+    // the problem of tile `i` of class z; false: no such tile
+    HTS_HD bool tile(int i, int z, Tile &t) const
+    {
+        const typename P::Cls c = this->cls(z);
+        const int s = i & ((1 << lg) - 1), m0 = (i >> lg) * P::BM, more = s < r;
+        t.cnt = q + more; t.first = s * q + (more ? s : r);
+        const int left = c.Hc * c.Wc * t.cnt - m0, pos = (more ? dq1 : dq).div(m0);
+        t.rows = left < P::BM ? left : P::BM;
+        t.x0 = m0 - pos * t.cnt;
+        t.ya = c.dW.div(pos); t.xa = pos - t.ya * c.Wc;
+        const bool wraps = t.xa + 1 == c.Wc;
+        t.yb = t.ya + wraps; t.xb = wraps ? 0 : t.xa + 1;
+        return left > 0;
     }
 };
 
