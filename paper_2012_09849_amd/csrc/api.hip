@@ -106,6 +106,21 @@ void carve(Ctx &c, Carver &cv)
 }
 }  // namespace
 
+// compute units that a stream's kernels run on: the device's, or those of its range (see hts_stream_create_cu_range)
+static int stream_cus(hipStream_t stream)
+{
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1 || cus > 1024) {
+        (void)hipGetLastError();
+        return 256;
+    }
+    uint32_t mask[32] = {};
+    int in_mask = 0;
+    if (hipExtStreamGetCUMask(stream, (uint32_t)((cus + 31) / 32), mask) != hipSuccess) (void)hipGetLastError();
+    else for (int i = 0; i < cus; ++i) in_mask += (int)(mask[i >> 5] >> (i & 31) & 1u);
+    return in_mask > 0 ? in_mask : cus;
+}
+
 extern "C" int32_t hts_create(const hts_net_desc *desc, int32_t max_act_batch, int32_t max_learn_batch, void *hip_stream,
                               hts_ctx **out)
 {
@@ -118,7 +133,7 @@ extern "C" int32_t hts_create(const hts_net_desc *desc, int32_t max_act_batch, i
     hts_ctx *h = new (std::nothrow) hts_ctx();
     if (!h) return HTS_ENOMEM;
     Ctx &c = h->c;
-    c.desc = *desc; c.g = g; c.stream = (hipStream_t)hip_stream;
+    c.desc = *desc; c.g = g; c.stream = (hipStream_t)hip_stream; c.cus = stream_cus(c.stream);
     c.max_act = max_act_batch; c.max_learn = max_learn_batch;
     c.max_b = max_act_batch > max_learn_batch ? max_act_batch : max_learn_batch;
     c.small_b = 128;

@@ -600,8 +600,8 @@ template <typename T> static hipError_t forward_t(Ctx &c, const uint8_t *obs, co
             // 72x96: 2048 22.6 / 23.8, 3072 34.4 / 31.6, 4096 43.9 / 40.7
             RegConvArgs r = {};
             r.in = (const bf16_t *)c.ws.act1; r.w = (const bf16_t *)c.ws.wf2; r.bias = hb + c.sh.b2; r.out = (bf16_t *)c.ws.act2; r.B = B;
-            if (sizeof(T) == 2 && !small && atari_grid && B >= 2048) e = launch_regconv<RegConv<Layer2, 20, 20, ConvFwd<bf16_t, Layer2, false>::SEG>>(r, c.stream);
-            else if (sizeof(T) == 2 && !small && foot_grid && B >= 3072) e = launch_regconv<RegConv<Layer2, 17, 23, ConvFwd<bf16_t, Layer2, false>::SEG>>(r, c.stream);
+            if (sizeof(T) == 2 && !small && atari_grid && B >= 2048) e = launch_regconv<RegConv<Layer2, 20, 20, ConvFwd<bf16_t, Layer2, false>::SEG>>(r, c.cus, c.stream);
+            else if (sizeof(T) == 2 && !small && foot_grid && B >= 3072) e = launch_regconv<RegConv<Layer2, 17, 23, ConvFwd<bf16_t, Layer2, false>::SEG>>(r, c.cus, c.stream);
             else
             if (small && few32(((p.M + 31) / 32) * 2))
                 e = launch_wsgemm16<ConvFwd<T, Layer2, false>, 8, ConvFwd<T, Layer2, false>::SEG>(p, c.stream);

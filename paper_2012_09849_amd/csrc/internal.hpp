@@ -63,6 +63,7 @@ struct Ctx {
     hts_net_desc desc;
     Geom g;
     hipStream_t stream;
+    int cus;                  // compute units that the stream's kernels run on
     int max_act, max_learn, max_b;
     int small_b;              // batches up to this size take the wave-per-segment forward kernels
     int fc_groups;            // ceil(F / FC_GROUP_K)

@@ -26,3 +26,23 @@ def test_rows_agree_bitwise(hts, shape, A, sizes, monkeypatch):  # noqa: F811
         got = _act(ctx, obs[n - k:].contiguous(), params, 5, 1, n - k, A)
         assert all(np.array_equal(x[n - k:], y) for x, y in zip(want, got)), k
     ctx.close()
+
+
+# As many workgroups as the stream has compute units: other shares of the batch, the same bits.
+@pytest.mark.parametrize("cus", [192, 40])
+def test_compute_unit_ranges_agree_bitwise(hts, cus):  # noqa: F811
+    n, A = 2305, 18
+    params = dev(syn.init_params(43, *ATARI, A, bias_scale=0.05))
+    obs = torch.randint(0, 256, (n, *ATARI), device="cuda", generator=torch.Generator(device="cuda").manual_seed(44), dtype=torch.uint8)
+    ctx = hts.Context(*ATARI, A, precision=1, max_act_batch=n)
+    want = _act(ctx, obs, params, 5, 1, 0, A)
+    ctx.close()
+    rng = hts.CuRangeStream(8, cus)
+    ctx = hts.Context(*ATARI, A, precision=1, max_act_batch=n, stream=rng.stream)
+    out = [torch.zeros(n, dtype=torch.int32, device="cuda"), torch.zeros(n, device="cuda"), torch.zeros(n, device="cuda"), torch.zeros(n, A, device="cuda")]
+    torch.cuda.synchronize()                      # what fills them runs on another stream
+    ctx.hts_act(obs, params, 5, 1, 0, *out)
+    torch.cuda.synchronize()
+    ctx.close()
+    rng.close()
+    assert all(np.array_equal(x, y.cpu().numpy()) for x, y in zip(want, out))
