@@ -38,6 +38,11 @@ def layer_flops(cfg):
             "fc": 2.0 * 512 * 64 * P3}
 
 
+# A launch of the weight gradients that does the work of several sites is timed under each of them: it is listed once, under fc_wgrad (bf16: FC
+# and the heads) or wgrads (binary32: all layers), and these names are left out.
+SHARED_SITES = {0: ("heads_wgrad", "fc_wgrad", "conv1_wgrad", "conv2_wgrad", "conv3_wgrad"), 1: ("heads_wgrad", "wgrads")}
+
+
 def site_work(cfg, P):
     """Algorithmic work PER LAUNCH of every launch site: name -> (kind, amount, rows per launch).
 
@@ -50,13 +55,15 @@ def site_work(cfg, P):
     for layer in ("conv1", "conv2", "conv3", "fc"):
         w[f"{layer}_fwd"] = ("flop", N * f[layer], N)
         w[f"{layer}_fwd_learn"] = ("flop", B * f[layer], B)
-    for layer in ("conv3", "conv2"):
-        w[f"{layer}_wgrad"] = ("flop", B * f[layer], B)
+    for layer in ("conv3", "conv2", "fc"):
         w[f"{layer}_dgrad"] = ("flop", B * f[layer], B)
-    w["conv1_wgrad"] = ("flop", B * f["conv1"], B)
-    w["fc_wgrad"] = ("flop", B * f["fc"], B)
-    w["fc_dgrad"] = ("flop", B * f["fc"], B)
-    w["wgrads"] = ("flop", B * (f["fc"] + f["conv1"] + f["conv2"] + f["conv3"]), B)      # binary32: one launch for all of them
+    heads = 2.0 * (cfg["A"] + 1) * 512
+    for layer in ("conv3", "conv2", "conv1"):
+        w[f"{layer}_wgrad"] = ("flop", B * f[layer], B)
+    w["fc_wgrad"] = ("flop", B * (f["fc"] + heads), B)
+    w["wgrads"] = ("flop", B * (f["fc"] + heads + f["conv1"] + f["conv2"] + f["conv3"]), B)
+    for name in SHARED_SITES[cfg["precision"]]:
+        w.pop(name, None)
     w["adam"] = ("byte", 28.0 * P, B)
     w["grad_norm"] = ("byte", 4.0 * P, B)
     w["gae"] = ("byte", 17.0 * T * N + 4.0 * N, N)
@@ -68,6 +75,8 @@ def time_sites(loop, steps=2):
     names = loop.ctx.profile_sites()
     per_step = {}
     for i, nm in enumerate(names):
+        if nm in SHARED_SITES[loop.cfg["precision"]]:
+            continue
         loop.ctx.hts_profile_begin(i)
         for _ in range(steps):
             loop.step()

@@ -218,7 +218,9 @@ int32_t hts_test_gemm(hts_ctx *ctx, int32_t precision, const float *A, const flo
  * the library).  Between hts_profile_begin(ctx, site) and hts_profile_end every launch of that site is bracketed by
  * a pair of HIP events recorded on the context's stream (at most 4096 launches; later ones are not timed).
  * hts_profile_end waits for the recorded events and returns the number of timed launches and the sum of their
- * durations in milliseconds (host pointers).  Timing does not change any result. */
+ * durations in milliseconds (host pointers).  Timing does not change any result.
+ * A launch that does the work of several sites is timed, whole, under each of them: the weight gradients of the heads and of
+ * FC in bfloat16, those of all five layers in binary32 ("wgrads" is the launch that several of them share). */
 int32_t     hts_profile_site_count(void);
 const char *hts_profile_site_name(int32_t site);
 int32_t     hts_profile_begin(hts_ctx *ctx, int32_t site);

@@ -662,7 +662,7 @@ template <typename T> static hipError_t backward_t(Ctx &c, const uint8_t *obs, c
     // operands in registers; 51 and 32 at 80 rows).  bfloat16's conv layers go out each right behind the input gradient whose output they read, while the caches still hold
     // it (on the tile kernel, together 115 us against 90 at 2048 rows of 72x96 frames). ----
     if constexpr (sizeof(T) == 2) {
-        SiteTimer tm(c, SITE_FC_WGRAD);
+        SiteTimer tm(c, SITE_FC_WGRAD, SITE_HEADS_WGRAD, SITE_WGRADS);
         e = launch_group(c.stream, SegmentJob<HeadsWgrad, 32>(ph, spgh), DmaJob<DmaFcWgrad, 1, 3>(DmaFcWgrad(pf)));
         if (e != hipSuccess) return e;
     }
@@ -735,7 +735,7 @@ template <typename T> static hipError_t backward_t(Ctx &c, const uint8_t *obs, c
         if (e != hipSuccess) return e;
     }
     if constexpr (sizeof(T) == 4) {
-        SiteTimer tm(c, SITE_WGRADS);
+        SiteTimer tm(c, SITE_WGRADS, SITE_HEADS_WGRAD, SITE_FC_WGRAD, SITE_CONV3_WGRAD, SITE_CONV2_WGRAD, SITE_CONV1_WGRAD);
         auto all = [&](auto p1) {
             if (small) return launch_group(c.stream, SegmentJob<HeadsWgrad, 32>(ph, spgh), SegmentJob<decltype(p1), 64>(p1, spg1), SegmentJob<ConvWgrad<T, Layer2>, 64>(p2, spg2),
                                            SegmentJob<ConvWgrad<T, Layer3>, 64>(p3, spg3), TileJob<FcWgrad<T>>(pf));

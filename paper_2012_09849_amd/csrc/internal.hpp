@@ -47,7 +47,7 @@ enum Site {
     SITE_STATS,
     // the learner's forward pass runs other kernels than an actor call of a few rows: its launches are sites of their own
     SITE_CONV1_FWD_LEARN, SITE_CONV2_FWD_LEARN, SITE_CONV3_FWD_LEARN, SITE_FC_FWD_LEARN,
-    SITE_WGRADS,      // the weight gradients that share a launch
+    SITE_WGRADS,      // the weight gradients that share a launch, which is timed under each one's own site too
     SITE_COUNT
 };
 constexpr int PROF_CAP = 4096;     // event pairs kept per profiling window
@@ -84,7 +84,8 @@ struct Ctx {
 struct SiteTimer {
     Ctx &c;
     bool on;
-    SiteTimer(Ctx &ctx, int site) : c(ctx), on(ctx.prof.site == site && ctx.prof.ev && ctx.prof.n < PROF_CAP)
+    // sites: the launch's own; several where it does the work of several
+    template <class... S> explicit SiteTimer(Ctx &ctx, S... sites) : c(ctx), on(((ctx.prof.site == sites) || ...) && ctx.prof.ev && ctx.prof.n < PROF_CAP)
     {
         if (on) on = (c.prof.seen++ % c.prof.every) == 0;
         if (on) (void)hipEventRecord(c.prof.ev[2 * c.prof.n], c.stream);
