@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 import torch
 
-from test_gpu_parity import _rollout, _split, dev, hts, oracle_hp  # noqa: F401
+from test_gpu_parity import ATARI, FOOT, _rollout, _split, dev, hts, oracle_hp  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -32,4 +32,24 @@ def test_f32_gradient_of_many_rows(hts, oracle, A, B):  # noqa: F811
                 continue
             err = np.linalg.norm(_split(got, shape, A)[name] - w) / np.linalg.norm(w)
             assert err <= 1.1e-5, (name, err)
+    ctx.close()
+
+
+# The register kernels on the frames of the two workloads, chunks and last blocks ragged; an indexed minibatch, whose conv1 reads its frames through
+# the index.  1e-4: binary32's bound for gradients (sums of 151 * 400 products are off by 1.5e-5 of their size, a gate of one row that opens on one
+# side only by some 5e-5); a row or a column left out would be 1e-2 and more.
+@pytest.mark.parametrize("shape,A,count,B", [(ATARI, 18, 160, 151), (FOOT, 19, 140, 133)])
+def test_f32_gradient_of_workload_frames(hts, oracle, shape, A, count, B):  # noqa: F811
+    net, params, obs, actions, old_logp, adv, ret = _rollout(oracle, shape, A, count, 700 + B, False)
+    index = torch.randperm(count, generator=torch.Generator().manual_seed(B)).to(torch.int32)[:B]
+    ctx = hts.Context(*shape, A, max_learn_batch=B)
+    hp = hts.HParams(algo=hts.ALGO_A2C)
+    g = torch.full((ctx.P,), float("nan"), device="cuda")
+    ctx.hts_loss_and_grads(dev(obs), dev(actions), None, dev(adv), dev(ret), dev(params), hp, g, index=index.cuda())
+    torch.cuda.synchronize()
+    got = _split(g.cpu().numpy().astype(np.float64), shape, A)
+    want, _ = oracle.loss_grads(net, params, obs, actions, old_logp, adv, ret, oracle_hp(oracle, hp), index=index.numpy(), threads=oracle.host_threads())
+    for name, w in _split(want, shape, A).items():
+        err = np.linalg.norm(got[name] - w) / np.linalg.norm(w)
+        assert err <= 1e-4, (name, err)
     ctx.close()

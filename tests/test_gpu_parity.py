@@ -761,15 +761,16 @@ def test_bf16_loss_and_grads(hts, oracle, shape, A, count, B, algo, small_batch,
     ctx.close()
 
 
-@pytest.mark.parametrize("shape,A,count,B", [(ATARI, 18, 140, 131), (FOOT, 19, 140, 133)])
+@pytest.mark.parametrize("shape,A,count,B", [(ATARI, 18, 140, 131), (FOOT, 19, 140, 133), (ATARI, 18, 220, 211)])
 def test_bf16_ragged_large_batch_agrees_with_small_batch_kernels(hts, oracle, shape, A, count, B, monkeypatch):
     """A minibatch just above the boundary between the kernel families, of a size that leaves the last group of
     every LDS-resident kernel part full and every tile kernel a ragged tail: the large-batch kernels (tile kernels,
     image kernels, split reductions) against the wave-per-segment kernels on the same bf16 problem.  The two differ in
     the order of the backward reductions only (forward bits are identical), so the gradients agree far inside the bf16
-    tolerance; the wave-per-segment kernels are the ones held against the oracle above.  The bf16 weight gradients of conv2
-    and conv3 have no wave-per-segment form: they are held against the operand-rounding oracle here (2e-2 and 2.5e-2 of a
-    tensor in the 2-norm, the bounds of the real minibatches: a gate that opens on one side only now and then)."""
+    tolerance; the wave-per-segment kernels are the ones held against the oracle above.  The bf16 weight gradients of conv2,
+    conv3, FC and the heads have one form only, so both sides run it: they are held against the operand-rounding oracle here (2e-2
+    and 2.5e-2 of a tensor in the 2-norm, the bounds of the real minibatches: a gate that opens on one side only now and then).
+    211 rows: FC's reduction takes four k-tiles of 64 rows, the last one ragged, through the three that LDS holds."""
     Cc, H, W = shape
     net, params, obs, actions, old_logp, adv, ret = _rollout(oracle, shape, A, count, 900 + count, True)
     index = syn.permutation(8, count)[:B]
@@ -797,7 +798,7 @@ def test_bf16_ragged_large_batch_agrees_with_small_batch_kernels(hts, oracle, sh
     qnet = oracle.make_net(Cc, H, W, A, operand_bf16=True)
     g_q, _ = oracle.loss_grads(qnet, params, obs, actions, old_logp, adv, ret, oracle_hp(oracle, hp), index=index,
                                threads=oracle.host_threads())
-    for name in ("conv2.w", "conv2.b", "conv3.w", "conv3.b"):
+    for name in ("conv2.w", "conv2.b", "conv3.w", "conv3.b", "fc.w", "fc.b", "pi.w", "pi.b", "v.w", "v.b"):
         want = _split(g_q, shape, A)[name]
         e = np.linalg.norm(_split(g_large, shape, A)[name] - want) / np.linalg.norm(want)
         assert e <= (2e-2 if shape == ATARI else 2.5e-2), (name, e)
