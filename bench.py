@@ -190,20 +190,20 @@ def source_digest():
 # counter reads for a plain copy of known size): workload -> ({launch site: bytes per launch}, digest of the kernel
 # sources the counters were taken on).
 TRAFFIC = {
-    "football_ppo_n16_t512_bf16": ({"conv1_fwd": 5092952, "conv1_fwd_learn": 279402479, "conv1_wgrad": 316592245,
-                                    "conv2_fwd": 2626326, "conv3_fwd": 1214359, "fc_fwd": 3465925}, "eaff6532ecd9de68"),
-    "atari_ppo_n32_t128_bf16": ({"conv1_fwd": 2846582, "conv1_fwd_learn": 55547061, "conv1_wgrad": 63732736,
-                                 "conv2_wgrad": 45523357}, "eaff6532ecd9de68"),
+    "football_ppo_n16_t512_bf16": ({"conv1_fwd": 5093376, "conv1_fwd_learn": 279397068, "conv1_wgrad": 313987379,
+                                    "conv2_fwd": 2626560, "conv3_fwd": 1214464, "fc_fwd": 3466240}, "035ebdf034e8cc63"),
+    "atari_ppo_n32_t128_bf16": ({"conv1_fwd": 2846720, "conv1_fwd_learn": 55549952, "conv1_wgrad": 63729868,
+                                 "conv2_wgrad": 45520896}, "035ebdf034e8cc63"),
 }
 
 
 # Average duration (us) of the same launch sites' kernels in the committed rocprofv3 kernel traces
 # (profiles/all_kernels_<workload>.txt), for comparison with the live event figure; same digest rule as TRAFFIC.
 TRACE_AVG_US = {
-    "football_ppo_n16_t512_bf16": ({"conv1_fwd": 6.33, "heads_act": 3.84, "conv2_fwd": 3.88, "conv3_fwd": 3.53,
-                                    "fc_fwd": 3.25, "conv1_fwd_learn": 86.93, "conv1_wgrad": 79.21}, "eaff6532ecd9de68"),
-    "atari_ppo_n32_t128_bf16": ({"conv1_fwd": 4.96, "heads_act": 3.73, "conv1_fwd_learn": 20.15, "conv1_wgrad": 20.03,
-                                 "conv2_wgrad": 14.22}, "eaff6532ecd9de68"),
+    "football_ppo_n16_t512_bf16": ({"conv1_fwd": 6.31, "heads_act": 3.84, "conv2_fwd": 3.84, "conv3_fwd": 3.51,
+                                    "fc_fwd": 3.22, "conv1_fwd_learn": 86.04, "conv1_wgrad": 79.45}, "035ebdf034e8cc63"),
+    "atari_ppo_n32_t128_bf16": ({"conv1_fwd": 4.91, "heads_act": 3.85, "conv1_fwd_learn": 20.05, "conv1_wgrad": 18.98,
+                                 "conv2_wgrad": 13.84}, "035ebdf034e8cc63"),
 }
 
 

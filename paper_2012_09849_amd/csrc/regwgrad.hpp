@@ -13,7 +13,7 @@
 //
 // The matrix instruction is a sequential fma chain, lowest k first, whatever its tile shape: the same bits as the tile
 // kernel's, chunk by chunk.  1024 rows of 84x84 frames, conv1, conv2, conv3, FC and the heads in one launch: 215 us on the tile kernel, 183
-// now (124 if the matrix pipes never waited).  Not kept: 64 x 64 blocks (fewer vector instructions, but tasks so long that a third of
+// now (122 at the matrix pipes' peak of 157.3 TFLOP/s).  Not kept: 64 x 64 blocks (fewer vector instructions, but tasks so long that a third of
 // the compute units end early: 208 us); blocks of 32 x 32 in segments of 64 for small minibatches (80 rows: 33.5 us against 31.5 of the
 // wave-per-segment bodies: chains of up to 192 steps).
 #pragma once
