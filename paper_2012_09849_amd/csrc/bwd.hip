@@ -548,15 +548,21 @@ static hipError_t launch_conv1_wgrad_slab(Ctx &c, const uint8_t *obs, const int3
     return hipGetLastError();
 }
 
-// bf16: gemm_dma_kernel.  Kernel time, us, register-staged tile kernel / 64x64 tiles of 3 stages / 64x128 of 2: 203 rows of 16x72x96
-// frames (160 workgroups of 64x64) 6.8 / 6.0 / 8.6, 512 rows of 4x84x84 (392) 8.7 / 8.6 / 9.7, 700 rows (539) 10.6 / 11.0 / 10.6,
-// 1024 rows (784) 14.1 / 13.7 / 11.8, 2048 rows of 16x72x96 19.6 / 19.1 / 18.2.  Around the cut, two 64x64 tiles a compute unit: 490
-// - / 8.4 / 9.4, 520 - / 9.9 / 10.0, 560 - / 10.8 / 10.2, 637 - / 11.2 / 11.1, 720 - / 11.6 / 12.1.
+// bf16: gemm_dma_kernel, by the number of 64x64 tiles.  us, 64x64 tiles of 3 stages / of 2 / 64x128 of 2 / 128x128 of 2, on 84x84 and 72x96 frames:
+// 160 tiles 4.5 / 5.9 / 6.9 / 7.7, 343 6.5 / 7.0 / 7.6 / 8.6, 490 6.9 / 7.2 / 8.0 / 8.7 (3 stages: three workgroups a compute unit); 520 8.0 / 7.5 / 7.9,
+// 588 8.5 / 7.7 / 8.6, 640 8.7 / 8.3 / 9.0, 735 - / 8.1 / 8.5, 760 - / 8.4 / 9.1, 784 10.3 / 9.1 / 8.9, 931 - / 9.9 / 9.2, 1078 11.7 / 12.7 / 11.0 / 11.6, 1280
+// 13.9 / 14.9 / 13.2 / 13.5.  Three workgroups of 64x128 and two of 128x128 fit a compute unit: the larger where the smaller would begin a
+// second round and it does not, 84x84 2048 rows (800 of 64x128, 400 of 128x128) 16.9 / 14.3, 72x96 2700 (860, 440) 17.6 / 14.4, 3072 18.5 / 15.2; else
+// 84x84 1800 (725, 375) 12.4 / 12.8, 3000 (1175, 600) 20.7 / 21.7, 72x96 2300 (720, 360) 13.6 / 13.7, 4096 (1280, 640) 20.8 / 22.5.
+// (With the rows straight from the accumulators, 64x128: 1024 rows of 84x84 11.8, now 8.9 to 10; 2048 of 72x96 18.5, now 13.2 to 14.2.)
 static hipError_t launch_fc_dgrad(const FcDgrad<float> &p, hipStream_t s) { return launch_gemm(p, s); }
 static hipError_t launch_fc_dgrad(const FcDgrad<bf16_t> &p, hipStream_t s)
 {
     typedef FcDgrad<bf16_t> P;
-    if (dma_workgroups(p, 64, 64) <= 512) return launch_dma(DmaTiles<P, 64, 64, 2, 2, 3>(p), s);
+    const int tiles = dma_workgroups(p, 64, 64);
+    if (tiles <= 512) return launch_dma(DmaTiles<P, 64, 64, 2, 2, 3>(p), s);
+    if (tiles <= 768) return launch_dma(DmaTiles<P, 64, 64, 2, 2, 2>(p), s);
+    if (dma_workgroups(p, 64, 128) > 768 && dma_workgroups(p, 128, 128) <= 512) return launch_dma(DmaTiles<P, 128, 128, 2, 2, 2>(p), s);
     return launch_dma(DmaTiles<P, 64, 128, 2, 2, 2>(p), s);
 }
 

@@ -328,6 +328,9 @@ template <typename T_> struct FcDgrad {
     HTS_HD Vec<T, VA> load_a(const CtxA &c, int k, int) const { return load_vec<T, VA>(c.p + k); }
     HTS_HD Vec<T, VB> load_b(const CtxB &c, int k, int) const { return load_vec<T, VB>(c.p + k); }
     HTS_HD int dma_k(int k0) const { return k0; }
+    static constexpr bool MASKED_ROWS = true;        // (LDS-copy kernel)
+    HTS_HD T *out_rows() const { return dy3; }
+    HTS_HD const T *mask_rows() const { return a3n; }
     static constexpr bool LANE_OWNS_ROW = true;
     struct Row { long long o; };
     HTS_HD Row row(int b) const { return {(long long)b * N}; }

@@ -52,3 +52,27 @@ def test_gradient_is_the_mean_of_its_halves(hts, oracle, shape, A, B, precision)
         mean = 0.5 * (first[name] + second[name])
         assert np.linalg.norm(w - mean) <= 3.2e-5 * np.linalg.norm(mean), name
     ctx.close()
+
+
+# The FC input gradient's tiles, whose rows leave through LDS, each with a batch that ends inside one: 64x64 of 3 stages (3 tiles of rows, 6 of
+# columns), of 2 (539 tiles), 64x128 (833) and 128x128 (825 of 64x128, 425 of 128x128); 64x128 tiles that end inside the last of 49 halves.
+# The wave-per-segment kernels add the same products in another order: bfloat16 rounds each layer's gradient to 2^-9, and a sum that ends near
+# a rounding edge may fall on either side, here and there.
+@pytest.mark.parametrize("shape,A,B", [((3, 44, 52), 7, 131), (ATARI, 18, 700), (ATARI, 18, 1030), (ATARI, 18, 2050)])
+def test_fc_input_gradient_tiles(hts, shape, A, B, monkeypatch):  # noqa: F811
+    g = torch.Generator(device="cuda").manual_seed(B)
+    params = dev(syn.init_params(33, *shape, A, bias_scale=0.05))
+    obs = torch.randint(0, 256, (B, *shape), device="cuda", generator=g, dtype=torch.uint8)
+    actions = torch.randint(0, A, (B,), device="cuda", generator=g, dtype=torch.int32)
+    adv, ret = torch.randn(B, device="cuda", generator=g), torch.randn(B, device="cuda", generator=g)
+    grads = []
+    for knob in ("0", "1000000"):
+        monkeypatch.setenv("HTS_SMALL_BATCH", knob)
+        ctx = hts.Context(*shape, A, precision=1, max_learn_batch=B)
+        out = torch.full((ctx.P,), float("nan"), device="cuda")
+        ctx.hts_loss_and_grads(obs, actions, None, adv, ret, params, hts.HParams(algo=hts.ALGO_A2C), out)
+        torch.cuda.synchronize()
+        grads.append(_split(out.cpu().numpy().astype(np.float64), shape, A))
+        ctx.close()
+    for name, w in grads[1].items():
+        assert np.linalg.norm(grads[0][name] - w) <= 2e-3 * np.linalg.norm(w), name
