@@ -38,9 +38,14 @@ def layer_flops(cfg):
             "fc": 2.0 * 512 * 64 * P3}
 
 
-# A launch of the weight gradients that does the work of several sites is timed under each of them: it is listed once, under fc_wgrad (bf16: FC
-# and the heads) or wgrads (binary32: all layers), and these names are left out.
-SHARED_SITES = {0: ("heads_wgrad", "fc_wgrad", "conv1_wgrad", "conv2_wgrad", "conv3_wgrad"), 1: ("heads_wgrad", "wgrads")}
+# A launch that does the work of several sites is timed under each of them: it is listed once, the weight gradients under fc_wgrad (bf16: FC
+# and the heads) or wgrads (binary32: all layers), conv1 and conv2 of 48 or more 4x84x84 frames in bf16 under conv1's name, and the others are left out.
+def shared_sites(cfg):
+    if cfg["precision"] == 0:
+        return ("heads_wgrad", "fc_wgrad", "conv1_wgrad", "conv2_wgrad", "conv3_wgrad")
+    convs = tuple(name for name, rows in (("conv2_fwd", cfg["N"]), ("conv2_fwd_learn", cfg["N"] * cfg["T"] // cfg["minibatches"]))
+                  if (cfg["C"], cfg["H"], cfg["W"]) == (4, 84, 84) and rows >= 48)
+    return ("heads_wgrad", "wgrads") + convs
 
 
 def site_work(cfg, P):
@@ -62,7 +67,10 @@ def site_work(cfg, P):
         w[f"{layer}_wgrad"] = ("flop", B * f[layer], B)
     w["fc_wgrad"] = ("flop", B * (f["fc"] + heads), B)
     w["wgrads"] = ("flop", B * (f["fc"] + heads + f["conv1"] + f["conv2"] + f["conv3"]), B)
-    for name in SHARED_SITES[cfg["precision"]]:
+    for name in shared_sites(cfg):
+        if name in ("conv2_fwd", "conv2_fwd_learn"):
+            both, rows = name.replace("conv2", "conv1"), w[name][2]
+            w[both] = ("flop", rows * (f["conv1"] + f["conv2"]), rows)
         w.pop(name, None)
     w["adam"] = ("byte", 28.0 * P, B)
     w["grad_norm"] = ("byte", 4.0 * P, B)
@@ -75,7 +83,7 @@ def time_sites(loop, steps=2):
     names = loop.ctx.profile_sites()
     per_step = {}
     for i, nm in enumerate(names):
-        if nm in SHARED_SITES[loop.cfg["precision"]]:
+        if nm in shared_sites(loop.cfg):
             continue
         loop.ctx.hts_profile_begin(i)
         for _ in range(steps):

@@ -4,6 +4,7 @@
 #include "dmagemm.hpp"
 #include "imgconv.hpp"
 #include "regconv.hpp"
+#include "conv12.hpp"
 
 #include <atomic>
 
@@ -11,8 +12,8 @@ namespace hts {
 
 // ------------------------------------------------------------------------------------------------------------
 // conv1 of bf16 batches beyond the wave-per-segment kernels, 4-channel frames whose bf16 image takes at most 64 KiB of LDS and
-// that the slab kernel below does not serve: shapes other than 4x84x84, and 4x84x84 frames at an address that is a multiple
-// of 4 but not of 16 bytes.  One workgroup per observation.
+// that conv12.hpp does not serve: shapes other than 4x84x84, and 4x84x84 frames at an address that is a multiple
+// of 4 but not of 8 bytes.  One workgroup per observation.
 // The frame is converted to bf16 ONCE into an LDS image [(c,y)][Wp] (the tile kernel converts every pixel four times,
 // once per patch that contains it, and spends most of its issue slots on that and on gather addresses); the matrix
 // instruction's position operand is then read straight from the image -- 8 consecutive k of conv1.w's (c,u,v) order
@@ -175,14 +176,14 @@ static hipError_t launch_conv1_image(Ctx &c, const uint8_t *obs, const int32_t *
 }
 
 // ------------------------------------------------------------------------------------------------------------
-// conv1 of bf16 batches of the two frame shapes of the paper's experiments (16x72x96 from 21 rows on, 4x84x84 from 64), whose
+// conv1 of bf16 batches of 16x72x96 frames from 21 rows on, whose
 // four-channel slab (4*H*W bytes, about 27 KB) fits twice into LDS as bf16: one workgroup per compute unit walks a share of
 // the observations, or, up to 128 of them, several workgroups share one (see launch_conv1_slab).
 // A frame passes in slabs of four channels.  Wavefronts 4-7 (producers) fetch slab q+2 into registers, convert slab q+1
 // to bf16 once into one of two LDS images [(c,y)][W] and copy the 32 x 256 slice of conv1.w that belongs to its
 // channels beside it; meanwhile wavefronts 0-3 (consumers, one per SIMD next to a producer) multiply slab q: position
 // tiles w, w+4, ... of 32 positions each, the matrix instruction's weight operand read from the LDS slice (shared by two
-// tiles; a four-channel frame is a single slab and its weights stay in the consumers' registers instead), its position
+// tiles), its position
 // operand straight from the image (8 consecutive k of conv1.w's (c,u,v) order are 8 neighbouring
 // pixels of one row).  A tile's running total stays in the consumer's registers across the frame's slabs, so the
 // channels' 64-long segment sums are added in channel order exactly as in Conv1Fwd: same bits as the other conv1
@@ -230,8 +231,8 @@ template <int NG, int H, int W, bool SHARED> __global__ __launch_bounds__(C1S_TH
     constexpr int IMG = 2 * SLAB;          // bytes of one bf16 image
     // slabs in flight in the producers' registers (walking a batch, four are no faster: 99 vs 96 us; with one observation per
     // workgroup all of it is requested at once)
-    constexpr int D = SHARED && NG > 2 ? NG : 2;
-    static_assert(SLAB % 16 == 0 && (NG == 1 || NG % D == 0), "slab shape");
+    constexpr int D = SHARED ? NG : 2;
+    static_assert(SLAB % 16 == 0 && NG % D == 0, "slab shape");
     extern __shared__ __attribute__((aligned(16))) unsigned char c1s_smem[];
     unsigned char *wl = c1s_smem + 2 * IMG;
     float *lbias = reinterpret_cast<float *>(wl + 2 * C1S_WBUF);
@@ -250,11 +251,11 @@ template <int NG, int H, int W, bool SHARED> __global__ __launch_bounds__(C1S_TH
     if (w >= 4) {
         // ---- producers ----
         const int pt = tid - (C1S_THREADS - PT);
-        constexpr int NWV = NG > 1 ? 4 : 0;                // 16-byte vectors of the weight slice per producer thread
+        constexpr int NWV = 4;                             // 16-byte vectors of the weight slice per producer thread
         uint4 raw[D][NP + NWV];                            // a slab's vectors, then its weight slice's
         // A thread's byte offsets inside a slab / a weight slice never change; what changes per slab is the same for the
         // whole workgroup and is kept in scalar registers, so a fetch is loads and nothing else.
-        uint32_t ioff[NP], woffs[NWV ? NWV : 1];
+        uint32_t ioff[NP], woffs[NWV];
         // the slab's vectors in order; for a share of an observation those of the rows it needs of each channel.  A vector
         // behind the last one repeats it.
         int nv = NV;
@@ -276,11 +277,9 @@ template <int NG, int H, int W, bool SHARED> __global__ __launch_bounds__(C1S_TH
             const uint8_t *src = a.obs + (row * C + 4 * cg) * (H * W);
 #pragma unroll
             for (int i = 0; i < NP; ++i) if (!SHARED || i * PT < nv) r[i] = *reinterpret_cast<const uint4 *>(src + ioff[i]);
-            if constexpr (NG > 1) {
-                const unsigned char *wsrc = reinterpret_cast<const unsigned char *>(a.w) + cg * 512;
+            const unsigned char *wsrc = reinterpret_cast<const unsigned char *>(a.w) + cg * 512;
 #pragma unroll
-                for (int i = 0; i < NWV; ++i) r[NP + i] = *reinterpret_cast<const uint4 *>(wsrc + woffs[i]);
-            }
+            for (int i = 0; i < NWV; ++i) r[NP + i] = *reinterpret_cast<const uint4 *>(wsrc + woffs[i]);
         };
         auto convert = [&](const uint4 (&r)[NP + NWV], int buf) {
             unsigned char *dst = c1s_smem + buf * IMG + (SHARED ? 0 : 32 * pt);
@@ -300,12 +299,10 @@ template <int NG, int H, int W, bool SHARED> __global__ __launch_bounds__(C1S_TH
                 *reinterpret_cast<bf16x8 *>(dst + at) = lo;
                 *reinterpret_cast<bf16x8 *>(dst + at + 16) = hi;
             }
-            if constexpr (NG > 1) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int v = pt + i * PT;
-                    *reinterpret_cast<uint4 *>(wl + buf * C1S_WBUF + (v >> 5) * C1S_WPITCH + (v & 31) * 16) = r[NP + i];
-                }
+            for (int i = 0; i < 4; ++i) {
+                const int v = pt + i * PT;
+                *reinterpret_cast<uint4 *>(wl + buf * C1S_WBUF + (v >> 5) * C1S_WPITCH + (v & 31) * 16) = r[NP + i];
             }
         };
 #pragma unroll
@@ -317,7 +314,6 @@ template <int NG, int H, int W, bool SHARED> __global__ __launch_bounds__(C1S_TH
 #pragma unroll
             for (int j = 0; j < D; ++j) {                      // slab q+1 sits in register set (j+1) % D
                 const int q = q0 + j;
-                if (NG % D != 0 && q >= nphase) break;         // (the same for the whole workgroup)
                 if (q + 1 < nphase) convert(raw[(j + 1) % D], (q & 1) ^ 1);
                 if (q + 1 + D < nphase) fetch(q + 1 + D, raw[(j + 1) % D]);
                 __syncthreads();
@@ -337,12 +333,6 @@ template <int NG, int H, int W, bool SHARED> __global__ __launch_bounds__(C1S_TH
     }
     const int mytiles = w < ntiles ? (ntiles - w + 3) / 4 : 0;       // the same for the whole wavefront
     const uint32_t woff = (uint32_t)(lrow * C1S_WPITCH + 16 * lk);
-    // a four-channel frame is one slab: its weights never change and stay in registers
-    bf16x8 breg[NG == 1 ? 16 : 1];
-    if constexpr (NG == 1) {
-#pragma unroll
-        for (int t = 0; t < 16; ++t) breg[t] = *reinterpret_cast<const bf16x8 *>(a.w + lrow * K + 16 * t + 8 * lk);
-    }
     f32x16 tot[C1S_TILES];
     // 8 pixels of one image row (8-byte aligned) as two single 8-byte reads.  Left alone, the compiler merges them
     // (or reads of two steps) into one two-address read, which the LDS serves at half the rate of two single ones --
@@ -385,8 +375,7 @@ template <int NG, int H, int W, bool SHARED> __global__ __launch_bounds__(C1S_TH
         bf16x8 wq[PD], aq[PD][NT];
         auto rd = [&](int e, int slot) {                  // both compile-time constants after unrolling
             const int ch = e >> 2, t = e & 3;
-            if constexpr (NG == 1) wq[slot] = breg[ch * 4 + t];
-            else wq[slot] = *reinterpret_cast<const bf16x8 *>(wb + 2 * (64 * ch + 16 * t));
+            wq[slot] = *reinterpret_cast<const bf16x8 *>(wb + 2 * (64 * ch + 16 * t));
 #pragma unroll
             for (int i = 0; i < NT; ++i) aq[slot][i] = read16(ib[i][ch] + 2 * (2 * t * W));
         };
@@ -468,7 +457,7 @@ template <int NG, int H, int W, bool SHARED> __global__ __launch_bounds__(C1S_TH
 #pragma unroll
         for (int cg = 0; cg < NG; ++cg) {
             const int buf = (s * NG + cg) & 1;
-            if (cg == 0) slab(buf, std::true_type{}, std::integral_constant<bool, NG == 1>{}, b);
+            if (cg == 0) slab(buf, std::true_type{}, std::false_type{}, b);
             else if (cg == NG - 1) slab(buf, std::false_type{}, std::true_type{}, b);
             else slab(buf, std::false_type{}, std::false_type{}, b);
             __syncthreads();
@@ -479,9 +468,10 @@ template <int NG, int H, int W, bool SHARED> __global__ __launch_bounds__(C1S_TH
 // true if the frame shape and pointers fit conv1_slab_kernel as it is instantiated
 static bool conv1_slab_fits(const Geom &g, const uint8_t *obs)
 {
-    const bool football = g.C == 16 && g.H == 72 && g.W == 96, atari = g.C == 4 && g.H == 84 && g.W == 84;
-    return (football || atari) && (g.P1 + 31) / 32 <= 4 * C1S_TILES && !(((uintptr_t)obs) & 15u);
+    return g.C == 16 && g.H == 72 && g.W == 96 && (g.P1 + 31) / 32 <= 4 * C1S_TILES && !(((uintptr_t)obs) & 15u);
 }
+// ... and conv12_kernel
+static bool conv12_fits(const Geom &g, const uint8_t *obs) { return g.C == 4 && g.H == C12_H && g.W == C12_H && !(((uintptr_t)obs) & 7u); }
 
 static hipError_t launch_conv1_slab(Ctx &c, const uint8_t *obs, const int32_t *index, int B)
 {
@@ -489,18 +479,16 @@ static hipError_t launch_conv1_slab(Ctx &c, const uint8_t *obs, const int32_t *i
     Conv1SlabArgs a;
     a.obs = obs; a.index = index; a.w = (const bf16_t *)c.ws.w1s; a.bias = c.ws.hb + c.sh.b1; a.out = (bf16_t *)c.ws.act1;
     a.B = B; a.W1 = g.W1; a.P1 = g.P1;
-    const bool football = g.C == 16;
     // At most half as many observations as compute units: each goes to as many workgroups as there are compute units for it (at
     // most one per position tile).  Kernel time at 16x72x96 frames, us, one workgroup per observation / shared: 16 rows 12.4 /
-    // 6.5, 32 12.4 / 6.8, 64 12.6 / 7.7, 128 13.5 / 11.4; 4x84x84: 64 7.7 / 6.0, 128 8.6 / 7.3.
+    // 6.5, 32 12.4 / 6.8, 64 12.6 / 7.7, 128 13.5 / 11.4.
     a.parts = B <= 128 ? 256 / B : 1;
     if (a.parts > (g.P1 + 31) / 32) a.parts = (g.P1 + 31) / 32;
     const bool shared = a.parts > 1;
-    void (*kern)(const Conv1SlabArgs) = football ? (shared ? conv1_slab_kernel<4, 72, 96, true> : conv1_slab_kernel<4, 72, 96, false>)
-                                                 : (shared ? conv1_slab_kernel<1, 84, 84, true> : conv1_slab_kernel<1, 84, 84, false>);
-    const size_t lds = football ? conv1_slab_lds<72, 96>() : conv1_slab_lds<84, 84>();
-    static std::atomic<bool> attr_set[4] = {};      // raise the dynamic-LDS limit once per instantiation (setting it twice is harmless)
-    std::atomic<bool> &set = attr_set[(football ? 1 : 0) + (shared ? 2 : 0)];
+    void (*kern)(const Conv1SlabArgs) = shared ? conv1_slab_kernel<4, 72, 96, true> : conv1_slab_kernel<4, 72, 96, false>;
+    const size_t lds = conv1_slab_lds<72, 96>();
+    static std::atomic<bool> attr_set[2] = {};      // raise the dynamic-LDS limit once per instantiation (setting it twice is harmless)
+    std::atomic<bool> &set = attr_set[shared ? 1 : 0];
     if (!set.load(std::memory_order_acquire)) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
@@ -554,7 +542,16 @@ template <typename T> static hipError_t forward_t(Ctx &c, const uint8_t *obs, co
     // at 32 rows, 98 workgroups: 12.6 -> 10.5 us; at 64 rows, 196: 13.2 -> 16.0 us); conv1 gains only with binary32
     // operands (its frame operand is bytes either way), up to about 200 workgroups.
     auto few32 = [&](int workgroups) { return workgroups < c.tile16_below; };
-    {
+    // conv1 and conv2 in one kernel
+    const bool conv12 = sizeof(T) == 2 && B >= c.conv12_rows && conv12_fits(g, obs);
+    if (conv12) {
+        Conv12Args a;
+        a.obs = obs; a.index = index; a.w1 = (const bf16_t *)c.ws.w1s; a.w2 = (const bf16_t *)c.ws.wf2; a.b1 = hb + c.sh.b1; a.b2 = hb + c.sh.b2;
+        a.out1 = learn ? (bf16_t *)c.ws.act1 : nullptr; a.out2 = (bf16_t *)c.ws.act2; a.B = B;
+        SiteTimer tm(c, learn ? SITE_CONV1_FWD_LEARN : SITE_CONV1_FWD, learn ? SITE_CONV2_FWD_LEARN : SITE_CONV2_FWD);
+        if ((e = launch_conv12(a, c.cus, c.stream)) != hipSuccess) return e;
+    }
+    if (!conv12) {
         Conv1Fwd<T> p;
         p.M = B * g.P1; p.N = 32; p.K = g.K1; p.klen = g.K1;
         p.obs = obs; p.index = index; p.w = (const T *)c.ws.w1s; p.bias = hb + c.sh.b1; p.out = (T *)c.ws.act1;
@@ -577,8 +574,6 @@ template <typename T> static hipError_t forward_t(Ctx &c, const uint8_t *obs, co
             else if (sizeof(T) == 2 && B >= c.conv1_slab_rows && conv1_slab_fits(g, obs)) e = launch_conv1_slab(c, obs, index, B);
             else if (small) e = g.K1 >= 1024 ? launch_wsgemm<Conv1Fwd<T>, 16, Conv1Fwd<T>::SEG, false, (sizeof(T) == 4)>(p, c.stream)
                                         : launch_wsgemm<Conv1Fwd<T>, 4, Conv1Fwd<T>::SEG, false>(p, c.stream);
-            // (against the LDS-image kernel, which is left with other four-channel shapes and misaligned frames, conv1 at 1024
-            // rows of 4x84x84 21.7 -> 19.0 us, an act call at 256 / 4096 rows 38.8 -> 36.7 / 203 -> 188 us)
             else if (sizeof(T) == 2 && conv1_image_fits(g, obs)) e = launch_conv1_image(c, obs, index, B);
             else e = launch_gemm(p, c.stream);
         }
@@ -586,7 +581,7 @@ template <typename T> static hipError_t forward_t(Ctx &c, const uint8_t *obs, co
     }
     const bool atari_grid = g.H1 == 20 && g.W1 == 20;      // 84x84 frames: conv2 sees 20x20, conv3 9x9
     const bool foot_grid = g.H1 == 17 && g.W1 == 23;       // 72x96 frames: conv2 sees 17x23, conv3 7x10
-    {
+    if (!conv12) {
         ConvFwd<T, Layer2, false> p;
         p.M = B * g.P2; p.N = 64; p.K = 512; p.klen = 512;
         p.in = (const T *)c.ws.act1; p.wf = (const T *)c.ws.wf2; p.bias = hb + c.sh.b2; p.out = (T *)c.ws.act2; p.out2 = nullptr;
