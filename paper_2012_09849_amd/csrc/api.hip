@@ -86,6 +86,7 @@ void carve(Ctx &c, Carver &cv)
     const size_t mb = (size_t)c.max_b, ml = (size_t)c.max_learn;
     cv.take(w.w1s, (size_t)32 * g.K1 * ts); cv.take(w.wf2, 64 * 512 * ts); cv.take(w.wf3, 64 * 576 * ts);
     cv.take(w.wfc, (size_t)512 * g.F * ts); cv.take(w.hb, (size_t)c.sh.count * 4);
+    if (ts == 2 && c.max_act > 0) { cv.take(w.w1q, (size_t)32 * g.K1 * ts); cv.take(w.w2q, 64 * 512 * ts); }
     cv.take(w.act1, mb * g.P1 * 32 * ts); cv.take(w.act2, mb * g.P2 * 64 * ts); cv.take(w.a3, mb * g.F * ts);
     cv.take(w.fc_part, (size_t)c.fc_groups * mb * 512 * 4);
     cv.take(w.adv_part, (1 + 2 * NRM_BLOCKS) * 8);
@@ -165,6 +166,9 @@ extern "C" int32_t hts_create(const hts_net_desc *desc, int32_t max_act_batch, i
         for (int *rows : {&c.conv1_slab_rows, &c.conv12_rows, &c.conv1_wgrad_slab_rows, &c.conv1_wgrad_image_rows})
             if (*rows <= c.small_b) *rows = c.small_b < (1 << 20) ? c.small_b + 1 : 1 << 20;
     }
+    // (the knobs above compare kernels of a layer each)
+    c.conv12_rows_kernel = !getenv("HTS_TILE16_BELOW") && !getenv("HTS_CONV1_SLAB_ROWS") && !getenv("HTS_SMALL_BATCH");
+    if (const char *cr = getenv("HTS_CONV12_ROWS_KERNEL")) c.conv12_rows_kernel = atoi(cr) != 0;     // tuning knob, same bits either way
     c.ws = Workspace();
     Carver size_pass;
     carve(c, size_pass);

@@ -28,6 +28,7 @@ __device__ __forceinline__ void load_vec(const float *p, float (&v)[8])
 //                         channel-innermost order f' = p*64 + c), through an LDS tile so both sides stay coalesced
 //   [nb_fc, +nb_conv)     conv2.w / conv3.w -> wf2, wf3 (taps outermost) and, for the learner, wd2, wd3
 //   [.., +nb_w1)          conv1.w -> w1s
+//                         (and conv1.w, conv2.w in fragment order -> w1q, w2q)
 //   [.., +nb_hb)          biases and heads -> hb (fp32)
 // ------------------------------------------------------------------------------------------------------------
 struct PrepArgs {
@@ -35,6 +36,7 @@ struct PrepArgs {
     Geom g;
     ShadowOffsets sh;
     void *w1s, *wf2, *wf3, *wfc, *wd2, *wd3, *wfcd;
+    void *w1q, *w2q;          // (null: not kept)
     float *hb;
     int nb_fc, nb_conv, nb_w1, nb_hb;
     int learn;
@@ -79,6 +81,7 @@ template <typename T> __global__ __launch_bounds__(256) void prep_kernel(const P
             const int n = i / 512, r = i % 512, c = r / 16, tap = r % 16;
             const T w = from_f32<T>(params[a.g.w2 + i]);
             wf2[n * 512 + tap * 32 + c] = w;
+            if (a.w2q) ((T *)a.w2q)[frag16(n, tap * 32 + c, 16)] = w;
             if (a.learn) wd2[c * 1024 + tap * 64 + n] = w;
         }
         if (i < 64 * 64 * 9) {                // conv3.w[n][c][u][v], 64 x 64 x 3 x 3
@@ -92,7 +95,11 @@ template <typename T> __global__ __launch_bounds__(256) void prep_kernel(const P
     blk -= a.nb_conv;
     if (blk < a.nb_w1) {
         const int i = blk * 256 + t;
-        if (i < 32 * a.g.K1) ((T *)a.w1s)[i] = from_f32<T>(params[a.g.w1 + i]);
+        if (i < 32 * a.g.K1) {
+            const T w = from_f32<T>(params[a.g.w1 + i]);
+            ((T *)a.w1s)[i] = w;
+            if (a.w1q) ((T *)a.w1q)[frag16(i / a.g.K1, i % a.g.K1, a.g.K1 / 32)] = w;
+        }
         return;
     }
     blk -= a.nb_w1;
@@ -119,6 +126,7 @@ static PrepArgs prep_args(const Ctx &c, const float *params, bool learn)
     PrepArgs a;
     a.params = params; a.g = c.g; a.sh = c.sh;
     a.w1s = c.ws.w1s; a.wf2 = c.ws.wf2; a.wf3 = c.ws.wf3; a.wfc = c.ws.wfc;
+    a.w1q = c.ws.w1q; a.w2q = c.ws.w2q;
     a.wd2 = c.ws.wd2; a.wd3 = c.ws.wd3; a.wfcd = c.ws.wfcd; a.hb = c.ws.hb;
     a.nb_fc = (512 / 64) * (c.g.F / 64);
     a.nb_conv = (64 * 64 * 9 + 255) / 256;
@@ -1200,6 +1208,7 @@ template <typename T> __global__ __launch_bounds__(256) void adam_shadow_kernel(
             const int n = i / 512, r = i % 512, c = r / 16, tap = r % 16;
             const T w = from_f32<T>(update(p.g.w2 + i));
             wf2[n * 512 + tap * 32 + c] = w;
+            if (p.w2q) ((T *)p.w2q)[frag16(n, tap * 32 + c, 16)] = w;
             if (p.learn) wd2[c * 1024 + tap * 64 + n] = w;
         }
         if (i < 64 * 64 * 9) {                // conv3.w[n][c][u][v], 64 x 64 x 3 x 3
@@ -1213,7 +1222,11 @@ template <typename T> __global__ __launch_bounds__(256) void adam_shadow_kernel(
     blk -= p.nb_conv;
     if (blk < p.nb_w1) {
         const int i = blk * 256 + t;
-        if (i < 32 * p.g.K1) ((T *)p.w1s)[i] = from_f32<T>(update(p.g.w1 + i));
+        if (i < 32 * p.g.K1) {
+            const T w = from_f32<T>(update(p.g.w1 + i));
+            ((T *)p.w1s)[i] = w;
+            if (p.w1q) ((T *)p.w1q)[frag16(i / p.g.K1, i % p.g.K1, p.g.K1 / 32)] = w;
+        }
         return;
     }
     blk -= p.nb_w1;
