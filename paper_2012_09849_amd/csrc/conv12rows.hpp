@@ -1,15 +1,16 @@
-// conv1 and conv2 forward of a few bf16 frames (actor) in one kernel: a workgroup forms some rows of a sample's conv2 output, and the
-// conv1 positions under them for itself.
+// conv1 and conv2 forward, and conv3 where it fits, of a few bf16 frames (actor) in one kernel: a workgroup forms some rows of a sample's
+// conv2 output, or a row of its conv3 output, and the positions of the layers below that it needs for itself.
 //
 // A call of few rows is a chain of launches, each with a start, a first round trip to memory and an end of its own, and little between them;
-// this takes one link out.  Neighbouring workgroups form the same conv1 rows twice, which costs matrix instructions of which a unit has plenty.
-// Eight wavefronts: all convert pixels to an LDS image and form conv1's segment sums (a segment is an input channel: one or two channels to a
-// wavefront, so that a weight is read by one wavefront only), which meet in LDS in binary32 and are added there in channel order;
-// four of them, 16 output channels each, then form conv2, whose weights they requested at the start.  Same k order, segments and epilogues as
-// the other kernels, hence the same bits.
-// What bounds it: a rollout's step of 16 4x84x84 frames takes 17.4 us with a launch for each layer and 14.1 with this, of which the kernel body, behind a
-// launch of 2.4, about 2: the first round trip, conv1 0.3, sums 0.4, conv2 and its store 1.0.  Weights from rows instead of in fragment order: 15.4
-// (16 lines an instruction, on two to four of an L2's channels); 16x72x96 frames, 16 rows 18.7, 17.4 from rows, 15.6.
+// this takes links out.  Neighbouring workgroups form the same positions again (conv1's up to 2.8 times), which costs matrix instructions of
+// which a unit has plenty.  Eight wavefronts: all convert pixels to an LDS image and form conv1's segment sums (a segment is an input channel: one
+// or two channels to a wavefront, so that a weight is read by one wavefront only), which meet in LDS in binary32 and are added there in channel
+// order; four of them, 16 output channels each, then form conv2, the others conv3, from weights that they requested at the start.  Same k order,
+// segments and epilogues as the other kernels, hence the same bits.
+// What bounds it: a rollout's step of 32 4x84x84 frames takes 19.0 us with a launch for each layer, 16.6 with conv1 and conv2 here and 13.6 with conv3
+// too.  The kernel's body of these 16.6, behind a launch of 2.4: the first round trip, conv1 1.1, sums 0.5, conv2 and its store 1.5.  Weights from
+// rows instead of in fragment order (16 lines an instruction, on two to four of an L2's channels): 17.4; 16x72x96 frames, 16 rows: 18.7, 17.4
+// from rows, 15.6.  Not kept: one row of conv2's output a workgroup of 4x84x84 frames (16 rows 14.1 against 12.8 with conv3).
 #pragma once
 #include "dmagemm.hpp"
 
@@ -18,17 +19,18 @@ namespace hts {
 struct Conv12RowsArgs {
     const uint8_t *obs;
     const int32_t *index;
-    const bf16_t *w1, *w2;  // [32][64 C], [64][512], in fragment order
-    const float *b1, *b2;
-    bf16_t *out;            // [B][HO*WO][64]
+    const bf16_t *w1, *w2, *w3;  // [32][64 C], [64][512], [64][576], in fragment order
+    const float *b1, *b2, *b3;
+    bf16_t *out;            // [B][HO*WO][64]; with conv3 [B][64][(HO-2)*(WO-2)]
     int B;
 };
 
-// NR_ rows of conv2's output, cut into XS_ pieces of a row
-template <int C_, int H_, int W_, int NR_, int XS_, int WAVES_PER_EU_> struct Conv12Rows {
-    static constexpr int C = C_, H = H_, W = W_, NR = NR_, XS = XS_, WAVES_PER_EU = WAVES_PER_EU_;
+// NR_ rows of conv2's output, cut into XS_ pieces of a row; CONV3_: the three rows under a row of conv3's output, and that row
+template <int C_, int H_, int W_, int NR_, int XS_, bool CONV3_ = false> struct Conv12Rows {
+    static constexpr int C = C_, H = H_, W = W_, NR = NR_, XS = XS_;
+    static constexpr bool CONV3 = CONV3_;
     static constexpr int H1 = (H - 8) / 4 + 1, W1 = (W - 8) / 4 + 1, HO = (H1 - 4) / 2 + 1, WO = (W1 - 4) / 2 + 1;
-    static constexpr int XO = WO / XS, PARTS = HO / NR * XS;                        // outputs of a row; workgroups of a sample
+    static constexpr int XO = WO / XS, PARTS = CONV3 ? HO - 2 : HO / NR * XS;       // outputs of a row; workgroups of a sample
     static constexpr int PH = 2 * NR + 2, PW = 2 * XO + 2, POS = PH * PW;           // conv1 positions
     static constexpr int IH = 4 * PH + 4, IW = 4 * PW + 4;                          // pixels under them
     static constexpr bool WHOLE = XS == 1 && IW == W;                               // rows of pixels lie one after the other
@@ -38,14 +40,16 @@ template <int C_, int H_, int W_, int NR_, int XS_, int WAVES_PER_EU_> struct Co
     static constexpr int IMG = C * CH, SUMS = C * POS * TP * 4, LDS = IMG + SUMS + POS * AP;
     static constexpr int PAIRS = C * 2 / 8;                                         // (channel, half of the outputs) of a wavefront
     static constexpr int TILES1 = POS / 16, OUTS = NR * XO, TILES2 = (OUTS + 15) / 16;
-    static_assert(HO % NR == 0 && WO % XS == 0 && POS % 16 == 0 && C % 4 == 0, "shares");
+    static constexpr int STEP = CONV3 ? 1 : NR, STEPS2 = CONV3 ? 18 : 16, AP2 = 144;        // rows from workgroup to workgroup; bytes of a conv2 pixel
+    static_assert(!CONV3 || (NR == 3 && XS == 1 && OUTS * AP2 <= SUMS && WO <= 18), "conv3");
+    static_assert((CONV3 || HO % NR == 0) && WO % XS == 0 && POS % 16 == 0 && C % 4 == 0, "shares");
     static_assert(W % 8 == 0 || WHOLE, "rows begin at a multiple of 8 bytes");
-    static_assert((H * W) % 8 == 0 && (WHOLE ? (8 * NR * W) % 8 == 0 && IH * W % 8 == 0 : (8 * XO) % 8 == 0), "vectors");
+    static_assert((H * W) % 8 == 0 && (WHOLE ? (8 * W) % 8 == 0 && IH * W % 8 == 0 : (8 * XO) % 8 == 0), "vectors");
     static_assert(WHOLE || 8 * XO * (XS - 1) + 8 * VR <= W, "the last vector of a row lies in it");
-    static_assert(8 * NR * (HO / NR - 1) + IH <= H && IMG % 16 == 0 && SUMS % 16 == 0 && LDS <= 160 * 1024, "shape");
+    static_assert(8 * STEP * (PARTS / XS - 1) + IH <= H && IMG % 16 == 0 && SUMS % 16 == 0 && LDS <= 160 * 1024, "shape");
 };
 
-template <class S> __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(S::WAVES_PER_EU, S::WAVES_PER_EU))) void conv12_rows_kernel(const Conv12RowsArgs a)
+template <class S> __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void conv12_rows_kernel(const Conv12RowsArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char c12r_smem[];
     constexpr int CPW = S::PAIRS > 1 ? S::PAIRS / 2 : 1, HPC = S::PAIRS > 1 ? 2 : 1;      // channels of a wavefront, halves of each
@@ -55,7 +59,7 @@ template <class S> __global__ __launch_bounds__(512) __attribute__((amdgpu_waves
     // a sample's workgroups on one XCD: they share pixels
     const int slot = (int)blockIdx.x >> 3, b = (slot / S::PARTS) * 8 + ((int)blockIdx.x & 7), part = slot % S::PARTS;
     if (b >= a.B) return;
-    const int oy0 = (part / S::XS) * S::NR, ox0 = (part % S::XS) * S::XO;
+    const int oy0 = (part / S::XS) * S::STEP, ox0 = (part % S::XS) * S::XO;
     const uint8_t *src = a.obs + (long long)(a.index ? a.index[b] : b) * (S::C * S::H * S::W) + 8 * oy0 * S::W + 8 * ox0;
     uint2 raw[S::NP];
 #pragma unroll
@@ -72,14 +76,15 @@ template <class S> __global__ __launch_bounds__(512) __attribute__((amdgpu_waves
 #pragma unroll
             for (int t = 0; t < 2; ++t) w1[c][h][t] = *reinterpret_cast<const bf16x8 *>(a.w1 + (((half0 + h) * (2 * S::C) + 2 * (ch0 + c) + t) * 64 + lane) * 8);
     const f32x4 bias1 = *reinterpret_cast<const f32x4 *>(a.b1 + 4 * (tid & 7));
-    // (waves 0-3, which form nothing of conv2, ask for bytes behind the end of an empty buffer: one count of loads under way for all, so that
-    // nobody waits for conv2's weights before they are used)
+    // Waves 4-7 form conv2, 0-3 conv3.  (Without it these ask for bytes behind the end of an empty buffer: one count of loads under way for
+    // all, so that nobody waits for conv2's weights before they are used.)
     const int oc = 16 * (w & 3);
-    const __amdgpu_buffer_rsrc_t from2 = dma_source(a.w2, w < 4 ? 0u : 64u * 1024u);
-    bf16x8 w2[16];
+    const __amdgpu_buffer_rsrc_t wsrc = dma_source(w < 4 && S::CONV3 ? a.w3 : a.w2, w < 4 ? (S::CONV3 ? 72u * 1024u : 0u) : 64u * 1024u);
+    const int wat = (w < 4 ? 18 * 64 : 16 * 64) * oc + 16 * lane;
+    bf16x8 w2[S::STEPS2];
 #pragma unroll
-    for (int t = 0; t < 16; ++t) w2[t] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(from2, oc * 1024 + 16 * lane, 1024 * t, 0));
-    const f32x4 bias2 = *reinterpret_cast<const f32x4 *>(a.b2 + oc + 4 * kq);
+    for (int t = 0; t < S::STEPS2; ++t) w2[t] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(wsrc, wat, 1024 * t, 0));
+    const f32x4 bias2 = *reinterpret_cast<const f32x4 *>((w < 4 && S::CONV3 ? a.b3 : a.b2) + oc + 4 * kq);
     __builtin_amdgcn_sched_barrier(0);
     // ---- pixels ----
 #pragma unroll
@@ -169,55 +174,85 @@ template <class S> __global__ __launch_bounds__(512) __attribute__((amdgpu_waves
         if (p < S::POS) *reinterpret_cast<Vec<bf16_t, 4> *>(act + p * S::AP + 8 * (tid & 7)) = o;
     }
     __syncthreads();
-    if (w < 4) return;
     // ---- conv2 ----
-    uint32_t at[S::TILES2];
+    auto conv2 = [&](unsigned char *act2) {
+        uint32_t at[S::TILES2];
 #pragma unroll
-    for (int i = 0; i < S::TILES2; ++i) {
-        const int q = min(16 * i + li, S::OUTS - 1), y = q / S::XO, x = q - y * S::XO;
-        at[i] = (uint32_t)((2 * y * S::PW + 2 * x) * S::AP + 16 * kq);
-    }
-    f32x4 tot[S::TILES2];
+        for (int i = 0; i < S::TILES2; ++i) {
+            const int q = min(16 * i + li, S::OUTS - 1), y = q / S::XO, x = q - y * S::XO;
+            at[i] = (uint32_t)((2 * y * S::PW + 2 * x) * S::AP + 16 * kq);
+        }
+        f32x4 tot[S::TILES2];
 #pragma unroll
-    for (int i = 0; i < S::TILES2; ++i) tot[i] = zero;
-    bf16x8 pv[4][S::TILES2][2];                                // four segments under way; segment sg: taps (u, v) and (u, v + 1)
-    auto read2 = [&](int sg) {
-        const int u = sg >> 1, v = 2 * (sg & 1);
-#pragma unroll
-        for (int i = 0; i < S::TILES2; ++i)
-#pragma unroll
-            for (int e = 0; e < 2; ++e) pv[sg & 3][i][e] = *reinterpret_cast<const bf16x8 *>(act + at[i] + (u * S::PW + v + e) * S::AP);
-    };
-    f32x4 acc[2][S::TILES2];
-    auto add = [&](int set) {
-#pragma unroll
-        for (int i = 0; i < S::TILES2; ++i)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) tot[i][r] += acc[set][i][r];
-    };
-#pragma unroll
-    for (int sg = 0; sg < 4; ++sg) read2(sg);
-#pragma unroll
-    for (int sg = 0; sg < 8; ++sg) {
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int e = 0; e < 2; ++e)
+        for (int i = 0; i < S::TILES2; ++i) tot[i] = zero;
+        bf16x8 pv[4][S::TILES2][2];                                // four segments under way; segment sg: taps (u, v) and (u, v + 1)
+        auto read2 = [&](int sg) {
+            const int u = sg >> 1, v = 2 * (sg & 1);
 #pragma unroll
             for (int i = 0; i < S::TILES2; ++i)
-                acc[sg & 1][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w2[2 * sg + e], pv[sg & 3][i][e], e == 0 ? zero : acc[sg & 1][i], 0, 0, 0);
-        if (sg < 4) read2(sg + 4);
-        if (sg > 0) add((sg - 1) & 1);                         // (the segment before: this one's products are under way)
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    add(1);
 #pragma unroll
-    for (int i = 0; i < S::TILES2; ++i) {
-        const int q = 16 * i + li, y = q / S::XO, x = q - y * S::XO;
-        if (q >= S::OUTS) continue;
-        Vec<bf16_t, 4> o;
+                for (int e = 0; e < 2; ++e) pv[sg & 3][i][e] = *reinterpret_cast<const bf16x8 *>(act + at[i] + (u * S::PW + v + e) * S::AP);
+        };
+        f32x4 acc[2][S::TILES2];
+        auto add = [&](int set) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) { const float t = tot[i][r] + bias2[r]; o[r] = from_f32<bf16_t>(t > 0.0f ? t : 0.0f); }
-        *reinterpret_cast<Vec<bf16_t, 4> *>(a.out + ((long long)b * (S::HO * S::WO) + (oy0 + y) * S::WO + ox0 + x) * 64 + oc + 4 * kq) = o;
+            for (int i = 0; i < S::TILES2; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) tot[i][r] += acc[set][i][r];
+        };
+#pragma unroll
+        for (int sg = 0; sg < 4; ++sg) read2(sg);
+#pragma unroll
+        for (int sg = 0; sg < 8; ++sg) {
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+#pragma unroll
+                for (int i = 0; i < S::TILES2; ++i)
+                    acc[sg & 1][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w2[2 * sg + e], pv[sg & 3][i][e], e == 0 ? zero : acc[sg & 1][i], 0, 0, 0);
+            if (sg < 4) read2(sg + 4);
+            if (sg > 0) add((sg - 1) & 1);                         // (the segment before: this one's products are under way)
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        add(1);
+#pragma unroll
+        for (int i = 0; i < S::TILES2; ++i) {
+            const int q = 16 * i + li, y = q / S::XO, x = q - y * S::XO;
+            if (q >= S::OUTS) continue;
+            Vec<bf16_t, 4> o;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) { const float t = tot[i][r] + bias2[r]; o[r] = from_f32<bf16_t>(t > 0.0f ? t : 0.0f); }
+            if constexpr (S::CONV3) *reinterpret_cast<Vec<bf16_t, 4> *>(act2 + q * S::AP2 + 2 * (oc + 4 * kq)) = o;
+            else *reinterpret_cast<Vec<bf16_t, 4> *>(a.out + ((long long)b * (S::HO * S::WO) + (oy0 + y) * S::WO + ox0 + x) * 64 + oc + 4 * kq) = o;
+        }
+    };
+    unsigned char *act2 = c12r_smem + S::IMG;                  // (over the sums)
+    if (w >= 4) conv2(act2);
+    if constexpr (S::CONV3) {
+        __syncthreads();
+        if (w >= 4) return;
+        // ---- conv3: positions of one row, segments of a tap row ----
+        constexpr int W3 = S::WO - 2, P3 = (S::HO - 2) * W3;
+        const unsigned char *from = act2 + min(li, W3 - 1) * S::AP2 + 16 * kq;
+        bf16x8 pv[18];
+#pragma unroll
+        for (int t = 0; t < 18; ++t) pv[t] = *reinterpret_cast<const bf16x8 *>(from + (t / 6 * S::WO + t / 2 % 3) * S::AP2 + t % 2 * 64);
+        f32x4 acc[3], tot = zero;
+#pragma unroll
+        for (int t = 0; t < 6; ++t)
+#pragma unroll
+            for (int u = 0; u < 3; ++u) acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w2[6 * u + t], pv[6 * u + t], t == 0 ? zero : acc[u], 0, 0, 0);
+#pragma unroll
+        for (int u = 0; u < 3; ++u)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) tot[r] += acc[u][r];
+        if (li < W3) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float t = tot[r] + bias2[r];
+                a.out[(long long)b * (64 * P3) + (oc + 4 * kq + r) * P3 + oy0 * W3 + li] = from_f32<bf16_t>(t > 0.0f ? t : 0.0f);
+            }
+        }
     }
 }
 

@@ -503,13 +503,13 @@ static hipError_t launch_conv1_slab(Ctx &c, const uint8_t *obs, const int32_t *i
 }
 
 // ... and conv12_rows_kernel: actor calls of so few rows that each workgroup has a compute unit of its XCD for itself (two workgroups on a
-// unit, or a second round, cost more than the launch they save).  A rollout's step, us, a launch each or conv12_kernel / this:
-// 4x84x84 frames 1 row 15.7 / 13.2, 8 16.4 / 13.9, 16 17.4 / 14.1, 24 18.7 / 15.1, 32 19.2 / 16.6, 48 21.0 / 18.2, 80 22.3 / 19.5 (96, 1.1 workgroups a
-// unit: 24.4 / 27.6); 16x72x96 1 17.0 / 14.4, 8 18.0 / 15.2, 16 18.7 / 15.6 (18: 19.2 / 23.7).  One row of conv2's output a workgroup while that
-// fits, else three: 24 rows 15.1 / 16.3, 32 rows (288 workgroups of one row) 16.7 / 16.5.
-typedef Conv12Rows<4, 84, 84, 1, 1, 2> C12R_ATARI1;
-typedef Conv12Rows<4, 84, 84, 3, 1, 2> C12R_ATARI3;
-typedef Conv12Rows<16, 72, 96, 1, 2, 2> C12R_FOOTBALL;
+// unit, or a second round, cost more than the launch they save).  A rollout's step, us, a launch for each layer (from 48 rows conv12_kernel) /
+// conv1 and conv2 here / conv3 too, a row of its output a workgroup: 4x84x84 frames 1 row 15.7 / 15.4 / 12.3, 8 16.3 / 15.4 / 12.7, 16 17.2 /
+// 15.6 / 12.8, 24 18.7 / 16.1 / 13.3, 32 19.0 / 16.7 / 13.6, 48 21.0 / 18.2, 80 22.3 / 19.5 (96, 1.1 workgroups a unit: 24.4 / 27.6); 16x72x96
+// 1 17.0 / 14.4, 8 18.0 / 15.2, 16 18.7 / 15.6 (18: 19.2 / 23.7).
+typedef Conv12Rows<4, 84, 84, 3, 1, true> C123R_ATARI;
+typedef Conv12Rows<4, 84, 84, 3, 1> C12R_ATARI;
+typedef Conv12Rows<16, 72, 96, 1, 2> C12R_FOOTBALL;
 template <class S> static bool conv12_rows_fits(const Ctx &c, const uint8_t *obs, int B)
 {
     return c.conv12_rows_kernel && c.g.C == S::C && c.g.H == S::H && c.g.W == S::W && !(((uintptr_t)obs) & 7u) && (B + 7) / 8 * S::PARTS <= c.cus / 8;
@@ -557,15 +557,16 @@ template <typename T> static hipError_t forward_t(Ctx &c, const uint8_t *obs, co
     // operands (its frame operand is bytes either way), up to about 200 workgroups.
     auto few32 = [&](int workgroups) { return workgroups < c.tile16_below; };
     // conv1 and conv2 in one kernel
-    const bool few = sizeof(T) == 2 && !learn && (conv12_rows_fits<C12R_ATARI3>(c, obs, B) || conv12_rows_fits<C12R_FOOTBALL>(c, obs, B));
+    const bool few = sizeof(T) == 2 && !learn && (conv12_rows_fits<C12R_ATARI>(c, obs, B) || conv12_rows_fits<C12R_FOOTBALL>(c, obs, B));
     const bool conv12 = few || (sizeof(T) == 2 && B >= c.conv12_rows && conv12_fits(g, obs));
+    const bool conv123 = few && conv12_rows_fits<C123R_ATARI>(c, obs, B);
     if (few) {
         Conv12RowsArgs a;
         a.obs = obs; a.index = index; a.w1 = (const bf16_t *)c.ws.w1q; a.w2 = (const bf16_t *)c.ws.w2q; a.b1 = hb + c.sh.b1; a.b2 = hb + c.sh.b2;
-        a.out = (bf16_t *)c.ws.act2; a.B = B;
-        SiteTimer tm(c, SITE_CONV1_FWD, SITE_CONV2_FWD);
-        if ((e = g.C == 16 ? launch_conv12_rows<C12R_FOOTBALL>(a, c.stream) : conv12_rows_fits<C12R_ATARI1>(c, obs, B) ? launch_conv12_rows<C12R_ATARI1>(a, c.stream)
-                 : launch_conv12_rows<C12R_ATARI3>(a, c.stream)) != hipSuccess) return e;
+        a.w3 = (const bf16_t *)c.ws.w3q; a.b3 = hb + c.sh.b3;
+        a.out = (bf16_t *)(conv123 ? c.ws.a3 : c.ws.act2); a.B = B;
+        SiteTimer tm(c, SITE_CONV1_FWD, SITE_CONV2_FWD, conv123 ? SITE_CONV3_FWD : SITE_CONV2_FWD);
+        if ((e = conv123 ? launch_conv12_rows<C123R_ATARI>(a, c.stream) : g.C == 16 ? launch_conv12_rows<C12R_FOOTBALL>(a, c.stream) : launch_conv12_rows<C12R_ATARI>(a, c.stream)) != hipSuccess) return e;
     } else if (conv12) {
         Conv12Args a;
         a.obs = obs; a.index = index; a.w1 = (const bf16_t *)c.ws.w1s; a.w2 = (const bf16_t *)c.ws.wf2; a.b1 = hb + c.sh.b1; a.b2 = hb + c.sh.b2;
@@ -628,7 +629,7 @@ template <typename T> static hipError_t forward_t(Ctx &c, const uint8_t *obs, co
         }
         if (e != hipSuccess) return e;
     }
-    {
+    if (!conv123) {
         ConvFwd<T, Layer3, true> p;
         p.M = B * g.P3; p.N = 64; p.K = 576; p.klen = 576;
         p.in = (const T *)c.ws.act2; p.wf = (const T *)c.ws.wf3; p.bias = hb + c.sh.b3; p.out = (T *)c.ws.a3;

@@ -32,7 +32,7 @@ struct Workspace {
     void *wf2, *wf3;          // conv2.w, conv3.w with taps outermost [64][(u,v,c)]
     void *wfc;                // fc.w [512][F]
     void *wd2, *wd3, *wfcd;   // learner only: conv weights for the input gradients; fc.w as [(p,c)][512]
-    void *w1q, *w2q;          // bf16 actor only: conv1.w (k = (c,u,v)) and conv2.w (k = (u,v,c)) in fragment order, see frag16
+    void *w1q, *w2q, *w3q;    // bf16 actor only: conv1.w (k = (c,u,v)), conv2.w and conv3.w (k = (u,v,c)) in fragment order, see frag16
     float *hb;                // fp32 block: biases of all layers and the two heads (offsets in Ctx::sh)
     // forward activations
     void *act1, *act2, *a3;   // T
@@ -80,7 +80,7 @@ struct Ctx {
     int fc_slices;            // slices of fc_part the last forward pass wrote (fc_groups, or 1)
     int conv1_slab_rows;      // bf16 batches of at least this many 16x72x96 frames take the slab conv1 forward kernel
     int conv12_rows;          // bf16 batches of at least this many 4x84x84 frames take conv1 and conv2 in one kernel
-    bool conv12_rows_kernel;  // bf16 actor calls of few 4x84x84 or 16x72x96 frames take conv1 and conv2 in one kernel, a workgroup for some rows
+    bool conv12_rows_kernel;  // bf16 actor calls of few 4x84x84 or 16x72x96 frames take conv1 and conv2, up to 32 of the former conv3 too, in one kernel, a workgroup for some rows
     int conv1_wgrad_slab_rows, conv1_wgrad_image_rows;      // likewise the weight-gradient kernels with the frame in LDS
     bool synced;              // the workspace's copy of the network matches the last parameter vector handed in
     bool synced_learn;        // ... including the learner-only parts

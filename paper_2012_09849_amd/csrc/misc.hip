@@ -28,7 +28,7 @@ __device__ __forceinline__ void load_vec(const float *p, float (&v)[8])
 //                         channel-innermost order f' = p*64 + c), through an LDS tile so both sides stay coalesced
 //   [nb_fc, +nb_conv)     conv2.w / conv3.w -> wf2, wf3 (taps outermost) and, for the learner, wd2, wd3
 //   [.., +nb_w1)          conv1.w -> w1s
-//                         (and conv1.w, conv2.w in fragment order -> w1q, w2q)
+//                         (and conv1.w, conv2.w, conv3.w in fragment order -> w1q, w2q, w3q)
 //   [.., +nb_hb)          biases and heads -> hb (fp32)
 // ------------------------------------------------------------------------------------------------------------
 struct PrepArgs {
@@ -36,7 +36,7 @@ struct PrepArgs {
     Geom g;
     ShadowOffsets sh;
     void *w1s, *wf2, *wf3, *wfc, *wd2, *wd3, *wfcd;
-    void *w1q, *w2q;          // (null: not kept)
+    void *w1q, *w2q, *w3q;    // (null: not kept)
     float *hb;
     int nb_fc, nb_conv, nb_w1, nb_hb;
     int learn;
@@ -88,6 +88,7 @@ template <typename T> __global__ __launch_bounds__(256) void prep_kernel(const P
             const int n = i / 576, r = i % 576, c = r / 9, tap = r % 9;
             const T w = from_f32<T>(params[a.g.w3 + i]);
             wf3[n * 576 + tap * 64 + c] = w;
+            if (a.w3q) ((T *)a.w3q)[frag16(n, tap * 64 + c, 18)] = w;
             if (a.learn) wd3[c * 576 + tap * 64 + n] = w;
         }
         return;
@@ -126,7 +127,7 @@ static PrepArgs prep_args(const Ctx &c, const float *params, bool learn)
     PrepArgs a;
     a.params = params; a.g = c.g; a.sh = c.sh;
     a.w1s = c.ws.w1s; a.wf2 = c.ws.wf2; a.wf3 = c.ws.wf3; a.wfc = c.ws.wfc;
-    a.w1q = c.ws.w1q; a.w2q = c.ws.w2q;
+    a.w1q = c.ws.w1q; a.w2q = c.ws.w2q; a.w3q = c.ws.w3q;
     a.wd2 = c.ws.wd2; a.wd3 = c.ws.wd3; a.wfcd = c.ws.wfcd; a.hb = c.ws.hb;
     a.nb_fc = (512 / 64) * (c.g.F / 64);
     a.nb_conv = (64 * 64 * 9 + 255) / 256;
@@ -1215,6 +1216,7 @@ template <typename T> __global__ __launch_bounds__(256) void adam_shadow_kernel(
             const int n = i / 576, r = i % 576, c = r / 9, tap = r % 9;
             const T w = from_f32<T>(update(p.g.w3 + i));
             wf3[n * 576 + tap * 64 + c] = w;
+            if (p.w3q) ((T *)p.w3q)[frag16(n, tap * 64 + c, 18)] = w;
             if (p.learn) wd3[c * 576 + tap * 64 + n] = w;
         }
         return;

@@ -1,5 +1,5 @@
-"""conv1 and conv2 of bf16 actor calls of few frames in one kernel, a workgroup for some rows of conv2's output, against a launch for each layer, bit for
-bit: sizes around the cuts between one row and three rows a workgroup and the other kernels, samples that do not fill the eight XCDs; parameters
+"""conv1 and conv2, or all three conv layers, of bf16 actor calls of few frames in one kernel, a workgroup for some rows, against a launch for each
+layer, bit for bit: sizes around the cuts between them and the other kernels, samples that do not fill the eight XCDs; parameters
 that an update has just changed; frames at a multiple of 8 bytes but not of 16, and of 4."""
 import numpy as np
 import pytest
@@ -16,7 +16,7 @@ def _frames(shape, n, seed):
     return torch.randint(0, 256, (n, *shape), device="cuda", generator=torch.Generator(device="cuda").manual_seed(seed), dtype=torch.uint8)
 
 
-@pytest.mark.parametrize("shape, sizes", [(ATARI, (1, 7, 8, 9, 24, 25, 47, 80, 81)), (FOOTBALL, (1, 5, 8, 9, 16, 17))])
+@pytest.mark.parametrize("shape, sizes", [(ATARI, (1, 7, 8, 9, 25, 32, 33, 47, 80, 81)), (FOOTBALL, (1, 5, 8, 9, 16, 17))])
 def test_actor_calls_agree_bitwise(hts, shape, sizes, monkeypatch):  # noqa: F811
     n, A = max(sizes), 19
     params, obs = dev(syn.init_params(61, *shape, A, bias_scale=0.05)), _frames(shape, n, 62)
