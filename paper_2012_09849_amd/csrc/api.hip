@@ -86,7 +86,7 @@ void carve(Ctx &c, Carver &cv)
     const size_t mb = (size_t)c.max_b, ml = (size_t)c.max_learn;
     cv.take(w.w1s, (size_t)32 * g.K1 * ts); cv.take(w.wf2, 64 * 512 * ts); cv.take(w.wf3, 64 * 576 * ts);
     cv.take(w.wfc, (size_t)512 * g.F * ts); cv.take(w.hb, (size_t)c.sh.count * 4);
-    if (ts == 2 && c.max_act > 0) { cv.take(w.w1q, (size_t)32 * g.K1 * ts); cv.take(w.w2q, 64 * 512 * ts); cv.take(w.w3q, 64 * 576 * ts); }
+    cv.take(w.w1q, (size_t)32 * g.K1 * ts); cv.take(w.w2q, 64 * 512 * ts); cv.take(w.w3q, 64 * 576 * ts);
     cv.take(w.act1, mb * g.P1 * 32 * ts); cv.take(w.act2, mb * g.P2 * 64 * ts); cv.take(w.a3, mb * g.F * ts);
     cv.take(w.fc_part, (size_t)c.fc_groups * mb * 512 * 4);
     cv.take(w.adv_part, (1 + 2 * NRM_BLOCKS) * 8);

@@ -588,8 +588,8 @@ template <typename T> static hipError_t forward_t(Ctx &c, const uint8_t *obs, co
             bool done = false;
             if constexpr (sizeof(T) == 4) {
                 if (small && few32((p.M + 31) / 64)) {
-                    e = g.K1 >= 1024 ? launch_wsgemm16<Conv1Fwd<T>, 16, Conv1Fwd<T>::SEG>(p, c.stream)
-                                     : launch_wsgemm16<Conv1Fwd<T>, 4, Conv1Fwd<T>::SEG>(p, c.stream);
+                    e = g.K1 >= 1024 ? launch_wsgemm16<Conv1Fwd<T>, 16, Conv1Fwd<T>::SEG, true>(p, c.stream, c.ws.w1q)
+                                     : launch_wsgemm16<Conv1Fwd<T>, 4, Conv1Fwd<T>::SEG, true>(p, c.stream, c.ws.w1q);
                     done = true;
                 }
             }
@@ -622,7 +622,7 @@ template <typename T> static hipError_t forward_t(Ctx &c, const uint8_t *obs, co
             else if (sizeof(T) == 2 && !small && foot_grid && B >= 3072) e = launch_regconv<RegConv<Layer2, 17, 23, ConvFwd<bf16_t, Layer2, false>::SEG>>(r, c.cus, c.stream);
             else
             if (small && few32(((p.M + 31) / 32) * 2))
-                e = launch_wsgemm16<ConvFwd<T, Layer2, false>, 8, ConvFwd<T, Layer2, false>::SEG>(p, c.stream);
+                e = launch_wsgemm16<ConvFwd<T, Layer2, false>, 8, ConvFwd<T, Layer2, false>::SEG, true>(p, c.stream, c.ws.w2q);
             else
             e = small ? launch_wsgemm<ConvFwd<T, Layer2, false>, 8, ConvFwd<T, Layer2, false>::SEG, false>(p, c.stream)
                       : launch_rows(p, c.stream);
@@ -639,7 +639,7 @@ template <typename T> static hipError_t forward_t(Ctx &c, const uint8_t *obs, co
         {
             SiteTimer tm(c, learn ? SITE_CONV3_FWD_LEARN : SITE_CONV3_FWD);
             if (small && few32(((p.M + 31) / 32) * 2))     // binary32: 6 segments of 96; bfloat16: 3 of 192 (the fold needs 4 wavefronts)
-                e = launch_wsgemm16<ConvFwd<T, Layer3, true>, (sizeof(T) == 4 ? 6 : 4), ConvFwd<T, Layer3, true>::SEG>(p, c.stream);
+                e = launch_wsgemm16<ConvFwd<T, Layer3, true>, (sizeof(T) == 4 ? 6 : 4), ConvFwd<T, Layer3, true>::SEG, true>(p, c.stream, c.ws.w3q);
             else if (small) e = launch_wsgemm<ConvFwd<T, Layer3, true>, (sizeof(T) == 4 ? 8 : 4), ConvFwd<T, Layer3, true>::SEG, false, true>(p, c.stream);
             else if (sizeof(T) == 2 && atari_grid) {       // large bf16 batch, 9x9 input: activations resident in LDS
                 ImgConvArgs a = {};
@@ -670,7 +670,7 @@ template <typename T> static hipError_t forward_t(Ctx &c, const uint8_t *obs, co
             // (also when 16-row tiles leave fewer padded rows: 80 rows are five tiles of 16 but three of 32; 13.8 -> 10.9 us)
             const bool less_padding = c.tile16_below > 0 && ((B + 15) / 16) * 16 < ((B + 31) / 32) * 32;
             if (small && (few32(((B + 31) / 32) * 16 * c.fc_groups) || less_padding))
-                e = launch_wsgemm16<FcFwd<T>, 8, FcFwd<T>::SEG>(p, c.stream, FC_GROUP_K / FcFwd<T>::SEG);
+                e = launch_wsgemm16<FcFwd<T>, 8, FcFwd<T>::SEG>(p, c.stream, nullptr, FC_GROUP_K / FcFwd<T>::SEG);
             else
             e = small ? launch_wsgemm<FcFwd<T>, 8, FcFwd<T>::SEG, false>(p, c.stream, FC_GROUP_K / FcFwd<T>::SEG)
                       : launch_rows(p, c.stream);

@@ -17,11 +17,13 @@ constexpr int FC_GROUP_K = 512;    // the FC layer's reduction is cut into group
 // Offsets inside Workspace::hb.
 struct ShadowOffsets { long long b1, b2, b3, fcb, piw, pib, vw, vb, count; };
 
-// Weights in fragment order: what a wavefront's lanes read for one 16x16x32 matrix instruction (16 outputs n, 32 k) lies together, 1 KB, in lane
-// order.  Read from rows, an instruction's operand lies in 16 lines, 64 bytes of each, of two to four of an L2's channels.  steps: K / 32
-__host__ __device__ __forceinline__ int frag16(int n, int k, int steps)
+// Weights in fragment order: what a wavefront's lanes read at once for 16x16 matrix instructions (16 outputs n, 32 k in bf16, 16 in binary32) lies
+// together, 1 KB, in lane order.  Lane 16 q + n has k = 8 q .. 8 q + 7 in bf16 (one instruction), q, q + 4, q + 8 and q + 12 in binary32 (four).
+// Read from rows, such an operand lies in 16 lines, 64 bytes of each, of two to four of an L2's channels.
+template <typename T> __host__ __device__ __forceinline__ int frag16(int n, int k, int K)
 {
-    return (((n >> 4) * steps + (k >> 5)) * 64 + ((k >> 3) & 3) * 16 + (n & 15)) * 8 + (k & 7);
+    if constexpr (sizeof(T) == 2) return (((n >> 4) * (K >> 5) + (k >> 5)) * 64 + ((k >> 3) & 3) * 16 + (n & 15)) * 8 + (k & 7);
+    else return (((n >> 4) * (K >> 4) + (k >> 4)) * 64 + (k & 3) * 16 + (n & 15)) * 4 + ((k >> 2) & 3);
 }
 
 struct Workspace {
@@ -32,7 +34,7 @@ struct Workspace {
     void *wf2, *wf3;          // conv2.w, conv3.w with taps outermost [64][(u,v,c)]
     void *wfc;                // fc.w [512][F]
     void *wd2, *wd3, *wfcd;   // learner only: conv weights for the input gradients; fc.w as [(p,c)][512]
-    void *w1q, *w2q, *w3q;    // bf16 actor only: conv1.w (k = (c,u,v)), conv2.w and conv3.w (k = (u,v,c)) in fragment order, see frag16
+    void *w1q, *w2q, *w3q;    // conv1.w (k = (c,u,v)), conv2.w and conv3.w (k = (u,v,c)) once more in fragment order, see frag16
     float *hb;                // fp32 block: biases of all layers and the two heads (offsets in Ctx::sh)
     // forward activations
     void *act1, *act2, *a3;   // T

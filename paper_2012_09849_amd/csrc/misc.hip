@@ -36,7 +36,7 @@ struct PrepArgs {
     Geom g;
     ShadowOffsets sh;
     void *w1s, *wf2, *wf3, *wfc, *wd2, *wd3, *wfcd;
-    void *w1q, *w2q, *w3q;    // (null: not kept)
+    void *w1q, *w2q, *w3q;
     float *hb;
     int nb_fc, nb_conv, nb_w1, nb_hb;
     int learn;
@@ -81,14 +81,14 @@ template <typename T> __global__ __launch_bounds__(256) void prep_kernel(const P
             const int n = i / 512, r = i % 512, c = r / 16, tap = r % 16;
             const T w = from_f32<T>(params[a.g.w2 + i]);
             wf2[n * 512 + tap * 32 + c] = w;
-            if (a.w2q) ((T *)a.w2q)[frag16(n, tap * 32 + c, 16)] = w;
+            ((T *)a.w2q)[frag16<T>(n, tap * 32 + c, 512)] = w;
             if (a.learn) wd2[c * 1024 + tap * 64 + n] = w;
         }
         if (i < 64 * 64 * 9) {                // conv3.w[n][c][u][v], 64 x 64 x 3 x 3
             const int n = i / 576, r = i % 576, c = r / 9, tap = r % 9;
             const T w = from_f32<T>(params[a.g.w3 + i]);
             wf3[n * 576 + tap * 64 + c] = w;
-            if (a.w3q) ((T *)a.w3q)[frag16(n, tap * 64 + c, 18)] = w;
+            ((T *)a.w3q)[frag16<T>(n, tap * 64 + c, 576)] = w;
             if (a.learn) wd3[c * 576 + tap * 64 + n] = w;
         }
         return;
@@ -99,7 +99,7 @@ template <typename T> __global__ __launch_bounds__(256) void prep_kernel(const P
         if (i < 32 * a.g.K1) {
             const T w = from_f32<T>(params[a.g.w1 + i]);
             ((T *)a.w1s)[i] = w;
-            if (a.w1q) ((T *)a.w1q)[frag16(i / a.g.K1, i % a.g.K1, a.g.K1 / 32)] = w;
+            ((T *)a.w1q)[frag16<T>(i / a.g.K1, i % a.g.K1, a.g.K1)] = w;
         }
         return;
     }
@@ -1209,14 +1209,14 @@ template <typename T> __global__ __launch_bounds__(256) void adam_shadow_kernel(
             const int n = i / 512, r = i % 512, c = r / 16, tap = r % 16;
             const T w = from_f32<T>(update(p.g.w2 + i));
             wf2[n * 512 + tap * 32 + c] = w;
-            if (p.w2q) ((T *)p.w2q)[frag16(n, tap * 32 + c, 16)] = w;
+            ((T *)p.w2q)[frag16<T>(n, tap * 32 + c, 512)] = w;
             if (p.learn) wd2[c * 1024 + tap * 64 + n] = w;
         }
         if (i < 64 * 64 * 9) {                // conv3.w[n][c][u][v], 64 x 64 x 3 x 3
             const int n = i / 576, r = i % 576, c = r / 9, tap = r % 9;
             const T w = from_f32<T>(update(p.g.w3 + i));
             wf3[n * 576 + tap * 64 + c] = w;
-            if (p.w3q) ((T *)p.w3q)[frag16(n, tap * 64 + c, 18)] = w;
+            ((T *)p.w3q)[frag16<T>(n, tap * 64 + c, 576)] = w;
             if (p.learn) wd3[c * 576 + tap * 64 + n] = w;
         }
         return;
@@ -1227,7 +1227,7 @@ template <typename T> __global__ __launch_bounds__(256) void adam_shadow_kernel(
         if (i < 32 * p.g.K1) {
             const T w = from_f32<T>(update(p.g.w1 + i));
             ((T *)p.w1s)[i] = w;
-            if (p.w1q) ((T *)p.w1q)[frag16(i / p.g.K1, i % p.g.K1, p.g.K1 / 32)] = w;
+            ((T *)p.w1q)[frag16<T>(i / p.g.K1, i % p.g.K1, p.g.K1)] = w;
         }
         return;
     }

@@ -313,8 +313,11 @@ __global__ __launch_bounds__(WAVES * 64) void wsgemm_kernel(const P p, const int
 // compare the kernel families bitwise), so with the same segments the results equal those of the other kernels.
 // Problems: A_ALONG_K and B_ALONG_K, plain store() epilogue (the forward layers).
 // ------------------------------------------------------------------------------------------------------------
-template <class P, int WAVES, int SEG>
-__global__ __launch_bounds__(WAVES * 64) void wsgemm16_kernel(const P p, const int spg)
+// BQ: the B operand, a weight matrix of whole tiles and segments, in fragment order (see frag16), straight into registers; else bq is not read.
+// A rollout's step, us, rows by way of LDS / fragments: binary32 84x84 frames 1 row 18.0 / 17.3, 16 21.6 / 20.5, 32 27.7 / 27.3, 16x72x96 frames 1 19.3 /
+// 18.3, 8 23.2 / 21.0, 16 30.5 / 25.5.  (FC's weights in this order would be written for every update of the learner, 3.2 MB in bf16.)
+template <class P, int WAVES, int SEG, bool BQ>
+__global__ __launch_bounds__(WAVES * 64) void wsgemm16_kernel(const P p, const int spg, const typename P::T *__restrict__ bq)
 {
     using T = typename P::T;
     using Tr = OperandTraits<T>;
@@ -326,8 +329,10 @@ __global__ __launch_bounds__(WAVES * 64) void wsgemm16_kernel(const P p, const i
     constexpr int LS = SEG + Tr::VEC;         // row pitch: a 16-byte step per row, so the 64 lanes of an operand read
                                               // (row i, k slot q) spread evenly over the banks
     constexpr int NA = 16 * SEG / VA / 64, NB = 16 * SEG / VB / 64;     // vectors per lane and panel
-    constexpr size_t PANEL_BYTES = (size_t)2 * 16 * LS * sizeof(T);
+    constexpr size_t PANEL_BYTES = (size_t)(BQ ? 1 : 2) * 16 * LS * sizeof(T);
     static_assert(PANEL_BYTES >= 1024, "the fold reuses a wavefront's panels for its 16x16 partial tile");
+    constexpr int FK = sizeof(T) == 4 ? 16 : 32, NQ = SEG / FK, FV = 16 / sizeof(T);      // k of a fragment; fragments of a segment; elements of a lane
+    static_assert(!BQ || SEG % FK == 0, "whole fragments");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int zb = blockIdx.z, M = rows_of(p, zb);
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -350,27 +355,33 @@ __global__ __launch_bounds__(WAVES * 64) void wsgemm16_kernel(const P p, const i
         const int kbeg = seg * SEG, kend = min(p.K, kbeg + SEG);
         Vec<T, VA> ra[NA];
         Vec<T, VB> rb[NB];
+        typedef T fragment __attribute__((ext_vector_type(FV)));
+        fragment rq[NQ];
+        if constexpr (BQ) {
+#pragma unroll
+            for (int j = 0; j < NQ; ++j) rq[j] = *reinterpret_cast<const fragment *>(bq + ((long long)((n0 >> 4) * (p.K / FK) + kbeg / FK + j) * 64 + lane) * FV);
+        }
 #pragma unroll
         for (int i = 0; i < NA; ++i) ra[i] = p.load_a(ca, kbeg + (pq + 4 * i) * VA, kend);
 #pragma unroll
-        for (int i = 0; i < NB; ++i) rb[i] = p.load_b(cb, kbeg + (pq + 4 * i) * VB, kend);
+        for (int i = 0; i < (BQ ? 0 : NB); ++i) rb[i] = p.load_b(cb, kbeg + (pq + 4 * i) * VB, kend);
 #pragma unroll
         for (int i = 0; i < NA; ++i) *reinterpret_cast<Vec<T, VA> *>(As + pr * LS + (pq + 4 * i) * VA) = ra[i];
 #pragma unroll
-        for (int i = 0; i < NB; ++i) *reinterpret_cast<Vec<T, VB> *>(Bs + pr * LS + (pq + 4 * i) * VB) = rb[i];
+        for (int i = 0; i < (BQ ? 0 : NB); ++i) *reinterpret_cast<Vec<T, VB> *>(Bs + pr * LS + (pq + 4 * i) * VB) = rb[i];
         // the panels are private to this wavefront and a wavefront's LDS operations execute in order
         __builtin_amdgcn_wave_barrier();
         f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
         if constexpr (sizeof(T) == 4) {        // slot t: lane (i, q) supplies k = 4 t + q
             const T *a = As + li * LS + kq, *b = Bs + li * LS + kq;
 #pragma unroll
-            for (int t = 0; t < SEG / 4; ++t) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[4 * t], b[4 * t], acc, 0, 0, 0);
+            for (int t = 0; t < SEG / 4; ++t) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[4 * t], BQ ? rq[BQ ? t / 4 : 0][t % 4] : b[4 * t], acc, 0, 0, 0);
         } else {                               // slot t: lane (i, q) supplies k = 32 t + 8 q .. + 7
             const T *a = As + li * LS + 8 * kq, *b = Bs + li * LS + 8 * kq;
 #pragma unroll
             for (int t = 0; t < SEG / 32; ++t)
                 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8 *>(a + 32 * t),
-                                                              *reinterpret_cast<const bf16x8 *>(b + 32 * t), acc, 0, 0, 0);
+                                                              BQ ? rq[BQ ? t : 0] : *reinterpret_cast<const bf16x8 *>(b + 32 * t), acc, 0, 0, 0);
         }
         return acc;
     };
@@ -405,14 +416,16 @@ __global__ __launch_bounds__(WAVES * 64) void wsgemm16_kernel(const P p, const i
     }
 }
 
-template <class P, int WAVES, int SEG> inline hipError_t launch_wsgemm16(const P &p, hipStream_t stream, int segs_per_group = 1 << 30)
+template <class P, int WAVES, int SEG, bool BQ = false>
+inline hipError_t launch_wsgemm16(const P &p, hipStream_t stream, const void *bq = nullptr, int segs_per_group = 1 << 30)
 {
+    if (BQ && (p.N % 16 != 0 || p.K % SEG != 0 || !bq)) return hipErrorInvalidValue;
     const int tiles = ((grid_rows(p) + 15) / 16) * ((p.N + 15) / 16);
     const int nseg = (p.K + SEG - 1) / SEG;
     if (tiles <= 0 || nseg <= 0) return hipSuccess;
     using T = typename P::T;
-    const size_t lds = (size_t)WAVES * 2 * 16 * (SEG + OperandTraits<T>::VEC) * sizeof(T);
-    auto kern = wsgemm16_kernel<P, WAVES, SEG>;
+    const size_t lds = (size_t)WAVES * (BQ ? 1 : 2) * 16 * (SEG + OperandTraits<T>::VEC) * sizeof(T);
+    auto kern = wsgemm16_kernel<P, WAVES, SEG, BQ>;
     static std::atomic<bool> attr_set{false};       // raise the dynamic-LDS limit once per instantiation (setting it twice is harmless)
     if (!attr_set.load(std::memory_order_acquire)) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
@@ -421,7 +434,7 @@ template <class P, int WAVES, int SEG> inline hipError_t launch_wsgemm16(const P
         attr_set.store(true, std::memory_order_release);
     }
     const int spg = segs_per_group < nseg ? segs_per_group : nseg;
-    hipLaunchKernelGGL(kern, dim3(tiles, (nseg + spg - 1) / spg, grid_batches(p)), dim3(WAVES * 64, 1, 1), lds, stream, p, spg);
+    hipLaunchKernelGGL(kern, dim3(tiles, (nseg + spg - 1) / spg, grid_batches(p)), dim3(WAVES * 64, 1, 1), lds, stream, p, spg, (const T *)bq);
     return hipGetLastError();
 }
 
