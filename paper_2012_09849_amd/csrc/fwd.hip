@@ -4,6 +4,7 @@
 #include "dmagemm.hpp"
 #include "imgconv.hpp"
 #include "regconv.hpp"
+#include "regconv3.hpp"
 #include "conv12.hpp"
 #include "conv12rows.hpp"
 
@@ -641,7 +642,19 @@ template <typename T> static hipError_t forward_t(Ctx &c, const uint8_t *obs, co
             if (small && few32(((p.M + 31) / 32) * 2))     // binary32: 6 segments of 96; bfloat16: 3 of 192 (the fold needs 4 wavefronts)
                 e = launch_wsgemm16<ConvFwd<T, Layer3, true>, (sizeof(T) == 4 ? 6 : 4), ConvFwd<T, Layer3, true>::SEG, true>(p, c.stream, c.ws.w3q);
             else if (small) e = launch_wsgemm<ConvFwd<T, Layer3, true>, (sizeof(T) == 4 ? 8 : 4), ConvFwd<T, Layer3, true>::SEG, false, true>(p, c.stream);
-            else if (sizeof(T) == 2 && atari_grid) {       // large bf16 batch, 9x9 input: activations resident in LDS
+            // Weights in registers: one sample a unit while that is all, else two at a time; in between, where a unit has three to five samples, imgconv's
+            // four at once have less in front of the first products.  us with an event bracket, imgconv / this, actor, 84x84 frames: 129 rows 10.5 / 8.7, 256
+            // 10.4 / 8.8, 300 10.7 / 10.0, 512 10.7 / 10.1, 768 11.2 / 12.1, 1024 11.8 / 12.4, 1536 16.8 / 15.3, 2048 17.6 / 16.8, 4096 26.7 / 24.5; 72x96: 203
+            // 10.2 / 8.8, 512 10.3 / 9.6, 1024 11.6 / 11.8, 2048 16.6 / 16.1; learner, 84x84: 256 11.0 / 9.5, 512 11.5 / 10.9, 1024 13.1 / 13.9, 2048 20.4 /
+            // 19.3; 72x96: 512 11.2 / 10.5, 2048 19.2 / 18.0
+            else if (sizeof(T) == 2 && (atari_grid || foot_grid) && (B <= 2 * c.cus || B >= 6 * c.cus)) {
+                RegConv3Args a = {};
+                a.in = (const bf16_t *)c.ws.act2; a.w = (const bf16_t *)c.ws.w3q; a.bias = hb + c.sh.b3;
+                a.out = (bf16_t *)c.ws.a3; a.out2 = learn ? (bf16_t *)c.ws.a3n : nullptr; a.B = B;
+                constexpr int SEG = ConvFwd<bf16_t, Layer3, true>::SEG;
+                if (atari_grid) e = B <= c.cus ? launch_regconv3<RegConv3<9, 9, 1, SEG>>(a, c.cus, c.stream) : launch_regconv3<RegConv3<9, 9, 2, SEG>>(a, c.cus, c.stream);
+                else e = B <= c.cus ? launch_regconv3<RegConv3<7, 10, 1, SEG>>(a, c.cus, c.stream) : launch_regconv3<RegConv3<7, 10, 2, SEG>>(a, c.cus, c.stream);
+            } else if (sizeof(T) == 2 && atari_grid) {       // large bf16 batch, 9x9 input: activations resident in LDS
                 ImgConvArgs a = {};
                 a.in = (const bf16_t *)c.ws.act2; a.w = (const bf16_t *)c.ws.wf3; a.bias = hb + c.sh.b3;
                 a.out = (bf16_t *)c.ws.a3; a.out2 = learn ? (bf16_t *)c.ws.a3n : nullptr; a.B = B;
