@@ -87,6 +87,8 @@ def load_library():
         lib.hts_normalize_advantages.argtypes = [C.c_void_p, C.c_void_p, C.c_int64]
         lib.hts_learner_step.argtypes = [C.c_void_p, C.POINTER(Buffer), C.c_void_p, C.POINTER(_OptStateC),
                                          C.POINTER(HParams), C.c_void_p]
+        lib.hts_learner_step_delayed.argtypes = [C.c_void_p, C.POINTER(Buffer), C.c_void_p, C.c_void_p, C.POINTER(_OptStateC),
+                                                 C.POINTER(HParams), C.c_void_p]
         lib.hts_loss_and_grads.argtypes = [C.c_void_p, C.POINTER(Buffer), C.c_void_p, C.POINTER(HParams), C.c_void_p,
                                            C.c_void_p]
         lib.hts_adam_apply.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.POINTER(_OptStateC), C.POINTER(HParams),
@@ -126,7 +128,7 @@ def _ptr(t, dtype, name):
         return None
     if not isinstance(t, torch.Tensor) or not t.is_cuda or t.dtype != dtype or not t.is_contiguous():
         raise HtsError(f"{name}: expected a contiguous {dtype} device tensor")
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()          # (every entry declares its argument types; an object for each address is 0.1 us of a call that the host bounds)
 
 
 def hts_adam_apply_static(params, grads, opt: OptState, hp: HParams, stream=None):

@@ -316,9 +316,13 @@ __global__ __launch_bounds__(WAVES * 64) void wsgemm_kernel(const P p, const int
 // BQ: the B operand, a weight matrix of whole tiles and segments, in fragment order (see frag16), straight into registers; else bq is not read.
 // A rollout's step, us, rows by way of LDS / fragments: binary32 84x84 frames 1 row 18.0 / 17.3, 16 21.6 / 20.5, 32 27.7 / 27.3, 16x72x96 frames 1 19.3 /
 // 18.3, 8 23.2 / 21.0, 16 30.5 / 25.5.  (FC's weights in this order would be written for every update of the learner, 3.2 MB in bf16.)
+template <class P> struct Wsgemm16Args { P p; const typename P::T *bq; int spg; };
 template <class P, int WAVES, int SEG, bool BQ>
-__global__ __launch_bounds__(WAVES * 64) void wsgemm16_kernel(const P p, const int spg, const typename P::T *__restrict__ bq)
+__global__ __launch_bounds__(WAVES * 64) void wsgemm16_kernel(const Wsgemm16Args<P> args)
 {
+    const P &p = args.p;
+    const int spg = args.spg;
+    const typename P::T *__restrict__ bq = args.bq;
     using T = typename P::T;
     using Tr = OperandTraits<T>;
     constexpr int VA = P::VA, VB = P::VB;
@@ -434,7 +438,7 @@ inline hipError_t launch_wsgemm16(const P &p, hipStream_t stream, const void *bq
         attr_set.store(true, std::memory_order_release);
     }
     const int spg = segs_per_group < nseg ? segs_per_group : nseg;
-    hipLaunchKernelGGL(kern, dim3(tiles, (nseg + spg - 1) / spg, grid_batches(p)), dim3(WAVES * 64, 1, 1), lds, stream, p, spg, (const T *)bq);
+    hipLaunchKernelGGL(kern, dim3(tiles, (nseg + spg - 1) / spg, grid_batches(p)), dim3(WAVES * 64, 1, 1), lds, stream, Wsgemm16Args<P>{p, (const T *)bq, spg});
     return hipGetLastError();
 }
 
