@@ -128,7 +128,7 @@ def _ptr(t, dtype, name):
         return None
     if not isinstance(t, torch.Tensor) or not t.is_cuda or t.dtype != dtype or not t.is_contiguous():
         raise HtsError(f"{name}: expected a contiguous {dtype} device tensor")
-    return t.data_ptr()          # (every entry declares its argument types; an object for each address is 0.1 us of a call that the host bounds)
+    return t.data_ptr()          # (every entry declares its argument types, so the address itself is enough)
 
 
 def hts_adam_apply_static(params, grads, opt: OptState, hp: HParams, stream=None):
