@@ -40,14 +40,14 @@ def layer_flops(cfg):
 
 # A launch that does the work of several sites is timed under each of them: it is listed once, the weight gradients under fc_wgrad (bf16: FC
 # and the heads) or wgrads (binary32: all layers), conv1 and conv2 in bf16 (4x84x84 frames: actor calls of any size, up to 32 rows with conv3,
-# and 48 or more rows of the learner; actor calls of up to 16 16x72x96 frames) under conv1's name, and the others are left out.
+# and 64 or more rows of the learner; actor calls of up to 16 16x72x96 frames) under conv1's name, and the others are left out.
 def shared_sites(cfg):
     if cfg["precision"] == 0:
         return ("heads_wgrad", "fc_wgrad", "conv1_wgrad", "conv2_wgrad", "conv3_wgrad")
     frame, convs = (cfg["C"], cfg["H"], cfg["W"]), ()
     if frame == (4, 84, 84) or (frame == (16, 72, 96) and cfg["N"] <= 16):
         convs += ("conv2_fwd", "conv3_fwd") if frame[0] == 4 and cfg["N"] <= 32 else ("conv2_fwd",)
-    if frame == (4, 84, 84) and cfg["N"] * cfg["T"] // cfg["minibatches"] >= 48:
+    if frame == (4, 84, 84) and cfg["N"] * cfg["T"] // cfg["minibatches"] >= 64:
         convs += ("conv2_fwd_learn",)
     return ("heads_wgrad", "wgrads") + convs
 

@@ -559,7 +559,7 @@ template <typename T> static hipError_t forward_t(Ctx &c, const uint8_t *obs, co
     auto few32 = [&](int workgroups) { return workgroups < c.tile16_below; };
     // conv1 and conv2 in one kernel
     const bool few = sizeof(T) == 2 && !learn && (conv12_rows_fits<C12R_ATARI>(c, obs, B) || conv12_rows_fits<C12R_FOOTBALL>(c, obs, B));
-    const bool conv12 = few || (sizeof(T) == 2 && B >= c.conv12_rows && conv12_fits(g, obs));
+    const bool conv12 = few || (sizeof(T) == 2 && B >= (learn ? c.conv12_learn_rows : c.conv12_rows) && conv12_fits(g, obs));
     const bool conv123 = few && conv12_rows_fits<C123R_ATARI>(c, obs, B);
     if (few) {
         Conv12RowsArgs a;

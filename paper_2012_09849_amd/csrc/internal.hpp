@@ -81,7 +81,7 @@ struct Ctx {
     int fc_fold_rows;         // batches of at least this many rows add the FC groups inside the FC kernel (one slice of fc_part)
     int fc_slices;            // slices of fc_part the last forward pass wrote (fc_groups, or 1)
     int conv1_slab_rows;      // bf16 batches of at least this many 16x72x96 frames take the slab conv1 forward kernel
-    int conv12_rows;          // bf16 batches of at least this many 4x84x84 frames take conv1 and conv2 in one kernel
+    int conv12_rows, conv12_learn_rows;       // bf16 actor calls and updates of at least this many 4x84x84 frames take conv1 and conv2 in one kernel
     bool conv12_rows_kernel;  // bf16 actor calls of few 4x84x84 or 16x72x96 frames take conv1 and conv2, up to 32 of the former conv3 too, in one kernel, a workgroup for some rows
     int conv1_wgrad_slab_rows, conv1_wgrad_image_rows;      // likewise the weight-gradient kernels with the frame in LDS
     bool synced;              // the workspace's copy of the network matches the last parameter vector handed in

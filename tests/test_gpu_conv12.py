@@ -6,6 +6,7 @@ import pytest
 import torch
 
 import hts_synth as syn
+from launches import launches
 from test_gpu_parity import ATARI, _act, dev, hts  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -81,3 +82,21 @@ def test_few_compute_units(hts):  # noqa: F811
     ctx.close()
     rng.close()
     assert all(np.array_equal(x, y.cpu().numpy()) for x, y in zip(want, out))
+
+
+# the learner's cut, by what an update launches: below it, one that was taken for the actor's made updates slower
+@pytest.mark.parametrize("cus, cut", [(None, 64), (96, 48)])
+def test_the_learners_cut(hts, cus, cut):  # noqa: F811
+    rng = hts.CuRangeStream(0, cus) if cus else None
+    stream, n, A = rng.stream if cus else torch.cuda.Stream(), 64, 18
+    ctx = hts.Context(*ATARI, A, precision=1, max_learn_batch=n, stream=stream)
+    params, obs, rows = dev(syn.init_params(59, *ATARI, A)), _frames(n, 60), torch.zeros(n, device="cuda")
+    actions, out = torch.zeros(n, dtype=torch.int32, device="cuda"), torch.zeros(ctx.P, device="cuda")
+    for B in (cut - 1, cut):
+        call = lambda: ctx.hts_loss_and_grads(obs[:B], actions[:B], None, rows[:B], rows[:B], params, hts.HParams(algo=hts.ALGO_A2C), out)
+        names = [x[0] for x in launches(call, stream)]
+        assert [x for x in names if "conv1" in x] and any("conv12_kernel" in x for x in names) == (B == cut), (B, names)
+    torch.cuda.synchronize()
+    ctx.close()
+    if rng:
+        rng.close()
