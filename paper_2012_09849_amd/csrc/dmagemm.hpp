@@ -44,16 +44,20 @@ template <class P, int BM_, int BN_, int WM_, int WN_, int STAGES_, int GROUP_ =
 template <class P, class = void> struct MaskedRows : std::false_type {};
 template <class P> struct MaskedRows<P, std::void_t<decltype(P::MASKED_ROWS)>> : std::integral_constant<bool, P::MASKED_ROWS> {};
 
-constexpr int wait_imm(int vm) { return (vm & 15) | ((vm >> 4) << 14) | (7 << 4); }       // vmcnt(vm) lgkmcnt(0)
+// vmcnt(VM) lgkmcnt(0)
+template <int VM> constexpr int wait_imm()
+{
+    static_assert(VM >= 0 && VM < 64, "vmcnt has six bits");
+    return (VM & 15) | ((VM >> 4) << 14) | (7 << 4);
+}
 
 // waits until at most min(ahead, AHEAD) k-tiles' copies (PER a tile) of this wavefront are under way, and for its LDS reads
 template <int AHEAD, int PER> __device__ __forceinline__ void wait_tiles(int ahead)
 {
-    static_assert(AHEAD * PER < 64, "vmcnt");
     if constexpr (AHEAD > 0) {
         if (ahead < AHEAD) { wait_tiles<AHEAD - 1, PER>(ahead); return; }
     }
-    __builtin_amdgcn_s_waitcnt(wait_imm(AHEAD * PER));
+    __builtin_amdgcn_s_waitcnt(wait_imm<AHEAD * PER>());
 }
 
 // step(t + U) for U = 0, 1, ... while there are k-tiles left

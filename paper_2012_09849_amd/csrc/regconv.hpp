@@ -81,7 +81,7 @@ template <class C> __global__ __launch_bounds__(512) __attribute__((amdgpu_waves
     }
     fetch(blockIdx.x + step, 1, 0, C::EARLY);
     asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(wait_imm(C::EARLY));             // the first group and the weights are there
+    __builtin_amdgcn_s_waitcnt(wait_imm<C::EARLY>());             // the first group and the weights are there
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     bf16x8 wt[STEPS];
@@ -97,9 +97,9 @@ template <class C> __global__ __launch_bounds__(512) __attribute__((amdgpu_waves
     for (int grp = blockIdx.x; grp < groups; grp += step, ++done) {
         // This wavefront's copies of the group have landed.  Behind them in order: the next group's copies and, of each of the last two
         // groups worked on, at least two stores.
-        if (done == 0) __builtin_amdgcn_s_waitcnt(wait_imm(PER));
-        else if (done == 1) __builtin_amdgcn_s_waitcnt(wait_imm(PER + 2));
-        else __builtin_amdgcn_s_waitcnt(wait_imm(PER + 4));
+        if (done == 0) __builtin_amdgcn_s_waitcnt(wait_imm<PER>());
+        else if (done == 1) __builtin_amdgcn_s_waitcnt(wait_imm<PER + 2>());
+        else __builtin_amdgcn_s_waitcnt(wait_imm<PER + 4>());
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
@@ -164,7 +164,7 @@ template <class C> __global__ __launch_bounds__(512) __attribute__((amdgpu_waves
         }
         s = s + 1 == C::STAGES ? 0 : s + 1;
     }
-    __builtin_amdgcn_s_waitcnt(wait_imm(0));       // no copy is under way when the workgroup's LDS is given back
+    __builtin_amdgcn_s_waitcnt(wait_imm<0>());       // no copy is under way when the workgroup's LDS is given back
 }
 
 // cus: compute units that the stream runs on, a workgroup for each (more than them go in rounds with as long a start each: 4096 rows of

@@ -31,7 +31,7 @@ template <int HIN_, int WIN_, int G_, int SEG_> struct RegConv3 {
     static constexpr int COPIES = (G * SAMPLE + 63) / 64, STAGE = COPIES * 1024, PER = (COPIES + 7) / 8, STAGES = 3;
     static constexpr int ROWS = G * PO, TILES = (ROWS + 31) / 32, OUT = G * PO * 128, STORES = (OUT / 16 + 511) / 512, LDS = STAGES * STAGE + OUT + 256;
     static_assert(STEPS % SEGSTEPS == 0 && PO * 128 % 16 == 0, "whole segments and vectors");
-    static_assert(LDS <= 160 * 1024 && PER + STORES < 64, "shape");
+    static_assert(LDS <= 160 * 1024, "shape");
 };
 
 template <class C, bool LEARN> __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void conv3_regconv_kernel(const RegConv3Args a)
@@ -70,9 +70,9 @@ template <class C, bool LEARN> __global__ __launch_bounds__(512) __attribute__((
     for (int grp = blockIdx.x; grp < groups; grp += step, ++done) {
         // This wavefront's copies of the group have landed.  Behind them in order: of the last two groups worked on at least STORES stores each,
         // and the next group's copies.
-        if (done == 0) __builtin_amdgcn_s_waitcnt(wait_imm(PER));
-        else if (done == 1) __builtin_amdgcn_s_waitcnt(wait_imm(PER + C::STORES));
-        else __builtin_amdgcn_s_waitcnt(wait_imm(PER + 2 * C::STORES));
+        if (done == 0) __builtin_amdgcn_s_waitcnt(wait_imm<PER>());
+        else if (done == 1) __builtin_amdgcn_s_waitcnt(wait_imm<PER + C::STORES>());
+        else __builtin_amdgcn_s_waitcnt(wait_imm<PER + 2 * C::STORES>());
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
@@ -148,7 +148,7 @@ template <class C, bool LEARN> __global__ __launch_bounds__(512) __attribute__((
         }
         s = s + 1 == C::STAGES ? 0 : s + 1;
     }
-    __builtin_amdgcn_s_waitcnt(wait_imm(0));       // no copy is under way when the workgroup's LDS is given back
+    __builtin_amdgcn_s_waitcnt(wait_imm<0>());       // no copy is under way when the workgroup's LDS is given back
 }
 
 template <class C> inline hipError_t launch_regconv3(const RegConv3Args &a, int cus, hipStream_t stream)
