@@ -1,6 +1,7 @@
 """conv1 and conv2 of bf16 batches of 4x84x84 frames in one kernel, against a launch each, bit for bit: one to five samples per workgroup, the
-last ones on some workgroups only; frames gathered by index and conv1's output kept for the backward pass; frames at a multiple of 8 bytes
-but not of 16; compute-unit ranges, whose workgroups walk more samples than rows of the index they hold at once."""
+last ones on some workgroups only; frames gathered by index and conv1's output kept for the backward pass; compute-unit ranges, of more
+samples than their units' workgroups hold row indices of; few frames at a multiple of 8 bytes but not of 16 (in the kernel of few rows: for this
+one see test_gpu_launched_kernels.py); the learner's first rows."""
 import numpy as np
 import pytest
 import torch
@@ -66,7 +67,7 @@ def test_gradients_agree_bitwise(hts, B, monkeypatch):  # noqa: F811
     assert bool(torch.isfinite(grads[0]).all()) and torch.equal(*grads)
 
 
-# 8 compute units and 600 rows: 75 samples for each, more than a workgroup's 64
+# 8 compute units and 600 rows would be 75 samples for each, more than a workgroup's 64: ten workgroups of 60
 def test_few_compute_units(hts):  # noqa: F811
     n, A = 600, 18
     params, obs = dev(syn.init_params(57, *ATARI, A, bias_scale=0.05)), _frames(n, 58)

@@ -1,5 +1,5 @@
 """conv1 of bf16 batches at the edges of its kernels: observations shared by 16, 3, 2 and 1 workgroups (each with the image
-rows under its position tiles only), first and last batch of each, against the kernels that serve other batch sizes, bit
+rows under its position tiles only; 4x84x84 frames take the kernels of conv1 and conv2 by now), first and last batch of each, against the kernels that serve other batch sizes, bit
 for bit; the gradient of small bf16 minibatches, whose weight gradients take the large batches' kernels; and the knob that
 sends them to the wave-per-segment ones."""
 import numpy as np

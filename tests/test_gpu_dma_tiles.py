@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 
 # workgroups of 64x64 FC tiles at these sizes (84x84): 168, 504, 560, 728, 728, 840, 896, 952; 4100 rows add the groups in the
-# kernel; conv2 has 512 workgroups at 809 rows and 513 at 810
+# kernel; 809 and 810 rows stand on either side of conv2's change of stages, which 4x84x84 frames no longer reach
 @pytest.mark.parametrize("shape,A,sizes", [(ATARI, 18, (129, 576, 577, 809, 810, 960, 961, 1030, 4100)), (FOOT, 19, (129, 203, 833, 1409)),
                                            ((3, 44, 52), 7, (129, 500, 2113))])
 def test_large_batches_agree_bitwise(hts, shape, A, sizes, monkeypatch):  # noqa: F811
@@ -33,7 +33,7 @@ def test_large_batches_agree_bitwise(hts, shape, A, sizes, monkeypatch):  # noqa
 
 
 # As for small minibatches (twice the rows, half the weight of each): binary32 sums of at most n = 700 * 400 terms in another
-# order, sqrt(n) 2^-24 = 3.2e-5.  350 rows take 64x64 tiles of the FC input gradient, 700 rows 64x128.  Three channels end
+# order, sqrt(n) 2^-24 = 3.2e-5.  bf16: 350 rows take 64x64 tiles of three stages of the FC input gradient, 700 rows of two.  Three channels end
 # conv1's weight gradient inside a column tile, whose bias column is binary32's to sum beside the tiles.
 @pytest.mark.parametrize("shape,A,B,precision", [(ATARI, 18, 350, 1), ((3, 44, 52), 7, 150, 1), (ATARI, 18, 330, 0), ((3, 44, 52), 7, 150, 0)])
 def test_gradient_is_the_mean_of_its_halves(hts, oracle, shape, A, B, precision):  # noqa: F811

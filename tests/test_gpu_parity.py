@@ -228,8 +228,8 @@ def test_conv1_slab_kernel_agrees_bitwise(hts, shape, A, N, monkeypatch):
     """Large bf16 batches of 16x72x96 frames take a conv1 kernel of their own (frame slabs of four channels resident in
     LDS, producer and consumer wavefronts); it adds the same 64-long segments in the same order as the tile kernel, so
     an observation's outputs do not depend on which of them served it.  N = 301 and 700 leave workgroups with
-    different numbers of observations (256 workgroups walk the batch).  4x84x84 frames take it too (there
-    against the LDS-image kernel of that shape)."""
+    different numbers of observations (256 workgroups walk the batch).  4x84x84 frames take the kernel of conv1
+    and conv2 instead, against the LDS-image kernel of that shape."""
     Cc, H, W = shape
     params = dev(syn.init_params(21, Cc, H, W, A, bias_scale=0.05))
     obs = dev(syn.obs_football(23, 1, N)[0] if shape == FOOT else syn.obs_atari(23, 1, N)[0])

@@ -1,5 +1,6 @@
 """conv2 of large bf16 batches, its weights in registers and its samples in LDS: on either side of its first sizes, with an odd sample
-at the end and with unequal numbers of groups per workgroup, against the wave-per-segment kernels bit for bit."""
+at the end and with unequal numbers of groups per workgroup, against the wave-per-segment kernels bit for bit.  (4x84x84 frames take conv1 and
+conv2 in one kernel by now: their sizes here are that one's, and other frames of their grids are in test_gpu_launched_kernels.py.)"""
 import numpy as np
 import pytest
 import torch
