@@ -202,20 +202,20 @@ def source_digest():
 # counter reads for a plain copy of known size): workload -> ({launch site: bytes per launch}, digest of the kernel
 # sources the counters were taken on).
 TRAFFIC = {
-    "football_ppo_n16_t512_bf16": ({"conv1_fwd": 5093376, "conv1_fwd_learn": 279397068, "conv1_wgrad": 313987379,
-                                    "conv2_fwd": 2626560, "conv3_fwd": 1214464, "fc_fwd": 3466240}, "035ebdf034e8cc63"),
-    "atari_ppo_n32_t128_bf16": ({"conv1_fwd": 2846720, "conv1_fwd_learn": 55549952, "conv1_wgrad": 63729868,
-                                 "conv2_wgrad": 45520896}, "035ebdf034e8cc63"),
+    "football_ppo_n16_t512_bf16": ({"conv1_fwd": 2947666, "conv1_fwd_learn": 279388461, "conv1_wgrad": 317993690,
+                                    "conv3_fwd": 1214288, "fc_fwd": 3474921}, "82647323d6511918"),
+    "atari_ppo_n32_t128_bf16": ({"conv1_fwd": 2450111, "conv1_fwd_learn": 66774590, "conv1_wgrad": 63729068,
+                                 "conv2_wgrad": 45539748}, "82647323d6511918"),
 }
 
 
 # Average duration (us) of the same launch sites' kernels in the committed rocprofv3 kernel traces
 # (profiles/all_kernels_<workload>.txt), for comparison with the live event figure; same digest rule as TRAFFIC.
 TRACE_AVG_US = {
-    "football_ppo_n16_t512_bf16": ({"conv1_fwd": 6.31, "heads_act": 3.84, "conv2_fwd": 3.84, "conv3_fwd": 3.51,
-                                    "fc_fwd": 3.22, "conv1_fwd_learn": 86.04, "conv1_wgrad": 79.45}, "035ebdf034e8cc63"),
-    "atari_ppo_n32_t128_bf16": ({"conv1_fwd": 4.91, "heads_act": 3.85, "conv1_fwd_learn": 20.05, "conv1_wgrad": 18.98,
-                                 "conv2_wgrad": 13.84}, "035ebdf034e8cc63"),
+    "football_ppo_n16_t512_bf16": ({"conv1_fwd": 7.14, "heads_act": 3.76, "conv3_fwd": 3.31, "fc_fwd": 3.23,
+                                    "conv1_fwd_learn": 86.96, "conv1_wgrad": 79.23}, "82647323d6511918"),
+    "atari_ppo_n32_t128_bf16": ({"conv1_fwd": 7.55, "heads_act": 3.82, "fc_fwd": 3.53, "conv1_fwd_learn": 26.30,
+                                 "conv1_wgrad": 19.26, "conv2_wgrad": 13.79}, "82647323d6511918"),
 }
 
 

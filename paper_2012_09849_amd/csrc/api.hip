@@ -153,8 +153,8 @@ extern "C" int32_t hts_create(const hts_net_desc *desc, int32_t max_act_batch, i
     // conv1 by the slab kernel against the wave-per-segment kernel, us: 16x72x96 frames 16 rows 6.5 / 5.6 (196 workgroups), 24
     // rows 6.8 / 8 (two rounds of workgroups from 21 rows on), 64 rows 7.7 / 16.8
     c.conv1_slab_rows = 21;
-    // conv1 and conv2 of 4x84x84 frames in one kernel against a launch each, act call, us: 16 rows 18.3 / 17.5, 32 19.4 / 19.2, 48 20.9 / 21.5, 64
-    // 21.4 / 23.5, 128 24.5 / 29.5, 200 26.7 / 35.0, 512 34.0 / 41.4, 1025 52.2 / 63.1, 8192 223 / 273; gradient 32 70.5 / 69.9, 48 74.1 / 73.9, 64 75.2 / 76.7
+    // conv1 and conv2 of 4x84x84 frames in one kernel against a launch each (actor calls of few rows that conv12_rows_kernel serves, on the whole device up
+    // to 80, never come to this cut), act call, us: 16 rows 18.3 / 17.5, 32 19.4 / 19.2, 48 20.9 / 21.5, 64 21.4 / 23.5, 128 24.5 / 29.5, 200 26.7 / 35.0, 512 34.0 / 41.4, 1025 52.2 / 63.1, 8192 223 / 273; gradient 32 70.5 / 69.9, 48 74.1 / 73.9, 64 75.2 / 76.7
     c.conv12_rows = 48;
     // An update, us, whole device: 48 rows 82.6 / 80.4, 49 82.9 / 80.8, 52 84.1 / 83.0, 60 84.2 / 83.4, 63 85.3 / 84.9, 64 83.5 / 83.7, 96 89.4 / 90.5; 240 compute
     // units 48 84.1 / 82.8, 64 84.2 / 87.6; 192 48 86.7 / 85.9, 56 87.1 / 87.1; 160 48 86.7 / 86.3, 56 90.2 / 90.7, 64 90.1 / 95.2; 96 48 98.8 / 102.1

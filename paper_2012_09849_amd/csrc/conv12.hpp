@@ -9,10 +9,10 @@
 // pixels, and 16-byte slot s of a pixel holds channel vector s ^ c12_swizzle(its row, its column in the plane).
 // Same k order, segments and epilogues as the other kernels, hence the same bits.
 // Conv1's 25 KB of a sample are not written and read again (actor), or not read (learner), and there is one launch and one first fetch less.
-// Kernel time, us, a launch each / this: 1024 rows 19.6 + 13.7 / 24.6, 4096 57 + 38 / 72; learner, which keeps conv1's output for its backward
-// pass, 1024 rows 20.1 + 14.1 / 27.0.  What bounds it: at 4096 rows 4.0 us a sample, of which the LDS is busy for 2.3 (position operands of both layers,
-// 1 KB an instruction), the matrix units for 1.5, the vector units for about 2 (segment sums, conversions, epilogues); conv1 alone takes 2.7,
-// conv2 alone 2.9.  168 registers a wavefront are what three to a SIMD leave, and all are in use.  Not kept: conv2's reads two segments
+// Medians of kernel traces, us, a launch each / this: 1024 rows 20 + 13.7 / 24.8, 4096 62 to 65 + 41 to 43 / 73 to 78; learner, which keeps conv1's output
+// for its backward pass, 1024 rows 20.3 + 14.1 / 26.9.  What bounds it, by the counters at 4096 rows: a sample takes 8.4 thousand of a unit's cycles, of which
+// the LDS is active for 4.5 (position operands of both layers, 1 KB an instruction; 0.95 of them bank conflicts), the matrix units for 3.2 and the vector units,
+// four cycles an instruction, for 3.8 (segment sums, conversions, epilogues).  168 registers a wavefront are what three to a SIMD leave, and all are in use.  Not kept: conv2's reads two segments
 // ahead (the same time), the next tile's reads ahead of a tile's sums (spills, 80 to 94 us at 4096 rows), the thirteenth tile by one of conv1's wavefronts (76).
 #pragma once
 #include "dmagemm.hpp"

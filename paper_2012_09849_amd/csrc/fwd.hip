@@ -507,7 +507,9 @@ static hipError_t launch_conv1_slab(Ctx &c, const uint8_t *obs, const int32_t *i
 // unit, or a second round, cost more than the launch they save).  A rollout's step, us, a launch for each layer (from 48 rows conv12_kernel) /
 // conv1 and conv2 here / conv3 too, a row of its output a workgroup: 4x84x84 frames 1 row 15.7 / 15.4 / 12.3, 8 16.3 / 15.4 / 12.7, 16 17.2 /
 // 15.6 / 12.8, 24 18.7 / 16.1 / 13.3, 32 19.0 / 16.7 / 13.6, 48 21.0 / 18.2, 80 22.3 / 19.5 (96, 1.1 workgroups a unit: 24.4 / 27.6); 16x72x96
-// 1 17.0 / 14.4, 8 18.0 / 15.2, 16 18.7 / 15.6 (18: 19.2 / 23.7).
+// 1 17.0 / 14.4, 8 18.0 / 15.2, 16 18.7 / 15.6 (18: 19.2 / 23.7).  On ranges of compute units, a launch for each layer / here: 192 units 24 84x84 frames
+// 19.4 / 13.5, 56 23.1 / 18.7, 128 units 16 19.0 / 13.0, 40 23.6 / 18.2; 72x96 frames 192 units 8 18.2 / 15.6, 128 units 8 18.7 / 15.6.  16 of the latter ask for 28
+// workgroups on each die, which 192 units (24 a die) don't have: 21.1, a launch for each layer.
 typedef Conv12Rows<4, 84, 84, 3, 1, true> C123R_ATARI;
 typedef Conv12Rows<4, 84, 84, 3, 1> C12R_ATARI;
 typedef Conv12Rows<16, 72, 96, 1, 2> C12R_FOOTBALL;
@@ -614,9 +616,10 @@ template <typename T> static hipError_t forward_t(Ctx &c, const uint8_t *obs, co
         {
             SiteTimer tm(c, learn ? SITE_CONV2_FWD_LEARN : SITE_CONV2_FWD);
             // (the kernel of imgconv.hpp, weights in LDS and rows staged in registers, measured slower than either: 20.4 us at B = 1024)
-            // Weights in registers, from where the machine's rate outweighs the 7 us until the first products.  us, LDS-copy tiles / this,
-            // 84x84 frames: 256 rows 7.3 / 8.4, 1024 13.8 / 15.0, 1536 19.4 / 19.4, 2048 24.4 / 23.2, 4096 43.5 / 38.2, 8192 105 / 80;
-            // 72x96: 2048 22.6 / 23.8, 3072 34.4 / 31.6, 4096 43.9 / 40.7
+            // Weights in registers, from where the machine's rate outweighs the 7 us until the first products.  (Of 4x84x84 frames only those that
+            // conv12.hpp does not serve, at an address that is no multiple of 8, come here; other channel counts all do.)  us, LDS-copy tiles / this, 84x84
+            // frames: 256 rows 7.3 / 8.4, 1024 13.8 / 15.0, 1536 19.4 / 19.4, 2048 24.4 / 23.2, 4096 43.5 / 38.2, 8192 105 / 80; 72x96:
+            // 2048 22.6 / 23.8, 3072 34.4 / 31.6, 4096 43.9 / 40.7
             RegConvArgs r = {};
             r.in = (const bf16_t *)c.ws.act1; r.w = (const bf16_t *)c.ws.wf2; r.bias = hb + c.sh.b2; r.out = (bf16_t *)c.ws.act2; r.B = B;
             if (sizeof(T) == 2 && !small && atari_grid && B >= 2048) e = launch_regconv<RegConv<Layer2, 20, 20, ConvFwd<bf16_t, Layer2, false>::SEG>>(r, c.cus, c.stream);
