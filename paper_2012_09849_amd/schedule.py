@@ -126,9 +126,11 @@ class OverlapLoop:
         self.learner_after = learner_after          # actor calls issued before the learner's calls (see step)
         N, T = cfg["N"], cfg["T"]
         # actor_cus: the actors' stream is confined to the first `actor_cus` compute units and the learner's to the
-        # rest.  It pays where the two sides' workgroups each want a whole compute unit's LDS (16x72x96 frames: the actor's
-        # conv1 and the learner's conv1 kernels), so that on shared compute units every actor call waits for a learner
-        # workgroup to leave; it costs where they interleave well anyway (4x84x84 frames).  Results do not depend on it.
+        # rest.  It can pay where workgroups of both sides want a compute unit's LDS for themselves (the actor's conv
+        # kernels, the learner's conv1 kernels), so that on shared units actor calls wait for learner workgroups to leave;
+        # it costs what the kernels of either side lose on fewer units.  ms an iteration, sequential / shared / confined:
+        # football_ppo 11.5 / 12.4 / 12.9 (192), its three-player form 5.47 / 5.03 / 4.42 (128), atari_ppo 4.57 / 4.65 /
+        # 3.95 (96), 6.64 (192), A2C 0.257 / 0.224 / -.  Results do not depend on it.
         self._masked = []
         if actor_cus:
             total = torch.cuda.get_device_properties(torch.cuda.current_device()).multi_processor_count
